@@ -24,6 +24,16 @@ namespace sun {
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
+// One 16-byte piece of the weights.  A launch of one row tile (up to 64 rows) reads every piece once, 1 KiB contiguous
+// per wave, and streams it past the caches; several row tiles share their fetches through L2 and load plainly.
+// Measured, 8B shape, plain -> streamed (us): gate/up at 1 / 64 rows 45.1 -> 41.0 / 47.6 -> 44.8, lm_head at 1 row
+// 193 -> 177, q/k/v and o unchanged (bound by the launch around them), and so are the 4-bit launches (a quarter of the bytes).
+template <bool STREAM>
+__device__ __forceinline__ u32x4 load_w16(const u32x4* p) {
+    if constexpr (STREAM) return load_stream(p);
+    else return *p;
+}
+
 struct ProjArgs {
     const u32x4* W;
     const uint32_t* SZ;
@@ -75,7 +85,7 @@ void proj_kernel(ProjArgs a) {
 
     auto load_w = [&](u32x4(&w)[WREGS], int st) {
 #pragma unroll
-        for (int j = 0; j < WREGS; ++j) w[j] = Wl[((size_t)st * WREGS + j) * 64];
+        for (int j = 0; j < WREGS; ++j) w[j] = load_w16<(MB <= 4)>(Wl + ((size_t)st * WREGS + j) * 64);
     };
     auto load_a = [&](int st) {
 #pragma unroll
