@@ -437,9 +437,10 @@ size_t sun_prefill_workspace_bytes(const sun_model_cfg* cfg, int n_tokens, int m
  * (first_pos > 0 continues a prompt that was prefilled in pieces); the result does not depend on
  * how a prompt is cut into pieces.
  *
- * It runs through the decode step's own kernels: the prompt is taken in blocks of up to 256
- * positions, row r of a block being the decode step of position first + r over the shared page
- * table, so it is exact but not tuned for long prompts (attention reads the cache once per row).
+ * SUN_BF16: the prompt is taken in blocks of up to 2048 positions (shorter ones if the workspace was sized for fewer
+ * tokens); the K/V of a block are in the pool before its attention, in which the block's rows share what they read of
+ * the cache.  SUN_F32: in blocks of up to 256 positions through the decode step's kernels, row r of a block being the
+ * decode step of position first + r over the shared page table.
  *
  *   token_ids   dev int32 [n_tokens]
  *   page_table  dev int32 [max_pages]   the request's row; entries 0 .. (first_pos+n_tokens-1)/16
@@ -447,7 +448,8 @@ size_t sun_prefill_workspace_bytes(const sun_model_cfg* cfg, int n_tokens, int m
  *   model_id    source-model tag; n_tokens is added to that model's count in the pool
  *   logits_out  dev fp32 [vocab] or NULL: logits after the last prompt token
  *   next_token_out dev int32 [1] or NULL: their greedy argmax
- *   workspace   dev, 256-byte aligned, >= sun_prefill_workspace_bytes(cfg, n_tokens, max_pages)
+ *   workspace   dev, 256-byte aligned, >= sun_prefill_workspace_bytes(cfg, n_tokens, max_pages) (SUN_BF16: one of
+ *               sun_prefill_workspace_bytes(cfg, 256, max_pages) bytes serves any longer prompt, more slowly)
  * `weights` must come from sun_weights_create (the prefill side stays in full precision, also
  * when decode is quantised: Section 3.3) and have the pool's shape.
  * Errors: SUN_ERR_NULL, SUN_ERR_SHAPE (also for 4-bit weights), SUN_ERR_MODEL_ID, SUN_ERR_SEQ_LEN (n_tokens < 1,

@@ -117,6 +117,7 @@ struct Workspace {
 
 constexpr int kMaxSplits = 16;
 constexpr int kMaxSplitsWide = 4;   // gate/up (2*ffn columns)
+constexpr int kMaxSplitsBlock = 8;  // projections of a prefill block of more than kMaxBatchTile rows
 
 static Workspace carve(const sun_model_cfg& c, int batch, int max_pages, char* base) {
     Workspace w{};
@@ -156,6 +157,33 @@ static Workspace carve(const sun_model_cfg& c, int batch, int max_pages, char* b
     w.logits = (float*)take((size_t)batch * c.vocab * 4);
     w.amax_val = (float*)take((size_t)batch * kArgmaxParts * 4);
     w.amax_idx = (int32_t*)take((size_t)batch * kArgmaxParts * 4);
+    w.bytes = off;
+    return w;
+}
+
+// Device memory of a prefill block of more than kMaxBatchTile rows (bf16): no decode plan, logits of one row.
+static Workspace carve_block(const sun_model_cfg& c, int rows, char* base) {
+    Workspace w{};
+    size_t off = 0;
+    auto take = [&](size_t n) {
+        char* p = base ? base + off : nullptr;
+        off += align_up(n);
+        return (void*)p;
+    };
+    const int H = c.hidden, QD = c.n_q_heads * c.head_dim, F = c.ffn, Nqkv = QD + 2 * c.n_kv_heads * c.head_dim;
+    const ATile t = atile_for_rows(rows);
+    w.x = (float*)take((size_t)rows * H * 4);
+    w.q = (float*)take((size_t)rows * QD * 4);
+    w.table = (float*)take((size_t)rows * c.head_dim * 4);
+    w.hA = take(atile_bytes(t, H));
+    w.aA = take(atile_bytes(t, QD));
+    w.uA = take(atile_bytes(t, F));
+    w.part = (float*)take((size_t)kMaxSplitsBlock * rows * std::max(Nqkv, H) * 4);
+    w.plan.max_chunks = std::max(rows, 32768 / c.n_q_heads);   // no fewer than attn_prefill_splits() asks for at any rows
+    w.plan.partial = (float*)take((size_t)w.plan.max_chunks * c.n_q_heads * (c.head_dim + 2) * 4);
+    w.logits = (float*)take((size_t)c.vocab * 4);
+    w.amax_val = (float*)take((size_t)kArgmaxParts * 4);
+    w.amax_idx = (int32_t*)take((size_t)kArgmaxParts * 4);
     w.bytes = off;
     return w;
 }
@@ -721,7 +749,7 @@ static int step_impl(sun_kv_pool* pool_, const sun_weights* weights_, bool want_
     {
         ProfScope p(prof, 7, st);
         SUN_HIP_CHECK(launch_embed(c, W.embed, token_ids, batch, ws.x, st));
-        SUN_HIP_CHECK(launch_rope_table(c, seq_lens, batch, ws.table, st));
+        SUN_HIP_CHECK(launch_rope_table(c, seq_lens, 0, batch, ws.table, st));
         SUN_HIP_CHECK(launch_attn_plan(ws.plan, seq_lens, 1, batch, page_tables, max_pages, (int)pool.lay.n_pages, c.n_kv_heads, st));
     }
     int down_parts = 0;
@@ -742,7 +770,7 @@ static int step_impl(sun_kv_pool* pool_, const sun_weights* weights_, bool want_
             }
             {
                 ProfScope p(prof, 7, st);
-                SUN_HIP_CHECK(launch_rope_append(pool, l, ws.part, sq, batch, ws.table, seq_lens, page_tables, max_pages,
+                SUN_HIP_CHECK(launch_rope_append(pool, l, ws.part, sq, batch, ws.table, seq_lens, 0, page_tables, max_pages,
                                                  batch, ws.q, L.qn, L.kn, L.bq, L.bk, L.bv, st));
             }
         } else {
@@ -750,7 +778,7 @@ static int step_impl(sun_kv_pool* pool_, const sun_weights* weights_, bool want_
             if (l > 0) SUN_HIP_CHECK(launch_residual_norm(c, ws.x, ws.o32, 1, batch, L.g1, batch, ws.h32, nullptr, nullptr, st));
             else SUN_HIP_CHECK(launch_residual_norm(c, ws.x, nullptr, 0, batch, L.g1, batch, ws.h32, nullptr, nullptr, st));
             SUN_HIP_CHECK(launch_proj_f32(L.qkv, ws.h32, batch, ws.qkv32, st));
-            SUN_HIP_CHECK(launch_rope_append(pool, l, ws.qkv32, 1, batch, ws.table, seq_lens, page_tables, max_pages,
+            SUN_HIP_CHECK(launch_rope_append(pool, l, ws.qkv32, 1, batch, ws.table, seq_lens, 0, page_tables, max_pages,
                                              batch, ws.q, L.qn, L.kn, L.bq, L.bk, L.bv, st));
         }
         {
@@ -1031,10 +1059,97 @@ static PrefillExtra carve_prefill(int rows, int max_pages, char* base) {
     return e;
 }
 
+// Rows per block of a bf16 prefill of more than kMaxBatchTile tokens: equal blocks of at most `most` rows, whole row
+// tiles (256) except for the last.
+static int prefill_block_rows(int n_tokens, int most) {
+    const int blocks = (n_tokens + most - 1) / most;
+    return std::min(n_tokens, ((n_tokens + blocks - 1) / blocks + 255) / 256 * 256);
+}
+
 size_t sun_prefill_workspace_bytes(const sun_model_cfg* cfg, int n_tokens, int max_pages) {
     if (!cfg || n_tokens < 1 || max_pages < 1 || check_cfg(cfg) != SUN_OK) return 0;
     const int rows = std::min(n_tokens, kMaxBatchTile);
-    return carve(*cfg, rows, max_pages, nullptr).bytes + carve_prefill(rows, max_pages, nullptr).bytes;
+    const size_t least = carve(*cfg, rows, max_pages, nullptr).bytes + carve_prefill(rows, max_pages, nullptr).bytes;
+    if (cfg->act_dtype != SUN_BF16 || n_tokens <= kMaxBatchTile) return least;
+    return std::max(least, carve_block(*cfg, prefill_block_rows(n_tokens, kMaxPrefillTile), nullptr).bytes);
+}
+
+// A block of a bf16 prefill: the layers over rows positions first .. first + rows - 1 of one request, then, for the
+// last block, the head over its last row.  Row r's K and V are in the pool before the block's attention starts, which
+// makes the masked attention over positions 0 .. first + r the causal forward of Eq. 2.
+static int prefill_block(KvPool& pool, const Weights& W, const Workspace& ws, int rows, int first, const int32_t* tokens,
+                         const int32_t* page_table, int max_pages, bool head, float* logits, int32_t* next, bool prof,
+                         hipStream_t st) {
+    const sun_model_cfg& c = W.cfg;
+    const int H = c.hidden, max_splits = rows > kMaxBatchTile ? kMaxSplitsBlock : kMaxSplits;
+    const int key_splits = std::max(1, std::min(attn_prefill_splits(c, rows, first), ws.plan.max_chunks / rows));
+    {
+        ProfScope p(prof, 7, st);
+        SUN_HIP_CHECK(launch_embed(c, W.embed, tokens, rows, ws.x, st));
+        SUN_HIP_CHECK(launch_rope_table(c, nullptr, first, rows, ws.table, st));
+    }
+    int down_parts = 0;
+    for (int l = 0; l < c.n_layers; ++l) {
+        const LayerW& L = W.layers[l];
+        {
+            ProfScope p(prof, 7, st);
+            SUN_HIP_CHECK(launch_residual_norm(c, ws.x, ws.part, down_parts, rows, L.g1, rows, nullptr, ws.hA, nullptr, st));
+        }
+        const int sq = proj_pick_splits(L.qkv, rows, max_splits);
+        {
+            ProfScope p(prof, 2, st);
+            SUN_HIP_CHECK(launch_proj(ProjLaunch{&L.qkv, ws.hA, nullptr, rows, EPI_STORE, sq, ws.part, L.qkv.N, rows}, st));
+        }
+        {
+            ProfScope p(prof, 7, st);
+            SUN_HIP_CHECK(launch_rope_append(pool, l, ws.part, sq, rows, ws.table, nullptr, first, page_table, max_pages, rows,
+                                             ws.q, L.qn, L.kn, L.bq, L.bk, L.bv, st));
+        }
+        {
+            ProfScope p(prof, 0, st);
+            SUN_HIP_CHECK(launch_attn_prefill(pool, l, ws.q, page_table, first, rows, key_splits, ws.plan.partial, ws.aA, st));
+        }
+        const int so = proj_pick_splits(L.o, rows, max_splits);
+        {
+            ProfScope p(prof, 3, st);
+            SUN_HIP_CHECK(launch_proj(ProjLaunch{&L.o, ws.aA, nullptr, rows, EPI_STORE, so, ws.part, H, rows}, st));
+        }
+        {
+            ProfScope p(prof, 7, st);
+            SUN_HIP_CHECK(launch_residual_norm(c, ws.x, ws.part, so, rows, L.g2, rows, nullptr, ws.hA, nullptr, st));
+        }
+        if (rows > 64) {   // as in a decode step: SwiGLU in the epilogue, the down projection's tile as output
+            ProfScope p(prof, 4, st);
+            SUN_HIP_CHECK(launch_proj(ProjLaunch{&L.gu, ws.hA, nullptr, rows, EPI_SWIGLU, 1, (float*)ws.uA, L.gu.N, rows}, st));
+        } else {
+            const int sg = proj_pick_splits(L.gu, rows, kMaxSplitsWide);
+            {
+                ProfScope p(prof, 4, st);
+                SUN_HIP_CHECK(launch_proj(ProjLaunch{&L.gu, ws.hA, nullptr, rows, EPI_STORE, sg, ws.part, L.gu.N, rows}, st));
+            }
+            ProfScope p(prof, 7, st);
+            SUN_HIP_CHECK(launch_swiglu_tile(ws.part, sg, rows, rows, c.ffn, ws.uA, nullptr, st));
+        }
+        down_parts = proj_pick_splits(L.down, rows, max_splits);
+        {
+            ProfScope p(prof, 5, st);
+            SUN_HIP_CHECK(launch_proj(ProjLaunch{&L.down, ws.uA, nullptr, rows, EPI_STORE, down_parts, ws.part, H, rows}, st));
+        }
+    }
+    if (!head) return SUN_OK;
+    const size_t last = (size_t)(rows - 1) * H;
+    {
+        ProfScope p(prof, 7, st);
+        SUN_HIP_CHECK(launch_residual_norm(c, ws.x + last, ws.part + last, down_parts, rows, W.gf, 1, nullptr, ws.hA, nullptr, st));
+    }
+    float* out = logits ? logits : ws.logits;
+    {
+        ProfScope p(prof, 6, st);
+        SUN_HIP_CHECK(launch_proj(ProjLaunch{&W.lm, ws.hA, nullptr, 1, EPI_STORE, 1, out, c.vocab, 1}, st));
+    }
+    ProfScope p(prof, 7, st);
+    if (next) SUN_HIP_CHECK(launch_argmax(out, 1, c.vocab, ws.amax_val, ws.amax_idx, next, st));
+    return SUN_OK;
 }
 
 int sun_prefill(sun_kv_pool* pool_, const sun_weights* weights_, int n_tokens, const int32_t* token_ids,
@@ -1078,7 +1193,30 @@ int sun_prefill(sun_kv_pool* pool_, const sun_weights* weights_, int n_tokens, c
         });
         if (vrc != SUN_OK) return vrc;
     }
-    // Row r of a block is the decode step of position first + r over the one page table: its
+    if (c.act_dtype == SUN_BF16) {
+        // the longest blocks that the workspace holds; one that was sized for fewer tokens gets shorter ones
+        int block = kMaxBatchTile;
+        if (n_tokens > kMaxBatchTile)
+            for (int most = kMaxPrefillTile; most > kMaxBatchTile; most /= 2) {
+                const int r = prefill_block_rows(n_tokens, most);
+                if (carve_block(c, r, nullptr).bytes <= workspace_bytes) {
+                    block = r;
+                    break;
+                }
+            }
+        for (int done = 0; done < n_tokens; done += block) {
+            const int rows = std::min(n_tokens - done, block);
+            const Workspace ws = rows > kMaxBatchTile ? carve_block(c, rows, (char*)workspace) : carve(c, rows, max_pages, (char*)workspace);
+            const bool last_block = done + rows == n_tokens;
+            if (int rc = prefill_block(pool, W, ws, rows, first_pos + done, token_ids + done, page_table, max_pages,
+                                       last_block && (logits_out || next_token_out), logits_out, next_token_out,
+                                       flags & SUN_PROFILE, st))
+                return rc;
+        }
+        pool.ingested[model_id] += n_tokens;
+        return SUN_OK;
+    }
+    // fp32: row r of a block is the decode step of position first + r over the one page table: its
     // attention spans positions 0..first + r, and the K/V of all rows of the block are in the
     // pool before the block's attention starts, which is the causal forward of Eq. 2.
     const unsigned step_flags = flags & ~SUN_VALIDATE;

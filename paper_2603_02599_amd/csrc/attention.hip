@@ -140,6 +140,16 @@ __device__ __forceinline__ uint32_t bf16_pair_hi(float a, float b, float& ra, fl
     return ha | (hb << 16);
 }
 
+// bf16 hi/lo split of two fp32 values with the hardware converter (round to nearest even)
+__device__ __forceinline__ void split_pair(float x0, float x1, uint32_t& hi, uint32_t& lo) {
+    typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
+    typedef float fl2 __attribute__((ext_vector_type(2)));
+    const bf2 h = __builtin_convertvector(fl2{x0, x1}, bf2);
+    hi = __builtin_bit_cast(uint32_t, h);
+    const bf2 l = __builtin_convertvector(fl2{x0 - bf16_lo(hi), x1 - bf16_hi(hi)}, bf2);
+    lo = __builtin_bit_cast(uint32_t, l);
+}
+
 // ---------------------------------------------------------------------------------
 // split kernel, matrix-core variant
 // ---------------------------------------------------------------------------------
@@ -254,16 +264,6 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     for (int b = 0; b < NB; ++b) O[b] = f32x4{0.f, 0.f, 0.f, 0.f};
     float m_run = -INFINITY, l_run = 0.f;
 
-    // bf16 hi/lo split of two fp32 values with the hardware converter (round to nearest even)
-    auto split2 = [&](float x0, float x1, uint32_t& hi, uint32_t& lo) {
-        typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
-        typedef float fl2 __attribute__((ext_vector_type(2)));
-        const bf2 h = __builtin_convertvector(fl2{x0, x1}, bf2);
-        hi = __builtin_bit_cast(uint32_t, h);
-        const bf2 l = __builtin_convertvector(fl2{x0 - bf16_lo(hi), x1 - bf16_hi(hi)}, bf2);
-        lo = __builtin_bit_cast(uint32_t, l);
-    };
-
     // One pipeline step = one 32-token page pair.  On entry K of the pair has been requested
     // earlier and V is still in flight.  K of the following pair (of this item or of the wave's
     // next item) is requested as soon as the score MFMAs have consumed the K registers, V of the
@@ -312,7 +312,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             uint32_t hi, lo;
-            split2(p[2 * e], p[2 * e + 1], hi, lo);
+            split_pair(p[2 * e], p[2 * e + 1], hi, lo);
             ph[e] = hi;
             pl[e] = lo;
         }
@@ -516,18 +516,18 @@ hipError_t launch_attn_split(const KvPool& pool, int layer, const AttnPlan& plan
 // combine: merge the chunk partials of a request in chunk order
 // ---------------------------------------------------------------------------------
 struct CombineArgs {
-    const int32_t* chunk_off;
+    const int32_t* chunk_off;  // NULL: every request has `uniform` chunks
     const float* partial;
     float* out_f32;
     uint16_t* out_tiled;
     float* qscale;
-    int Hq, D, batch, out_mb;
+    int Hq, D, batch, out_mb, uniform;
 };
 
 __global__ __launch_bounds__(128) void attn_combine_kernel(CombineArgs a) {
     const int b = blockIdx.y, col = blockIdx.x * 128 + threadIdx.x;
     const int h = col / a.D, j = col % a.D;
-    const int c0 = a.chunk_off[b], c1 = a.chunk_off[b + 1];
+    const int c0 = a.chunk_off ? a.chunk_off[b] : b * a.uniform, c1 = a.chunk_off ? a.chunk_off[b + 1] : c0 + a.uniform;
     const size_t stride = (size_t)a.Hq * (a.D + 2);
     const float* p = a.partial + (size_t)c0 * stride + (size_t)h * (a.D + 2);
     // chunks are merged in order, eight at a time so that their loads are in flight together
@@ -589,11 +589,12 @@ __global__ __launch_bounds__(128) void attn_combine_kernel(CombineArgs a) {
     }
 }
 
-hipError_t launch_attn_combine(const sun_model_cfg& cfg, const AttnPlan& plan, int batch, float* out_f32,
-                               void* out_tiled, float* qscale, hipStream_t st) {
+static hipError_t launch_combine(const sun_model_cfg& cfg, const int32_t* chunk_off, int uniform, const float* partial,
+                                 int batch, float* out_f32, void* out_tiled, float* qscale, hipStream_t st) {
     CombineArgs a{};
-    a.chunk_off = plan.chunk_off;
-    a.partial = plan.partial;
+    a.chunk_off = chunk_off;
+    a.uniform = uniform;
+    a.partial = partial;
     a.out_f32 = out_f32;
     a.out_tiled = (uint16_t*)out_tiled;
     a.qscale = qscale;
@@ -605,6 +606,315 @@ hipError_t launch_attn_combine(const sun_model_cfg& cfg, const AttnPlan& plan, i
     if (cols % 128) return hipErrorInvalidValue;
     hipLaunchKernelGGL(attn_combine_kernel, dim3(cols / 128, batch), dim3(128), 0, st, a);
     return hipGetLastError();
+}
+
+hipError_t launch_attn_combine(const sun_model_cfg& cfg, const AttnPlan& plan, int batch, float* out_f32,
+                               void* out_tiled, float* qscale, hipStream_t st) {
+    return launch_combine(cfg, plan.chunk_off, 0, plan.partial, batch, out_f32, out_tiled, qscale, st);
+}
+
+// ---------------------------------------------------------------------------------
+// prefill: the causal attention of a block of consecutive positions of one request
+// ---------------------------------------------------------------------------------
+// Eq. 2's attention for `rows` rows at once.  A wave owns 32 query rows of one head, a workgroup four waves (the heads of a
+// group, or heads of neighbouring row blocks, all of one KV head), and the K and V of 32 keys pass through LDS once for
+// all of them: the row-by-row kernel above reads the whole cache once per row (1024 rows of the 8B shape: 240 us a layer
+// and 38 for its combine, here 53; 3000 rows behind 1003 keys: 2670 us a layer and 180, here 366).  Bound by the
+// matrix cores and the softmax between them (32 instructions of 32 cycles and some 200 vector instructions per wave
+// and tile, two waves per SIMD); both planes of q and of P, as in a decode step.
+//   S^T[key, row] = K . q^T, so that a lane holds 16 scores of one row and its running maximum needs one exchange;
+//   O^T[dim, row] += V^T . P^T, whose second operand is exactly the scores the lane holds, and whose rescaling needs no
+//   exchange at all.  K and V go from memory straight into three LDS slots, two tiles ahead.
+// blockIdx.x is the KV head: with eight of them each XCD keeps one head's K and V in its own L2.
+struct PrefillAttnArgs {
+    const uint16_t* kbase;
+    const uint16_t* vbase;
+    int64_t k_page, k_head, v_page, v_head;
+    const float* q;              // [rows, Hq*D], rotated
+    const int32_t* page_table;   // the request's row
+    uint16_t* out;               // two-plane tile of the O projection [rows, Hq*D] (one split), or
+    float* partial;              // [rows][splits][Hq][D + 2] (o[D], m, l)
+    int rows, first, Hq, G, n_pages, mb, tiles_per_split;
+    float qscale;                // log2(e) / sqrt(D)
+};
+
+template <int D>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void attn_prefill_kernel(PrefillAttnArgs a) {
+    constexpr int NWV = 4;
+    constexpr int KS = D / 16;              // k-steps of the score product
+    constexpr int DB = D / 32;              // 32-row blocks of the output (dims)
+    constexpr int OCT = D / 8;              // 16-byte units of a K row
+    constexpr int KI = 32 * OCT / 64;       // fetch instructions (1 KiB) of a tile's K; as many for its V
+    constexpr int PER = (2 * KI + NWV - 1) / NWV;
+    constexpr int TILE_UNITS = 2 * KI * 64; // K, then V: 16 KiB at D = 128
+    constexpr int NBUF = 3;
+    __shared__ u32x4 lds[NBUF * TILE_UNITS];
+
+    const int tid = threadIdx.x, lane = tid & 63, c32 = lane & 31, h = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // A wave's item is (32 rows, query head of the group); four consecutive items share a workgroup.  The longest start first.
+    const int n_items = (a.rows + 31) / 32 * a.G, item0 = (int)(gridDim.y - 1 - blockIdx.y) * NWV, item = item0 + wave;
+    const int blk = item / a.G, hkv = blockIdx.x, hq = hkv * a.G + item % a.G;
+    const int row = blk * 32 + c32;                                // this lane's query row
+    const int qpos = a.first + row;
+    const int total = a.first + a.rows;                            // positions that hold a key
+    const int my_first = a.first + blk * 32;                       // first position of the wave's rows
+    const auto tiles_of = [&](int bl) { return (a.first + min(a.rows, bl * 32 + 32) - 1) / 32 + 1; };
+    const int t_begin = blockIdx.z * a.tiles_per_split;            // this split's tiles of 32 keys
+    const int t_end = min(tiles_of(min(item0 + NWV - 1, n_items - 1) / a.G), t_begin + a.tiles_per_split);
+    const int my_end = item < n_items ? min(tiles_of(blk), t_end) : 0;
+
+    // q as the second operand (columns = query rows): 8 dims per lane and k-step, hi and lo bf16
+    bf16x8 qhi[KS], qlo[KS];
+    {
+        const float* qp = a.q + ((size_t)min(row, a.rows - 1) * a.Hq + hq) * D + h * 8;
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            const f32x4 v0 = *reinterpret_cast<const f32x4*>(qp + s * 16), v1 = *reinterpret_cast<const f32x4*>(qp + s * 16 + 4);
+            const float x[8] = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
+            u32x4 hi, lo;
+#pragma unroll
+            for (int p = 0; p < 4; ++p) {
+                float ra, rb;
+                hi[p] = bf16_pair_hi(x[2 * p] * a.qscale, x[2 * p + 1] * a.qscale, ra, rb);
+                lo[p] = pack_bf16(ra, rb);
+            }
+            qhi[s] = __builtin_bit_cast(bf16x8, hi);
+            qlo[s] = __builtin_bit_cast(bf16x8, lo);
+        }
+    }
+    // Fetch instruction j of a tile.  K (j < KI): LDS row rho holds the token whose score the MFMA puts into row rho; rho
+    // = 8 i + 4 h + e belongs to lane half h, which is to hold eight consecutive tokens of each page for the second
+    // product: token 8 h + 4 i + e (i = 0, 1), the same 16 further on for the second page.  The 16-byte units of a row are
+    // exchanged by the row's number, so that a fragment read meets every bank once.  V: fragment order, (page, 32-dim block)
+    // per instruction.
+    const uint16_t *kb = a.kbase + hkv * a.k_head, *vb = a.vbase + hkv * a.v_head;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) u32x4*)lds;
+    int pg_sel[PER];
+    uint32_t lane_off[PER];
+    bool is_k[PER];
+    uint32_t dst[PER];
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        const int j = min(wave + i * NWV, 2 * KI - 1);             // past the last one: that one again, the same bytes
+        is_k[i] = j < KI;
+        if (is_k[i]) {
+            const int rho = j * (64 / OCT) + lane / OCT, u = lane % OCT;
+            const int r16 = rho & 15, tok = 8 * ((r16 >> 2) & 1) + 4 * (r16 >> 3) + (r16 & 3);
+            pg_sel[i] = (j * (64 / OCT)) >> 4;
+            lane_off[i] = (tok * OCT + (u ^ (rho & (OCT - 1)))) * 16;
+        } else {
+            const int f = j - KI;
+            pg_sel[i] = f / DB;
+            lane_off[i] = (((f % DB) * 32 + c32) * 2 + h) * 16;
+        }
+        dst[i] = lds0 + j * 1024;
+    }
+    uint32_t fill = 0;
+    int fill_tile = t_begin;
+    auto page_of = [&](int p) {   // past the last page: the last one (its keys are masked)
+        return min(max(load_uniform(a.page_table + min(p, (total - 1) / kPageTokens)), 0), a.n_pages - 1);
+    };
+    int pgA = page_of(2 * t_begin), pgB = page_of(2 * t_begin + 1);
+    auto issue = [&]() {
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            const int64_t pg = pg_sel[i] ? pgB : pgA;
+            lds_dma16(is_k[i] ? kb + pg * a.k_page : vb + pg * a.v_page, lane_off[i], dst[i] + fill);
+        }
+        fill = fill + TILE_UNITS * 16 == NBUF * TILE_UNITS * 16 ? 0 : fill + TILE_UNITS * 16;
+        fill_tile = min(fill_tile + 1, t_end - 1);                 // past the end the last tile again (it is not read)
+        pgA = page_of(2 * fill_tile);
+        pgB = page_of(2 * fill_tile + 1);
+    };
+
+    f32x16 O[DB];
+#pragma unroll
+    for (int d = 0; d < DB; ++d)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) O[d][r] = 0.f;
+    float m_run = -INFINITY, l_run = 0.f;
+    bool poisoned = false;   // a key this row attends to has a V that is not finite
+
+    if (t_begin < t_end) {
+#pragma unroll
+        for (int b = 0; b < NBUF - 1; ++b) issue();
+    }
+    int at = 0;
+    for (int t = t_begin; t < t_end; ++t) {
+        // tile t has landed for every wave, and every wave is done with tile t - 1: its slot takes tile t + 2
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_waitcnt(0xc07f);
+        asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(PER * (NBUF - 2)) : "memory");
+        issue();
+        if (t < my_end) {
+            const u32x4* kt = lds + at * TILE_UNITS;
+            const u32x4* vt = kt + KI * 64 + lane;
+            f32x16 S;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) S[r] = 0.f;
+#pragma unroll
+            for (int s = 0; s < KS; ++s) {
+                const bf16x8 kf = __builtin_bit_cast(bf16x8, kt[c32 * OCT + ((s * 2 + h) ^ (c32 & (OCT - 1)))]);
+                S = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qhi[s], S, 0, 0, 0);
+                S = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qlo[s], S, 0, 0, 0);
+            }
+            // this lane: its query row, keys t*32 + 16 (r >> 3) + 8 h + (r & 7)
+            const bool diag = t * 32 + 31 > my_first;
+            if (diag) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) S[r] = t * 32 + 16 * (r >> 3) + 8 * h + (r & 7) <= qpos ? S[r] : -INFINITY;
+            }
+            float mloc = S[0];
+#pragma unroll
+            for (int r = 1; r < 16; ++r) mloc = fmaxf(mloc, S[r]);
+            mloc = fmaxf(mloc, __shfl_xor(mloc, 32));
+            // a split may begin behind a row's last key: all its scores are masked then, and its weights have to be zeros
+            const float m_new = fmaxf(m_run, mloc), m_use = m_new == -INFINITY ? 0.f : m_new;
+            const float alpha = __builtin_amdgcn_exp2f(m_run - m_use);
+            m_run = m_new;
+            float psum = 0.f;
+            bf16x8 phi[2], plo[2];
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                u32x4 hi, lo;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float p0 = __builtin_amdgcn_exp2f(S[k * 8 + 2 * e] - m_use), p1 = __builtin_amdgcn_exp2f(S[k * 8 + 2 * e + 1] - m_use);
+                    psum += p0 + p1;
+                    uint32_t wh, wl;
+                    split_pair(p0, p1, wh, wl);
+                    hi[e] = wh;
+                    lo[e] = wl;
+                }
+                phi[k] = __builtin_bit_cast(bf16x8, hi);
+                plo[k] = __builtin_bit_cast(bf16x8, lo);
+            }
+            l_run = l_run * alpha + psum;
+            if (__any(alpha != 1.f)) {
+#pragma unroll
+                for (int d = 0; d < DB; ++d)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) O[d][r] *= alpha;
+            }
+            // V of a key that a row does not see meets a zero weight, which only a finite V survives.  In the tiles where
+            // that can happen, keys whose V is not finite are left out of the product and mark the rows that do see them;
+            // slots past the prompt, which may hold anything, are left out as well.
+            uint32_t keep[2][4];
+            if (diag) {
+#pragma unroll
+                for (int k = 0; k < 2; ++k) {
+                    uint32_t bad = 0;   // this lane half's eight keys of page k
+#pragma unroll 1
+                    for (int d = 0; d < DB; ++d) {
+                        const u32x4 v = vt[(k * DB + d) * 64];
+#pragma unroll
+                        for (int w = 0; w < 4; ++w) {
+                            bad |= (v[w] & 0x00007f80u) == 0x00007f80u ? 1u << (2 * w) : 0u;
+                            bad |= (v[w] & 0x7f800000u) == 0x7f800000u ? 2u << (2 * w) : 0u;
+                        }
+                    }
+#pragma unroll
+                    for (int o = 1; o < 32; o <<= 1) bad |= __shfl_xor(bad, o);
+                    const int key0 = t * 32 + k * 16;
+                    const int held = min(max(total - key0 - 8 * h, 0), 8);   // of the eight, how many hold a key
+                    bad |= 0xffu & ~((1u << held) - 1u);
+#pragma unroll
+                    for (int w = 0; w < 4; ++w)
+                        keep[k][w] = (bad >> (2 * w) & 1 ? 0u : 0x0000ffffu) | (bad >> (2 * w + 1) & 1 ? 0u : 0xffff0000u);
+                    const uint32_t other = __shfl_xor(bad, 32), both = h ? (bad << 8) | other : bad | (other << 8);
+                    poisoned = poisoned || (both & ((1u << min(max(qpos - key0 + 1, 0), 16)) - 1u)) != 0;
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < 2; ++k)
+#pragma unroll
+                for (int d = 0; d < DB; ++d) {
+                    u32x4 v = vt[(k * DB + d) * 64];
+                    if (diag) {
+#pragma unroll
+                        for (int w = 0; w < 4; ++w) v[w] &= keep[k][w];
+                    }
+                    const bf16x8 vf = __builtin_bit_cast(bf16x8, v);
+                    O[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, phi[k], O[d], 0, 0, 0);
+                    O[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, plo[k], O[d], 0, 0, 0);
+                }
+        }
+        at = at + 1 == NBUF ? 0 : at + 1;
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // nothing is in flight into LDS when the workgroup ends
+    const float l_tot = poisoned ? __builtin_nanf("") : l_run + __shfl_xor(l_run, 32);
+    if (row >= a.rows) return;
+    if (a.partial) {
+        float* o = a.partial + (((size_t)row * gridDim.z + blockIdx.z) * a.Hq + hq) * (D + 2);
+#pragma unroll
+        for (int d = 0; d < DB; ++d)
+#pragma unroll
+            for (int i = 0; i < 8; ++i)   // an even number of floats apart, so 8-byte aligned
+                *reinterpret_cast<float2*>(o + d * 32 + (i >> 1) * 8 + h * 4 + (i & 1) * 2) = float2{O[d][i * 2], O[d][i * 2 + 1]};
+        if (h == 0) *reinterpret_cast<float2*>(o + D) = float2{m_run, l_tot};
+        return;
+    }
+    const float inv = 1.f / l_tot;
+    // lane: row c32, dims 32 d + 8 i + 4 h + 0..3: half of a 16-byte unit per plane
+    uint2* out = reinterpret_cast<uint2*>(a.out);
+#pragma unroll
+    for (int d = 0; d < DB; ++d)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            float y[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) y[e] = O[d][i * 4 + e] * inv;
+            uint2 hi, lo;
+            hi.x = pack_bf16(y[0], y[1]);
+            hi.y = pack_bf16(y[2], y[3]);
+            lo.x = pack_bf16(y[0] - bf16_lo(hi.x), y[1] - bf16_hi(hi.x));
+            lo.y = pack_bf16(y[2] - bf16_lo(hi.y), y[3] - bf16_hi(hi.y));
+            const int k8 = (hq * D + d * 32) / 8 + i;
+            out[atile_unit(ATile{a.mb}, 0, row, k8) * 2 + h] = hi;
+            out[atile_unit(ATile{a.mb}, 1, row, k8) * 2 + h] = lo;
+        }
+}
+
+// Key splits of a prefill block: enough workgroups for the 256 compute units, none of them shorter than eight tiles.
+int attn_prefill_splits(const sun_model_cfg& c, int rows, int first) {
+    const int G = c.n_q_heads / c.n_kv_heads;
+    const int wgs = ((rows + 31) / 32 * G + 3) / 4 * c.n_kv_heads, tiles = (first + rows - 1) / 32 + 1;
+    return max(1, min(256 / wgs, tiles / 8));
+}
+
+hipError_t launch_attn_prefill(const KvPool& pool, int layer, const float* q, const int32_t* page_table, int first, int rows,
+                               int splits, float* partial, void* out_tiled, hipStream_t st) {
+    const sun_model_cfg& c = pool.cfg;
+    const sun_kv_layout& L = pool.lay;
+    const int D = c.head_dim, G = c.n_q_heads / c.n_kv_heads;
+    if (L.k_dim != 1 || L.k_token != D || L.v_token != 1 || L.v_dim != kPageTokens || rows < 1 || splits < 1) return hipErrorInvalidValue;
+    PrefillAttnArgs a{};
+    a.kbase = pool.base + L.k_off + (int64_t)layer * L.k_layer;
+    a.vbase = pool.base + L.v_off + (int64_t)layer * L.v_layer;
+    a.k_page = L.k_page;
+    a.k_head = L.k_head;
+    a.v_page = L.v_page;
+    a.v_head = L.v_head;
+    a.q = q;
+    a.page_table = page_table;
+    a.out = (uint16_t*)out_tiled;
+    a.partial = splits > 1 ? partial : nullptr;
+    a.rows = rows;
+    a.first = first;
+    a.Hq = c.n_q_heads;
+    a.G = G;
+    a.n_pages = (int)L.n_pages;
+    a.mb = atile_for_rows(rows).MB;
+    a.tiles_per_split = ((first + rows - 1) / 32 + 1 + splits - 1) / splits;
+    a.qscale = kLog2e / sqrtf((float)D);
+    const dim3 grid(c.n_kv_heads, ((rows + 31) / 32 * G + 3) / 4, splits);
+    if (D == 64) hipLaunchKernelGGL(attn_prefill_kernel<64>, grid, dim3(256), 0, st, a);
+    else if (D == 128) hipLaunchKernelGGL(attn_prefill_kernel<128>, grid, dim3(256), 0, st, a);
+    else return hipErrorInvalidValue;
+    if (hipError_t e = hipGetLastError()) return e;
+    return splits > 1 ? launch_combine(c, nullptr, splits, partial, rows, nullptr, out_tiled, nullptr, st) : hipSuccess;
 }
 
 }  // namespace sun

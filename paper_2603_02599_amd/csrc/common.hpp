@@ -39,7 +39,8 @@ __host__ __device__ inline void attn_chunking(int n, int batch, int Hkv, int& n_
     n_small = (n - n_full * ch + kAttnSmall - 1) / kAttnSmall;
 }
 constexpr int kGroup = 128;         // quantisation group along K (Appendix A.1)
-constexpr int kMaxBatchTile = 256;  // rows one projection launch covers
+constexpr int kMaxBatchTile = 256;  // rows of a decode batch
+constexpr int kMaxPrefillTile = 2048;  // rows of a prefill block (bf16 projections only)
 
 // ---- bf16 <-> f32 (round to nearest even) ----
 __device__ __forceinline__ uint16_t f32_to_bf16_bits(float f) {
@@ -63,7 +64,7 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
 // stack amplifies that noise beyond the parity tolerance.
 // A [rows, K] is stored so that one staging step of the MFMA projection kernels is a linear
 // copy into LDS and each 16-byte unit (8 consecutive k of one row) is one lane's A operand of a
-// 32x32x16 MFMA.  With MB = number of 32-row blocks of real rows (1, 2, 4 or 8) the tiling has
+// 32x32x16 MFMA.  With MB = number of 32-row blocks of real rows (1, 2, 4 or a multiple of 8) the tiling has
 // 2*MB blocks, plane p of row block r at block p*MB + r:
 //   unit(p, b, k/8) = ((chunk * 8 + kk) * 2*MB + p*MB + b/32) * 64 + half * 32 + b%32
 // with chunk = k / 128, g = (k % 128) / 8, half = g / 8, kk = g % 8.  Lane-half `half` of k-step
@@ -73,7 +74,7 @@ struct ATile {
     int MB;
 };
 __host__ __device__ __forceinline__ ATile atile_for_rows(int rows) {
-    return ATile{rows <= 32 ? 1 : rows <= 64 ? 2 : rows <= 128 ? 4 : 8};
+    return ATile{rows <= 32 ? 1 : rows <= 64 ? 2 : rows <= 128 ? 4 : (rows + 255) / 256 * 8};
 }
 __host__ __device__ __forceinline__ size_t atile_unit(ATile t, int plane, int b, int k8) {
     const int chunk = k8 >> 4, g = k8 & 15;
@@ -129,6 +130,17 @@ __device__ __forceinline__ float qtile_inv(float amax) { return amax > 0.f ? kQM
 // in place.  Pays where an instruction reads long contiguous runs; see the attention kernel.
 typedef uint32_t u32x4_s __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ u32x4_s load_stream(const u32x4_s* p) { return __builtin_nontemporal_load(p); }
+
+// 16 bytes a lane from memory straight into LDS: lane i's, at base + lane_bytes, land at lds_byte + 16 i.  No register
+// holds the data and the compiler does not know of the request: whoever reads the place waits for it by hand (vmcnt,
+// then the workgroup's barrier).  base and lds_byte are the same for the whole wave.
+__device__ __forceinline__ void lds_dma16(const void* base, uint32_t lane_bytes, uint32_t lds_byte) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_byte), "v"(lane_bytes), "s"(base) : "memory");
+}
+// Read-only data of the launch at an address that is the same for the whole wave, through the scalar cache.
+__device__ __forceinline__ int32_t load_uniform(const int32_t* p) {
+    return *(const __attribute__((address_space(4))) int32_t*)(uintptr_t)p;
+}
 
 // ---- wave reductions (all lanes receive the result; fixed order => deterministic) ----
 __device__ __forceinline__ float wave_sum(float v) {

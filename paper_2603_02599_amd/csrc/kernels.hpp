@@ -15,7 +15,7 @@ struct ProjLaunch {
     const Mat* W;
     const void* A;         // tiled bf16 activations [rows, K]
     const float* qscale;   // W4 only: [K/128][MB*32] pairs (scale, sum of integers as int bits) of the fixed-point tile A
-    int rows;              // valid rows (<= 256)
+    int rows;              // valid rows (<= 256; bf16 weights: <= kMaxPrefillTile)
     int epilogue;
     int splits;            // split-K factor (EPI_STORE only); partial s is written at out + s*ld_rows*ldo
     float* out;
@@ -64,6 +64,14 @@ hipError_t launch_attn_split(const KvPool& pool, int layer, const AttnPlan& plan
 hipError_t launch_attn_combine(const sun_model_cfg& cfg, const AttnPlan& plan, int batch, float* out_f32,
                                void* out_tiled, float* qscale, hipStream_t st);
 
+// Causal attention of `rows` consecutive positions first .. first + rows - 1 of one request over positions 0 .. its own;
+// K and V of all of them are in the pool.  q fp32 [rows, Hq*d], rotated; out: two-plane tile of the O projection.
+// splits > 1: the keys are split and merged again, partial is scratch of [rows][splits][Hq][d + 2] floats.
+hipError_t launch_attn_prefill(const KvPool& pool, int layer, const float* q, const int32_t* page_table, int first, int rows,
+                               int splits, float* partial, void* out_tiled, hipStream_t st);
+// how many splits the block wants
+int attn_prefill_splits(const sun_model_cfg& c, int rows, int first);
+
 // ---------------- everything else (misc.hip) ----------------
 
 hipError_t launch_embed(const sun_model_cfg& cfg, const void* embed, const int32_t* tokens, int batch, float* x,
@@ -95,11 +103,13 @@ struct ServeArgs {
 // Between two steps (advance) and/or before the first (reset): record tokens, retire, grow, admit.
 hipError_t launch_serve(const ServeArgs& a, const int32_t* next, int32_t* tokens_out, int32_t* req_out, bool reset,
                         bool advance, hipStream_t st);
-hipError_t launch_rope_table(const sun_model_cfg& cfg, const int32_t* seq_lens, int batch, float* table,
+// position of row b: seq_lens[b], or first_pos + b when seq_lens is NULL
+hipError_t launch_rope_table(const sun_model_cfg& cfg, const int32_t* seq_lens, int first_pos, int batch, float* table,
                              hipStream_t st);
 // qkv partial sums [nparts][ld_rows][Nqkv] -> rotated q fp32 [batch, Hq*d]; K,V (bf16) appended to the pool.
+// seq_lens NULL: row b is position first_pos + b of one request, whose page-table row is page_tables.
 hipError_t launch_rope_append(const KvPool& pool, int layer, const float* qkv, int nparts, int ld_rows,
-                              const float* table, const int32_t* seq_lens, const int32_t* page_tables, int max_pages,
+                              const float* table, const int32_t* seq_lens, int first_pos, const int32_t* page_tables, int max_pages,
                               int batch, float* q_out, const void* q_norm, const void* k_norm, const void* bq, const void* bk,
                               const void* bv, hipStream_t st);
 hipError_t launch_swiglu_f32(const float* gu, int batch, int ffn, float* u, hipStream_t st);

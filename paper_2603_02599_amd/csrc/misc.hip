@@ -177,10 +177,10 @@ struct RopeScale {
     double factor, low_freq, high_freq;
 };
 
-__global__ __launch_bounds__(64) void rope_table_kernel(const int32_t* __restrict__ seq_lens, int d, double base,
+__global__ __launch_bounds__(64) void rope_table_kernel(const int32_t* __restrict__ seq_lens, int first_pos, int d, double base,
                                                         RopeScale rs, float* __restrict__ table) {
     const int b = blockIdx.x;
-    const double pos = (double)seq_lens[b];
+    const double pos = (double)(seq_lens ? seq_lens[b] : first_pos + b);
     for (int j = threadIdx.x; j < d / 2; j += 64) {
         double theta = pow(base, -2.0 * (double)j / (double)d);
         if (rs.scaling == 1) {
@@ -198,11 +198,11 @@ __global__ __launch_bounds__(64) void rope_table_kernel(const int32_t* __restric
     }
 }
 
-hipError_t launch_rope_table(const sun_model_cfg& cfg, const int32_t* seq_lens, int batch, float* table,
+hipError_t launch_rope_table(const sun_model_cfg& cfg, const int32_t* seq_lens, int first_pos, int batch, float* table,
                              hipStream_t st) {
     const RopeScale rs{cfg.rope_scaling, cfg.rope_original_max_position, (double)cfg.rope_factor,
                        (double)cfg.rope_low_freq_factor, (double)cfg.rope_high_freq_factor};
-    hipLaunchKernelGGL(rope_table_kernel, dim3(batch), dim3(64), 0, st, seq_lens, cfg.head_dim, (double)cfg.rope_base, rs,
+    hipLaunchKernelGGL(rope_table_kernel, dim3(batch), dim3(64), 0, st, seq_lens, first_pos, cfg.head_dim, (double)cfg.rope_base, rs,
                        table);
     return hipGetLastError();
 }
@@ -217,7 +217,7 @@ struct RopeArgs {
     float* q_out;
     uint16_t* pool;
     int64_t k_base, k_page, k_head, k_token, k_dim, v_base, v_page, v_head, v_token, v_dim;
-    int nparts, ld_rows, Hq, Hkv, D, max_pages, n_pages;
+    int nparts, ld_rows, Hq, Hkv, D, max_pages, n_pages, first_pos;
     const void* qn;  // head-norm gains [D] for q and k heads, or NULL (no head norm)
     const void* kn;
     const void *bq, *bk, *bv;  // projection biases [Hq*D], [Hkv*D], [Hkv*D] (element type as the gains), or NULL
@@ -229,8 +229,9 @@ __global__ __launch_bounds__(64) void rope_append_kernel(RopeArgs a) {
     const int b = blockIdx.y, hh = blockIdx.x, D = a.D, half = D / 2;
     const int Nqkv = (a.Hq + 2 * a.Hkv) * D;
     // lengths and page ids are validated on the host under SUN_VALIDATE; clamp so bad input cannot fault
-    const int L = min(max(a.seq_lens[b], 0), a.max_pages * kPageTokens - 1);
-    const int page = min(max(a.page_tables[(size_t)b * a.max_pages + L / kPageTokens], 0), a.n_pages - 1);
+    const int L = min(max(a.seq_lens ? a.seq_lens[b] : a.first_pos + b, 0), a.max_pages * kPageTokens - 1);
+    const int32_t* pt = a.page_tables + (a.seq_lens ? (size_t)b * a.max_pages : 0);
+    const int page = min(max(pt[L / kPageTokens], 0), a.n_pages - 1);
     const int slot = L % kPageTokens;
     const float* src = a.qkv + (size_t)b * Nqkv + (size_t)hh * D;
     const size_t pstride = (size_t)a.ld_rows * Nqkv;
@@ -283,7 +284,7 @@ __global__ __launch_bounds__(64) void rope_append_kernel(RopeArgs a) {
 }
 
 hipError_t launch_rope_append(const KvPool& pool, int layer, const float* qkv, int nparts, int ld_rows,
-                              const float* table, const int32_t* seq_lens, const int32_t* page_tables, int max_pages,
+                              const float* table, const int32_t* seq_lens, int first_pos, const int32_t* page_tables, int max_pages,
                               int batch, float* q_out, const void* q_norm, const void* k_norm, const void* bq, const void* bk,
                               const void* bv, hipStream_t st) {
     const sun_model_cfg& c = pool.cfg;
@@ -293,6 +294,7 @@ hipError_t launch_rope_append(const KvPool& pool, int layer, const float* qkv, i
     a.qkv = qkv;
     a.table = table;
     a.seq_lens = seq_lens;
+    a.first_pos = first_pos;
     a.page_tables = page_tables;
     a.q_out = q_out;
     a.pool = pool.base;

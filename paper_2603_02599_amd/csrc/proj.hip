@@ -445,6 +445,202 @@ void proj_tall_kernel(ProjArgs a) {
     }
 }
 
+// ---------------------------------------------------------------------------------
+// bf16 weights, many rows (prefill blocks; the vocabulary projection above 128 rows)
+// ---------------------------------------------------------------------------------
+// Bound by the matrix cores (and the clock they leave: see the figures).  A workgroup of eight waves covers 256 rows x
+// 256 columns; a wave owns 64 rows x 128 columns, so that the eight fragments it reads from LDS per k-step feed sixteen
+// matrix instructions (both activation planes against the same weight fragment).  Both operands are stored in
+// fragment order, so a stage (two k-steps, 48 fragments of 1 KiB) goes from memory straight into one of three LDS
+// slots, two stages ahead, without passing through registers.  The requests leave between the matrix instructions,
+// where the memory pipeline's back pressure is covered: all of a stage's requests at its start cost 10 %.
+// Larger tiles than the kernel above because what limits there is the traffic from L2 into the compute units:
+// 24 bytes per cycle here against 47.  Measured, 28 672 x 4096, both planes counted: 1024 rows 369 us = 1.30 PFLOP/s,
+// 2048 rows 721 us = 1.33 (four / eight launches of the 128 x 256 kernel: 505 / 1010 us; the instructions alone, no
+// loads: 322 / 591; the same code on zeros, which draw less power and leave the clock up: 294 / 583).
+// Measured and left out: 128 x 256 tiles in this scheme (1024 rows 430 us; at 256 rows no faster than the kernel
+// above), four or five slots, a deeper ring for the weights than for the activations, streaming loads for the
+// weights (the row tiles share them through L2: 775 us), a rotated start along k, other workgroup orders.
+template <int EPI>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void proj_wide_kernel(ProjArgs a) {
+    constexpr int RB = 8, CB = 8;                       // row blocks and column strips of a workgroup
+    constexpr int AF = 2 * 2 * RB, WF = 2 * CB;         // operand fragments (1 KiB) of a stage: two k-steps
+    constexpr int STAGE_UNITS = (AF + WF) * 64;         // 16-byte units (48 KiB)
+    constexpr int NBUF = 3;
+    constexpr int WA = AF / 8, PER = WA + WF / 8;       // fragments a wave fetches per stage: four of A, two of W
+    __shared__ u32x4 lds_all[NBUF * STAGE_UNITS];
+
+    const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int ch = wave & 1, rh = wave >> 1;            // column half, 64-row group
+    const int n_strips = a.N / 32;
+    const int strip0 = blockIdx.x * CB;
+    const int split = blockIdx.y;
+    const int mb_off = blockIdx.z * RB;
+    const int s0 = split * a.stages_per_split;
+    const int s1 = min(a.n_stages, s0 + a.stages_per_split);
+    const int n = s1 - s0;
+    const size_t kch8 = (size_t)(a.K / 128) * 8;        // k-steps of a strip
+
+    // what this wave fetches of every stage, activations first
+    const u32x4* src[PER];
+    uint32_t dst[PER];
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) u32x4*)lds_all;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        if (i < WA) {
+            const int f = wave * WA + i, ks = f / (2 * RB), blk = f % (2 * RB);
+            const int gb = blk < RB ? mb_off + blk : a.mb_rows + mb_off + (blk - RB);  // hi planes, then lo planes
+            src[i] = a.A + ((size_t)(s0 * 2 + ks) * (2 * a.mb_rows) + gb) * 64;
+            dst[i] = lds0 + f * 1024;
+        } else {
+            const int f = wave * (WF / 8) + (i - WA), ks = f / CB, blk = f % CB;
+            const int strip = min(strip0 + blk, n_strips - 1);  // past the last strip: any valid one, its result is dropped
+            src[i] = a.W + ((size_t)strip * kch8 + s0 * 2 + ks) * 64;
+            dst[i] = lds0 + (AF + f) * 1024;
+        }
+    }
+    const size_t step_a = (size_t)4 * a.mb_rows * 64, step_w = 128;  // units from one stage to the next
+    uint32_t fill = 0;                                  // ring offset and number of the stage that is requested next
+    int fill_st = 0;
+    auto issue = [&](int i) {                           // past the end the last stage again (it is not read)
+        lds_dma16(src[i], lane * 16, dst[i] + fill);
+        if (fill_st + 1 < n) src[i] += i < WA ? step_a : step_w;
+    };
+    auto issued = [&]() {
+        fill += STAGE_UNITS * 16;
+        if (fill == NBUF * STAGE_UNITS * 16) fill = 0;
+        ++fill_st;
+    };
+    f32x16 acc[4][2];
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int m = 0; m < 2; ++m)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[s][m][r] = 0.f;
+
+    struct Frags {
+        u32x4 a[2][2], w[4];
+    };
+    int at = 0;                                         // ring slot that is read
+    auto read = [&](Frags& f, int ks) {
+        const u32x4* p = lds_all + at * STAGE_UNITS + lane;
+#pragma unroll
+        for (int pl = 0; pl < 2; ++pl)
+#pragma unroll
+            for (int m = 0; m < 2; ++m) f.a[pl][m] = p[(ks * 2 * RB + pl * RB + rh * 2 + m) * 64];
+#pragma unroll
+        for (int s = 0; s < 4; ++s) f.w[s] = p[(AF + ks * CB + ch * 4 + s) * 64];
+    };
+    // 16 matrix instructions, the requests i0 .. i0 + 2 of the stage being fetched between them
+    auto mma = [&](const Frags& f, int i0) {
+#pragma unroll
+        for (int pl = 0; pl < 2; ++pl)
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+#pragma unroll
+                for (int m = 0; m < 2; ++m)
+                    acc[s][m] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, f.a[pl][m]),
+                                                                      __builtin_bit_cast(bf16x8, f.w[s]), acc[s][m], 0, 0, 0);
+                const int g = pl * 4 + s;
+                if ((g & 1) && g < 6) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    issue(i0 + (g >> 1));
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+    };
+    // The oldest stage in flight has landed for every wave, and every wave has its fragments of the stage before in
+    // registers, so that stage's slot may be overwritten.
+    auto enter = [&]() {
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_waitcnt(0xc07f);             // lgkmcnt(0)
+        asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(PER * (NBUF - 2)) : "memory");
+    };
+    if (n > 0) {
+#pragma unroll
+        for (int b = 0; b < NBUF - 1; ++b) {
+#pragma unroll
+            for (int i = 0; i < PER; ++i) issue(i);
+            issued();
+        }
+        Frags f0, f1;
+        enter();
+        read(f0, 0);
+        for (int st = 0; st < n; ++st) {
+            read(f1, 1);
+            __builtin_amdgcn_sched_barrier(0);
+            mma(f0, 0);
+            mma(f1, 3);
+            issued();
+            at = at + 1 == NBUF ? 0 : at + 1;
+            if (st + 1 < n) {
+                enter();
+                read(f0, 0);
+            }
+        }
+    }
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");  // nothing is in flight into LDS any more
+    const int my_strip = strip0 + ch * 4;
+    const int col = lane & 31, row0 = (mb_off + rh * 2) * 32;
+    if constexpr (EPI == EPI_SWIGLU) {
+        // A strip's 32 columns are 16 gate columns followed by the 16 up columns of the same u columns (the
+        // packing order of the pair): lane c < 16 fetches its up value from lane c + 16 and owns u column
+        // strip*16 + c.  The results leave as the tile the down projection reads: hi and lo plane, 16-byte units
+        // of 8 consecutive u columns of one row, gathered through the wave's own piece of the idle ring.
+        uint16_t* sw = reinterpret_cast<uint16_t*>(lds_all) + (size_t)wave * (2 * 64 * 16);
+        u32x4* tile = reinterpret_cast<u32x4*>(a.out);
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            const int nb = my_strip + s;
+#pragma unroll
+            for (int m = 0; m < 2; ++m)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const float g = acc[s][m][r];
+                    const float up = __shfl_xor(g, 16);
+                    const float y = g / (1.f + __expf(-g)) * up;
+                    const uint16_t hi = f32_to_bf16_bits(y);
+                    const uint16_t lo = f32_to_bf16_bits(y - bf16_bits_to_f32(hi));
+                    const int rl = m * 32 + 8 * (r >> 2) + 4 * half + (r & 3);  // row inside the wave's rows
+                    if (col < 16) {
+                        sw[(0 * 64 + rl) * 16 + col] = hi;
+                        sw[(1 * 64 + rl) * 16 + col] = lo;
+                    }
+                }
+            __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): the wave's LDS writes have landed (no other wave reads them)
+            __builtin_amdgcn_wave_barrier();
+            if (nb < n_strips) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {    // 64 rows x 2 units x 2 planes = 256 units, 64 lanes
+                    const int idx = i * 64 + lane;
+                    const int plane = idx >> 7, rem = idx & 127, rl = rem >> 1, un = rem & 1;
+                    const u32x4 v = *reinterpret_cast<const u32x4*>(sw + ((size_t)plane * 64 + rl) * 16 + un * 8);
+                    if (row0 + rl < a.rows) tile[atile_unit(ATile{a.mb_rows}, plane, row0 + rl, nb * 2 + un)] = v;
+                }
+            }
+            __builtin_amdgcn_s_waitcnt(0xc07f);  // the reads are done before the next strip overwrites the piece
+            __builtin_amdgcn_wave_barrier();
+        }
+    } else {
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            const int nb = my_strip + s;
+            if (nb >= n_strips) continue;
+            float* o = a.out + (size_t)split * a.ld_rows * a.ldo + nb * 32 + col;
+#pragma unroll
+            for (int m = 0; m < 2; ++m)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int b = row0 + m * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
+                    if (b < a.rows) o[(size_t)b * a.ldo] = acc[s][m][r];
+                }
+        }
+    }
+}
+
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef int i32x16 __attribute__((ext_vector_type(16)));
 
@@ -644,6 +840,18 @@ static hipError_t launch_proj_tall(const ProjArgs& a, int epilogue, int splits, 
     return hipGetLastError();
 }
 
+static hipError_t launch_proj_wide(const ProjArgs& a, int epilogue, int splits, hipStream_t st) {
+    dim3 grid((a.N / 32 + 7) / 8, splits, (a.rows + 255) / 256);
+    if (epilogue == EPI_SWIGLU) {
+        if (splits != 1) return hipErrorInvalidValue;
+        hipLaunchKernelGGL((proj_wide_kernel<EPI_SWIGLU>), grid, dim3(512), 0, st, a);
+        return hipGetLastError();
+    }
+    if (epilogue != EPI_STORE) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((proj_wide_kernel<EPI_STORE>), grid, dim3(512), 0, st, a);
+    return hipGetLastError();
+}
+
 // Split-K factor of the launch above 128 rows (bf16; workgroups of 128 rows x 256 columns).  All workgroups do
 // equal work and one round of at most 256 of them is wanted: the largest split that stays within the round
 // (each split costs a slab of partial sums, but the matrix-core time of a workgroup goes with its stages;
@@ -736,13 +944,36 @@ static ProjShape proj_pick(const Mat& W, int rows, int max_splits) {
     return best;
 }
 
-static bool use_tall(const Mat& W, int rows) {
-    // the wide vocabulary projection runs several rounds of workgroups, two of the strip kernel's on a compute unit
-    // at a time: measured faster there than one of these
-    return W.kind == MAT_BF16_PACKED && rows > 128 && (W.N / 32 + 7) / 8 <= 256;
+// Which kernel multiplies more than 128 rows (bf16).  256 x 256 tiles want whole rounds of 256 workgroups without a
+// split along k: a prefill block (rows > 256) and the vocabulary projection have them (8B shape, 256 rows: lm_head 405
+// us against 535 with the strip kernel).  A batch's other projections do not: the 128 x 256 tiles of the tall kernel
+// take 24 / 40 / 75 / 130 us (o, q/k/v, down, gate/up) where the wide kernel, split finer, takes 27 to 40 % longer.
+static bool use_wide(const Mat& W, int rows) {
+    return W.kind == MAT_BF16_PACKED && (rows > kMaxBatchTile || (rows > 128 && (W.N / 32 + 7) / 8 >= 256));
+}
+static bool use_tall(const Mat& W, int rows) { return W.kind == MAT_BF16_PACKED && rows > 128 && !use_wide(W, rows); }
+
+// Split-K factor of a wide launch: whole rounds of 256 workgroups cost stages x 0.95 us (2048 cycles of matrix
+// instructions at the clock they leave) plus about 8 us each, a split the writing and reading of its slab.
+static int wide_pick_splits(const Mat& W, int rows, int max_splits) {
+    const int stages = W.K / 32;
+    const long long tiles = (long long)((W.N / 32 + 7) / 8) * ((rows + 255) / 256);
+    int best = 1;
+    double best_us = 0;
+    for (int s = 1; s <= max(1, min(max_splits, stages / 8)); ++s) {
+        const int sps = (stages + s - 1) / s;
+        if ((stages + sps - 1) / sps != s) continue;
+        const double us = (double)((tiles * s + 255) / 256) * (sps * 0.95 + 8.0) + (double)s * rows * W.N * 8e-6 / 5.0;
+        if (best_us == 0 || us < best_us) {
+            best_us = us;
+            best = s;
+        }
+    }
+    return best;
 }
 
 int proj_pick_splits(const Mat& W, int rows, int max_splits) {
+    if (use_wide(W, rows)) return wide_pick_splits(W, rows, max_splits);
     if (use_tall(W, rows)) return tall_pick_splits(W, rows, max_splits);
     return proj_pick(W, rows, max_splits).splits;
 }
@@ -780,7 +1011,7 @@ hipError_t launch_proj(const ProjLaunch& p, hipStream_t st) {
     const Mat& W = *p.W;
     const bool w4 = W.kind == MAT_W4_PACKED;
     if (!w4 && W.kind != MAT_BF16_PACKED) return hipErrorInvalidValue;
-    if (p.rows < 1 || p.rows > kMaxBatchTile || W.N % 32 || W.K % 128) return hipErrorInvalidValue;
+    if (p.rows < 1 || p.rows > (w4 ? kMaxBatchTile : kMaxPrefillTile) || W.N % 32 || W.K % 128) return hipErrorInvalidValue;
     const ATile at = atile_for_rows(p.rows);
     ProjArgs a{};
     a.W = (const u32x4*)W.w;
@@ -814,6 +1045,13 @@ hipError_t launch_proj(const ProjLaunch& p, hipStream_t st) {
         }
         if (t.mb == 2) return launch_proj_nw<2, 128>(a, nw, p.epilogue, splits, t.mtiles, st);
         return launch_proj_nw<4, 128>(a, nw, p.epilogue, splits, t.mtiles, st);
+    }
+    if (use_wide(W, p.rows)) {
+        const int want = p.epilogue == EPI_SWIGLU ? 1 : max(1, p.splits);
+        const int stg = kch * 4, per = (stg + want - 1) / want;
+        a.n_stages = stg;
+        a.stages_per_split = per;
+        return launch_proj_wide(a, p.epilogue, (stg + per - 1) / per, st);
     }
     if (use_tall(W, p.rows)) {
         const int want = p.epilogue == EPI_SWIGLU ? 1 : max(1, p.splits);

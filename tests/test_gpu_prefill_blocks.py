@@ -1,0 +1,111 @@
+"""The bf16 prefill in blocks of up to 2048 rows: 256 x 256 projection tiles, masked attention over the paged cache with the
+keys of a block shared by its rows (split and merged again where there are few rows), the head for the last row only.
+Sizes where that can go wrong: one row past a row tile, ragged tails, blocks that continue a cached prefix off a page or
+tile boundary, few rows behind many keys, head counts that do not fill a workgroup, both head widths.  Against the
+oracle's cache-free causal forward, with the bounds of test_gpu_prefill.py."""
+import dataclasses
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2603_02599_amd import binding as sun, workloads as wl
+from test_gpu_prefill import PREFILL_ABS_TOL, _one_request_case, _prefill, _written_mask
+
+pytestmark = pytest.mark.gpu
+
+G1 = dataclasses.replace(wl.SMALL128, name="small_g1", n_q_heads=4, n_kv_heads=4)
+G3 = dataclasses.replace(wl.SMALL128, name="small_g3", n_q_heads=6, n_kv_heads=2)
+
+
+@pytest.fixture(scope="module")
+def H():
+    import gpu_harness
+    assert torch.cuda.is_available(), "these tests need the MI355X"
+    sun.lib()
+    return gpu_harness
+
+
+@pytest.mark.parametrize("shape,T,cuts", [
+    (wl.SMALL128, 257, []), (wl.SMALL128, 700, [40, 641]), (wl.SMALL128, 450, [1, 33, 47]), (wl.SMALL_G5, 330, [300]),
+    (wl.TINY_Q, 290, [5]), (G1, 300, [270]), (G3, 100, [31])],
+    ids=["g4-257", "g4-few-rows-behind-640-keys", "g4-off-tile", "g5-330", "d64-g2-290", "g1-300", "g3-100"])
+def test_prefill_blocks_equal_the_causal_forward(H, shape, T, cuts):
+    H.say(f"prefill blocks {shape.name} T={T} cuts={cuts}")
+    case, rng = _one_request_case(H, shape, "bf16", T, seed=700 + T)
+    toks = rng.integers(0, shape.vocab, size=T).astype(np.int32)
+    before = H.to_np(case.pool_mem).copy()
+    st, table = H.layout_strides(case.lay), case.work.page_tables[0]
+    logits, K, V = H.orc.full_forward(H.orc.make_cfg(shape), case.oracle_params(), toks, round_kv=True, want_kv=True)
+    expect = before.copy()
+    H.orc.kv_ingest(expect, st, H.orc.bf16_bits(K), H.orc.bf16_bits(V), 0, table)
+    for a, b in zip([0] + cuts, cuts + [T]):
+        got, nxt = _prefill(case, toks[a:b], a, 1)
+        H.check_logits(got[None], logits[b - 1][None], "bf16")
+        H.check_next_tokens(np.array([nxt]), logits[b - 1][None], 2e-2)
+    after = H.to_np(case.pool_mem).copy()
+    mask = _written_mask(H, st, after.size, shape.n_layers, shape.n_kv_heads, shape.head_dim, table, 0, T)
+    H.check_appended_kv(after, expect, before, mask, "bf16", abs_tol=PREFILL_ABS_TOL, max_off_frac=0.6)
+
+
+def test_prefill_takes_a_workspace_sized_for_256_tokens(H):
+    """A workspace that serves 256 rows serves a longer prompt in shorter blocks, with the same result up to rounding."""
+    T = 600
+    case, rng = _one_request_case(H, wl.SMALL128, "bf16", T, seed=741)
+    toks = torch.from_numpy(rng.integers(0, wl.SMALL128.vocab, size=T).astype(np.int32)).cuda()
+    row = case.tables[0].contiguous()
+    full, least = (sun.sun_prefill_workspace_bytes(case.cfg, n, row.numel()) for n in (T, 256))
+    assert least <= full
+    got = []
+    for nbytes in (full, least):
+        ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+        logits = torch.full((wl.SMALL128.vocab,), float("nan"), device="cuda")
+        sun.sun_prefill(case.pool, case.weights, toks, row, 0, 0, logits, None, ws, flags=sun.SUN_VALIDATE)
+        torch.cuda.synchronize()
+        got.append(logits.cpu().numpy())
+    H.check_logits(got[1][None], got[0][None], "bf16")
+    with pytest.raises(sun.SunError) as e:
+        sun.sun_prefill(case.pool, case.weights, toks, row, 0, 0, logits, None, ws[:least - 256], flags=0)
+    assert e.value.status == 4
+
+
+@pytest.mark.parametrize("bad_at,T", [(20, 50), (0, 33), (63, 300)])
+def test_a_row_that_is_not_finite_reaches_later_rows_only(H, bad_at, T):
+    """A prompt token whose embedding is NaN: the entries before it are those of the prompt without it, bit for bit in the
+    first layer and finite in all, the entries after it and the logits are NaN (it is attended to by every later row)."""
+    shape = wl.SMALL128
+    case, rng = _one_request_case(H, shape, "bf16", T, seed=750 + bad_at)
+    toks = rng.integers(1, shape.vocab, size=T).astype(np.int32)
+    clean, _ = _prefill(case, toks, 0, 0)
+    ok = H.to_np(case.pool_mem).copy()
+    case.w["embed"][0] = float("nan")
+    toks[bad_at] = 0
+    got, _ = _prefill(case, toks, 0, 0)
+    after = H.to_np(case.pool_mem).copy()
+    case.w["embed"][0] = 0.0
+    st, table = H.layout_strides(case.lay), case.work.page_tables[0]
+    sizes = (after.size, shape.n_layers, shape.n_kv_heads, shape.head_dim, table)
+    early = _written_mask(H, st, *sizes, 0, bad_at) if bad_at else np.zeros(after.size, bool)
+    late = _written_mask(H, st, *sizes, bad_at, T - bad_at)
+    assert np.isfinite(clean).all() and np.isnan(got).all()
+    value = lambda bits: (bits.astype(np.uint32) << 16).view(np.float32)
+    assert np.array_equal(after[early], ok[early])      # every operation of an earlier row is the same one
+    layer = np.zeros(after.size, bool)
+    layer[int(st["k_layer"]):] = True                   # from the second layer on; in the first only the token's own entry is NaN
+    assert np.isnan(value(after[late & layer])).all()
+
+
+@pytest.mark.parametrize("rows", [129, 200, 256])
+def test_wide_vocabulary_projection(H, rows):
+    """The vocabulary projection above 128 rows (256 x 256 tiles, a ragged last column tile) against float64."""
+    shape = dataclasses.replace(wl.SMALL128, name="small_wide", vocab=65536 + 96)
+    cfg = sun.make_cfg(shape, "bf16")
+    w = wl.make_weights(shape, "bf16", H.DEV, 77)
+    W = sun.sun_weights_create(cfg, w)
+    x = torch.randn((rows, shape.hidden), device=H.DEV, generator=torch.Generator(device=H.DEV).manual_seed(rows))
+    out = torch.full((rows, shape.vocab), float("nan"), device=H.DEV)
+    ws = torch.empty(sun.sun_workspace_bytes(cfg, rows, 1), dtype=torch.uint8, device=H.DEV)
+    sun.sun_linear(W, 0, 4, x, out, ws)
+    torch.cuda.synchronize()
+    want = x.double() @ w["wlm"].double().t()
+    assert ((out.double() - want).abs() <= 2e-4 + 1e-5 * want.abs()).all()
