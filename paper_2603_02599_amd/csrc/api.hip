@@ -103,7 +103,7 @@ static sun_kv_layout make_layout(const sun_model_cfg& c, int64_t n_pages) {
 struct Workspace {
     float* x;
     void *hA, *aA, *uA;         // bf16 tiled activations
-    float *h32, *a32, *u32, *gu32, *qkv32, *o32;  // fp32 path
+    float *a32, *u32, *qkv32;   // fp32 path
     float* qs;           // 4-bit path: (scale, integer sum) of every row and 128-wide group of the current activations
     float* part;
     float* q;
@@ -140,12 +140,9 @@ static Workspace carve(const sun_model_cfg& c, int batch, int max_pages, char* b
         w.qs = (float*)take((size_t)(std::max(std::max(H, QD), F) / 128 + 1) * mb * 32 * 8);  // scale and integer sum per row and group
         w.part = (float*)take(std::max((size_t)kMaxSplits * batch * std::max(Nqkv, H), (size_t)kMaxSplitsWide * batch * 2 * F) * 4);
     } else {
-        w.h32 = (float*)take((size_t)batch * H * 4);
         w.a32 = (float*)take((size_t)batch * QD * 4);
         w.u32 = (float*)take((size_t)batch * F * 4);
-        w.gu32 = (float*)take((size_t)batch * 2 * F * 4);
         w.qkv32 = (float*)take((size_t)batch * Nqkv * 4);
-        w.o32 = (float*)take((size_t)batch * H * 4);
     }
     const size_t mc = attn_max_chunks(batch, max_pages, c.n_kv_heads);
     w.plan.max_chunks = (int)std::min<size_t>(mc, 0x7fffffff);
@@ -748,9 +745,8 @@ static int step_impl(sun_kv_pool* pool_, const sun_weights* weights_, bool want_
 
     {
         ProfScope p(prof, 7, st);
-        SUN_HIP_CHECK(launch_embed(c, W.embed, token_ids, batch, ws.x, st));
-        SUN_HIP_CHECK(launch_rope_table(c, seq_lens, 0, batch, ws.table, st));
-        SUN_HIP_CHECK(launch_attn_plan(ws.plan, seq_lens, 1, batch, page_tables, max_pages, (int)pool.lay.n_pages, c.n_kv_heads, st));
+        SUN_HIP_CHECK(launch_step_begin(c, W.embed, token_ids, seq_lens, batch, ws.x, ws.table, ws.plan, page_tables, max_pages,
+                                        (int)pool.lay.n_pages, st));
     }
     int down_parts = 0;
     for (int l = 0; l < c.n_layers; ++l) {
@@ -759,7 +755,7 @@ static int step_impl(sun_kv_pool* pool_, const sun_weights* weights_, bool want_
         if (bf) {
             {
                 ProfScope p(prof, 7, st);
-                SUN_HIP_CHECK(launch_residual_norm(c, ws.x, ws.part, down_parts, batch, L.g1, batch, nullptr, ws.hA,
+                SUN_HIP_CHECK(launch_residual_norm(c, ws.x, ws.part, down_parts, batch, L.g1, batch, ws.hA,
                                                    W.quant ? ws.qs : nullptr, st));
             }
             const int sq = proj_pick_splits(L.qkv, batch, kMaxSplits);
@@ -775,9 +771,7 @@ static int step_impl(sun_kv_pool* pool_, const sun_weights* weights_, bool want_
             }
         } else {
             ProfScope p(prof, 7, st);
-            if (l > 0) SUN_HIP_CHECK(launch_residual_norm(c, ws.x, ws.o32, 1, batch, L.g1, batch, ws.h32, nullptr, nullptr, st));
-            else SUN_HIP_CHECK(launch_residual_norm(c, ws.x, nullptr, 0, batch, L.g1, batch, ws.h32, nullptr, nullptr, st));
-            SUN_HIP_CHECK(launch_proj_f32(L.qkv, ws.h32, batch, ws.qkv32, st));
+            SUN_HIP_CHECK(launch_proj_f32(L.qkv, ws.x, batch, L.g1, c.rms_eps, F32_STORE, ws.qkv32, st));
             SUN_HIP_CHECK(launch_rope_append(pool, l, ws.qkv32, 1, batch, ws.table, seq_lens, 0, page_tables, max_pages,
                                              batch, ws.q, L.qn, L.kn, L.bq, L.bk, L.bv, st));
         }
@@ -800,7 +794,7 @@ static int step_impl(sun_kv_pool* pool_, const sun_weights* weights_, bool want_
             }
             {
                 ProfScope p(prof, 7, st);
-                SUN_HIP_CHECK(launch_residual_norm(c, ws.x, ws.part, so, batch, L.g2, batch, nullptr, ws.hA,
+                SUN_HIP_CHECK(launch_residual_norm(c, ws.x, ws.part, so, batch, L.g2, batch, ws.hA,
                                                    W.quant ? ws.qs : nullptr, st));
             }
             if (!W.quant && batch > 64) {
@@ -831,18 +825,15 @@ static int step_impl(sun_kv_pool* pool_, const sun_weights* weights_, bool want_
             down_parts = sd;
         } else {
             ProfScope p(prof, 7, st);
-            SUN_HIP_CHECK(launch_proj_f32(L.o, ws.a32, batch, ws.o32, st));
-            SUN_HIP_CHECK(launch_residual_norm(c, ws.x, ws.o32, 1, batch, L.g2, batch, ws.h32, nullptr, nullptr, st));
-            SUN_HIP_CHECK(launch_proj_f32(L.gu, ws.h32, batch, ws.gu32, st));
-            SUN_HIP_CHECK(launch_swiglu_f32(ws.gu32, batch, c.ffn, ws.u32, st));
-            SUN_HIP_CHECK(launch_proj_f32(L.down, ws.u32, batch, ws.o32, st));
+            SUN_HIP_CHECK(launch_proj_f32(L.o, ws.a32, batch, nullptr, 0.f, F32_ADD, ws.x, st));
+            SUN_HIP_CHECK(launch_proj_f32(L.gu, ws.x, batch, L.g2, c.rms_eps, F32_SWIGLU, ws.u32, st));
+            SUN_HIP_CHECK(launch_proj_f32(L.down, ws.u32, batch, nullptr, 0.f, F32_ADD, ws.x, st));
         }
     }
     if (!with_head) return SUN_OK;  // a caller that only wants the cache entries (all but the last prefill block)
-    {
+    if (bf) {
         ProfScope p(prof, 7, st);
-        if (bf) SUN_HIP_CHECK(launch_residual_norm(c, ws.x, ws.part, down_parts, batch, W.gf, batch, nullptr, ws.hA, nullptr, st));
-        else SUN_HIP_CHECK(launch_residual_norm(c, ws.x, ws.o32, 1, batch, W.gf, batch, ws.h32, nullptr, nullptr, st));
+        SUN_HIP_CHECK(launch_residual_norm(c, ws.x, ws.part, down_parts, batch, W.gf, batch, ws.hA, nullptr, st));
     }
     {
         ProfScope p(prof, 6, st);
@@ -850,7 +841,7 @@ static int step_impl(sun_kv_pool* pool_, const sun_weights* weights_, bool want_
             ProjLaunch pl{&W.lm, ws.hA, nullptr, batch, EPI_STORE, 1, logits, c.vocab, batch};
             SUN_HIP_CHECK(launch_proj(pl, st));
         } else {
-            SUN_HIP_CHECK(launch_proj_f32(W.lm, ws.h32, batch, logits, st));
+            SUN_HIP_CHECK(launch_proj_f32(W.lm, ws.x, batch, W.gf, c.rms_eps, F32_STORE, logits, st));
         }
     }
     {
@@ -1085,15 +1076,14 @@ static int prefill_block(KvPool& pool, const Weights& W, const Workspace& ws, in
     const int key_splits = std::max(1, std::min(attn_prefill_splits(c, rows, first), ws.plan.max_chunks / rows));
     {
         ProfScope p(prof, 7, st);
-        SUN_HIP_CHECK(launch_embed(c, W.embed, tokens, rows, ws.x, st));
-        SUN_HIP_CHECK(launch_rope_table(c, nullptr, first, rows, ws.table, st));
+        SUN_HIP_CHECK(launch_embed_rope(c, W.embed, tokens, nullptr, first, rows, ws.x, ws.table, st));
     }
     int down_parts = 0;
     for (int l = 0; l < c.n_layers; ++l) {
         const LayerW& L = W.layers[l];
         {
             ProfScope p(prof, 7, st);
-            SUN_HIP_CHECK(launch_residual_norm(c, ws.x, ws.part, down_parts, rows, L.g1, rows, nullptr, ws.hA, nullptr, st));
+            SUN_HIP_CHECK(launch_residual_norm(c, ws.x, ws.part, down_parts, rows, L.g1, rows, ws.hA, nullptr, st));
         }
         const int sq = proj_pick_splits(L.qkv, rows, max_splits);
         {
@@ -1116,7 +1106,7 @@ static int prefill_block(KvPool& pool, const Weights& W, const Workspace& ws, in
         }
         {
             ProfScope p(prof, 7, st);
-            SUN_HIP_CHECK(launch_residual_norm(c, ws.x, ws.part, so, rows, L.g2, rows, nullptr, ws.hA, nullptr, st));
+            SUN_HIP_CHECK(launch_residual_norm(c, ws.x, ws.part, so, rows, L.g2, rows, ws.hA, nullptr, st));
         }
         if (rows > 64) {   // as in a decode step: SwiGLU in the epilogue, the down projection's tile as output
             ProfScope p(prof, 4, st);
@@ -1140,7 +1130,7 @@ static int prefill_block(KvPool& pool, const Weights& W, const Workspace& ws, in
     const size_t last = (size_t)(rows - 1) * H;
     {
         ProfScope p(prof, 7, st);
-        SUN_HIP_CHECK(launch_residual_norm(c, ws.x + last, ws.part + last, down_parts, rows, W.gf, 1, nullptr, ws.hA, nullptr, st));
+        SUN_HIP_CHECK(launch_residual_norm(c, ws.x + last, ws.part + last, down_parts, rows, W.gf, 1, ws.hA, nullptr, st));
     }
     float* out = logits ? logits : ws.logits;
     {
@@ -1329,12 +1319,7 @@ int sun_linear(const sun_weights* weights_, int layer, int mat, int batch, const
     const Mat& M = mat == 4 ? W.lm : mat == 0 ? W.layers[layer].qkv : mat == 1 ? W.layers[layer].o
                                  : mat == 2 ? W.layers[layer].gu : W.layers[layer].down;
     if (c.act_dtype == SUN_F32) {
-        if (mat == 2) {
-            SUN_HIP_CHECK(launch_proj_f32(M, x, batch, ws.gu32, st));
-            SUN_HIP_CHECK(launch_swiglu_f32(ws.gu32, batch, c.ffn, out, st));
-        } else {
-            SUN_HIP_CHECK(launch_proj_f32(M, x, batch, out, st));
-        }
+        SUN_HIP_CHECK(launch_proj_f32(M, x, batch, nullptr, 0.f, mat == 2 ? F32_SWIGLU : F32_STORE, out, st));
         return SUN_OK;
     }
     // the tiled input goes to the buffer the step uses for this projection's input

@@ -19,6 +19,7 @@
 // reduce 256 bf16 values per token for several query heads; the kernel stays HBM
 // bound.  An fp32 vector-ALU variant serves the fp32 parity configuration.
 #include "kernels.hpp"
+#include "rows.hpp"
 
 namespace sun {
 
@@ -39,81 +40,137 @@ size_t attn_max_chunks(int batch, int max_pages, int Hkv) {
 }
 
 // ---------------------------------------------------------------------------------
-// plan: chunk counts of every request and their prefix sums (one block)
+// plan: chunk counts of every request, their prefix sums, and one record per work item
 // ---------------------------------------------------------------------------------
-__global__ __launch_bounds__(1024) void attn_plan_kernel(const int32_t* __restrict__ n_or_len, int len_plus, int batch,
-                                                         int32_t* __restrict__ chunk_off, int32_t* __restrict__ full_off,
-                                                         int32_t* __restrict__ small_off, int max_tokens, int Hkv) {
-    __shared__ int scan_f[1024], scan_s[1024];
-    const int t = threadIdx.x;
-    int nf = 0, ns = 0, ch = 0;
-    if (t < batch) attn_chunking(min(max(n_or_len[t] + len_plus, 1), max_tokens), batch, Hkv, nf, ns, ch);
-    scan_f[t] = nf;
-    scan_s[t] = ns;
-    __syncthreads();
-    for (int o = 1; o < 1024; o <<= 1) {
-        const int vf = t >= o ? scan_f[t - o] : 0, vs = t >= o ? scan_s[t - o] : 0;
-        __syncthreads();
-        scan_f[t] += vf;
-        scan_s[t] += vs;
-        __syncthreads();
-    }
-    if (t < batch) {
-        full_off[t + 1] = scan_f[t];
-        small_off[t + 1] = scan_s[t];
-        chunk_off[t + 1] = scan_f[t] + scan_s[t];
-        if (t == 0) full_off[0] = small_off[0] = chunk_off[0] = 0;
-    }
-}
+// Items of all full chunks come first, ordered (request, kv head, chunk), then the items of all small chunks in the same
+// order.  Record: the chunk's page ids (clamped into the pool, -1 where the chunk has no page), then request, kv head,
+// first and one-past-last token, and the chunk's slot in the partial array (chunks of a request in token order).
+// Every workgroup sums up the chunk counts of all requests for itself (at most 1024 of them, four a thread), so that no
+// launch has to come first; workgroup 0 stores the prefix sums for the kernels that follow.
+struct PlanArgs {
+    const int32_t* n_or_len;
+    const int32_t* page_tables;
+    int32_t *chunk_off, *full_off, *small_off, *records;
+    int len_plus, batch, max_pages, n_pages, Hkv;
+};
 
-// One record per work item.  Items of all full chunks come first, ordered (request, kv head,
-// chunk), then the items of all small chunks in the same order.  Record: the chunk's page ids
-// (clamped into the pool, -1 where the chunk has no page), then request, kv head, first and
-// one-past-last token, and the chunk's slot in the partial array (chunks of a request in token
-// order).
-__global__ __launch_bounds__(256) void attn_records_kernel(const int32_t* __restrict__ n_or_len, int len_plus, int batch,
-                                                           const int32_t* __restrict__ chunk_off,
-                                                           const int32_t* __restrict__ full_off,
-                                                           const int32_t* __restrict__ small_off,
-                                                           const int32_t* __restrict__ page_tables, int max_pages,
-                                                           int n_pages, int Hkv, int32_t* __restrict__ records) {
-    const int total_full = full_off[batch] * Hkv, total = chunk_off[batch] * Hkv;
-    for (int item = blockIdx.x * 16 + (threadIdx.x >> 4); item < total; item += gridDim.x * 16) {
-        const int slot = threadIdx.x & 15;
+__device__ __forceinline__ void attn_plan_block(const PlanArgs& a, int block, int n_blocks) {
+    __shared__ int f_off[1025], s_off[1025], wave_f[4], wave_s[4];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, max_tokens = a.max_pages * kPageTokens;
+    int nf[4], ns[4], f = 0, sm = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int r = tid * 4 + i;
+        int ch;
+        nf[i] = ns[i] = 0;
+        if (r < a.batch) attn_chunking(min(max(a.n_or_len[r] + a.len_plus, 1), max_tokens), a.batch, a.Hkv, nf[i], ns[i], ch);
+        f += nf[i];
+        sm += ns[i];
+    }
+    int fi = f, si = sm;   // inclusive over the wave, then over the workgroup
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int uf = __shfl_up(fi, o), us = __shfl_up(si, o);
+        if (lane >= o) {
+            fi += uf;
+            si += us;
+        }
+    }
+    if (lane == 63) {
+        wave_f[wave] = fi;
+        wave_s[wave] = si;
+    }
+    __syncthreads();
+    int bf = fi - f, bs = si - sm;
+#pragma unroll
+    for (int w = 0; w < 4; ++w)
+        if (w < wave) {
+            bf += wave_f[w];
+            bs += wave_s[w];
+        }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int r = tid * 4 + i;
+        if (r <= a.batch) {
+            f_off[r] = bf;
+            s_off[r] = bs;
+        }
+        bf += nf[i];
+        bs += ns[i];
+    }
+    if (tid == 255 && a.batch == 1024) {
+        f_off[1024] = bf;
+        s_off[1024] = bs;
+    }
+    __syncthreads();
+    if (block == 0)
+        for (int r = tid; r <= a.batch; r += 256) {
+            a.full_off[r] = f_off[r];
+            a.small_off[r] = s_off[r];
+            a.chunk_off[r] = f_off[r] + s_off[r];
+        }
+    const int total_full = f_off[a.batch] * a.Hkv, total = total_full + s_off[a.batch] * a.Hkv;
+    for (int item = block * 16 + (tid >> 4); item < total; item += n_blocks * 16) {
+        const int slot = tid & 15;
         const bool is_full = item < total_full;
-        const int32_t* off = is_full ? full_off : small_off;
+        const int* off = is_full ? f_off : s_off;
         const int idx = is_full ? item : item - total_full;
-        int lo = 0, hi = batch;  // request whose item range [off[r]*Hkv, off[r+1]*Hkv) holds idx
+        int lo = 0, hi = a.batch;  // request whose item range [off[r]*Hkv, off[r+1]*Hkv) holds idx
         while (hi - lo > 1) {
             const int mid = (lo + hi) >> 1;
-            if (off[mid] * Hkv <= idx) lo = mid; else hi = mid;
+            if (off[mid] * a.Hkv <= idx) lo = mid; else hi = mid;
         }
         const int req = lo, nc = off[req + 1] - off[req];
-        const int local = idx - off[req] * Hkv, head = local / nc, cj = local % nc;
-        const int n = min(max(n_or_len[req] + len_plus, 1), max_pages * kPageTokens);
-        const int nfull = full_off[req + 1] - full_off[req];
-        const int ch = attn_full_chunk(n, batch, Hkv);
+        const int local = idx - off[req] * a.Hkv, head = local / nc, cj = local % nc;
+        const int n = min(max(a.n_or_len[req] + a.len_plus, 1), max_tokens);
+        const int nfull = f_off[req + 1] - f_off[req];
+        const int ch = attn_full_chunk(n, a.batch, a.Hkv);
         const int t0 = is_full ? cj * ch : nfull * ch + cj * kAttnSmall;
         const int t1 = is_full ? t0 + ch : min(n, t0 + kAttnSmall);
         const int npages = (t1 - t0 + kPageTokens - 1) / kPageTokens;
-        int32_t* rec = records + (size_t)item * kRecInts;
-        rec[slot] = slot < npages ? min(max(page_tables[(size_t)req * max_pages + t0 / kPageTokens + slot], 0), n_pages - 1) : -1;
+        int32_t* rec = a.records + (size_t)item * kRecInts;
+        rec[slot] = slot < npages ? min(max(a.page_tables[(size_t)req * a.max_pages + t0 / kPageTokens + slot], 0), a.n_pages - 1) : -1;
         if (slot < 8) {
-            const int vals[8] = {req, head, t0, t1, chunk_off[req] + (is_full ? cj : nfull + cj), 0, 0, 0};
+            const int vals[8] = {req, head, t0, t1, f_off[req] + s_off[req] + (is_full ? cj : nfull + cj), 0, 0, 0};
             rec[16 + slot] = vals[slot];
         }
     }
 }
 
+__global__ __launch_bounds__(256) void attn_plan_kernel(PlanArgs a) { attn_plan_block(a, blockIdx.x, gridDim.x); }
+
+static PlanArgs plan_args(const AttnPlan& plan, const int32_t* n_or_len, int len_plus, int batch, const int32_t* page_tables,
+                          int max_pages, int n_pages, int Hkv, int& blocks) {
+    const long long items = (long long)plan.max_chunks * Hkv;
+    blocks = (int)max(1LL, min((items + 15) / 16, 1024LL));
+    return PlanArgs{n_or_len, page_tables, plan.chunk_off, plan.full_off, plan.small_off, plan.records, len_plus, batch,
+                    max_pages, n_pages, Hkv};
+}
+
 hipError_t launch_attn_plan(const AttnPlan& plan, const int32_t* n_or_len, int len_plus, int batch,
                             const int32_t* page_tables, int max_pages, int n_pages, int Hkv, hipStream_t st) {
     if (batch > 1024) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(attn_plan_kernel, dim3(1), dim3(1024), 0, st, n_or_len, len_plus, batch, plan.chunk_off,
-                       plan.full_off, plan.small_off, max_pages * kPageTokens, Hkv);
-    const long long items = (long long)plan.max_chunks * Hkv;
-    const int grid = (int)max(1LL, min((items + 15) / 16, 1024LL));
-    hipLaunchKernelGGL(attn_records_kernel, dim3(grid), dim3(256), 0, st, n_or_len, len_plus, batch, plan.chunk_off,
-                       plan.full_off, plan.small_off, page_tables, max_pages, n_pages, Hkv, plan.records);
+    int blocks;
+    const PlanArgs a = plan_args(plan, n_or_len, len_plus, batch, page_tables, max_pages, n_pages, Hkv, blocks);
+    hipLaunchKernelGGL(attn_plan_kernel, dim3(blocks), dim3(256), 0, st, a);
+    return hipGetLastError();
+}
+
+// ---------------- first launch of a decode step ----------------
+// What depends on the step's inputs alone, in one launch instead of four (each costs 3 to 5 us beside its work):
+// workgroups 0 .. batch - 1 gather a row's embedding and its rotary table, the others make the attention plan.
+__global__ __launch_bounds__(256) void step_begin_kernel(EmbedRope e, PlanArgs a) {
+    if ((int)blockIdx.x < a.batch) embed_rope_row(e, blockIdx.x);
+    else attn_plan_block(a, blockIdx.x - a.batch, gridDim.x - a.batch);
+}
+
+hipError_t launch_step_begin(const sun_model_cfg& cfg, const void* embed, const int32_t* tokens, const int32_t* seq_lens, int batch,
+                             float* x, float* table, const AttnPlan& plan, const int32_t* page_tables, int max_pages,
+                             int n_pages, hipStream_t st) {
+    if (batch > 1024) return hipErrorInvalidValue;
+    int blocks;
+    const PlanArgs a = plan_args(plan, seq_lens, 1, batch, page_tables, max_pages, n_pages, cfg.n_kv_heads, blocks);
+    hipLaunchKernelGGL(step_begin_kernel, dim3(batch + blocks), dim3(256), 0, st, make_embed_rope(cfg, embed, tokens, seq_lens, 0, x, table), a);
     return hipGetLastError();
 }
 
@@ -390,34 +447,63 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 }
 
 // ---------------------------------------------------------------------------------
-// split kernel, fp32 vector-ALU variant (parity configuration); one wave per item
+// split kernel, fp32 vector-ALU variant (parity configuration); a workgroup of four waves per item
 // ---------------------------------------------------------------------------------
+// Bound by latency: an item is at most a few KiB.  One load per thread and phase where the chunk is short (64 tokens, 64
+// dims): four lanes share a token's dot products (a quarter of the dims each, every query head of the group from one
+// read of K), and a dim's sum over the tokens is split over the pages.  With one wave walking its item serially the
+// launch of the tiny configuration (8 requests of 16 to 128 tokens) took 28.9 us; this one takes 6.3.
 template <int D>
-__global__ __launch_bounds__(64) void attn_split_f32_kernel(AttnArgs a, int G) {
-    __shared__ float sc[8][CH];
-    const int lane = threadIdx.x;
+__global__ __launch_bounds__(256) void attn_split_f32_kernel(AttnArgs a, int G) {
+    constexpr int DQ = D / 4;           // dims of a lane in the score phase
+    constexpr int NG = 256 / D;         // page groups in the output phase: 4 or 2
+    __shared__ float qs[8 * D], sc[8][CH], red[NG][8][D];
+    __shared__ int pages[CH / kPageTokens];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int total_items = a.chunk_off[a.batch] * a.Hkv;
     for (int item = blockIdx.x; item < total_items; item += gridDim.x) {
         const int32_t* rec = a.records + (size_t)item * kRecInts;
         const int req = rec[16], head = rec[17], t0 = rec[18], t1 = rec[19], chunk_idx = rec[20], cnt = t1 - t0;
-        const int32_t* pt = a.page_tables + (size_t)req * a.max_pages;
         const uint16_t* kb = a.kbase + head * a.k_head;
         const uint16_t* vb = a.vbase + head * a.v_head;
+        __syncthreads();  // the previous item's last reads of LDS
+        if (tid < CH / kPageTokens) pages[tid] = max(rec[tid], 0);  // the record's page ids are clamped into the pool already
+        const float* qp = a.q + ((size_t)req * a.Hq + head * G) * D;
+        for (int i = tid; i < G * D; i += 256) qs[i] = qp[i];
         __syncthreads();
-        // scores: lane <-> token
-        for (int g = 0; g < G; ++g) {
-            const float* qp = a.q + ((size_t)req * a.Hq + head * G + g) * D;
-            for (int tt = lane; tt < cnt; tt += 64) {
-                const int t = t0 + tt;
-                const uint16_t* kr = kb + (int64_t)min(max(pt[t / kPageTokens], 0), a.n_pages - 1) * a.k_page + (t % kPageTokens) * D;
-                float acc = 0.f;
-                for (int j = 0; j < D; ++j) acc = fmaf(qp[j], bf16_bits_to_f32(kr[j]), acc);
-                sc[g][tt] = acc * a.qscale;
+        // scores: four lanes per token
+        const int sub = tid & 3;
+        for (int tt = tid >> 2; tt < (cnt + 63) / 64 * 64; tt += 64) {
+            float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+            if (tt < cnt) {
+                const u32x4* kr = reinterpret_cast<const u32x4*>(kb + (int64_t)pages[tt / kPageTokens] * a.k_page + (tt % kPageTokens) * D + sub * DQ);
+                u32x4 kw[DQ / 8];
+#pragma unroll
+                for (int i = 0; i < DQ / 8; ++i) kw[i] = kr[i];
+#pragma unroll
+                for (int g = 0; g < 8; ++g) {
+                    if (g >= G) break;
+                    const float* qg = qs + g * D + sub * DQ;
+#pragma unroll
+                    for (int i = 0; i < DQ / 8; ++i)
+#pragma unroll
+                        for (int w = 0; w < 4; ++w) {
+                            acc[g] = fmaf(qg[i * 8 + 2 * w], bf16_lo(kw[i][w]), acc[g]);
+                            acc[g] = fmaf(qg[i * 8 + 2 * w + 1], bf16_hi(kw[i][w]), acc[g]);
+                        }
+                }
+            }
+#pragma unroll
+            for (int g = 0; g < 8; ++g) {
+                if (g >= G) break;
+                float v = acc[g] + __shfl_xor(acc[g], 1);
+                v += __shfl_xor(v, 2);
+                if (sub == 0 && tt < cnt) sc[g][tt] = v * a.qscale;
             }
         }
         __syncthreads();
         float* pbase = a.partial + ((size_t)chunk_idx * a.Hq + head * G) * (D + 2);
-        for (int g = 0; g < G; ++g) {
+        for (int g = wave; g < G; g += 4) {
             float mx = -INFINITY;
             for (int tt = lane; tt < cnt; tt += 64) mx = fmaxf(mx, sc[g][tt]);
             mx = wave_max(mx);
@@ -428,21 +514,42 @@ __global__ __launch_bounds__(64) void attn_split_f32_kernel(AttnArgs a, int G) {
                 sum += p;
             }
             sum = wave_sum(sum);
-            __syncthreads();
-            // output: lane <-> dim
-            for (int j = lane; j < D; j += 64) {
-                float acc = 0.f;
-                for (int tt = 0; tt < cnt; ++tt) {
-                    const int t = t0 + tt;
-                    const uint16_t* vr = vb + (int64_t)min(max(pt[t / kPageTokens], 0), a.n_pages - 1) * a.v_page + j * kPageTokens + (t % kPageTokens);
-                    acc = fmaf(sc[g][tt], bf16_bits_to_f32(*vr), acc);
-                }
-                pbase[(size_t)g * (D + 2) + j] = acc;
-            }
             if (lane == 0) {
                 pbase[(size_t)g * (D + 2) + D] = mx;
                 pbase[(size_t)g * (D + 2) + D + 1] = sum;
             }
+        }
+        __syncthreads();
+        // output: a thread per dim and page group; 16 tokens of a page are 32 contiguous bytes of V^T
+        const int j = tid % D, grp = tid / D;
+        float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        for (int pg = grp; pg * kPageTokens < cnt; pg += NG) {
+            const u32x4* vr = reinterpret_cast<const u32x4*>(vb + (int64_t)pages[pg] * a.v_page + j * kPageTokens);
+            const u32x4 v0 = vr[0], v1 = vr[1];
+#pragma unroll
+            for (int e = 0; e < kPageTokens; ++e) {
+                const int tt = pg * kPageTokens + e;
+                const uint32_t w = e < 8 ? v0[(e & 7) >> 1] : v1[(e & 7) >> 1];
+                if (tt < cnt) {   // slots past the end of the cache may hold anything
+                    const float v = e & 1 ? bf16_hi(w) : bf16_lo(w);
+#pragma unroll
+                    for (int g = 0; g < 8; ++g) {
+                        if (g >= G) break;
+                        acc[g] = fmaf(sc[g][tt], v, acc[g]);
+                    }
+                }
+            }
+        }
+#pragma unroll
+        for (int g = 0; g < 8; ++g)
+            if (g < G) red[grp][g][j] = acc[g];
+        __syncthreads();
+        for (int i = tid; i < G * D; i += 256) {
+            const int g = i / D, jj = i % D;
+            float v = red[0][g][jj];
+#pragma unroll
+            for (int r = 1; r < NG; ++r) v += red[r][g][jj];
+            pbase[(size_t)g * (D + 2) + jj] = v;
         }
     }
 }
@@ -493,8 +600,8 @@ hipError_t launch_attn_split(const KvPool& pool, int layer, const AttnPlan& plan
     if (f32_exact) {
         if (G > 8) return hipErrorInvalidValue;
         const int grid = (int)max(1LL, min(items, 4096LL));
-        if (D == 64) hipLaunchKernelGGL(attn_split_f32_kernel<64>, dim3(grid), dim3(64), 0, st, a, G);
-        else if (D == 128) hipLaunchKernelGGL(attn_split_f32_kernel<128>, dim3(grid), dim3(64), 0, st, a, G);
+        if (D == 64) hipLaunchKernelGGL(attn_split_f32_kernel<64>, dim3(grid), dim3(256), 0, st, a, G);
+        else if (D == 128) hipLaunchKernelGGL(attn_split_f32_kernel<128>, dim3(grid), dim3(256), 0, st, a, G);
         else return hipErrorInvalidValue;
         return hipGetLastError();
     }

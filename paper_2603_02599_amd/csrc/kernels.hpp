@@ -26,8 +26,10 @@ struct ProjLaunch {
 int proj_pick_splits(const Mat& W, int rows, int max_splits);
 hipError_t launch_proj(const ProjLaunch& p, hipStream_t st);
 
-// fp32 activations path (vector ALU): out[b][n] = sum_k W[n][k] x[b][k], out row-major [rows, N].
-hipError_t launch_proj_f32(const Mat& W, const float* x, int rows, float* out, hipStream_t st);
+// fp32 activations path (vector ALU): y[b][n] = sum_k W[n][k] h[b][k] with h = x, or rmsnorm(x) * gain when gain is given;
+// row-major, out[b][n] = y, out[b][n] += y (out is not x), or for a gate/up pair out [rows, N/2] = silu(gate) * up.
+enum F32Epilogue { F32_STORE = 0, F32_ADD = 1, F32_SWIGLU = 2 };
+hipError_t launch_proj_f32(const Mat& W, const float* x, int rows, const void* gain, float eps, int epilogue, float* out, hipStream_t st);
 
 // packing (weights load time)
 size_t packed_bf16_bytes(int N, int K);
@@ -54,6 +56,10 @@ struct AttnPlan {           // device arrays inside the workspace
 size_t attn_max_chunks(int batch, int max_pages, int Hkv);
 hipError_t launch_attn_plan(const AttnPlan& plan, const int32_t* n_or_len, int len_plus, int batch,
                             const int32_t* page_tables, int max_pages, int n_pages, int Hkv, hipStream_t st);
+// First launch of a decode step: launch_embed_rope and launch_attn_plan (n_tokens = seq_lens + 1) together.
+hipError_t launch_step_begin(const sun_model_cfg& cfg, const void* embed, const int32_t* tokens, const int32_t* seq_lens, int batch,
+                             float* x, float* table, const AttnPlan& plan, const int32_t* page_tables, int max_pages,
+                             int n_pages, hipStream_t st);
 // n_tokens(i) = n_or_len[i] + len_plus.  q fp32 [batch, Hq*d].  The chunk counts of the batch (all chunks, full
 // chunks) when the host knows the lengths, else < 0.
 hipError_t launch_attn_split(const KvPool& pool, int layer, const AttnPlan& plan, const float* q,
@@ -74,13 +80,14 @@ int attn_prefill_splits(const sun_model_cfg& c, int rows, int first);
 
 // ---------------- everything else (misc.hip) ----------------
 
-hipError_t launch_embed(const sun_model_cfg& cfg, const void* embed, const int32_t* tokens, int batch, float* x,
-                        hipStream_t st);
-// x[b] += sum_s partial[s][b] (s ascending; nparts may be 0); then h = rmsnorm(x; g).
-// h_f32: row-major fp32 or NULL; h_tiled: tiled bf16 or NULL; with qscale given h_tiled is the fixed-point tile of a
-// 4-bit projection instead and qscale receives its (scale, integer sum) pairs.
+// Embedding rows and rotary tables; position of row b: seq_lens[b], or first_pos + b when seq_lens is NULL.
+hipError_t launch_embed_rope(const sun_model_cfg& cfg, const void* embed, const int32_t* tokens, const int32_t* seq_lens,
+                             int first_pos, int rows, float* x, float* table, hipStream_t st);
+// x[b] += sum_s partial[s][b] (s ascending; nparts may be 0); then h = rmsnorm(x; g) (bf16 gains).
+// h_tiled: two-plane tiled bf16; with qscale given the fixed-point tile of a 4-bit projection instead, and qscale
+// receives its (scale, integer sum) pairs.
 hipError_t launch_residual_norm(const sun_model_cfg& cfg, float* x, const float* partial, int nparts, int ld_rows,
-                                const void* gain, int batch, float* h_f32, void* h_tiled, float* qscale, hipStream_t st);
+                                const void* gain, int batch, void* h_tiled, float* qscale, hipStream_t st);
 // k_src, v_src: bf16 [n_layers][n_tokens][Hkv][d]; token t lands at position first_pos + t of the request whose
 // page-table row is given.
 hipError_t launch_kv_ingest(const KvPool& pool, const void* k_src, const void* v_src, int n_tokens, int first_pos,
@@ -103,16 +110,12 @@ struct ServeArgs {
 // Between two steps (advance) and/or before the first (reset): record tokens, retire, grow, admit.
 hipError_t launch_serve(const ServeArgs& a, const int32_t* next, int32_t* tokens_out, int32_t* req_out, bool reset,
                         bool advance, hipStream_t st);
-// position of row b: seq_lens[b], or first_pos + b when seq_lens is NULL
-hipError_t launch_rope_table(const sun_model_cfg& cfg, const int32_t* seq_lens, int first_pos, int batch, float* table,
-                             hipStream_t st);
 // qkv partial sums [nparts][ld_rows][Nqkv] -> rotated q fp32 [batch, Hq*d]; K,V (bf16) appended to the pool.
 // seq_lens NULL: row b is position first_pos + b of one request, whose page-table row is page_tables.
 hipError_t launch_rope_append(const KvPool& pool, int layer, const float* qkv, int nparts, int ld_rows,
                               const float* table, const int32_t* seq_lens, int first_pos, const int32_t* page_tables, int max_pages,
                               int batch, float* q_out, const void* q_norm, const void* k_norm, const void* bq, const void* bk,
                               const void* bv, hipStream_t st);
-hipError_t launch_swiglu_f32(const float* gu, int batch, int ffn, float* u, hipStream_t st);
 // gate/up partial sums (projection column order) -> silu(g)*u as two-plane tiled bf16, or as fixed-point tile + qscale
 hipError_t launch_swiglu_tile(const float* part, int nparts, int ld_rows, int rows, int ffn, void* tiled, float* qscale,
                               hipStream_t st);
@@ -120,7 +123,8 @@ hipError_t launch_swiglu_tile(const float* part, int nparts, int ld_rows, int ro
 // with plain loads or with the streaming loads the attention kernel uses for K and V
 hipError_t launch_hbm_read_probe(const void* src, long long n_blocks, int block_units, const int32_t* perm, int grid,
                                  bool stream, uint32_t* sink, hipStream_t st);
-constexpr int kArgmaxParts = 16;  // slices of a logits row searched by separate workgroups
+constexpr int kArgmaxParts = 16;    // slices of a logits row searched by separate workgroups
+constexpr int kArgmaxOne = 4096;    // a row of at most this many logits is searched by one
 // part_val / part_idx: scratch [batch][kArgmaxParts]
 hipError_t launch_argmax(const float* logits, int batch, int vocab, float* part_val, int32_t* part_idx, int32_t* next,
                          hipStream_t st);

@@ -1,0 +1,80 @@
+"""A decode step at the sizes where the fp32 kernels, the step's first launch and the argmax can go wrong: widths that are
+not a multiple of four or do not start on 16 bytes, row counts around the eight of a wave, head widths and group sizes,
+more requests than a thread of the plan sums up, vocabularies that leave ragged slices, ties across slices.  Against the
+oracle, with the bounds of the other parity tests."""
+import dataclasses
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2603_02599_amd import binding as sun, workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+ODD = dataclasses.replace(wl.TINY, name="odd", ffn=689, vocab=1031)
+WIDE = dataclasses.replace(wl.TINY, name="wide", n_q_heads=8, n_kv_heads=1, head_dim=128, vocab=5000)
+
+
+@pytest.fixture(scope="module")
+def H():
+    import gpu_harness
+    assert torch.cuda.is_available(), "these tests need the MI355X"
+    sun.lib()
+    return gpu_harness
+
+
+@pytest.mark.parametrize("shape,dtype,batch,lo,hi,quant", [
+    (ODD, "f32", 1, 5, 5, None), (ODD, "f32", 9, 1, 70, None), (WIDE, "f32", 7, 60, 300, None), (WIDE, "f32", 8, 1, 17, None),
+    (wl.TINY_Q, "f32", 17, 1, 40, "asym"), (wl.TINY, "f32", 65, 200, 700, None), (wl.SMALL128, "bf16", 255, 1, 60, None),
+    (wl.TINY_QWEN, "f32", 3, 15, 33, None)],
+    ids=["odd-1", "odd-9", "g8-d128-7", "g8-d128-8", "w4-17", "65-full-chunks", "bf16-255", "head-norm-3"])
+def test_step_at_the_edges(H, shape, dtype, batch, lo, hi, quant):
+    work = wl.make_workload("cfg1", shape=shape, dtype=dtype, batch=batch, seed=900 + batch)
+    rng = np.random.default_rng(batch)
+    work.seq_lens = rng.integers(lo, hi + 1, size=batch).astype(np.int32)
+    work.page_tables, work.n_pages = wl.deal_page_tables(work.seq_lens, rng)
+    case = H.GpuCase(work, quant_mode=quant)
+    ref = H.run_oracle(case, list(range(batch)))
+    for host_lens in (True, False):
+        case.logits.fill_(float("nan"))
+        case.step(flags=sun.SUN_VALIDATE, host_lens=host_lens)
+        H.check_logits(case.logits.cpu().numpy(), ref["logits"], dtype)
+        H.check_next_tokens(case.next.cpu().numpy(), ref["logits"], 1e-4 if dtype == "f32" else 2e-2)
+
+
+def test_f32_weights_that_do_not_start_on_16_bytes(H):
+    """The same matrices behind pointers that are four bytes off a 16-byte boundary: the same logits up to fp32 sums."""
+    work = wl.make_workload("cfg1", seed=950)
+    case = H.GpuCase(work)
+    case.step()
+    want = case.logits.cpu().numpy()
+
+    def off(t):
+        buf = torch.empty(t.numel() + 1, dtype=t.dtype, device=t.device)
+        buf[1:] = t.reshape(-1)
+        return buf[1:].view(t.shape)
+    w = {k: [off(t) for t in v] if isinstance(v, list) else off(v) if isinstance(v, torch.Tensor) else v for k, v in case.w.items()}
+    assert w["wq"][0].data_ptr() % 16 == 4
+    case.weights = sun.sun_weights_create(case.cfg, w)
+    case.step()
+    assert np.abs(case.logits.cpu().numpy() - want).max() <= 2e-5   # two fp32 sums of 688 terms, a fifth of the parity bar
+
+
+@pytest.mark.parametrize("vocab,dtype", [(1024, "f32"), (5001, "f32"), (4100, "f32"), (8224, "bf16")])
+def test_argmax_takes_the_lowest_index_of_a_tie(H, vocab, dtype):
+    shape = dataclasses.replace(wl.TINY if dtype == "f32" else wl.TINY_Q, name="tie", vocab=vocab)
+    work = wl.make_workload("cfg1", shape=shape, dtype=dtype, seed=960)
+    case = H.GpuCase(work)
+    case.step()
+    best = int(case.next.cpu()[0])
+    wlm = case.w["wlm"].clone()
+    for places in ([best, 7, 8], [vocab - 1, best], [0, vocab // 2, vocab - 1], [vocab - 2, vocab - 1]):
+        w = dict(case.w)
+        w["wlm"] = wlm.clone()
+        w["wlm"][best] = 0.0
+        w["wlm"][places] = wlm[best]
+        case.weights = sun.sun_weights_create(case.cfg, w)
+        case.step()
+        row = case.logits.cpu().numpy()[0]
+        assert int(case.next.cpu()[0]) == min(places) == int(np.argmax(row))
