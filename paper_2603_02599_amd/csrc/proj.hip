@@ -646,7 +646,9 @@ typedef int i32x16 __attribute__((ext_vector_type(16)));
 
 // 4-bit weights: MR 32-row blocks per workgroup (the launches use MR = 1: 32-row tiles, see proj_tiling), one
 // stage = one 128-wide group = four int8 MFMA k-steps, three stages of activations in the LDS ring.
-template <int MR, int NW>
+// OCT: row octets of a tile that the epilogue scales: 4, or as many as a launch of at most 16 rows has rows in (the epilogue
+// is most of the vector instructions: gate/up at 5 rows 19.1 -> 17.2 us, the step of 8 layers 924 -> 885).
+template <int MR, int NW, int OCT>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, MR == 1 ? 4 : 2)))
 void proj_w4_kernel(ProjArgs a) {
     constexpr int STEPS = 4;
@@ -744,7 +746,7 @@ void proj_w4_kernel(ProjArgs a) {
 #pragma unroll
         for (int m = 0; m < MR; ++m)
 #pragma unroll
-            for (int rr = 0; rr < 4; ++rr) {
+            for (int rr = 0; rr < OCT; ++rr) {
                 const f32x4 sx4 = *reinterpret_cast<const f32x4*>(sxp + m * 32 + 8 * rr + 4 * half);
                 const i32x4 xs4 = *reinterpret_cast<const i32x4*>(xsp + m * 32 + 8 * rr + 4 * half);
 #pragma unroll
@@ -801,7 +803,9 @@ static hipError_t launch_proj_w4(const ProjArgs& a, int nw, int splits, int mtil
     const auto go = [&](auto nwc) {
         constexpr int NW = decltype(nwc)::value;
         dim3 grid((a.N / 32 + NW - 1) / NW, splits, mtiles), block(NW * 64);
-        hipLaunchKernelGGL((proj_w4_kernel<MR, NW>), grid, block, 0, st, a);
+        if (a.rows <= 8) hipLaunchKernelGGL((proj_w4_kernel<MR, NW, 1>), grid, block, 0, st, a);
+        else if (a.rows <= 16) hipLaunchKernelGGL((proj_w4_kernel<MR, NW, 2>), grid, block, 0, st, a);
+        else hipLaunchKernelGGL((proj_w4_kernel<MR, NW, 4>), grid, block, 0, st, a);
         return hipGetLastError();
     };
     switch (nw) {
@@ -886,7 +890,8 @@ struct ProjShape {
 // its vector-ALU epilogue and by the wait for the matrix cores between epilogues, not by the weight
 // stream (a quarter of the bytes, and the row tiles of a column strip run side by side and share
 // their fetches); with one row block a wave needs 128 registers instead of 230, four waves share a
-// SIMD instead of two and cover each other's waits (8B shape, qkv / o / gate-up / down in us: batch 64
+// SIMD instead of two and cover each other's waits.  Only tiles that hold a row are launched (150 rows: 5 of the
+// activation tiling's 8, gate/up 102 -> 81 us) (8B shape, qkv / o / gate-up / down in us: batch 64
 // 16.2 / 11.9 / 32.7 / 21.6 -> 15.0 / 11.1 / 30.0 / 20.5; batch 256 30.9 / 22.7 / 104.6 / 60.2 -> 27.8 / 20.6 /
 // 90.9 / 50.7; results bit-identical).
 struct ProjTiling {
@@ -894,7 +899,7 @@ struct ProjTiling {
 };
 static ProjTiling proj_tiling(const Mat& W, int rows) {
     const int mbr = atile_for_rows(rows).MB;  // 32-row blocks of the activation tiling: 1, 2, 4 or 8
-    if (W.kind == MAT_W4_PACKED) return ProjTiling{2, mbr};
+    if (W.kind == MAT_W4_PACKED) return ProjTiling{2, (rows + 31) / 32};  // no tile without a row
     if (mbr <= 2) return ProjTiling{2 * mbr, 1};
     return ProjTiling{8, mbr / 4};
 }

@@ -78,3 +78,28 @@ def test_argmax_takes_the_lowest_index_of_a_tie(H, vocab, dtype):
         case.step()
         row = case.logits.cpu().numpy()[0]
         assert int(case.next.cpu()[0]) == min(places) == int(np.argmax(row))
+
+
+@pytest.mark.parametrize("rows", [1, 8, 9, 16, 17, 33, 65, 97, 150, 161, 256])
+def test_w4_projections_at_the_edges_of_row_tiles(H, rows):
+    """One row more or less than an octet of the scaled rows or a 32-row tile; an odd number of tiles.  Against float64 of the
+    dequantised matrices, with the bound of a 4-bit projection (its activations are rounded to 16 bits a group)."""
+    shape = wl.SMALL128
+    cfg = sun.make_cfg(shape, "bf16")
+    w = wl.make_weights(shape, "bf16", H.DEV, 78)
+    quant = {k: [sun.sun_quantize_w4(m, 128, "asym") for m in w[k]] for k in sun.QUANT_KEYS}
+    W = sun.sun_qweights_create(cfg, w, quant)
+
+    def dense(q, s, z):
+        codes = torch.stack([q & 15, q >> 4], 2).view(q.shape[0], -1, 128).double()
+        return ((codes - z.double().unsqueeze(2)) * s.double().unsqueeze(2)).view(q.shape[0], -1)
+    mats = {0: ["wq", "wk", "wv"], 1: ["wo"], 3: ["wd"]}
+    ws = torch.empty(sun.sun_workspace_bytes(cfg, rows, 1), dtype=torch.uint8, device=H.DEV)
+    for mat, keys in mats.items():
+        M = torch.cat([dense(*quant[k][1]) for k in keys])
+        x = torch.randn((rows, M.shape[1]), device=H.DEV, generator=torch.Generator(device=H.DEV).manual_seed(rows + mat))
+        out = torch.full((rows, M.shape[0]), float("nan"), device=H.DEV)
+        sun.sun_linear(W, 1, mat, x, out, ws)
+        torch.cuda.synchronize()
+        want = x.double() @ M.t()
+        assert ((out.double() - want).abs() <= 1e-3 + 1e-4 * want.abs()).all(), mat
