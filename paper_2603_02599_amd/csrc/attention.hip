@@ -631,39 +631,37 @@ struct CombineArgs {
     int Hq, D, batch, out_mb, uniform;
 };
 
+// A workgroup merges 128 columns of a request: one head of 128 dims or two of 64, each wave for itself.  Bound by the latency
+// of the partials, which the split kernel has just written: the chunks' maxima and sums are read first, a lane per chunk,
+// so that the outputs' loads depend on nothing but each other's order and sixteen of them are in flight per thread.
+// With a running maximum over eight chunks at a time (24 loads a round, each round waiting for the one before):
+// 8B shape, 16 / 256 requests 6.4 -> 5.1 / 21.7 -> 18.0 us, 14B shape, 24 requests of 17 k tokens 24.4 -> 17.0.
 __global__ __launch_bounds__(128) void attn_combine_kernel(CombineArgs a) {
-    const int b = blockIdx.y, col = blockIdx.x * 128 + threadIdx.x;
-    const int h = col / a.D, j = col % a.D;
+    const int b = blockIdx.y, col = blockIdx.x * 128 + threadIdx.x, lane = threadIdx.x & 63;
+    const int h = col / a.D, j = col % a.D;   // a wave's 64 columns are of one head
     const int c0 = a.chunk_off ? a.chunk_off[b] : b * a.uniform, c1 = a.chunk_off ? a.chunk_off[b + 1] : c0 + a.uniform;
+    const int n = c1 - c0;
     const size_t stride = (size_t)a.Hq * (a.D + 2);
     const float* p = a.partial + (size_t)c0 * stride + (size_t)h * (a.D + 2);
-    // chunks are merged in order, eight at a time so that their loads are in flight together
-    float M = -INFINITY, num = 0.f, den = 0.f;
-    for (int cb = 0; cb < c1 - c0; cb += 8) {
-        float m8[8], l8[8], o8[8];
+    float M = -INFINITY;
+    for (int c = lane; c < n; c += 64) M = fmaxf(M, p[c * stride + a.D]);
+    M = wave_max(M);
+    float num = 0.f, den = 0.f;
+    for (int cb = 0; cb < n; cb += 64) {  // 64 chunks' weights a pass, one per lane; chunks are added in order
+        const int c = cb + lane, cnt = min(n - cb, 64);
+        const float w = c < n ? exp2f(p[c * stride + a.D] - M) : 0.f;
+        if (c < n) den = fmaf(w, p[c * stride + a.D + 1], den);
+        const float* pj = p + (size_t)cb * stride + j;
+        for (int k0 = 0; k0 < cnt; k0 += 16) {
+            float o[16];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int c = min(cb + i, c1 - c0 - 1);
-            m8[i] = p[c * stride + a.D];
-            l8[i] = p[c * stride + a.D + 1];
-            o8[i] = p[c * stride + j];
+            for (int i = 0; i < 16; ++i) o[i] = pj[min(k0 + i, cnt - 1) * stride];
+#pragma unroll
+            for (int i = 0; i < 16; ++i)
+                if (k0 + i < cnt) num = fmaf(__uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(w), k0 + i)), o[i], num);
         }
-        float Mn = M;
-#pragma unroll
-        for (int i = 0; i < 8; ++i)
-            if (cb + i < c1 - c0) Mn = fmaxf(Mn, m8[i]);
-        const float sc = exp2f(M - Mn);
-        num *= sc;
-        den *= sc;
-        M = Mn;
-#pragma unroll
-        for (int i = 0; i < 8; ++i)
-            if (cb + i < c1 - c0) {
-                const float w = exp2f(m8[i] - M);
-                den = fmaf(w, l8[i], den);
-                num = fmaf(w, o8[i], num);
-            }
     }
+    den = wave_sum(den);
     const float v = num / den;
     if (a.out_f32) a.out_f32[(size_t)b * a.Hq * a.D + col] = v;
     if (a.out_tiled && !a.qscale) {
