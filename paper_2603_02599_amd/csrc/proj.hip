@@ -47,6 +47,27 @@ struct ProjArgs {
     int mb_rows;   // 32-row blocks of real rows in the activation tiling (it holds twice as many: hi and lo plane)
 };
 
+// SwiGLU of a strip's accumulators.  A strip's 32 columns are 16 gate columns followed by the 16 up columns of the same u
+// columns (the packing order of the pair), so lane c and lane c + 16 hold gate and up of u column c for the same sixteen
+// rows of a row block.  They share the work: of every pair of rows the gate lane finishes one and the up lane the
+// other, one exchange per pair.  sw: this wave's scratch, [plane][32 row blocks' rows][16] bf16, rows rl0 + 0..31.
+template <int ROWS>
+__device__ __forceinline__ void swiglu_strip(const f32x16& acc, uint16_t* sw, int rl0) {
+    const int lane = threadIdx.x & 63, half = lane >> 5, col = lane & 31;
+    const bool up_lane = col >= 16;
+#pragma unroll
+    for (int r = 0; r < 16; r += 2) {
+        const float got = __shfl_xor(up_lane ? acc[r] : acc[r + 1], 16);
+        const float g = up_lane ? got : acc[r], up = up_lane ? acc[r + 1] : got;
+        const float y = g / (1.f + __expf(-g)) * up;
+        const uint16_t hi = f32_to_bf16_bits(y);
+        const uint16_t lo = f32_to_bf16_bits(y - bf16_bits_to_f32(hi));
+        const int rl = rl0 + 8 * (r >> 2) + 4 * half + (r & 3) + (up_lane ? 1 : 0);
+        sw[(0 * ROWS + rl) * 16 + (col & 15)] = hi;
+        sw[(1 * ROWS + rl) * 16 + (col & 15)] = lo;
+    }
+}
+
 // MB counts the 32-row operand blocks of the workgroup: MR = MB/2 blocks of rows, each present
 // as a hi and a lo bf16 plane (operand block m < MR is the hi plane of row block m, block MR+m
 // its lo plane); both are multiplied with the same weight fragment into the same accumulator.
@@ -189,27 +210,12 @@ void proj_kernel(ProjArgs a) {
 
     const int col = lane & 31;
     if constexpr (EPI == EPI_SWIGLU) {
-        // The wave's 32 columns are 16 gate columns followed by the 16 up columns of the same u columns (the
-        // packing order of the pair): lane c < 16 fetches its up value from lane c + 16 and owns u column
-        // nb*16 + c.  The results leave as the tile the down projection reads: hi and lo plane, 16-byte units
+        // The results leave as the tile the down projection reads: hi and lo plane, 16-byte units
         // of 8 consecutive u columns of one row, gathered through the wave's own piece of the (now idle)
         // activation ring.  Every wave has passed the barrier that follows the last stage.
         uint16_t* sw = reinterpret_cast<uint16_t*>(&lds[0][0]) + (size_t)wave * (MR * 32 * 16 * 2);
 #pragma unroll
-        for (int m = 0; m < MR; ++m)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const float g = acc[m][r];
-                const float up = __shfl_xor(g, 16);
-                const float y = g / (1.f + __expf(-g)) * up;
-                const uint16_t hi = f32_to_bf16_bits(y);
-                const uint16_t lo = f32_to_bf16_bits(y - bf16_bits_to_f32(hi));
-                const int rl = m * 32 + 8 * (r >> 2) + 4 * half + (r & 3);  // row inside the workgroup's tile
-                if (col < 16) {
-                    sw[(0 * MR * 32 + rl) * 16 + col] = hi;
-                    sw[(1 * MR * 32 + rl) * 16 + col] = lo;
-                }
-            }
+        for (int m = 0; m < MR; ++m) swiglu_strip<MR * 32>(acc[m], sw, m * 32);
         __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): the wave's LDS writes have landed (no other wave reads them)
         __builtin_amdgcn_wave_barrier();
         u32x4* tile = reinterpret_cast<u32x4*>(a.out);
@@ -244,7 +250,8 @@ void proj_kernel(ProjArgs a) {
 // owns column pair c and row group h (MRW row blocks of 32; 2 in every launch: 128-row
 // workgroups).  The two row groups of a column pair request the same weights (HBM sees them once).
 // The activation stage is 64 wide (four k-steps) and shared by all waves.
-// Used above 128 rows.  Up to 128 rows the strip kernel stays (measured on the 14B shape at batch
+// The next stage's weights are requested between the matrix instructions (all of them in front: gate/up at 256 rows 126 ->
+// 120 us, the others 40.3 -> 38.7 on average).  Used above 128 rows.  Up to 128 rows the strip kernel stays (measured on the 14B shape at batch
 // 128: gate/up 103 against 119 us, the rest equal).  A variant with four waves of 128 rows x 64
 // columns, one per SIMD with its accumulators in the upper half of the register file, requests no
 // weight twice but was 10 to 90 % slower: one wave per SIMD cannot cover its own waits.
@@ -257,7 +264,7 @@ void proj_tall_kernel(ProjArgs a) {
     constexpr int KK = 4;                      // k-steps per stage (64 of k)
     constexpr int STAGE_UNITS = KK * MB * 64;
     constexpr int NT = RH * NWC * 64;
-    constexpr int NBUF = (MRT <= 2) ? 3 : 2;   // a third weight stage in registers does not fit beside 64 + 64 accumulators
+    constexpr int NBUF = 2;                    // a third weight stage in registers does not fit beside 64 + 64 accumulators
     constexpr int UPT = (STAGE_UNITS + NT - 1) / NT;
     static_assert(STAGE_UNITS % NT == 0, "every thread stages the same number of units");
     __shared__ u32x4 lds_all[NBUF * STAGE_UNITS];
@@ -285,7 +292,7 @@ void proj_tall_kernel(ProjArgs a) {
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[s][m][r] = 0.f;
 
-    u32x4 w0[2][KK], w1[2][KK], w2[NBUF == 3 ? 2 : 1][NBUF == 3 ? KK : 1], areg[UPT];
+    u32x4 w0[2][KK], w1[2][KK], areg[UPT];
 
     auto load_w = [&](u32x4(&w)[2][KK], int st) {
         const size_t off = ((size_t)st * KK) * 64;   // in k-steps of 64 lanes
@@ -309,7 +316,8 @@ void proj_tall_kernel(ProjArgs a) {
 #pragma unroll
         for (int i = 0; i < UPT; ++i) lds_all[buf * STAGE_UNITS + i * NT + tid] = areg[i];
     };
-    auto compute = [&](int buf, const u32x4(&w)[2][KK]) {
+    // the next stage's weights are requested between the k-steps' matrix instructions
+    auto compute = [&](int buf, const u32x4(&w)[2][KK], u32x4(&wn)[2][KK], int nst) {
         // this wave's operand blocks of a k-step: hi and lo plane of its MRW row blocks
         const u32x4* src = lds_all + buf * STAGE_UNITS + lane;
         u32x4 afr[2][2 * MRW];
@@ -334,63 +342,36 @@ void proj_tall_kernel(ProjArgs a) {
                         const bf16x8 afrag = __builtin_bit_cast(bf16x8, afr[kk & 1][pl * MRW + m]);
                         acc[s][m] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(afrag, bfrag, acc[s][m], 0, 0, 0);
                     }
+                __builtin_amdgcn_sched_barrier(0);
+                const size_t off = ((size_t)nst * KK + kk) * 64;
+                wn[s][kk] = s ? Wl1[off] : Wl0[off];
             }
         }
     };
 
     if (s0 < s1) {
-        if constexpr (NBUF == 3) {
-            auto phase = [&](const u32x4(&wcur)[2][KK], u32x4(&wn)[2][KK], int bufc, int bufn, int st) {
-                const int nx = min(st + 2, s1 - 1);
-                load_a(nx);  // before the weights: the LDS store below then waits for these only
-                load_w(wn, nx);
-                compute(bufc, wcur);
-                store_a(bufn);
-                __syncthreads();
-            };
-            const int sA = min(s0 + 1, s1 - 1);
-            load_w(w0, s0);
-            load_a(s0);
-            store_a(0);
-            load_w(w1, sA);
-            load_a(sA);
+        load_w(w0, s0);
+        load_a(s0);
+        store_a(0);
+        __syncthreads();
+        for (int st = s0; st < s1; st += 2) {
+            const int n1 = min(st + 1, s1 - 1);
+            load_a(n1);
+            compute(0, w0, w1, n1);
             store_a(1);
             __syncthreads();
-            for (int st = s0; st < s1; st += 3) {
-                phase(w0, w2, 0, 2, st);
-                if (st + 1 >= s1) break;
-                phase(w1, w0, 1, 0, st + 1);
-                if (st + 2 >= s1) break;
-                phase(w2, w1, 2, 1, st + 2);
-            }
-        } else {
-            load_w(w0, s0);
-            load_a(s0);
+            if (st + 1 >= s1) break;
+            const int n2 = min(st + 2, s1 - 1);
+            load_a(n2);
+            compute(1, w1, w0, n2);
             store_a(0);
             __syncthreads();
-            for (int st = s0; st < s1; st += 2) {
-                const int n1 = min(st + 1, s1 - 1);
-                load_a(n1);
-                load_w(w1, n1);
-                compute(0, w0);
-                store_a(1);
-                __syncthreads();
-                if (st + 1 >= s1) break;
-                const int n2 = min(st + 2, s1 - 1);
-                load_a(n2);
-                load_w(w0, n2);
-                compute(1, w1);
-                store_a(0);
-                __syncthreads();
-            }
         }
     }
 
     const int col = lane & 31;
     if constexpr (EPI == EPI_SWIGLU) {
-        // A strip's 32 columns are 16 gate columns followed by the 16 up columns of the same u columns (the
-        // packing order of the pair): lane c < 16 fetches its up value from lane c + 16 and owns u column
-        // strip*16 + c.  The results leave as the tile the down projection reads: hi and lo plane, 16-byte units
+        // The results leave as the tile the down projection reads: hi and lo plane, 16-byte units
         // of 8 consecutive u columns of one row, gathered through the wave's own piece of the (now idle)
         // activation ring.  Every wave has passed the barrier that follows the last stage.
         uint16_t* sw = reinterpret_cast<uint16_t*>(lds_all) + (size_t)wave * (MRW * 32 * 16 * 2);
@@ -399,20 +380,7 @@ void proj_tall_kernel(ProjArgs a) {
         for (int s = 0; s < 2; ++s) {
             const int nb = 2 * cp + s;
 #pragma unroll
-            for (int m = 0; m < MRW; ++m)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const float g = acc[s][m][r];
-                    const float up = __shfl_xor(g, 16);
-                    const float y = g / (1.f + __expf(-g)) * up;
-                    const uint16_t hi = f32_to_bf16_bits(y);
-                    const uint16_t lo = f32_to_bf16_bits(y - bf16_bits_to_f32(hi));
-                    const int rl = m * 32 + 8 * (r >> 2) + 4 * half + (r & 3);  // row inside the wave's rows
-                    if (col < 16) {
-                        sw[(0 * MRW * 32 + rl) * 16 + col] = hi;
-                        sw[(1 * MRW * 32 + rl) * 16 + col] = lo;
-                    }
-                }
+            for (int m = 0; m < MRW; ++m) swiglu_strip<MRW * 32>(acc[s][m], sw, m * 32);
             __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): the wave's LDS writes have landed (no other wave reads them)
             __builtin_amdgcn_wave_barrier();
             if (nb < n_strips) {
@@ -586,9 +554,7 @@ void proj_wide_kernel(ProjArgs a) {
     const int my_strip = strip0 + ch * 4;
     const int col = lane & 31, row0 = (mb_off + rh * 2) * 32;
     if constexpr (EPI == EPI_SWIGLU) {
-        // A strip's 32 columns are 16 gate columns followed by the 16 up columns of the same u columns (the
-        // packing order of the pair): lane c < 16 fetches its up value from lane c + 16 and owns u column
-        // strip*16 + c.  The results leave as the tile the down projection reads: hi and lo plane, 16-byte units
+        // The results leave as the tile the down projection reads: hi and lo plane, 16-byte units
         // of 8 consecutive u columns of one row, gathered through the wave's own piece of the idle ring.
         uint16_t* sw = reinterpret_cast<uint16_t*>(lds_all) + (size_t)wave * (2 * 64 * 16);
         u32x4* tile = reinterpret_cast<u32x4*>(a.out);
@@ -596,20 +562,7 @@ void proj_wide_kernel(ProjArgs a) {
         for (int s = 0; s < 4; ++s) {
             const int nb = my_strip + s;
 #pragma unroll
-            for (int m = 0; m < 2; ++m)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const float g = acc[s][m][r];
-                    const float up = __shfl_xor(g, 16);
-                    const float y = g / (1.f + __expf(-g)) * up;
-                    const uint16_t hi = f32_to_bf16_bits(y);
-                    const uint16_t lo = f32_to_bf16_bits(y - bf16_bits_to_f32(hi));
-                    const int rl = m * 32 + 8 * (r >> 2) + 4 * half + (r & 3);  // row inside the wave's rows
-                    if (col < 16) {
-                        sw[(0 * 64 + rl) * 16 + col] = hi;
-                        sw[(1 * 64 + rl) * 16 + col] = lo;
-                    }
-                }
+            for (int m = 0; m < 2; ++m) swiglu_strip<64>(acc[s][m], sw, m * 32);
             __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): the wave's LDS writes have landed (no other wave reads them)
             __builtin_amdgcn_wave_barrier();
             if (nb < n_strips) {
