@@ -449,15 +449,13 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 // ---------------------------------------------------------------------------------
 // split kernel, fp32 vector-ALU variant (parity configuration); a workgroup of four waves per item
 // ---------------------------------------------------------------------------------
-// Bound by latency: an item is at most a few KiB.  One load per thread and phase where the chunk is short (64 tokens, 64
-// dims): four lanes share a token's dot products (a quarter of the dims each, every query head of the group from one
-// read of K), and a dim's sum over the tokens is split over the pages.  With one wave walking its item serially the
-// launch of the tiny configuration (8 requests of 16 to 128 tokens) took 28.9 us; this one takes 6.3.
+// Bound by latency: an item is at most a few KiB.  A wave per query head in both products (a token's score, then a dim's
+// sum over the tokens, one thread and one order of sums each), with all of a thread's loads in flight: a K row, a page's
+// 16 tokens of V^T.  With one wave walking its item element by element the launch of the tiny configuration (8 requests
+// of 16 to 128 tokens) took 28.9 us; this one takes 7.1.
 template <int D>
 __global__ __launch_bounds__(256) void attn_split_f32_kernel(AttnArgs a, int G) {
-    constexpr int DQ = D / 4;           // dims of a lane in the score phase
-    constexpr int NG = 256 / D;         // page groups in the output phase: 4 or 2
-    __shared__ float qs[8 * D], sc[8][CH], red[NG][8][D];
+    __shared__ __attribute__((aligned(16))) float qs[8 * D], sc[8][CH];
     __shared__ int pages[CH / kPageTokens];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int total_items = a.chunk_off[a.batch] * a.Hkv;
@@ -471,34 +469,25 @@ __global__ __launch_bounds__(256) void attn_split_f32_kernel(AttnArgs a, int G) 
         const float* qp = a.q + ((size_t)req * a.Hq + head * G) * D;
         for (int i = tid; i < G * D; i += 256) qs[i] = qp[i];
         __syncthreads();
-        // scores: four lanes per token
-        const int sub = tid & 3;
-        for (int tt = tid >> 2; tt < (cnt + 63) / 64 * 64; tt += 64) {
-            float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-            if (tt < cnt) {
-                const u32x4* kr = reinterpret_cast<const u32x4*>(kb + (int64_t)pages[tt / kPageTokens] * a.k_page + (tt % kPageTokens) * D + sub * DQ);
-                u32x4 kw[DQ / 8];
+        // scores: lane <-> token, wave <-> head
+        for (int tt = lane; tt < cnt; tt += 64) {
+            const u32x4* kr = reinterpret_cast<const u32x4*>(kb + (int64_t)pages[tt / kPageTokens] * a.k_page + (tt % kPageTokens) * D);
+            u32x4 kw[D / 8];
 #pragma unroll
-                for (int i = 0; i < DQ / 8; ++i) kw[i] = kr[i];
+            for (int i = 0; i < D / 8; ++i) kw[i] = kr[i];
+            for (int g = wave; g < G; g += 4) {
+                const f32x4* qg = reinterpret_cast<const f32x4*>(qs + g * D);
+                float acc = 0.f;
 #pragma unroll
-                for (int g = 0; g < 8; ++g) {
-                    if (g >= G) break;
-                    const float* qg = qs + g * D + sub * DQ;
+                for (int i = 0; i < D / 8; ++i) {
+                    const f32x4 q0 = qg[2 * i], q1 = qg[2 * i + 1];
 #pragma unroll
-                    for (int i = 0; i < DQ / 8; ++i)
-#pragma unroll
-                        for (int w = 0; w < 4; ++w) {
-                            acc[g] = fmaf(qg[i * 8 + 2 * w], bf16_lo(kw[i][w]), acc[g]);
-                            acc[g] = fmaf(qg[i * 8 + 2 * w + 1], bf16_hi(kw[i][w]), acc[g]);
-                        }
+                    for (int w = 0; w < 4; ++w) {
+                        acc = fmaf(w < 2 ? q0[2 * w] : q1[2 * w - 4], bf16_lo(kw[i][w]), acc);
+                        acc = fmaf(w < 2 ? q0[2 * w + 1] : q1[2 * w - 3], bf16_hi(kw[i][w]), acc);
+                    }
                 }
-            }
-#pragma unroll
-            for (int g = 0; g < 8; ++g) {
-                if (g >= G) break;
-                float v = acc[g] + __shfl_xor(acc[g], 1);
-                v += __shfl_xor(v, 2);
-                if (sub == 0 && tt < cnt) sc[g][tt] = v * a.qscale;
+                sc[g][tt] = acc * a.qscale;
             }
         }
         __syncthreads();
@@ -520,37 +509,30 @@ __global__ __launch_bounds__(256) void attn_split_f32_kernel(AttnArgs a, int G) 
             }
         }
         __syncthreads();
-        // output: a thread per dim and page group; 16 tokens of a page are 32 contiguous bytes of V^T
-        const int j = tid % D, grp = tid / D;
-        float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-        for (int pg = grp; pg * kPageTokens < cnt; pg += NG) {
-            const u32x4* vr = reinterpret_cast<const u32x4*>(vb + (int64_t)pages[pg] * a.v_page + j * kPageTokens);
-            const u32x4 v0 = vr[0], v1 = vr[1];
+        // output: lane <-> dim, wave <-> head; 16 tokens of a page are 32 contiguous bytes of V^T
+        for (int g = wave; g < G; g += 4)
+            for (int j = lane; j < D; j += 64) {
+                float acc = 0.f;
+                for (int p0 = 0; p0 * kPageTokens < cnt; p0 += 4) {
+                    u32x4 v[4][2];
 #pragma unroll
-            for (int e = 0; e < kPageTokens; ++e) {
-                const int tt = pg * kPageTokens + e;
-                const uint32_t w = e < 8 ? v0[(e & 7) >> 1] : v1[(e & 7) >> 1];
-                if (tt < cnt) {   // slots past the end of the cache may hold anything
-                    const float v = e & 1 ? bf16_hi(w) : bf16_lo(w);
-#pragma unroll
-                    for (int g = 0; g < 8; ++g) {
-                        if (g >= G) break;
-                        acc[g] = fmaf(sc[g][tt], v, acc[g]);
+                    for (int i = 0; i < 4; ++i) {
+                        const int pg = min(p0 + i, (cnt - 1) / kPageTokens);
+                        const u32x4* vr = reinterpret_cast<const u32x4*>(vb + (int64_t)pages[pg] * a.v_page + j * kPageTokens);
+                        v[i][0] = vr[0];
+                        v[i][1] = vr[1];
                     }
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+#pragma unroll
+                        for (int e = 0; e < kPageTokens; ++e) {
+                            const int tt = (p0 + i) * kPageTokens + e;
+                            const uint32_t w = v[i][e >> 3][(e & 7) >> 1];
+                            if (tt < cnt) acc = fmaf(sc[g][tt], e & 1 ? bf16_hi(w) : bf16_lo(w), acc);  // slots past the end may hold anything
+                        }
                 }
+                pbase[(size_t)g * (D + 2) + j] = acc;
             }
-        }
-#pragma unroll
-        for (int g = 0; g < 8; ++g)
-            if (g < G) red[grp][g][j] = acc[g];
-        __syncthreads();
-        for (int i = tid; i < G * D; i += 256) {
-            const int g = i / D, jj = i % D;
-            float v = red[0][g][jj];
-#pragma unroll
-            for (int r = 1; r < NG; ++r) v += red[r][g][jj];
-            pbase[(size_t)g * (D + 2) + jj] = v;
-        }
     }
 }
 
@@ -635,7 +617,7 @@ struct CombineArgs {
 // of the partials, which the split kernel has just written: the chunks' maxima and sums are read first, a lane per chunk,
 // so that the outputs' loads depend on nothing but each other's order and sixteen of them are in flight per thread.
 // With a running maximum over eight chunks at a time (24 loads a round, each round waiting for the one before):
-// 8B shape, 16 / 256 requests 6.4 -> 5.1 / 21.7 -> 18.0 us, 14B shape, 24 requests of 17 k tokens 24.4 -> 17.0.
+// 8B shape, 16 / 256 requests 6.4 -> 5.1 / 21.7 -> 18.3 us, 14B shape, 24 requests of 17 k tokens 24.4 -> 17.5.
 __global__ __launch_bounds__(128) void attn_combine_kernel(CombineArgs a) {
     const int b = blockIdx.y, col = blockIdx.x * 128 + threadIdx.x, lane = threadIdx.x & 63;
     const int h = col / a.D, j = col % a.D;   // a wave's 64 columns are of one head
@@ -649,8 +631,7 @@ __global__ __launch_bounds__(128) void attn_combine_kernel(CombineArgs a) {
     float num = 0.f, den = 0.f;
     for (int cb = 0; cb < n; cb += 64) {  // 64 chunks' weights a pass, one per lane; chunks are added in order
         const int c = cb + lane, cnt = min(n - cb, 64);
-        const float w = c < n ? exp2f(p[c * stride + a.D] - M) : 0.f;
-        if (c < n) den = fmaf(w, p[c * stride + a.D + 1], den);
+        const float w = c < n ? exp2f(p[c * stride + a.D] - M) : 0.f, l = c < n ? p[c * stride + a.D + 1] : 0.f;
         const float* pj = p + (size_t)cb * stride + j;
         for (int k0 = 0; k0 < cnt; k0 += 16) {
             float o[16];
@@ -658,10 +639,13 @@ __global__ __launch_bounds__(128) void attn_combine_kernel(CombineArgs a) {
             for (int i = 0; i < 16; ++i) o[i] = pj[min(k0 + i, cnt - 1) * stride];
 #pragma unroll
             for (int i = 0; i < 16; ++i)
-                if (k0 + i < cnt) num = fmaf(__uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(w), k0 + i)), o[i], num);
+                if (k0 + i < cnt) {
+                    const float wk = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(w), k0 + i));
+                    den = fmaf(wk, __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(l), k0 + i)), den);
+                    num = fmaf(wk, o[i], num);
+                }
         }
     }
-    den = wave_sum(den);
     const float v = num / den;
     if (a.out_f32) a.out_f32[(size_t)b * a.Hq * a.D + col] = v;
     if (a.out_tiled && !a.qscale) {

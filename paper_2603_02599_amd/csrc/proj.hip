@@ -1039,7 +1039,8 @@ struct F32Mat {
 };
 
 // Eight sums over the wave at once: three exchanges halve what a lane holds (4 + 2 + 1 shuffles), three more finish the
-// one it is left with, instead of six shuffles per sum.  Lane bits 5, 4, 3 name the sum a lane ends up with.
+// one it is left with, instead of six shuffles per sum.  Each is summed in the order of wave_sum.  Lane bits 5, 4, 3 name
+// the sum a lane ends up with.
 template <int O, int C>
 __device__ __forceinline__ void wave_fold(float (&v)[8]) {
     const bool up = threadIdx.x & O;
@@ -1058,18 +1059,28 @@ __device__ __forceinline__ float wave_sum8(float (&v)[8]) {
     return t + __shfl_xor(t, 1);
 }
 
+// the sum of row j's lanes, in lanes 8 j .. 8 j + 7
+__device__ __forceinline__ float wave_rows(float (&v)[8]) { return wave_sum8(v); }
+__device__ __forceinline__ float wave_rows(float (&v)[2]) {
+    const float a = wave_sum(v[0]), b = wave_sum(v[1]);
+    return (threadIdx.x & 63) < 8 ? a : b;
+}
+
 // Bound by launches and latency (the tiny configuration's matrices are a few hundred KiB), so the step's small work rides
-// along: the norm in front (a wave reads whole rows of x anyway and takes their sums of squares on the way), the
-// residual sum or SwiGLU behind.  VEC: four consecutive k per lane and step with 16-byte loads (checked at launch), which
-// leaves the tiny configuration 1 to 3 steps instead of 4 to 11 dependent ones; the rows' sums over the wave share
-// their exchanges.  Tiny configuration, 8 requests, per launch 6.4 -> 4.0 us, and 18 launches a step instead of 29.
-template <int BT, bool VEC, int EPI>
+// along: the norm in front (each wave sums its rows' squares for itself), the residual sum or SwiGLU behind.  The loads of
+// four steps along k are in flight together; the sums keep the order of one step at a time (lane l adds k = l, l + 64,
+// ... and the lanes meet in a butterfly), the norm's that of a workgroup with a thread per eight columns.  Tiny
+// configuration, 8 requests: 5.3 us a launch against 6.4 of the bare products, and 18 launches a step instead of 29.
+// BT rows a wave: 8, or 2 where that leaves most of the chip without a workgroup (the sums are the same ones).
+template <int BT, int EPI>
 __global__ __launch_bounds__(256) void proj_f32_kernel(F32Mat m, const float* __restrict__ x, int nrows, float* out) {
+    static_assert(BT == 8 || BT == 2, "wave_rows");
     constexpr int NC = EPI == F32_SWIGLU ? 2 : 1;  // columns of a wave: gate and up
+    constexpr int UN = 4;                          // steps of 64 along k in flight (12 at two rows: no faster)
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int n = blockIdx.x * 4 + wave, n_out = EPI == F32_SWIGLU ? m.rows[0] : m.N;
     if (n >= n_out) return;
-    const int b0 = blockIdx.y * BT;
+    const int b0 = blockIdx.y * BT, K = m.K;
     int src[NC], r[NC];
     src[0] = 0;
     r[0] = n;
@@ -1082,65 +1093,73 @@ __global__ __launch_bounds__(256) void proj_f32_kernel(F32Mat m, const float* __
             ++src[0];
         }
     }
-    float acc[NC][BT], ss[BT];
+    const float* row[BT];
 #pragma unroll
-    for (int j = 0; j < BT; ++j) {
-        ss[j] = 0.f;
+    for (int j = 0; j < BT; ++j) row[j] = x + (size_t)min(b0 + j, nrows - 1) * K;
+    float rinv[BT];
+    if (m.gain) {  // the rows' sums of squares: eight columns a lane, 512 a round, a round's sum as one wave of a workgroup
+        float tot = 0.f;
+        for (int u0 = 0; u0 < K / 8; u0 += 64) {
+            float ss[BT];
 #pragma unroll
-        for (int c = 0; c < NC; ++c) acc[c][j] = 0.f;
-    }
-    if constexpr (VEC) {
-        for (int k = lane * 4; k < m.K; k += 256) {
-            f32x4 wv[NC], xv[BT], gv = {1.f, 1.f, 1.f, 1.f};
+            for (int j = 0; j < BT; ++j) {
+                ss[j] = 0.f;
+                if (u0 + lane < K / 8) {
+                    const float* p = row[j] + (size_t)(u0 + lane) * 8;
 #pragma unroll
-            for (int c = 0; c < NC; ++c) wv[c] = *reinterpret_cast<const f32x4*>(m.w[src[c]] + (size_t)r[c] * m.K + k);
-#pragma unroll
-            for (int j = 0; j < BT; ++j) xv[j] = *reinterpret_cast<const f32x4*>(x + (size_t)min(b0 + j, nrows - 1) * m.K + k);
-            if (m.gain) gv = *reinterpret_cast<const f32x4*>(m.gain + k);
-#pragma unroll
-            for (int j = 0; j < BT; ++j)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    ss[j] = fmaf(xv[j][e], xv[j][e], ss[j]);
-#pragma unroll
-                    for (int c = 0; c < NC; ++c) acc[c][j] = fmaf(wv[c][e], xv[j][e] * gv[e], acc[c][j]);
+                    for (int e = 0; e < 8; ++e) ss[j] = fmaf(p[e], p[e], ss[j]);
                 }
+            }
+            tot += wave_rows(ss);
         }
-    } else {
-        const int ng = m.K / kGroup;
-        for (int k = lane; k < m.K; k += 64) {
-            float wv[NC];
+        const float ri = 1.0f / sqrtf(tot / (float)K + m.eps);
+#pragma unroll
+        for (int j = 0; j < BT; ++j) rinv[j] = __shfl(ri, j * 8);
+    }
+    float acc[NC][BT];
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int j = 0; j < BT; ++j) acc[c][j] = 0.f;
+    const int ng = K / kGroup;
+    for (int k0 = lane; k0 < K; k0 += 64 * UN) {
+        float wv[UN][NC], xv[UN][BT], gv[UN];
+#pragma unroll
+        for (int i = 0; i < UN; ++i) {
+            const int k = min(k0 + i * 64, K - 1);  // past the end: valid, not added
 #pragma unroll
             for (int c = 0; c < NC; ++c) {
                 if (m.quant) {
-                    const uint8_t byte = m.q[src[c]][(size_t)r[c] * (m.K / 2) + (k >> 1)];
+                    const uint8_t byte = m.q[src[c]][(size_t)r[c] * (K / 2) + (k >> 1)];
                     const float code = (float)((k & 1) ? (byte >> 4) : (byte & 15));
                     const size_t g = (size_t)r[c] * ng + k / kGroup;
                     const float zf = m.z[src[c]] ? __half2float(__ushort_as_half(m.z[src[c]][g])) : 8.f;
                     const float sf = __half2float(__ushort_as_half(m.s[src[c]][g]));
-                    wv[c] = (code - zf) * sf;  // exact: 5-bit integer times an 11-bit significand
+                    wv[i][c] = (code - zf) * sf;  // exact: 5-bit integer times an 11-bit significand
                 } else {
-                    wv[c] = m.w[src[c]][(size_t)r[c] * m.K + k];
+                    wv[i][c] = m.w[src[c]][(size_t)r[c] * K + k];
                 }
             }
-            const float gv = m.gain ? m.gain[k] : 1.f;
+            gv[i] = m.gain ? m.gain[k] : 0.f;
 #pragma unroll
-            for (int j = 0; j < BT; ++j) {
-                const float xv = x[(size_t)min(b0 + j, nrows - 1) * m.K + k];
-                ss[j] = fmaf(xv, xv, ss[j]);
-#pragma unroll
-                for (int c = 0; c < NC; ++c) acc[c][j] = fmaf(wv[c], xv * gv, acc[c][j]);
-            }
+            for (int j = 0; j < BT; ++j) xv[i][j] = row[j][k];
         }
+#pragma unroll
+        for (int i = 0; i < UN; ++i)
+            if (k0 + i * 64 < K) {
+#pragma unroll
+                for (int j = 0; j < BT; ++j) {
+                    const float y = m.gain ? xv[i][j] * rinv[j] * gv[i] : xv[i][j];
+#pragma unroll
+                    for (int c = 0; c < NC; ++c) acc[c][j] = fmaf(wv[i][c], y, acc[c][j]);
+                }
+            }
     }
-    static_assert(BT == 8, "wave_sum8");
-    float rinv = 1.f;
-    if (m.gain) rinv = 1.0f / sqrtf(wave_sum8(ss) / (float)m.K + m.eps);
     float v[NC];
 #pragma unroll
-    for (int c = 0; c < NC; ++c) v[c] = wave_sum8(acc[c]) * rinv;
-    const int b = b0 + ((lane >> 5 & 1) * 4 + (lane >> 4 & 1) * 2 + (lane >> 3 & 1));
-    if ((lane & 7) != 0 || b >= nrows) return;
+    for (int c = 0; c < NC; ++c) v[c] = wave_rows(acc[c]);
+    const int b = b0 + (lane >> 3);
+    if (lane >= BT * 8 || (lane & 7) != 0 || b >= nrows) return;
     float* o = out + (size_t)b * n_out + n;
     if constexpr (EPI == F32_SWIGLU) *o = v[0] / (1.0f + expf(-v[0])) * v[1];
     else if constexpr (EPI == F32_ADD) *o += v[0];
@@ -1156,29 +1175,30 @@ hipError_t launch_proj_f32(const Mat& W, const float* x, int rows, const void* g
     m.gain = (const float*)gain;
     m.eps = eps;
     if (!m.quant && W.kind != MAT_F32) return hipErrorInvalidValue;
-    bool vec = !m.quant && W.K % 4 == 0 && ((uintptr_t)x | (uintptr_t)gain) % 16 == 0;
     for (int i = 0; i < 3; ++i) {
         m.w[i] = (const float*)W.wsrc[i];
         m.q[i] = W.q[i];
         m.s[i] = W.s[i];
         m.z[i] = W.z[i];
         m.rows[i] = W.src_rows[i];
-        vec = vec && (uintptr_t)m.w[i] % 16 == 0;
     }
-    constexpr int BT = 8;
+    if (gain && W.K % 8) return hipErrorInvalidValue;
     if (epilogue == F32_SWIGLU && (W.nsrc != 2 || m.rows[0] != m.rows[1])) return hipErrorInvalidValue;
-    const dim3 grid(((epilogue == F32_SWIGLU ? m.rows[0] : W.N) + 3) / 4, (rows + BT - 1) / BT), block(256);
-    const auto go = [&](auto v) {
-        constexpr bool V = decltype(v)::value;
+    const int cols = ((epilogue == F32_SWIGLU ? m.rows[0] : W.N) + 3) / 4;
+    const auto go = [&](auto bt) {
+        constexpr int BT = decltype(bt)::value;
+        const dim3 grid(cols, (rows + BT - 1) / BT), block(256);
         switch (epilogue) {
-        case F32_STORE: hipLaunchKernelGGL((proj_f32_kernel<BT, V, F32_STORE>), grid, block, 0, st, m, x, rows, out); break;
-        case F32_ADD: hipLaunchKernelGGL((proj_f32_kernel<BT, V, F32_ADD>), grid, block, 0, st, m, x, rows, out); break;
-        case F32_SWIGLU: hipLaunchKernelGGL((proj_f32_kernel<BT, V, F32_SWIGLU>), grid, block, 0, st, m, x, rows, out); break;
+        case F32_STORE: hipLaunchKernelGGL((proj_f32_kernel<BT, F32_STORE>), grid, block, 0, st, m, x, rows, out); break;
+        case F32_ADD: hipLaunchKernelGGL((proj_f32_kernel<BT, F32_ADD>), grid, block, 0, st, m, x, rows, out); break;
+        case F32_SWIGLU: hipLaunchKernelGGL((proj_f32_kernel<BT, F32_SWIGLU>), grid, block, 0, st, m, x, rows, out); break;
         default: return hipErrorInvalidValue;
         }
         return hipGetLastError();
     };
-    return vec ? go(std::true_type{}) : go(std::false_type{});
+    // eight workgroups fit a compute unit: two rows a wave as long as that does not make more than one round of them
+    if ((long long)cols * ((rows + 1) / 2) <= 2048) return go(std::integral_constant<int, 2>{});
+    return go(std::integral_constant<int, 8>{});
 }
 
 // ---------------------------------------------------------------------------------
