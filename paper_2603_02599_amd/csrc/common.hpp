@@ -137,6 +137,10 @@ __device__ __forceinline__ u32x4_s load_stream(const u32x4_s* p) { return __buil
 __device__ __forceinline__ void lds_dma16(const void* base, uint32_t lane_bytes, uint32_t lds_byte) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_byte), "v"(lane_bytes), "s"(base) : "memory");
 }
+// The same with 4 bytes a lane: lane i's land at lds_byte + 4 i.
+__device__ __forceinline__ void lds_dma4(const void* base, uint32_t lane_bytes, uint32_t lds_byte) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(lds_byte), "v"(lane_bytes), "s"(base) : "memory");
+}
 // Read-only data of the launch at an address that is the same for the whole wave, through the scalar cache.
 __device__ __forceinline__ int32_t load_uniform(const int32_t* p) {
     return *(const __attribute__((address_space(4))) int32_t*)(uintptr_t)p;

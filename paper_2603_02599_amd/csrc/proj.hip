@@ -597,168 +597,164 @@ void proj_wide_kernel(ProjArgs a) {
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef int i32x16 __attribute__((ext_vector_type(16)));
 
-// 4-bit weights: MR 32-row blocks per workgroup (the launches use MR = 1: 32-row tiles, see proj_tiling), one
-// stage = one 128-wide group = four int8 MFMA k-steps, three stages of activations in the LDS ring.
+// 4-bit weights: a 32-row tile per workgroup (see proj_tiling), one stage = one 128-wide group = four int8 MFMA k-steps.
+// Bound by what a short launch has around its steady state (latency of the stages, the vector epilogue), so stages are
+// requested far ahead without registers to hold them: the activations and their scales go straight into one of three LDS
+// slots, two stages ahead, and the registers that this frees hold the codes three stages ahead instead of two.  8B shape,
+// against both through registers two stages ahead (us): 5 rows qkv 7.3 -> 6.8, gate/up 17.2 -> 16.1, o and down 10.3 ->
+// 8.5 on average; 64 rows gate/up 30.2 -> 29.2; bit-identical.  Codes four and activations three stages ahead (128
+// registers): 64 rows 28.7, 5 rows 17.0, not better.
 // OCT: row octets of a tile that the epilogue scales: 4, or as many as a launch of at most 16 rows has rows in (the epilogue
 // is most of the vector instructions: gate/up at 5 rows 19.1 -> 17.2 us, the step of 8 layers 924 -> 885).
-template <int MR, int NW, int OCT>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, MR == 1 ? 4 : 2)))
+template <int NW, int OCT>
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 4)))
 void proj_w4_kernel(ProjArgs a) {
-    constexpr int STEPS = 4;
-    constexpr int STAGE_UNITS = STEPS * 2 * MR * 64;  // 16-byte units of activations per stage (two planes)
-    constexpr int NT = NW * 64;
-    constexpr int UPT = (STAGE_UNITS + NT - 1) / NT;
-    __shared__ u32x4 lds[3][STAGE_UNITS];
-    __shared__ __attribute__((aligned(16))) float sx_lds[4][MR * 32];  // ring over groups: scale of each row ...
-    __shared__ __attribute__((aligned(16))) int xs_lds[4][MR * 32];    // ... and its sum of integers
+    constexpr int STEPS = 4, PA = 2, PW = 3, NBUF = PA + 1;
+    constexpr int FR = STEPS * 2, ITEMS = FR + 1, PER = (ITEMS + NW - 1) / NW;  // 1 KiB fragments of a stage, and its scales
+    constexpr int STAGE_BYTES = FR * 1024 + 256;
+    __shared__ __attribute__((aligned(16))) uint8_t lds[NBUF * STAGE_BYTES];
 
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, half = lane >> 5;
+    const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int nb = blockIdx.x * NW + wave;
     const bool active = nb < a.N / 32;
     const int split = blockIdx.y;
-    const int mb_off = blockIdx.z * MR;
+    const int mb = blockIdx.z;
     const int s0 = split * a.stages_per_split;
-    const int s1 = min(a.n_stages, s0 + a.stages_per_split);
+    const int n = min(a.n_stages, s0 + a.stages_per_split) - s0;
     const int kch = a.K / 128;
 
     // waves past the last column block work on block 0 and drop their result (keeps the loop branch-free)
-    const u32x4* Wl = a.W + ((size_t)(active ? nb : 0) * kch) * 2 * 64 + lane;
+    const u32x4* Wl = a.W + ((size_t)(active ? nb : 0) * kch + s0) * 2 * 64 + lane;
     const uint32_t* SZl = a.SZ + ((size_t)(active ? nb : 0) * (a.s_only ? (kch + 1) >> 1 : kch)) * 32 + (lane & 31);
-    const float2* QS = reinterpret_cast<const float2*>(a.qscale);
 
-    f32x16 acc[MR];
-    i32x16 ih[MR], il[MR];
+    // what this wave fetches of every stage: fragments (k-step, plane), and as the last item the rows' (scale, sum) pairs
+    const uint8_t* src[PER];
+    uint32_t dst[PER], step[PER];
+    bool frag[PER];
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)lds;
 #pragma unroll
-    for (int m = 0; m < MR; ++m)
+    for (int i = 0; i < PER; ++i) {
+        const int f = min(wave * PER + i, ITEMS - 1);   // past the last: that one again, the same bytes
+        frag[i] = f < FR;
+        src[i] = frag[i] ? (const uint8_t*)(a.A + ((size_t)(s0 * FR + f) * a.mb_rows + mb) * 64)
+                         : (const uint8_t*)(a.qscale + ((size_t)s0 * a.mb_rows + mb) * 64);
+        step[i] = frag[i] ? FR * a.mb_rows * 1024 : a.mb_rows * 256;
+        dst[i] = lds0 + f * 1024;
+    }
+    int fill = 0, fill_st = 0;
+    auto fetch = [&]() {                                // the next stage; past the end the last one again (it is not read)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[m][r] = 0.f;
-
-    u32x4 w0[2], w1[2], w2[2], areg[UPT];
-    uint32_t sz0 = 0, sz1 = 0, sz2 = 0;
-    float2 qreg = float2{0.f, 0.f};
-
-    auto load_w = [&](u32x4(&w)[2], uint32_t& sz, int st) {
-        w[0] = Wl[((size_t)st * 2) * 64];
-        w[1] = Wl[((size_t)st * 2 + 1) * 64];
-        sz = SZl[(size_t)(a.s_only ? st >> 1 : st) * 32];
-    };
-    auto load_a = [&](int st) {
-#pragma unroll
-        for (int i = 0; i < UPT; ++i) {
-            const int u = min(i * NT + tid, STAGE_UNITS - 1);  // past the stage: re-read its last unit, never stored
-            const int sp = u / (MR * 64), rem = u % (MR * 64);  // sp = step * 2 + plane
-            areg[i] = a.A[((size_t)(st * 8 + sp) * a.mb_rows + mb_off + (rem >> 6)) * 64 + (rem & 63)];
+        for (int i = 0; i < PER; ++i) {
+            if (frag[i]) lds_dma16(src[i], lane * 16, dst[i] + fill);
+            else lds_dma4(src[i], lane * 4, dst[i] + fill);
+            if (fill_st + 1 < n) src[i] += step[i];
         }
-        if (tid < MR * 32) qreg = QS[(size_t)st * (a.mb_rows * 32) + mb_off * 32 + tid];
+        ++fill_st;
+        fill = fill + STAGE_BYTES == NBUF * STAGE_BYTES ? 0 : fill + STAGE_BYTES;
     };
-    auto store_a = [&](int buf, int st) {
+    f32x16 acc;
 #pragma unroll
-        for (int i = 0; i < UPT; ++i)
-            if (STAGE_UNITS % NT == 0 || i * NT + tid < STAGE_UNITS) lds[buf][i * NT + tid] = areg[i];
-        if (tid < MR * 32) {
-            sx_lds[st & 3][tid] = qreg.x;
-            xs_lds[st & 3][tid] = __float_as_int(qreg.y);
-        }
+    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+    u32x4 w[PW + 1][2];
+    uint32_t sz[PW + 1];
+    auto load_w = [&](int slot, int st) {
+        const int t = min(st, n - 1);
+        w[slot][0] = Wl[(size_t)t * 2 * 64];
+        w[slot][1] = Wl[((size_t)t * 2 + 1) * 64];
+        sz[slot] = SZl[(size_t)(a.s_only ? (s0 + t) >> 1 : s0 + t) * 32];
     };
-    auto compute = [&](int buf, const u32x4(&w)[2], uint32_t sz, int st) {
-        u32x4 afr[2][2 * MR];  // operands of one k-step (both planes), read one step ahead
-#pragma unroll
-        for (int i = 0; i < 2 * MR; ++i) afr[0][i] = lds[buf][i * 64 + lane];
+    int at = 0;
+    auto compute = [&](int slot, int st) {
+        const u32x4* A = reinterpret_cast<const u32x4*>(lds + at) + lane;
+        i32x16 ih, il;
+        u32x4 afr[2][2];  // operands of one k-step (both planes), read one step ahead
+        afr[0][0] = A[0];
+        afr[0][1] = A[64];
 #pragma unroll
         for (int s = 0; s < STEPS; ++s) {
             if (s + 1 < STEPS) {
-#pragma unroll
-                for (int i = 0; i < 2 * MR; ++i) afr[(s + 1) & 1][i] = lds[buf][((s + 1) * 2 * MR + i) * 64 + lane];
+                afr[(s + 1) & 1][0] = A[(s + 1) * 128];
+                afr[(s + 1) & 1][1] = A[(s + 1) * 128 + 64];
             }
             __builtin_amdgcn_sched_barrier(0);
-            const uint32_t wa = w[s >> 1][(s & 1) * 2], wb = w[s >> 1][(s & 1) * 2 + 1];
+            const uint32_t wa = w[slot][s >> 1][(s & 1) * 2], wb = w[slot][s >> 1][(s & 1) * 2 + 1];
             const i32x4 bfrag = {(int)(wa & 0x0F0F0F0Fu), (int)((wa >> 4) & 0x0F0F0F0Fu), (int)(wb & 0x0F0F0F0Fu),
                                  (int)((wb >> 4) & 0x0F0F0F0Fu)};
+            const i32x4 ah = __builtin_bit_cast(i32x4, afr[s & 1][0]), al = __builtin_bit_cast(i32x4, afr[s & 1][1]);
+            if (s == 0) {
+                i32x16 zero;
 #pragma unroll
-            for (int m = 0; m < MR; ++m) {
-                const i32x4 ah = __builtin_bit_cast(i32x4, afr[s & 1][m]), al = __builtin_bit_cast(i32x4, afr[s & 1][MR + m]);
-                if (s == 0) {
-                    i32x16 zero;
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) zero[r] = 0;
-                    ih[m] = __builtin_amdgcn_mfma_i32_32x32x32_i8(ah, bfrag, zero, 0, 0, 0);
-                    il[m] = __builtin_amdgcn_mfma_i32_32x32x32_i8(al, bfrag, zero, 0, 0, 0);
-                } else {
-                    ih[m] = __builtin_amdgcn_mfma_i32_32x32x32_i8(ah, bfrag, ih[m], 0, 0, 0);
-                    il[m] = __builtin_amdgcn_mfma_i32_32x32x32_i8(al, bfrag, il[m], 0, 0, 0);
-                }
+                for (int r = 0; r < 16; ++r) zero[r] = 0;
+                ih = __builtin_amdgcn_mfma_i32_32x32x32_i8(ah, bfrag, zero, 0, 0, 0);
+                il = __builtin_amdgcn_mfma_i32_32x32x32_i8(al, bfrag, zero, 0, 0, 0);
+            } else {
+                ih = __builtin_amdgcn_mfma_i32_32x32x32_i8(ah, bfrag, ih, 0, 0, 0);
+                il = __builtin_amdgcn_mfma_i32_32x32x32_i8(al, bfrag, il, 0, 0, 0);
             }
         }
         // scale-only layout: pick this group's half of the dword; the zero point is 8 everywhere
-        const uint32_t szg = a.s_only ? (((sz >> (16 * (st & 1))) & 0xffffu) | 0x48000000u) : sz;
+        const uint32_t szg = a.s_only ? (((sz[slot] >> (16 * ((s0 + st) & 1))) & 0xffffu) | 0x48000000u) : sz[slot];
         const __half2 h2 = __builtin_bit_cast(__half2, szg);
         const float sc = __low2float(h2);
         const int nzi = -(int)__high2float(h2);  // zero points are integer codes (Appendix A.1)
-        const float* sxp = sx_lds[st & 3];
-        const int* xsp = xs_lds[st & 3];
+        const u32x4* Q = reinterpret_cast<const u32x4*>(lds + at + FR * 1024) + 2 * half;
 #pragma unroll
-        for (int m = 0; m < MR; ++m)
+        for (int rr = 0; rr < OCT; ++rr) {
+            const u32x4 q01 = Q[rr * 4], q23 = Q[rr * 4 + 1];   // (scale, sum of integers) of four rows
+            const float sx[4] = {__uint_as_float(q01[0]), __uint_as_float(q01[2]), __uint_as_float(q23[0]), __uint_as_float(q23[2])};
+            const int xs[4] = {(int)q01[1], (int)q01[3], (int)q23[1], (int)q23[3]};
 #pragma unroll
-            for (int rr = 0; rr < OCT; ++rr) {
-                const f32x4 sx4 = *reinterpret_cast<const f32x4*>(sxp + m * 32 + 8 * rr + 4 * half);
-                const i32x4 xs4 = *reinterpret_cast<const i32x4*>(xsp + m * 32 + 8 * rr + 4 * half);
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int e = rr * 4 + q;
-                    int tot = (ih[m][e] << 8) + il[m][e];
-                    asm("v_mad_i32_i24 %0, %1, %2, %0" : "+v"(tot) : "v"(nzi), "v"(xs4[q]));  // tot -= Z * sum xi, one instruction
-                    acc[m][e] = fmaf((float)tot, sc * sx4[q], acc[m][e]);
-                }
+            for (int q = 0; q < 4; ++q) {
+                const int e = rr * 4 + q;
+                int tot = (ih[e] << 8) + il[e];
+                asm("v_mad_i32_i24 %0, %1, %2, %0" : "+v"(tot) : "v"(nzi), "v"(xs[q]));  // tot -= Z * sum xi, one instruction
+                acc[e] = fmaf((float)tot, sc * sx[q], acc[e]);
             }
+        }
+        at = at + STAGE_BYTES == NBUF * STAGE_BYTES ? 0 : at + STAGE_BYTES;
     };
-
-    // Steady state without branches around the loads, so that the requests of the following stages stay in
-    // flight while this stage is computed; past the end the last stage is re-read and never used.
-    if (s0 < s1) {
-        auto phase = [&](const u32x4(&wc)[2], uint32_t szc, u32x4(&wn)[2], uint32_t& szn, int bufc, int bufn, int st) {
-            const int nx = min(st + 2, s1 - 1);
-            load_a(nx);  // before the weights: the LDS store below then waits for these only
-            load_w(wn, szn, nx);
-            compute(bufc, wc, szc, st);
-            store_a(bufn, nx);
-            __syncthreads();
+    if (n > 0) {
+#pragma unroll
+        for (int i = 0; i < PA; ++i) fetch();
+#pragma unroll
+        for (int i = 0; i < PW; ++i) load_w(i, i);
+        auto phase = [&](int slot, int st) {
+            // stage st of the activations has landed for every wave, and everybody is done with stage st - 1
+            __builtin_amdgcn_sched_barrier(0);
+            __builtin_amdgcn_s_waitcnt(0xc07f);
+            asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(3 + (PA - 1) * (PER + 3)) : "memory");
+            fetch();
+            load_w((slot + PW) % (PW + 1), st + PW);
+            __builtin_amdgcn_sched_barrier(0);
+            compute(slot, st);
         };
-        const int sA = min(s0 + 1, s1 - 1);
-        load_w(w0, sz0, s0);
-        load_a(s0);
-        store_a(0, s0);
-        load_w(w1, sz1, sA);
-        load_a(sA);
-        store_a(1, sA);
-        __syncthreads();
-        for (int st = s0; st < s1; st += 3) {
-            phase(w0, sz0, w2, sz2, 0, 2, st);
-            if (st + 1 >= s1) break;
-            phase(w1, sz1, w0, sz0, 1, 0, st + 1);
-            if (st + 2 >= s1) break;
-            phase(w2, sz2, w1, sz1, 2, 1, st + 2);
+        for (int st = 0; st < n;) {
+#pragma unroll
+            for (int i = 0; i <= PW; ++i) {
+                phase(i, st);
+                if (++st >= n) break;
+            }
         }
     }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");    // nothing is in flight into LDS when the workgroup ends
     if (!active) return;
     const int col = lane & 31;
     float* o = a.out + (size_t)split * a.ld_rows * a.ldo + nb * 32 + col;
 #pragma unroll
-    for (int m = 0; m < MR; ++m)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int b = (mb_off + m) * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
-            if (b < a.rows) o[(size_t)b * a.ldo] = acc[m][r];
-        }
+    for (int r = 0; r < OCT * 4; ++r) {
+        const int b = mb * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
+        if (b < a.rows) o[(size_t)b * a.ldo] = acc[r];
+    }
 }
 
-template <int MR>
 static hipError_t launch_proj_w4(const ProjArgs& a, int nw, int splits, int mtiles, hipStream_t st) {
     const auto go = [&](auto nwc) {
         constexpr int NW = decltype(nwc)::value;
         dim3 grid((a.N / 32 + NW - 1) / NW, splits, mtiles), block(NW * 64);
-        if (a.rows <= 8) hipLaunchKernelGGL((proj_w4_kernel<MR, NW, 1>), grid, block, 0, st, a);
-        else if (a.rows <= 16) hipLaunchKernelGGL((proj_w4_kernel<MR, NW, 2>), grid, block, 0, st, a);
-        else hipLaunchKernelGGL((proj_w4_kernel<MR, NW, 4>), grid, block, 0, st, a);
+        if (a.rows <= 8) hipLaunchKernelGGL((proj_w4_kernel<NW, 1>), grid, block, 0, st, a);
+        else if (a.rows <= 16) hipLaunchKernelGGL((proj_w4_kernel<NW, 2>), grid, block, 0, st, a);
+        else hipLaunchKernelGGL((proj_w4_kernel<NW, 4>), grid, block, 0, st, a);
         return hipGetLastError();
     };
     switch (nw) {
@@ -999,7 +995,7 @@ hipError_t launch_proj(const ProjLaunch& p, hipStream_t st) {
         const int nw = proj_pick_waves(W, p.rows, splits);
         if (w4) {
             if (p.epilogue != EPI_STORE) return hipErrorInvalidValue;
-            return launch_proj_w4<1>(a, nw, splits, t.mtiles, st);
+            return launch_proj_w4(a, nw, splits, t.mtiles, st);
         }
         if (t.mb == 2) return launch_proj_nw<2, 128>(a, nw, p.epilogue, splits, t.mtiles, st);
         return launch_proj_nw<4, 128>(a, nw, p.epilogue, splits, t.mtiles, st);
