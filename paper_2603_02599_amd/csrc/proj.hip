@@ -901,14 +901,16 @@ static ProjShape proj_pick(const Mat& W, int rows, int max_splits) {
 // Which kernel multiplies more than 128 rows (bf16).  256 x 256 tiles want whole rounds of 256 workgroups without a
 // split along k: a prefill block (rows > 256) and the vocabulary projection have them (8B shape, 256 rows: lm_head 405
 // us against 535 with the strip kernel).  A batch's other projections do not: the 128 x 256 tiles of the tall kernel
-// take 24 / 40 / 75 / 130 us (o, q/k/v, down, gate/up) where the wide kernel, split finer, takes 27 to 40 % longer.
+// take 24 / 40 / 75 / 120 us (o, q/k/v, down, gate/up) where the wide kernel, split finer, takes 27 to 40 % longer.
 static bool use_wide(const Mat& W, int rows) {
     return W.kind == MAT_BF16_PACKED && (rows > kMaxBatchTile || (rows > 128 && (W.N / 32 + 7) / 8 >= 256));
 }
 static bool use_tall(const Mat& W, int rows) { return W.kind == MAT_BF16_PACKED && rows > 128 && !use_wide(W, rows); }
 
 // Split-K factor of a wide launch: whole rounds of 256 workgroups cost stages x 0.95 us (2048 cycles of matrix
-// instructions at the clock they leave) plus about 8 us each, a split the writing and reading of its slab.
+// instructions) plus about 8 us each, a split the writing and reading of its slab.  With every unit busy on random data
+// the clock falls and a stage takes up to 1.4 us; that figure gives the same split for 45 of 48 launches of the 8B and
+// 14B shapes (q/k/v, o, down at 300 to 2048 rows).
 static int wide_pick_splits(const Mat& W, int rows, int max_splits) {
     const int stages = W.K / 32;
     const long long tiles = (long long)((W.N / 32 + 7) / 8) * ((rows + 255) / 256);
