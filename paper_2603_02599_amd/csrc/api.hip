@@ -797,10 +797,7 @@ static int step_impl(sun_kv_pool* pool_, const sun_weights* weights_, bool want_
                 SUN_HIP_CHECK(launch_residual_norm(c, ws.x, ws.part, so, batch, L.g2, batch, ws.hA,
                                                    W.quant ? ws.qs : nullptr, st));
             }
-            if (!W.quant && batch > 64) {
-                // bf16 above 64 rows (no split-K there): SwiGLU in the epilogue, the down projection's tile as
-                // output.  Up to 64 rows the two-way split over 256 workgroups plus a separate SwiGLU kernel is
-                // faster: unsplit, the 28672 columns make 224 workgroups and leave 32 compute units idle.
+            if (proj_fuses_swiglu(L.gu, batch)) {   // SwiGLU in the epilogue, the down projection's tile as output
                 ProfScope p(prof, 4, st);
                 ProjLaunch pl{&L.gu, ws.hA, nullptr, batch, EPI_SWIGLU, 1, (float*)ws.uA, L.gu.N, batch};
                 SUN_HIP_CHECK(launch_proj(pl, st));
@@ -1108,7 +1105,7 @@ static int prefill_block(KvPool& pool, const Weights& W, const Workspace& ws, in
             ProfScope p(prof, 7, st);
             SUN_HIP_CHECK(launch_residual_norm(c, ws.x, ws.part, so, rows, L.g2, rows, ws.hA, nullptr, st));
         }
-        if (rows > 64) {   // as in a decode step: SwiGLU in the epilogue, the down projection's tile as output
+        if (proj_fuses_swiglu(L.gu, rows)) {   // as in a decode step
             ProfScope p(prof, 4, st);
             SUN_HIP_CHECK(launch_proj(ProjLaunch{&L.gu, ws.hA, nullptr, rows, EPI_SWIGLU, 1, (float*)ws.uA, L.gu.N, rows}, st));
         } else {

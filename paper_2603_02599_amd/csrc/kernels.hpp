@@ -24,6 +24,7 @@ struct ProjLaunch {
 };
 // Chooses the split-K factor the step uses for this matrix and row count.
 int proj_pick_splits(const Mat& W, int rows, int max_splits);
+bool proj_fuses_swiglu(const Mat& gu, int rows);  // gate/up: one launch with EPI_SWIGLU rather than slabs and launch_swiglu_tile
 hipError_t launch_proj(const ProjLaunch& p, hipStream_t st);
 
 // fp32 activations path (vector ALU): y[b][n] = sum_k W[n][k] h[b][k] with h = x, or rmsnorm(x) * gain when gain is given;

@@ -826,7 +826,7 @@ static int chunks_per_split(int kch, int splits) { return (kch + splits - 1) / s
 // Waves per workgroup (each wave owns 32 columns) and split-K factor.  A compute unit's share of
 // the HBM bandwidth does not grow with the number of workgroups it hosts, so the launch is only
 // as fast as the most loaded unit: the pair is chosen to spread the weight bytes evenly over the
-// 256 compute units (N = 6144 -> 6 waves x 8 splits, N = 28672 -> 7 waves x 2 splits, ...), with a
+// 256 compute units (N = 6144 -> 6 waves x 8 splits, N = 4096 -> 4 x 8, ...), with a
 // fixed charge per workgroup for filling and draining its pipeline.  Depends on the matrix and the
 // row-count class only.  The bf16 kernel above 64 rows keeps 4 waves; 4-bit launches of several row tiles have
 // a rule of their own (w4_tiles_pick).
@@ -926,6 +926,17 @@ static int wide_pick_splits(const Mat& W, int rows, int max_splits) {
         }
     }
     return best;
+}
+
+// Gate/up: SwiGLU in the epilogue, which needs every sum whole (no split along k), or slabs and a kernel of their own.
+// bf16 only (the 4-bit down projection wants its input's group sums).  Above 64 rows the epilogue always wins.  Up to 64
+// rows it does where the columns alone nearly fill the chip, from 208 workgroups of four waves on; it saves a launch and
+// the slabs.  A layer, hidden 4096, slabs -> epilogue (us), at 1 / 16 / 64 rows: 160 workgroups (ffn 10240) 111 / 117 / 134 ->
+// 114 / 119 / 141, 192 (12288) 120 / 126 / 143 -> 118 / 123 / 145, 256 (16384) 134 / 138 / 158 -> 130 / 134 / 153, 448
+// (28672) 177 / 185 / 212 -> 175 / 179 / 198; hidden 2048 alike; hidden 5120 with 216 (14B shape): 176 / 193 / 268 -> 177 /
+// 191 / 266; 8B shape (224), step of 8 layers: 1167 / 1279 / 1792 -> 1150 / 1243 / 1759.
+bool proj_fuses_swiglu(const Mat& gu, int rows) {
+    return gu.kind == MAT_BF16_PACKED && (rows > 64 || (gu.N / 32 + 3) / 4 >= 208);
 }
 
 int proj_pick_splits(const Mat& W, int rows, int max_splits) {

@@ -103,3 +103,21 @@ def test_w4_projections_at_the_edges_of_row_tiles(H, rows):
         torch.cuda.synchronize()
         want = x.double() @ M.t()
         assert ((out.double() - want).abs() <= 1e-3 + 1e-4 * want.abs()).all(), mat
+
+
+@pytest.mark.parametrize("ffn", [13184, 13312, 16512], ids=["206-workgroups", "208-workgroups", "ragged-strips"])
+@pytest.mark.parametrize("batch", [1, 33, 64])
+def test_gate_up_on_both_sides_of_the_fused_epilogue(H, ffn, batch):
+    """Below 208 workgroups of columns the gate/up sums go through slabs and a SwiGLU kernel, from there on through the
+    projection's epilogue; 1032 strips leave waves of the last workgroup without columns."""
+    shape = dataclasses.replace(wl.SMALL128, name="ffn", ffn=ffn)
+    work = wl.make_workload("cfg1", shape=shape, dtype="bf16", batch=batch, seed=970 + batch)
+    rng = np.random.default_rng(batch)
+    work.seq_lens = rng.integers(1, 40, size=batch).astype(np.int32)
+    work.page_tables, work.n_pages = wl.deal_page_tables(work.seq_lens, rng)
+    case = H.GpuCase(work)
+    ref = H.run_oracle(case, list(range(batch)))
+    case.logits.fill_(float("nan"))
+    case.step(flags=sun.SUN_VALIDATE)
+    H.check_logits(case.logits.cpu().numpy(), ref["logits"], "bf16")
+    H.check_next_tokens(case.next.cpu().numpy(), ref["logits"], 2e-2)
