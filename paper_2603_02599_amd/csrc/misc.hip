@@ -409,10 +409,25 @@ hipError_t launch_argmax(const float* logits, int batch, int vocab, float* part_
 // pool keeps it transposed ([dim][token]).  Only the positions of the source are written, so a chunk can
 // be appended to a partly filled page.  A page id outside the pool skips the page.
 //
-// Bound by HBM: every byte is read once and written once, nothing is used again, so loads and stores stream past
-// the caches (32 layers x 4096 tokens of 8 heads, 537 MB in and out: 189 us through the caches, 169 us streamed,
-// 6.4 TB/s read plus written).  Two heads to a workgroup (a source run of 512 bytes a token) is slower, 175 us: half
-// the workgroups, each with twice the work around its one barrier.
+// Bound by HBM: every byte is read once and written once.  A cache larger than what the L2s of the chip hold (32 MB) streams
+// past them (32 layers x 4096 tokens of 8 heads, 537 MB in and out: 189 us through the caches, 169 us streamed, 6.4 TB/s
+// read plus written; 24.3 -> 21.7 us for a hand-over of 25 us).  A smaller one is a launch and its latency, and what it
+// leaves in the caches the next step reads: through them (0.5 to 8.4 MB 7.4 us, streamed 7.6).  Two heads to a workgroup
+// (a source run of 512 bytes a token) is slower, 175 us for the 537 MB: half the workgroups, each with twice the work
+// around its one barrier.
+constexpr size_t kIngestStreamBytes = 32u << 20;  // bytes of the source, from which the launch streams
+
+template <bool STREAM, typename T>
+__device__ __forceinline__ T ingest_load(const T* p) {
+    if constexpr (STREAM) return load_stream(p);
+    else return *p;
+}
+template <bool STREAM, typename T>
+__device__ __forceinline__ void ingest_store(T v, T* p) {
+    if constexpr (STREAM) __builtin_nontemporal_store(v, p);
+    else *p = v;
+}
+
 struct IngestArgs {
     uint16_t* kbase;  // pool base + k_off
     uint16_t* vbase;
@@ -423,6 +438,7 @@ struct IngestArgs {
     int n_tokens, first_pos, Hkv, D, n_pages;
 };
 
+template <bool STREAM>
 __global__ __launch_bounds__(256) void kv_ingest_kernel(IngestArgs a) {
     __shared__ uint16_t tile[kPageTokens][128 + 8];
     const int lp = a.first_pos / kPageTokens + blockIdx.x, h = blockIdx.y, l = blockIdx.z, tid = threadIdx.x;
@@ -437,9 +453,9 @@ __global__ __launch_bounds__(256) void kv_ingest_kernel(IngestArgs a) {
         const int s = idx / cpt, c = idx % cpt;
         if (s < s_lo || s >= s_hi) continue;
         const size_t so = (((size_t)l * a.n_tokens + (p0 + s - a.first_pos)) * a.Hkv + h) * D + c * 8;
-        const u32x4 k = load_stream(reinterpret_cast<const u32x4*>(a.k_src + so));
-        const u32x4 v = load_stream(reinterpret_cast<const u32x4*>(a.v_src + so));
-        __builtin_nontemporal_store(k, reinterpret_cast<u32x4*>(kd + s * D + c * 8));
+        const u32x4 k = ingest_load<STREAM>(reinterpret_cast<const u32x4*>(a.k_src + so));
+        const u32x4 v = ingest_load<STREAM>(reinterpret_cast<const u32x4*>(a.v_src + so));
+        ingest_store<STREAM>(k, reinterpret_cast<u32x4*>(kd + s * D + c * 8));
         *reinterpret_cast<u32x4*>(&tile[s][c * 8]) = v;
     }
     __syncthreads();
@@ -453,7 +469,7 @@ __global__ __launch_bounds__(256) void kv_ingest_kernel(IngestArgs a) {
             u32x4 o;
 #pragma unroll
             for (int j = 0; j < 4; ++j) o[j] = (uint32_t)e[2 * j] | ((uint32_t)e[2 * j + 1] << 16);
-            __builtin_nontemporal_store(o, reinterpret_cast<u32x4*>(vd + dim * kPageTokens + s0));
+            ingest_store<STREAM>(o, reinterpret_cast<u32x4*>(vd + dim * kPageTokens + s0));
         } else {
             for (int j = 0; j < 8; ++j)
                 if (s0 + j >= s_lo && s0 + j < s_hi) vd[dim * kPageTokens + s0 + j] = tile[s0 + j][dim];
@@ -482,7 +498,10 @@ hipError_t launch_kv_ingest(const KvPool& pool, const void* k_src, const void* v
     a.D = c.head_dim;
     a.n_pages = (int)L.n_pages;
     const int pages = (first_pos + n_tokens - 1) / kPageTokens - first_pos / kPageTokens + 1;
-    hipLaunchKernelGGL(kv_ingest_kernel, dim3(pages, c.n_kv_heads, c.n_layers), dim3(256), 0, st, a);
+    const size_t bytes = (size_t)2 * c.n_layers * n_tokens * c.n_kv_heads * c.head_dim * 2;
+    const dim3 grid(pages, c.n_kv_heads, c.n_layers);
+    if (bytes > kIngestStreamBytes) hipLaunchKernelGGL(kv_ingest_kernel<true>, grid, dim3(256), 0, st, a);
+    else hipLaunchKernelGGL(kv_ingest_kernel<false>, grid, dim3(256), 0, st, a);
     return hipGetLastError();
 }
 

@@ -121,3 +121,22 @@ def test_gate_up_on_both_sides_of_the_fused_epilogue(H, ffn, batch):
     case.step(flags=sun.SUN_VALIDATE)
     H.check_logits(case.logits.cpu().numpy(), ref["logits"], "bf16")
     H.check_next_tokens(case.next.cpu().numpy(), ref["logits"], 2e-2)
+
+
+@pytest.mark.parametrize("tokens,first", [(4096, 5), (4097, 5), (4133, 0)], ids=["through-the-caches", "streamed", "streamed-aligned"])
+def test_ingest_on_both_sides_of_the_streaming_rule(H, tokens, first):
+    """A hand-over of more than 32 MB (8 KB a token here) streams past the caches: the pool bit for bit as the oracle's."""
+    shape = dataclasses.replace(wl.LLAMA_8B, name="ingest", n_layers=2)
+    cfg = sun.make_cfg(shape, "bf16")
+    n_pages = (tokens + first + 15) // 16 + 3
+    mem = torch.empty(sun.sun_kv_pool_bytes(cfg, n_pages) // 2, dtype=torch.bfloat16, device="cuda")
+    wl.fill_kv_pool(mem, 62)
+    pool = sun.sun_kv_pool_create(cfg, mem, 16, 1)
+    host = H.to_np(mem).copy()
+    row = np.random.default_rng(tokens).permutation(n_pages).astype(np.int32)
+    k = torch.randn((2, tokens, shape.n_kv_heads, shape.head_dim), device="cuda").to(torch.bfloat16)
+    v = torch.randn_like(k)
+    sun.sun_kv_pool_ingest(pool, 0, k, v, first, torch.from_numpy(row).cuda(), flags=sun.SUN_VALIDATE)
+    H.orc.kv_ingest(host, H.layout_strides(pool.layout()), H.to_np(k), H.to_np(v), first, row)
+    torch.cuda.synchronize()
+    assert np.array_equal(H.to_np(mem), host)
