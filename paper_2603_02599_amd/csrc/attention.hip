@@ -613,11 +613,13 @@ struct CombineArgs {
     int Hq, D, batch, out_mb, uniform;
 };
 
-// A workgroup merges 128 columns of a request: one head of 128 dims or two of 64, each wave for itself.  Bound by the latency
-// of the partials, which the split kernel has just written: the chunks' maxima and sums are read first, a lane per chunk,
-// so that the outputs' loads depend on nothing but each other's order and sixteen of them are in flight per thread.
-// With a running maximum over eight chunks at a time (24 loads a round, each round waiting for the one before):
-// 8B shape, 16 / 256 requests 6.4 -> 5.1 / 21.7 -> 18.3 us, 14B shape, 24 requests of 17 k tokens 24.4 -> 17.5.
+// A workgroup merges 128 columns of a request: one head of 128 dims or two of 64, each wave for itself.  Chunks are added in
+// token order under a running maximum that moves once per eight chunks.  Bound by the latency of the partials, which the
+// split kernel has just written: 64 chunks' maxima and sums are read at once, a lane per chunk, and their weights and the
+// eights' rescaling factors computed there, so that the outputs' loads depend on nothing but each other's order and sixteen
+// of them are in flight per thread.  With the outputs'
+// loads of a round behind the rescaling of the one before (24 loads a round): 8B shape, 16 / 256 requests 6.4 -> 5.3 /
+// 21.7 -> 17.6 us, 14B shape, 24 requests of 17 k tokens 24.4 -> 17.0.
 __global__ __launch_bounds__(128) void attn_combine_kernel(CombineArgs a) {
     const int b = blockIdx.y, col = blockIdx.x * 128 + threadIdx.x, lane = threadIdx.x & 63;
     const int h = col / a.D, j = col % a.D;   // a wave's 64 columns are of one head
@@ -625,13 +627,23 @@ __global__ __launch_bounds__(128) void attn_combine_kernel(CombineArgs a) {
     const int n = c1 - c0;
     const size_t stride = (size_t)a.Hq * (a.D + 2);
     const float* p = a.partial + (size_t)c0 * stride + (size_t)h * (a.D + 2);
-    float M = -INFINITY;
-    for (int c = lane; c < n; c += 64) M = fmaxf(M, p[c * stride + a.D]);
-    M = wave_max(M);
-    float num = 0.f, den = 0.f;
-    for (int cb = 0; cb < n; cb += 64) {  // 64 chunks' weights a pass, one per lane; chunks are added in order
+    float M = -INFINITY, num = 0.f, den = 0.f;
+    for (int cb = 0; cb < n; cb += 64) {
         const int c = cb + lane, cnt = min(n - cb, 64);
-        const float w = c < n ? exp2f(p[c * stride + a.D] - M) : 0.f, l = c < n ? p[c * stride + a.D + 1] : 0.f;
+        const float m = c < n ? p[c * stride + a.D] : -INFINITY, l = c < n ? p[c * stride + a.D + 1] : 0.f;
+        float top = m;                        // maximum up to the end of the lane's eight
+#pragma unroll
+        for (int o = 1; o < 8; o <<= 1) top = fmaxf(top, __shfl_xor(top, o));
+#pragma unroll
+        for (int o = 8; o < 64; o <<= 1) {
+            const float t = __shfl_up(top, o);
+            if (lane >= o) top = fmaxf(top, t);
+        }
+        top = fmaxf(top, M);
+        float prev = __shfl_up(top, 8);       // and up to its start
+        if (lane < 8) prev = M;
+        const float w = c < n ? exp2f(m - top) : 0.f, sc = exp2f(prev - top);
+        M = __shfl(top, 63);
         const float* pj = p + (size_t)cb * stride + j;
         for (int k0 = 0; k0 < cnt; k0 += 16) {
             float o[16];
@@ -640,6 +652,11 @@ __global__ __launch_bounds__(128) void attn_combine_kernel(CombineArgs a) {
 #pragma unroll
             for (int i = 0; i < 16; ++i)
                 if (k0 + i < cnt) {
+                    if (i % 8 == 0) {
+                        const float s = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(sc), k0 + i));
+                        num *= s;
+                        den *= s;
+                    }
                     const float wk = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(w), k0 + i));
                     den = fmaf(wk, __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(l), k0 + i)), den);
                     num = fmaf(wk, o[i], num);

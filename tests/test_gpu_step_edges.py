@@ -140,3 +140,63 @@ def test_ingest_on_both_sides_of_the_streaming_rule(H, tokens, first):
     H.orc.kv_ingest(host, H.layout_strides(pool.layout()), H.to_np(k), H.to_np(v), first, row)
     torch.cuda.synchronize()
     assert np.array_equal(H.to_np(mem), host)
+
+
+def test_chunks_are_merged_in_groups_of_eight(H):
+    """The merge of a request's chunks adds them in token order under a running maximum that moves once per eight chunks, for
+    one chunk, ragged groups and more than a wave's 64.  The inputs make every chunk's maximum, sum (1) and output exact (one
+    key per chunk counts, with a bf16 score and value), so the sums can be repeated bit for bit; an order of its own (one
+    maximum for all chunks, say) agrees in about two outputs of three."""
+    shape, B = wl.SMALL128, 64
+    rng = np.random.default_rng(980)
+    lens = rng.integers(1, 3000, size=B).astype(np.int32)
+    lens[:4] = [1, 64, 17 * 1024 + 40, 66 * 256]
+    cfg = sun.make_cfg(shape, "bf16")
+    tables, n_pages = wl.deal_page_tables(lens - 1, rng)
+    n_pages += 1
+    D, Hkv, G = shape.head_dim, shape.n_kv_heads, shape.n_q_heads // shape.n_kv_heads
+    bf = lambda a: torch.from_numpy(np.ascontiguousarray(a, np.float32)).to(torch.bfloat16)
+    host = np.zeros(sun.sun_kv_pool_bytes(cfg, n_pages) // 2, np.uint16)
+    mem = torch.empty(host.size, dtype=torch.bfloat16, device=H.DEV)
+    pool = sun.sun_kv_pool_create(cfg, mem, 16, 1)
+    st = H.layout_strides(pool.layout())
+    chunks = []
+    for b, n in enumerate(lens):
+        full = max(int(n) // 256 - 1, 0)       # the chunk grid from 64 requests up
+        starts = [256 * i for i in range(full)] + list(range(256 * full, int(n), 64))
+        ends = starts[1:] + [int(n)]
+        keys = [int(rng.integers(a, z)) for a, z in zip(starts, ends)]
+        K = np.zeros((shape.n_layers, n, Hkv, D), np.float32)
+        V = np.zeros_like(K)
+        K[..., 0] = -30000.0
+        K[0, keys, :, 0] = bf(rng.normal(0, 3, (len(keys), Hkv))).float().numpy()
+        V[0, keys] = bf(rng.normal(0, 1, (len(keys), Hkv, D))).float().numpy()
+        H.orc.kv_ingest(host, st, H.to_np(bf(K)), H.to_np(bf(V)), 0, tables[b])
+        chunks.append((K[0, keys, :, 0], V[0, keys]))
+    mem.copy_(torch.from_numpy(host.view(np.int16)).view(torch.bfloat16))
+    scale = np.float32(1.4426950408889634) / np.sqrt(np.float32(D))
+    x = np.float32(1) / scale                  # the query whose scaled value is exactly 1
+    x = next(c for c in (x, np.nextafter(x, np.float32(0)), np.nextafter(x, np.float32(99))) if c * scale == 1)
+    q = np.zeros((B, shape.n_q_heads, D), np.float32)
+    q[:, :, 0] = x
+    out = torch.full((B, shape.q_dim), float("nan"), device=H.DEV)
+    ws = torch.empty(sun.sun_workspace_bytes(cfg, B, tables.shape[1]), dtype=torch.uint8, device=H.DEV)
+    sun.sun_paged_attention(pool, 0, torch.from_numpy(q.reshape(B, -1)).to(H.DEV), torch.from_numpy(tables).to(H.DEV),
+                            torch.from_numpy(lens).to(H.DEV), out, ws)
+    got = out.cpu().numpy().reshape(B, Hkv, G, D)
+    exp2 = lambda a: torch.exp2(torch.from_numpy(np.asarray(a, np.float32)).to(H.DEV)).cpu().numpy()
+    fma = lambda a, c, d: (a.astype(np.float64) * c + d).astype(np.float32)
+    same = 0
+    for b, (m, o) in enumerate(chunks):
+        M, num, den = np.full(Hkv, -np.inf, np.float32), np.zeros((Hkv, D), np.float32), np.zeros(Hkv, np.float32)
+        for c0 in range(0, len(m), 8):
+            Mn = np.maximum(M, m[c0:c0 + 8].max(0))
+            sc, w, M = exp2(M - Mn), exp2(m[c0:c0 + 8] - Mn), Mn
+            num, den = num * sc[:, None], den * sc
+            for i in range(len(w)):
+                den = fma(w[i], 1.0, den)
+                num = fma(w[i][:, None], o[c0 + i], num)
+        want = (num / den[:, None])[:, None]
+        assert np.abs(got[b] - want).max() <= 1e-5 * np.abs(o).max()
+        same += int((got[b] == want).sum())
+    assert same >= 0.999 * got.size, same / got.size   # what is left: sums rounded twice, and exponentials an ulp apart
