@@ -105,6 +105,24 @@ def test_w4_projections_at_the_edges_of_row_tiles(H, rows):
         assert ((out.double() - want).abs() <= 1e-3 + 1e-4 * want.abs()).all(), mat
 
 
+@pytest.mark.parametrize("rows,full", [(66, 128), (96, 128), (129, 256), (150, 256), (225, 256)])
+def test_w4_rows_do_not_depend_on_the_rows_beside_them(H, rows, full):
+    """The split along k goes with the class of the row count, so the rows of a smaller batch are those of the full one, bit
+    for bit, also where fewer row tiles are launched."""
+    shape = dataclasses.replace(wl.SMALL128, name="w4_rows", n_layers=1, hidden=4096, n_q_heads=32, n_kv_heads=8)
+    cfg = sun.make_cfg(shape, "bf16")
+    w = wl.make_weights(shape, "bf16", H.DEV, 79)
+    W = sun.sun_qweights_create(cfg, w, {k: [sun.sun_quantize_w4(m, 128, "asym") for m in w[k]] for k in sun.QUANT_KEYS})
+    x = torch.randn((full, 4096), device=H.DEV, generator=torch.Generator(device=H.DEV).manual_seed(rows))
+    got = []
+    for n in (rows, full):
+        out = torch.full((n, 4096), float("nan"), device=H.DEV)
+        sun.sun_linear(W, 0, 1, x[:n], out, torch.empty(sun.sun_workspace_bytes(cfg, n, 1), dtype=torch.uint8, device=H.DEV))
+        torch.cuda.synchronize()
+        got.append(out.cpu().numpy())
+    assert np.isfinite(got[0]).all() and np.array_equal(got[0], got[1][:rows])
+
+
 @pytest.mark.parametrize("ffn", [13184, 13312, 16512], ids=["206-workgroups", "208-workgroups", "ragged-strips"])
 @pytest.mark.parametrize("batch", [1, 33, 64])
 def test_gate_up_on_both_sides_of_the_fused_epilogue(H, ffn, batch):
