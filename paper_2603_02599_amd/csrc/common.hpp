@@ -133,13 +133,19 @@ __device__ __forceinline__ u32x4_s load_stream(const u32x4_s* p) { return __buil
 
 // 16 bytes a lane from memory straight into LDS: lane i's, at base + lane_bytes, land at lds_byte + 16 i.  No register
 // holds the data and the compiler does not know of the request: whoever reads the place waits for it by hand (vmcnt,
-// then the workgroup's barrier).  base and lds_byte are the same for the whole wave.
+// then the workgroup's barrier).  base and lds_byte are the same for the whole wave.  A vector memory instruction may read a
+// scalar register that a vector instruction (a lane read, say) wrote only five wait states later, and the compiler inserts
+// none in front of assembly; a scalar copy of base carries no such delay and fills the wait state that m0 wants.
 __device__ __forceinline__ void lds_dma16(const void* base, uint32_t lane_bytes, uint32_t lds_byte) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_byte), "v"(lane_bytes), "s"(base) : "memory");
+    uint64_t copy;
+    asm volatile("s_mov_b32 m0, %1\n\ts_mov_b64 %0, %3\n\tglobal_load_lds_dwordx4 %2, %0"
+                 : "=&s"(copy) : "s"(lds_byte), "v"(lane_bytes), "s"(base) : "memory", "m0");
 }
 // The same with 4 bytes a lane: lane i's land at lds_byte + 4 i.
 __device__ __forceinline__ void lds_dma4(const void* base, uint32_t lane_bytes, uint32_t lds_byte) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(lds_byte), "v"(lane_bytes), "s"(base) : "memory");
+    uint64_t copy;
+    asm volatile("s_mov_b32 m0, %1\n\ts_mov_b64 %0, %3\n\tglobal_load_lds_dword %2, %0"
+                 : "=&s"(copy) : "s"(lds_byte), "v"(lane_bytes), "s"(base) : "memory", "m0");
 }
 // Read-only data of the launch at an address that is the same for the whole wave, through the scalar cache.
 __device__ __forceinline__ int32_t load_uniform(const int32_t* p) {

@@ -1,0 +1,83 @@
+"""What the compiler makes of device code whose correctness it cannot see: requests from memory straight into LDS are
+written as inline assembly, and waits for them are counted by hand.  The sources are compiled to assembly here (no GPU) and read."""
+import os
+import re
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2603_02599_amd", "csrc")
+
+
+def assembly(src, out):
+    """kernel name -> its instructions, one string each, labels included"""
+    from paper_2603_02599_amd.build import FLAGS
+    flags = [f for f in FLAGS if f != "-fPIC"]
+    subprocess.run(["hipcc", *flags, "--offload-device-only", "-S", str(src), "-o", str(out)], check=True, capture_output=True)
+    kernels, name = {}, None
+    for line in open(out):
+        line = line.split(";")[0].strip()
+        m = re.fullmatch(r"(_Z\w+):", line)
+        if m:
+            name = m.group(1)
+            kernels[name] = []
+        elif line.startswith(".Lfunc_end"):
+            name = None
+        elif name and line and not line.startswith("."):
+            kernels[name].append(line)
+        elif name and re.fullmatch(r"\.LBB\w+:", line):
+            kernels[name].append(line)
+    return kernels
+
+
+PROBE = r"""
+#include "common.hpp"
+using namespace sun;
+typedef __attribute__((address_space(3))) unsigned lds_t;
+typedef __attribute__((address_space(1))) const void* global_t;
+__global__ void probe_base(const unsigned* where, unsigned* out) {
+    __shared__ unsigned buf[512];
+    const int lane = threadIdx.x & 63;
+    const unsigned lo = __builtin_amdgcn_readfirstlane(where[lane * 2]), hi = __builtin_amdgcn_readfirstlane(where[lane * 2 + 1]);
+    REQUEST((const void*)((uint64_t)hi << 32 | lo), lane * 4, (uint32_t)(uintptr_t)(lds_t*)buf);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    out[lane] = buf[lane];
+}
+__global__ void probe_m0(const unsigned* a, const unsigned* b, unsigned* out) {
+    __shared__ unsigned buf[1024];
+    const int lane = threadIdx.x & 63;
+    lds_t* l = (lds_t*)buf;
+    __builtin_amdgcn_global_load_lds((global_t)(a + lane), l, 4, 0, 0);
+    REQUEST(b, lane * 4, (uint32_t)(uintptr_t)l + 2048);
+    __builtin_amdgcn_global_load_lds((global_t)(a + 64 + lane), l, 4, 256, 0);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    out[lane] = buf[lane] + buf[lane + 64] + buf[lane + 512];
+}
+"""
+
+
+@pytest.mark.parametrize("request_fn", ["lds_dma4", "lds_dma16"])
+def test_requests_into_lds_are_safe_by_themselves(tmp_path, request_fn):
+    """The statement's base may come from a lane read right before it: a vector memory instruction reads a scalar register that
+    a scalar instruction wrote, or five wait states lie between the vector instruction that wrote it and the read.  And
+    the statement overwrites m0: code around it that uses m0 has to set it again."""
+    src = tmp_path / "probe.hip"
+    src.write_text(PROBE.replace('"common.hpp"', f'"{CSRC}/common.hpp"').replace("REQUEST", request_fn))
+    k = assembly(src, tmp_path / "probe.s")
+    code = next(v for n, v in k.items() if "probe_base" in n)
+    at = next(i for i, s in enumerate(code) if s.startswith("global_load_lds"))
+    base = re.search(r"s\[(\d+):(\d+)\]", code[at]).groups()
+    states, writer = 0, None
+    for s in reversed(code[:at]):
+        if re.match(rf"(v_readfirstlane_b32 s({base[0]}|{base[1]})|s_\w+ s\[{base[0]}:{base[1]}\]),", s):
+            writer = s
+            break
+        states += int(s.split()[1]) + 1 if s.startswith("s_nop") else 1
+    assert writer and (writer.startswith("s_") or states >= 5), (writer, states)
+    code = next(v for n, v in k.items() if "probe_m0" in n)
+    uses = [i for i, s in enumerate(code) if s.startswith("global_load_lds")]
+    sets = [i for i, s in enumerate(code) if re.match(r"s_\w+ m0\b", s)]
+    assert len(uses) == 3
+    for a, b in zip([-1] + uses, uses):
+        assert any(a < i < b for i in sets), "a request without m0 of its own"
