@@ -81,3 +81,57 @@ def test_requests_into_lds_are_safe_by_themselves(tmp_path, request_fn):
     assert len(uses) == 3
     for a, b in zip([-1] + uses, uses):
         assert any(a < i < b for i in sets), "a request without m0 of its own"
+
+
+def fewest_loads_between_waits(code, wait):
+    """Over every path from a hand-counted wait (and its barrier) to the next one: the fewest vector loads that follow the
+    path's last request into LDS.  None where no path leads from one wait to another."""
+    label = {s[:-1]: i for i, s in enumerate(code) if s.endswith(":")}
+    at = {i for i, s in enumerate(code) if s == wait and code[i + 1] == "s_barrier"}
+    assert at, wait
+    fewest = None
+    for start in at:
+        todo, best = [(start + 2, 0)], {}
+        while todo:
+            i, n = todo.pop()
+            if i >= len(code) or best.get(i, 1 << 30) <= n:
+                continue
+            best[i] = n
+            s = code[i]
+            if i in at:
+                fewest = n if fewest is None else min(fewest, n)
+                continue
+            if s.startswith("global_load_lds"):
+                n = 0
+            elif re.match(r"(global|buffer|flat|scratch)_load", s):
+                n += 1
+            if s.startswith("s_endpgm"):
+                continue
+            if s.startswith("s_branch"):
+                todo.append((label[s.split()[1]], n))
+                continue
+            if s.startswith("s_cbranch"):
+                todo.append((label[s.split()[1]], n))
+            todo.append((i + 1, n))
+    return fewest
+
+
+@pytest.mark.parametrize("waves", [4, 5, 6, 7])
+def test_the_4_bit_kernel_waits_for_the_stage_it_reads(projection_code, waves):
+    """Its wait counts what is requested behind a stage's fragments: three vector loads (codes and scales), the next stage's
+    requests, three loads more.  Were the compiler to merge or move those loads, the wait would be too short: so every way
+    round the loop has to hold three of them behind its requests into LDS."""
+    per = -(-9 // waves)       # nine requests a stage, shared by the waves
+    wait = f"s_waitcnt vmcnt({3 + per + 3})"
+    kernels = [v for n, v in projection_code.items() if f"proj_w4_kernelILi{waves}E" in n]
+    assert len(kernels) == 3
+    for code in kernels:
+        assert fewest_loads_between_waits(code, wait) >= 3
+        assert not any(s.startswith("scratch_") for s in code)
+        loads = [i for i, s in enumerate(code) if s.startswith("global_load_dword") and i > code.index(wait)]
+        assert fewest_loads_between_waits(code[:loads[1]] + ["s_nop 0"] + code[loads[1] + 1:], wait) < 3
+
+
+@pytest.fixture(scope="module")
+def projection_code(tmp_path_factory):
+    return assembly(os.path.join(CSRC, "proj.hip"), tmp_path_factory.mktemp("asm") / "proj.s")
