@@ -432,6 +432,15 @@ void sun_weights_destroy(sun_weights* w) {
     delete p;
 }
 
+static void mark_streamed(Weights& w, size_t packed_bytes) {
+    const bool stream = packed_bytes > kStreamWeightBytes;
+    for (int l = 0; l < w.cfg.n_layers; ++l) {
+        LayerW& L = w.layers[l];
+        L.qkv.stream = L.o.stream = L.gu.stream = L.down.stream = stream;
+    }
+    w.lm.stream = stream;
+}
+
 static int check_ptr_arrays(const void* const* const arrs[], int n_arrs, int n_layers) {
     for (int a = 0; a < n_arrs; ++a) {
         if (!arrs[a]) return fail(SUN_ERR_NULL, "a per-layer pointer array is NULL");
@@ -511,6 +520,7 @@ int sun_weights_create(const sun_model_cfg* cfg, const sun_weight_ptrs* d, void*
         pack(L.down, 3, d->wd[l], nullptr, nullptr, c.hidden, 0, 0, 1, 0);
     }
     pack(w->lm, 4, d->wlm, nullptr, nullptr, c.vocab, 0, 0, 1, 0);
+    mark_streamed(*w, off);
     if (e == hipSuccess && bf) e = hipStreamSynchronize(st);
     if (e != hipSuccess) {
         sun_weights_destroy((sun_weights*)w);
@@ -627,6 +637,7 @@ int sun_qweights_create(const sun_model_cfg* cfg, const sun_qweight_ptrs* d, int
             m.src_rows[0] = c.vocab;
         }
     }
+    mark_streamed(*w, off);
     if (e == hipSuccess && bf) e = hipStreamSynchronize(st);
     if (e != hipSuccess) {
         sun_weights_destroy((sun_weights*)w);

@@ -164,6 +164,10 @@ __device__ __forceinline__ float wave_max(float v) {
     return v;
 }
 
+// Packed weights of a model from which they are streamed past the caches: the memory-side cache's 256 MB, in which those of a
+// smaller model stay from one step to the next.
+constexpr size_t kStreamWeightBytes = (size_t)256 << 20;
+
 // ---- handles ----
 struct KvPool {
     sun_model_cfg cfg;
@@ -183,6 +187,7 @@ struct Mat {
     const void* sz = nullptr;  // W4_PACKED: half2 (scale, zero) per (32-row block, group, row); or, with
                                // s_only, the fp16 scales alone, two groups per dword (zero point 8 everywhere)
     bool s_only = false;
+    bool stream = false;       // BF16_PACKED: the model's weights together exceed kStreamWeightBytes
     // W4_LOGICAL (fp32 activations): logical arrays, up to two stacked sources (gate, up)
     const uint8_t* q[3] = {nullptr, nullptr, nullptr};
     const uint16_t* s[3] = {nullptr, nullptr, nullptr};

@@ -25,9 +25,14 @@ namespace sun {
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 // One 16-byte piece of the weights.  A launch of one row tile (up to 64 rows) reads every piece once, 1 KiB contiguous
-// per wave, and streams it past the caches; several row tiles share their fetches through L2 and load plainly.
+// per wave, and streams it past the caches where the whole model is larger than the memory-side cache (kStreamWeightBytes);
+// several row tiles share their fetches through L2 and load plainly, and so does a model that stays in the cache from one
+// step to the next.
 // Measured, 8B shape, plain -> streamed (us): gate/up at 1 / 64 rows 45.1 -> 41.0 / 47.6 -> 44.8, lm_head at 1 row
 // 193 -> 177, q/k/v and o unchanged (bound by the launch around them), and so are the 4-bit launches (a quarter of the bytes).
+// Steps at 1 / 8 / 64 requests, hidden 1024, by the model's weights, plain against streamed (us): 146 MB 237 / 253 / 300
+// against 252 / 266 / 314, 214 MB 370 / 398 / 477 against 387 / 420 / 485, 259 MB 476 / 515 / 603 against 486 / 506 / 599, 304 MB
+// 605 / 640 / 722 against 581 / 622 / 710, 575 MB 1189 / 1266 / 1421 against 1108 / 1216 / 1393.
 template <bool STREAM>
 __device__ __forceinline__ u32x4 load_w16(const u32x4* p) {
     if constexpr (STREAM) return load_stream(p);
@@ -71,7 +76,7 @@ __device__ __forceinline__ void swiglu_strip(const f32x16& acc, uint16_t* sw, in
 // MB counts the 32-row operand blocks of the workgroup: MR = MB/2 blocks of rows, each present
 // as a hi and a lo bf16 plane (operand block m < MR is the hi plane of row block m, block MR+m
 // its lo plane); both are multiplied with the same weight fragment into the same accumulator.
-template <int MB, int KS, int NW, int EPI, int NBUF>
+template <int MB, int KS, int NW, int EPI, int NBUF, bool STREAM>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void proj_kernel(ProjArgs a) {
     constexpr int MR = MB / 2;
@@ -106,7 +111,7 @@ void proj_kernel(ProjArgs a) {
 
     auto load_w = [&](u32x4(&w)[WREGS], int st) {
 #pragma unroll
-        for (int j = 0; j < WREGS; ++j) w[j] = load_w16<(MB <= 4)>(Wl + ((size_t)st * WREGS + j) * 64);
+        for (int j = 0; j < WREGS; ++j) w[j] = load_w16<STREAM>(Wl + ((size_t)st * WREGS + j) * 64);
     };
     auto load_a = [&](int st) {
 #pragma unroll
@@ -766,17 +771,17 @@ static hipError_t launch_proj_w4(const ProjArgs& a, int nw, int splits, int mtil
     return hipErrorInvalidValue;
 }
 
-template <int MB, int KS, int NW = 4>
+template <int MB, int KS, int NW, bool STREAM>
 static hipError_t launch_proj_t(const ProjArgs& a, int epilogue, int splits, int mtiles, hipStream_t st) {
     constexpr int NBUF = (MB * KS * 64 * 3 <= 49152) ? 3 : 2;  // LDS ring: 3 stages when they fit in 48 KB
     dim3 grid((a.N / 32 + NW - 1) / NW, splits, mtiles), block(NW * 64);
     if (epilogue == EPI_SWIGLU) {
         if (splits != 1) return hipErrorInvalidValue;
-        hipLaunchKernelGGL((proj_kernel<MB, KS, NW, EPI_SWIGLU, NBUF>), grid, block, 0, st, a);
+        hipLaunchKernelGGL((proj_kernel<MB, KS, NW, EPI_SWIGLU, NBUF, STREAM>), grid, block, 0, st, a);
         return hipGetLastError();
     }
     if (epilogue != EPI_STORE) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((proj_kernel<MB, KS, NW, EPI_STORE, NBUF>), grid, block, 0, st, a);
+    hipLaunchKernelGGL((proj_kernel<MB, KS, NW, EPI_STORE, NBUF, STREAM>), grid, block, 0, st, a);
     return hipGetLastError();
 }
 
@@ -967,12 +972,17 @@ static int proj_pick_waves(const Mat& W, int rows, int splits) {
 }
 
 template <int MB, int KS>
-static hipError_t launch_proj_nw(const ProjArgs& a, int nw, int epilogue, int splits, int mtiles, hipStream_t st) {
+static hipError_t launch_proj_nw(const ProjArgs& a, int nw, bool stream, int epilogue, int splits, int mtiles, hipStream_t st) {
+    const auto go = [&](auto nwc) {
+        constexpr int NW = decltype(nwc)::value;
+        return stream ? launch_proj_t<MB, KS, NW, true>(a, epilogue, splits, mtiles, st)
+                      : launch_proj_t<MB, KS, NW, false>(a, epilogue, splits, mtiles, st);
+    };
     switch (nw) {
-    case 4: return launch_proj_t<MB, KS, 4>(a, epilogue, splits, mtiles, st);
-    case 5: return launch_proj_t<MB, KS, 5>(a, epilogue, splits, mtiles, st);
-    case 6: return launch_proj_t<MB, KS, 6>(a, epilogue, splits, mtiles, st);
-    case 7: return launch_proj_t<MB, KS, 7>(a, epilogue, splits, mtiles, st);
+    case 4: return go(std::integral_constant<int, 4>{});
+    case 5: return go(std::integral_constant<int, 5>{});
+    case 6: return go(std::integral_constant<int, 6>{});
+    case 7: return go(std::integral_constant<int, 7>{});
     }
     return hipErrorInvalidValue;
 }
@@ -1013,8 +1023,8 @@ hipError_t launch_proj(const ProjLaunch& p, hipStream_t st) {
             if (p.epilogue != EPI_STORE) return hipErrorInvalidValue;
             return launch_proj_w4(a, nw, splits, t.mtiles, st);
         }
-        if (t.mb == 2) return launch_proj_nw<2, 128>(a, nw, p.epilogue, splits, t.mtiles, st);
-        return launch_proj_nw<4, 128>(a, nw, p.epilogue, splits, t.mtiles, st);
+        if (t.mb == 2) return launch_proj_nw<2, 128>(a, nw, W.stream, p.epilogue, splits, t.mtiles, st);
+        return launch_proj_nw<4, 128>(a, nw, W.stream, p.epilogue, splits, t.mtiles, st);
     }
     if (use_wide(W, p.rows)) {
         const int want = p.epilogue == EPI_SWIGLU ? 1 : max(1, p.splits);
@@ -1032,7 +1042,7 @@ hipError_t launch_proj(const ProjLaunch& p, hipStream_t st) {
     }
     a.n_stages = kch * 2;
     a.stages_per_split = cps * 2;
-    return launch_proj_t<8, 64>(a, p.epilogue, splits, t.mtiles, st);
+    return launch_proj_t<8, 64, 4, false>(a, p.epilogue, splits, t.mtiles, st);
 }
 
 // ---------------------------------------------------------------------------------

@@ -218,3 +218,29 @@ def test_chunks_are_merged_in_groups_of_eight(H):
         assert np.abs(got[b] - want).max() <= 1e-5 * np.abs(o).max()
         same += int((got[b] == want).sum())
     assert same >= 0.999 * got.size, same / got.size   # what is left: sums rounded twice, and exponentials an ulp apart
+
+
+@pytest.mark.parametrize("rows", [1, 32, 33, 64])
+def test_projections_on_both_sides_of_the_streaming_rule(H, rows):
+    """A model of more than 256 MB of weights streams them past the caches, a smaller one loads them plainly: the same sums bit
+    for bit, and those of float64."""
+    small = dataclasses.replace(wl.SMALL128, name="below", n_layers=1, hidden=1024, vocab=4096)
+    large = dataclasses.replace(small, name="above", vocab=131072)
+    w = wl.make_weights(large, "bf16", H.DEV, 80)
+    x = torch.randn((rows, 1024), device=H.DEV, generator=torch.Generator(device=H.DEV).manual_seed(rows))
+    got = {}
+    for shape in (small, large):
+        cfg = sun.make_cfg(shape, "bf16")
+        assert (sun.sun_weights_pack_bytes(cfg) > 256 << 20) == (shape is large)
+        W = sun.sun_weights_create(cfg, {**w, "embed": w["embed"][:shape.vocab], "wlm": w["wlm"][:shape.vocab].contiguous()})
+        ws = torch.empty(sun.sun_workspace_bytes(cfg, rows, 1), dtype=torch.uint8, device=H.DEV)
+        for mat, n in ((0, shape.q_dim + 2 * shape.kv_dim), (2, shape.ffn), (4, shape.vocab)):
+            out = torch.full((rows, n), float("nan"), device=H.DEV)
+            sun.sun_linear(W, 0, mat, x, out, ws)
+            torch.cuda.synchronize()
+            got[shape.name, mat] = out
+    for mat in (0, 2, 4):
+        a, b = got["below", mat], got["above", mat]
+        assert torch.equal(a, b[:, :a.shape[1]]), mat
+    want = x.double() @ w["wlm"].double().t()
+    assert ((got["above", 4].double() - want).abs() <= 2e-4 + 1e-5 * want.abs()).all()
