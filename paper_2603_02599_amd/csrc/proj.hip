@@ -907,13 +907,22 @@ static ProjShape proj_pick(const Mat& W, int rows, int max_splits) {
 }
 
 // Which kernel multiplies more than 128 rows (bf16).  256 x 256 tiles want whole rounds of 256 workgroups without a
-// split along k: a prefill block (rows > 256) and the vocabulary projection have them (8B shape, 256 rows: lm_head 405
-// us against 535 with the strip kernel).  A batch's other projections do not: the 128 x 256 tiles of the tall kernel
-// take 24 / 40 / 75 / 120 us (o, q/k/v, down, gate/up) where the wide kernel, split finer, takes 27 to 40 % longer.
+// split along k: a prefill block (rows > 256) and a vocabulary projection have them.  A batch's other projections do not: the
+// 128 x 256 tiles of the tall kernel (8B shape, 256 rows: o, q/k/v, down, gate/up 27 / 34 / 63 / 123 us) beat the wide kernel,
+// split finer, by 27 to 40 %.
+// Columns that just exceed one round pay a second one, and more so the shorter k is: there the strip kernel stays (128-row tiles,
+// two workgroups on a compute unit).  Strip -> wide kernel at 256 rows (us): hidden 1024 with 66 048 / 80 000 / 84 000 / 98 304
+// columns 92 -> 98 / 96 -> 99 / 106 -> 100 / 120 -> 109, hidden 2048 with 66 048 / 72 032 / 76 000 / 98 304
+// 175 -> 185 / 186 -> 186 / 190 -> 187 / 242 -> 201,
+// hidden 4096 with 65 568 / 80 000 / 128 256 359 -> 350 / 403 -> 374 / 635 -> 458, one whole round (65 536) 311 -> 233.
 static bool use_wide(const Mat& W, int rows) {
-    return W.kind == MAT_BF16_PACKED && (rows > kMaxBatchTile || (rows > 128 && (W.N / 32 + 7) / 8 >= 256));
+    if (W.kind != MAT_BF16_PACKED) return false;
+    const int tiles = (W.N / 32 + 7) / 8;
+    return rows > kMaxBatchTile || (rows > 128 && (tiles == 256 || (tiles > 256 && (W.K >= 4096 || tiles >= (W.K >= 2048 ? 288 : 320)))));
 }
-static bool use_tall(const Mat& W, int rows) { return W.kind == MAT_BF16_PACKED && rows > 128 && !use_wide(W, rows); }
+static bool use_tall(const Mat& W, int rows) {
+    return W.kind == MAT_BF16_PACKED && rows > 128 && !use_wide(W, rows) && (W.N / 32 + 7) / 8 <= 256;
+}
 
 // Split-K factor of a wide launch: whole rounds of 256 workgroups cost stages x 0.95 us (2048 cycles of matrix
 // instructions) plus about 8 us each, a split the writing and reading of its slab.  With every unit busy on random data

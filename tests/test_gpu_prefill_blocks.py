@@ -109,3 +109,21 @@ def test_wide_vocabulary_projection(H, rows):
     torch.cuda.synchronize()
     want = x.double() @ w["wlm"].double().t()
     assert ((out.double() - want).abs() <= 2e-4 + 1e-5 * want.abs()).all()
+
+
+@pytest.mark.parametrize("rows", [129, 256])
+@pytest.mark.parametrize("hidden,vocab", [(512, 65536), (512, 65568), (512, 81632), (512, 81664), (2048, 73440), (2048, 73472), (4096, 65568)])
+def test_vocabulary_projection_on_both_sides_of_the_wide_rule(H, hidden, vocab, rows):
+    """One round of 256 column tiles, just past it, and the last column count of the strip kernel and the first of the wide one
+    behind it (319 / 320 tiles, from hidden 2048 on 287 / 288, from 4096 on any), against float64."""
+    shape = dataclasses.replace(wl.SMALL128, name="small_head", n_layers=1, hidden=hidden, vocab=vocab)
+    cfg = sun.make_cfg(shape, "bf16")
+    w = wl.make_weights(shape, "bf16", H.DEV, 81)
+    W = sun.sun_weights_create(cfg, w)
+    x = torch.randn((rows, hidden), device=H.DEV, generator=torch.Generator(device=H.DEV).manual_seed(rows))
+    out = torch.full((rows, vocab), float("nan"), device=H.DEV)
+    ws = torch.empty(sun.sun_workspace_bytes(cfg, rows, 1), dtype=torch.uint8, device=H.DEV)
+    sun.sun_linear(W, 0, 4, x, out, ws)
+    torch.cuda.synchronize()
+    want = x.double() @ w["wlm"].double().t()
+    assert ((out.double() - want).abs() <= 2e-4 + 1e-5 * want.abs()).all()
