@@ -136,6 +136,8 @@ __device__ __forceinline__ u32x4_s load_stream(const u32x4_s* p) { return __buil
 // then the workgroup's barrier).  base and lds_byte are the same for the whole wave.  A vector memory instruction may read a
 // scalar register that a vector instruction (a lane read, say) wrote only five wait states later, and the compiler inserts
 // none in front of assembly; a scalar copy of base carries no such delay and fills the wait state that m0 wants.
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"   // m0 is a reserved register: it is overwritten here, and nobody is promised its value
 __device__ __forceinline__ void lds_dma16(const void* base, uint32_t lane_bytes, uint32_t lds_byte) {
     uint64_t copy;
     asm volatile("s_mov_b32 m0, %1\n\ts_mov_b64 %0, %3\n\tglobal_load_lds_dwordx4 %2, %0"
@@ -147,6 +149,7 @@ __device__ __forceinline__ void lds_dma4(const void* base, uint32_t lane_bytes, 
     asm volatile("s_mov_b32 m0, %1\n\ts_mov_b64 %0, %3\n\tglobal_load_lds_dword %2, %0"
                  : "=&s"(copy) : "s"(lds_byte), "v"(lane_bytes), "s"(base) : "memory", "m0");
 }
+#pragma clang diagnostic pop
 // Read-only data of the launch at an address that is the same for the whole wave, through the scalar cache.
 __device__ __forceinline__ int32_t load_uniform(const int32_t* p) {
     return *(const __attribute__((address_space(4))) int32_t*)(uintptr_t)p;
