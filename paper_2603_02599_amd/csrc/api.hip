@@ -140,7 +140,7 @@ static Workspace carve(const sun_model_cfg& c, int batch, int max_pages, char* b
         w.qs = (float*)take((size_t)(std::max(std::max(H, QD), F) / 128 + 1) * mb * 32 * 8);  // scale and integer sum per row and group
         w.part = (float*)take(std::max((size_t)kMaxSplits * batch * std::max(Nqkv, H), (size_t)kMaxSplitsWide * batch * 2 * F) * 4);
     } else {
-        w.a32 = (float*)take((size_t)batch * QD * 4);
+        w.a32 = (float*)take((size_t)batch * std::max(QD, H) * 4);  // attention's output; before and after it a normed input
         w.u32 = (float*)take((size_t)batch * F * 4);
         w.qkv32 = (float*)take((size_t)batch * Nqkv * 4);
     }
@@ -721,6 +721,15 @@ static ChunkHint chunks_from_host(const int32_t* host, int len_plus, int batch, 
     return ChunkHint{(int)std::min<long long>(tot, 0x7fffffff), (int)std::min<long long>(full, 0x7fffffff)};
 }
 
+// fp32: out = projection of rmsnorm(x; gain); a normed input that is not computed inside the projection lies where
+// attention's output does before and after
+static hipError_t f32_norm_proj(const sun_model_cfg& c, const Mat& M, const Workspace& ws, const void* gain, int batch, int epilogue,
+                                float* out, hipStream_t st) {
+    if (f32_fuses_norm(M, batch, epilogue)) return launch_proj_f32(M, ws.x, batch, gain, c.rms_eps, epilogue, out, st);
+    if (hipError_t e = launch_residual_norm(c, ws.x, nullptr, 0, batch, gain, batch, ws.a32, nullptr, nullptr, st)) return e;
+    return launch_proj_f32(M, ws.a32, batch, nullptr, 0.f, epilogue, out, st);
+}
+
 static int step_impl(sun_kv_pool* pool_, const sun_weights* weights_, bool want_quant, int batch,
                      const int32_t* token_ids, const int32_t* page_tables, int max_pages, const int32_t* seq_lens,
                      const int32_t* seq_lens_host, const int32_t* model_ids, float* logits_out,
@@ -766,7 +775,7 @@ static int step_impl(sun_kv_pool* pool_, const sun_weights* weights_, bool want_
         if (bf) {
             {
                 ProfScope p(prof, 7, st);
-                SUN_HIP_CHECK(launch_residual_norm(c, ws.x, ws.part, down_parts, batch, L.g1, batch, ws.hA,
+                SUN_HIP_CHECK(launch_residual_norm(c, ws.x, ws.part, down_parts, batch, L.g1, batch, nullptr, ws.hA,
                                                    W.quant ? ws.qs : nullptr, st));
             }
             const int sq = proj_pick_splits(L.qkv, batch, kMaxSplits);
@@ -782,7 +791,7 @@ static int step_impl(sun_kv_pool* pool_, const sun_weights* weights_, bool want_
             }
         } else {
             ProfScope p(prof, 7, st);
-            SUN_HIP_CHECK(launch_proj_f32(L.qkv, ws.x, batch, L.g1, c.rms_eps, F32_STORE, ws.qkv32, st));
+            SUN_HIP_CHECK(f32_norm_proj(c, L.qkv, ws, L.g1, batch, F32_STORE, ws.qkv32, st));
             SUN_HIP_CHECK(launch_rope_append(pool, l, ws.qkv32, 1, batch, ws.table, seq_lens, 0, page_tables, max_pages,
                                              batch, ws.q, L.qn, L.kn, L.bq, L.bk, L.bv, st));
         }
@@ -805,7 +814,7 @@ static int step_impl(sun_kv_pool* pool_, const sun_weights* weights_, bool want_
             }
             {
                 ProfScope p(prof, 7, st);
-                SUN_HIP_CHECK(launch_residual_norm(c, ws.x, ws.part, so, batch, L.g2, batch, ws.hA,
+                SUN_HIP_CHECK(launch_residual_norm(c, ws.x, ws.part, so, batch, L.g2, batch, nullptr, ws.hA,
                                                    W.quant ? ws.qs : nullptr, st));
             }
             if (proj_fuses_swiglu(L.gu, batch)) {   // SwiGLU in the epilogue, the down projection's tile as output
@@ -834,14 +843,14 @@ static int step_impl(sun_kv_pool* pool_, const sun_weights* weights_, bool want_
         } else {
             ProfScope p(prof, 7, st);
             SUN_HIP_CHECK(launch_proj_f32(L.o, ws.a32, batch, nullptr, 0.f, F32_ADD, ws.x, st));
-            SUN_HIP_CHECK(launch_proj_f32(L.gu, ws.x, batch, L.g2, c.rms_eps, F32_SWIGLU, ws.u32, st));
+            SUN_HIP_CHECK(f32_norm_proj(c, L.gu, ws, L.g2, batch, F32_SWIGLU, ws.u32, st));
             SUN_HIP_CHECK(launch_proj_f32(L.down, ws.u32, batch, nullptr, 0.f, F32_ADD, ws.x, st));
         }
     }
     if (!with_head) return SUN_OK;  // a caller that only wants the cache entries (all but the last prefill block)
     if (bf) {
         ProfScope p(prof, 7, st);
-        SUN_HIP_CHECK(launch_residual_norm(c, ws.x, ws.part, down_parts, batch, W.gf, batch, ws.hA, nullptr, st));
+        SUN_HIP_CHECK(launch_residual_norm(c, ws.x, ws.part, down_parts, batch, W.gf, batch, nullptr, ws.hA, nullptr, st));
     }
     {
         ProfScope p(prof, 6, st);
@@ -849,7 +858,7 @@ static int step_impl(sun_kv_pool* pool_, const sun_weights* weights_, bool want_
             ProjLaunch pl{&W.lm, ws.hA, nullptr, batch, EPI_STORE, 1, logits, c.vocab, batch};
             SUN_HIP_CHECK(launch_proj(pl, st));
         } else {
-            SUN_HIP_CHECK(launch_proj_f32(W.lm, ws.x, batch, W.gf, c.rms_eps, F32_STORE, logits, st));
+            SUN_HIP_CHECK(f32_norm_proj(c, W.lm, ws, W.gf, batch, F32_STORE, logits, st));
         }
     }
     {
@@ -1091,7 +1100,7 @@ static int prefill_block(KvPool& pool, const Weights& W, const Workspace& ws, in
         const LayerW& L = W.layers[l];
         {
             ProfScope p(prof, 7, st);
-            SUN_HIP_CHECK(launch_residual_norm(c, ws.x, ws.part, down_parts, rows, L.g1, rows, ws.hA, nullptr, st));
+            SUN_HIP_CHECK(launch_residual_norm(c, ws.x, ws.part, down_parts, rows, L.g1, rows, nullptr, ws.hA, nullptr, st));
         }
         const int sq = proj_pick_splits(L.qkv, rows, max_splits);
         {
@@ -1114,7 +1123,7 @@ static int prefill_block(KvPool& pool, const Weights& W, const Workspace& ws, in
         }
         {
             ProfScope p(prof, 7, st);
-            SUN_HIP_CHECK(launch_residual_norm(c, ws.x, ws.part, so, rows, L.g2, rows, ws.hA, nullptr, st));
+            SUN_HIP_CHECK(launch_residual_norm(c, ws.x, ws.part, so, rows, L.g2, rows, nullptr, ws.hA, nullptr, st));
         }
         if (proj_fuses_swiglu(L.gu, rows)) {   // as in a decode step
             ProfScope p(prof, 4, st);
@@ -1138,7 +1147,7 @@ static int prefill_block(KvPool& pool, const Weights& W, const Workspace& ws, in
     const size_t last = (size_t)(rows - 1) * H;
     {
         ProfScope p(prof, 7, st);
-        SUN_HIP_CHECK(launch_residual_norm(c, ws.x + last, ws.part + last, down_parts, rows, W.gf, 1, ws.hA, nullptr, st));
+        SUN_HIP_CHECK(launch_residual_norm(c, ws.x + last, ws.part + last, down_parts, rows, W.gf, 1, nullptr, ws.hA, nullptr, st));
     }
     float* out = logits ? logits : ws.logits;
     {

@@ -30,6 +30,7 @@ hipError_t launch_proj(const ProjLaunch& p, hipStream_t st);
 // fp32 activations path (vector ALU): y[b][n] = sum_k W[n][k] h[b][k] with h = x, or rmsnorm(x) * gain when gain is given;
 // row-major, out[b][n] = y, out[b][n] += y (out is not x), or for a gate/up pair out [rows, N/2] = silu(gate) * up.
 enum F32Epilogue { F32_STORE = 0, F32_ADD = 1, F32_SWIGLU = 2 };
+bool f32_fuses_norm(const Mat& W, int rows, int epilogue);  // the norm inside the projection rather than in a launch of its own
 hipError_t launch_proj_f32(const Mat& W, const float* x, int rows, const void* gain, float eps, int epilogue, float* out, hipStream_t st);
 
 // packing (weights load time)
@@ -84,11 +85,11 @@ int attn_prefill_splits(const sun_model_cfg& c, int rows, int first);
 // Embedding rows and rotary tables; position of row b: seq_lens[b], or first_pos + b when seq_lens is NULL.
 hipError_t launch_embed_rope(const sun_model_cfg& cfg, const void* embed, const int32_t* tokens, const int32_t* seq_lens,
                              int first_pos, int rows, float* x, float* table, hipStream_t st);
-// x[b] += sum_s partial[s][b] (s ascending; nparts may be 0); then h = rmsnorm(x; g) (bf16 gains).
-// h_tiled: two-plane tiled bf16; with qscale given the fixed-point tile of a 4-bit projection instead, and qscale
+// x[b] += sum_s partial[s][b] (s ascending; nparts may be 0); then h = rmsnorm(x; g).
+// h_f32 (fp32 gains): row-major.  Else h_tiled (bf16 gains): two-plane tiled bf16; with qscale given the fixed-point tile of a 4-bit projection instead, and qscale
 // receives its (scale, integer sum) pairs.
 hipError_t launch_residual_norm(const sun_model_cfg& cfg, float* x, const float* partial, int nparts, int ld_rows,
-                                const void* gain, int batch, void* h_tiled, float* qscale, hipStream_t st);
+                                const void* gain, int batch, float* h_f32, void* h_tiled, float* qscale, hipStream_t st);
 // k_src, v_src: bf16 [n_layers][n_tokens][Hkv][d]; token t lands at position first_pos + t of the request whose
 // page-table row is given.
 hipError_t launch_kv_ingest(const KvPool& pool, const void* k_src, const void* v_src, int n_tokens, int first_pos,

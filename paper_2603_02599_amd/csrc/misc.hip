@@ -36,6 +36,7 @@ struct NormArgs {
     float* x;
     const float* partial;
     const void* gain;
+    float* h_f32;    // F32 only: row-major
     uint16_t* h_tiled;
     float2* qscale;  // not NULL: h_tiled is the fixed-point tile of a 4-bit projection, and this its scales and sums
     int nparts, ld_rows, H, mb;
@@ -44,6 +45,7 @@ struct NormArgs {
 
 // One 8-element unit per thread and pass (up to two passes, i.e. hidden <= 16 * blockDim), all
 // slab loads of a unit independent of one another so that they are in flight together.
+template <bool F32>
 __global__ __launch_bounds__(1024) void residual_norm_kernel(NormArgs a) {
     __shared__ float red[16];
     const int b = blockIdx.x, tid = threadIdx.x, H = a.H, nunits = H / 8, nthreads = blockDim.x;
@@ -97,15 +99,23 @@ __global__ __launch_bounds__(1024) void residual_norm_kernel(NormArgs a) {
         float y[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
         if (u < nunits) {
             float g[8];
-            const u32x4 gw = *reinterpret_cast<const u32x4*>((const uint16_t*)a.gain + u * 8);
+            if constexpr (F32) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                g[2 * e] = bf16_lo(gw[e]);
-                g[2 * e + 1] = bf16_hi(gw[e]);
+                for (int e = 0; e < 8; ++e) g[e] = ((const float*)a.gain)[u * 8 + e];
+            } else {
+                const u32x4 gw = *reinterpret_cast<const u32x4*>((const uint16_t*)a.gain + u * 8);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    g[2 * e] = bf16_lo(gw[e]);
+                    g[2 * e + 1] = bf16_hi(gw[e]);
+                }
             }
 #pragma unroll
             for (int e = 0; e < 8; ++e) y[e] = v[it][e] * rinv * g[e];
-            if (!a.qscale) {
+            if constexpr (F32) {
+                *reinterpret_cast<f32x4*>(a.h_f32 + (size_t)b * H + u * 8) = f32x4{y[0], y[1], y[2], y[3]};
+                *reinterpret_cast<f32x4*>(a.h_f32 + (size_t)b * H + u * 8 + 4) = f32x4{y[4], y[5], y[6], y[7]};
+            } else if (!a.qscale) {
                 u32x4 o, ol;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
@@ -116,17 +126,18 @@ __global__ __launch_bounds__(1024) void residual_norm_kernel(NormArgs a) {
                 reinterpret_cast<u32x4*>(a.h_tiled)[atile_unit(ATile{a.mb}, 1, b, u)] = ol;
             }
         }
-        if (a.qscale)  // fixed-point tile of a 4-bit projection: 16 consecutive units (lanes) form one 128-wide group
+        if (!F32 && a.qscale)  // fixed-point tile of a 4-bit projection: 16 consecutive units (lanes) form one 128-wide group
             qtile_group16((uint8_t*)a.h_tiled, a.qscale, ATile{a.mb}, b, u, u < nunits, y);
     }
 }
 
 hipError_t launch_residual_norm(const sun_model_cfg& cfg, float* x, const float* partial, int nparts, int ld_rows,
-                                const void* gain, int batch, void* h_tiled, float* qscale, hipStream_t st) {
+                                const void* gain, int batch, float* h_f32, void* h_tiled, float* qscale, hipStream_t st) {
     NormArgs a{};
     a.x = x;
     a.partial = partial;
     a.gain = gain;
+    a.h_f32 = h_f32;
     a.h_tiled = (uint16_t*)h_tiled;
     a.qscale = (float2*)qscale;
     a.nparts = nparts;
@@ -137,7 +148,8 @@ hipError_t launch_residual_norm(const sun_model_cfg& cfg, float* x, const float*
     if (cfg.hidden % 8 || cfg.hidden > 16 * 1024) return hipErrorInvalidValue;
     const int units = cfg.hidden / 8;
     const int threads = units <= 1024 ? (units + 63) / 64 * 64 : ((units + 1) / 2 + 63) / 64 * 64;
-    hipLaunchKernelGGL(residual_norm_kernel, dim3(batch), dim3(threads), 0, st, a);
+    if (h_f32) hipLaunchKernelGGL(residual_norm_kernel<true>, dim3(batch), dim3(threads), 0, st, a);
+    else hipLaunchKernelGGL(residual_norm_kernel<false>, dim3(batch), dim3(threads), 0, st, a);
     return hipGetLastError();
 }
 

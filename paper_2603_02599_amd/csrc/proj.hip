@@ -1098,16 +1098,15 @@ __device__ __forceinline__ float wave_rows(float (&v)[2]) {
 }
 
 // Bound by launches and latency (the tiny configuration's matrices are a few hundred KiB), so the step's small work rides
-// along: the norm in front (each wave sums its rows' squares for itself), the residual sum or SwiGLU behind.  The loads of
-// four steps along k are in flight together; the sums keep the order of one step at a time (lane l adds k = l, l + 64,
+// along: the norm in front (f32_fuses_norm; each wave sums its rows' squares for itself), the residual sum or SwiGLU behind.  The
+// loads of UN steps along k are in flight together; the sums keep the order of one step at a time (lane l adds k = l, l + 64,
 // ... and the lanes meet in a butterfly), the norm's that of a workgroup with a thread per eight columns.  Tiny
 // configuration, 8 requests: 5.3 us a launch against 6.4 of the bare products, and 18 launches a step instead of 29.
-// BT rows a wave: 8, or 2 where that leaves most of the chip without a workgroup (the sums are the same ones).
-template <int BT, int EPI>
+// BT rows a wave: 8 or 2 (f32_two_rows; the sums are the same ones).
+template <int BT, int UN, bool NORM, int EPI>
 __global__ __launch_bounds__(256) void proj_f32_kernel(F32Mat m, const float* __restrict__ x, int nrows, float* out) {
     static_assert(BT == 8 || BT == 2, "wave_rows");
     constexpr int NC = EPI == F32_SWIGLU ? 2 : 1;  // columns of a wave: gate and up
-    constexpr int UN = 4;                          // steps of 64 along k in flight (12 at two rows: no faster)
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int n = blockIdx.x * 4 + wave, n_out = EPI == F32_SWIGLU ? m.rows[0] : m.N;
     if (n >= n_out) return;
@@ -1128,7 +1127,7 @@ __global__ __launch_bounds__(256) void proj_f32_kernel(F32Mat m, const float* __
 #pragma unroll
     for (int j = 0; j < BT; ++j) row[j] = x + (size_t)min(b0 + j, nrows - 1) * K;
     float rinv[BT];
-    if (m.gain) {  // the rows' sums of squares: eight columns a lane, 512 a round, a round's sum as one wave of a workgroup
+    if constexpr (NORM) {  // the rows' sums of squares: eight columns a lane, 512 a round, a round's sum as one wave of a workgroup
         float tot = 0.f;
         for (int u0 = 0; u0 < K / 8; u0 += 64) {
             float ss[BT];
@@ -1171,7 +1170,7 @@ __global__ __launch_bounds__(256) void proj_f32_kernel(F32Mat m, const float* __
                     wv[i][c] = m.w[src[c]][(size_t)r[c] * K + k];
                 }
             }
-            gv[i] = m.gain ? m.gain[k] : 0.f;
+            if constexpr (NORM) gv[i] = m.gain[k];
 #pragma unroll
             for (int j = 0; j < BT; ++j) xv[i][j] = row[j][k];
         }
@@ -1180,7 +1179,8 @@ __global__ __launch_bounds__(256) void proj_f32_kernel(F32Mat m, const float* __
             if (k0 + i * 64 < K) {
 #pragma unroll
                 for (int j = 0; j < BT; ++j) {
-                    const float y = m.gain ? xv[i][j] * rinv[j] * gv[i] : xv[i][j];
+                    float y = xv[i][j];
+                    if constexpr (NORM) y = y * rinv[j] * gv[i];
 #pragma unroll
                     for (int c = 0; c < NC; ++c) acc[c][j] = fmaf(wv[i][c], y, acc[c][j]);
                 }
@@ -1195,6 +1195,27 @@ __global__ __launch_bounds__(256) void proj_f32_kernel(F32Mat m, const float* __
     if constexpr (EPI == F32_SWIGLU) *o = v[0] / (1.0f + expf(-v[0])) * v[1];
     else if constexpr (EPI == F32_ADD) *o += v[0];
     else *o = v[0];
+}
+
+static int f32_out_cols(const Mat& W, int epilogue) { return epilogue == F32_SWIGLU ? W.src_rows[0] : W.N; }
+
+// The norm rides along as long as summing each row's squares in every wave costs less than the launch it saves, about 4 us.
+// Step of 4 layers, inside / launch of its own (us): hidden 256, ffn 688 at 8 / 32 / 64 / 128 rows 142 / 170 / 188 / 238 against
+// 164 / 177 / 187 / 217, hidden 512, ffn 1024 at 8 / 32 / 64 rows 178 / 221 / 275 against 195 / 220 / 258, hidden 1024, ffn 2816 at
+// 4 / 8 / 64 rows 269 / 307 / 768 against 274 / 287 / 612, hidden 2048 at 256 rows 10.8 ms against 7.7.  Above 8192 columns the norm
+// kernel sums in another order than a wave does here.
+bool f32_fuses_norm(const Mat& W, int rows, int epilogue) {
+    return W.K <= 8192 && (long long)f32_out_cols(W, epilogue) * rows * W.K <= (W.K <= 512 ? 1 << 24 : 1 << 23);
+}
+
+// Two rows a wave, or eight: two where eight would leave most of the chip without a workgroup (eight workgroups fit a compute
+// unit), as long as the matrix, which every group of rows reads again, is not the larger cost.  Down projection, two / eight
+// rows a wave (us): 1024 x 2816 at 1 / 8 / 16 rows 9.3 / 12.9 / 22.8 against 13.3 / 13.8 / 15.4, 2048 x 2048 at 1 / 4 / 8 rows 8.7 /
+// 10.1 / 17.1 against 11.8 / 11.8 / 11.9, 2048 x 6144 at 8 rows 47 against 52, 4096 x 14336 at 1 / 4 / 8 rows 97 / 104 / 203 against
+// 130 / 129 / 130.
+static bool f32_two_rows(const Mat& W, int cols, int rows) {
+    const int groups = (rows + 1) / 2;
+    return groups == 1 || (long long)cols * groups <= (groups == 2 || W.K >= 4096 ? 2048 : 1024);
 }
 
 hipError_t launch_proj_f32(const Mat& W, const float* x, int rows, const void* gain, float eps, int epilogue, float* out, hipStream_t st) {
@@ -1215,21 +1236,31 @@ hipError_t launch_proj_f32(const Mat& W, const float* x, int rows, const void* g
     }
     if (gain && W.K % 8) return hipErrorInvalidValue;
     if (epilogue == F32_SWIGLU && (W.nsrc != 2 || m.rows[0] != m.rows[1])) return hipErrorInvalidValue;
-    const int cols = ((epilogue == F32_SWIGLU ? m.rows[0] : W.N) + 3) / 4;
-    const auto go = [&](auto bt) {
-        constexpr int BT = decltype(bt)::value;
+    const int cols = (f32_out_cols(W, epilogue) + 3) / 4;
+    const auto go = [&](auto bt, auto un) {
+        constexpr int BT = decltype(bt)::value, UN = decltype(un)::value;
         const dim3 grid(cols, (rows + BT - 1) / BT), block(256);
-        switch (epilogue) {
-        case F32_STORE: hipLaunchKernelGGL((proj_f32_kernel<BT, F32_STORE>), grid, block, 0, st, m, x, rows, out); break;
-        case F32_ADD: hipLaunchKernelGGL((proj_f32_kernel<BT, F32_ADD>), grid, block, 0, st, m, x, rows, out); break;
-        case F32_SWIGLU: hipLaunchKernelGGL((proj_f32_kernel<BT, F32_SWIGLU>), grid, block, 0, st, m, x, rows, out); break;
-        default: return hipErrorInvalidValue;
+        if (gain) {
+            switch (epilogue) {
+            case F32_STORE: hipLaunchKernelGGL((proj_f32_kernel<BT, UN, true, F32_STORE>), grid, block, 0, st, m, x, rows, out); break;
+            case F32_SWIGLU: hipLaunchKernelGGL((proj_f32_kernel<BT, UN, true, F32_SWIGLU>), grid, block, 0, st, m, x, rows, out); break;
+            default: return hipErrorInvalidValue;
+            }
+        } else {
+            switch (epilogue) {
+            case F32_STORE: hipLaunchKernelGGL((proj_f32_kernel<BT, UN, false, F32_STORE>), grid, block, 0, st, m, x, rows, out); break;
+            case F32_ADD: hipLaunchKernelGGL((proj_f32_kernel<BT, UN, false, F32_ADD>), grid, block, 0, st, m, x, rows, out); break;
+            case F32_SWIGLU: hipLaunchKernelGGL((proj_f32_kernel<BT, UN, false, F32_SWIGLU>), grid, block, 0, st, m, x, rows, out); break;
+            default: return hipErrorInvalidValue;
+            }
         }
         return hipGetLastError();
     };
-    // eight workgroups fit a compute unit: two rows a wave as long as that does not make more than one round of them
-    if ((long long)cols * ((rows + 1) / 2) <= 2048) return go(std::integral_constant<int, 2>{});
-    return go(std::integral_constant<int, 8>{});
+    // steps of 64 along k in flight: four for one group of rows (2048 x 6144 at 8 rows 52 us, one step 60), one where several
+    // groups of waves cover each other's waits (at 16 / 32 / 256 rows 60 / 77 / 591 us, four steps 54 / 111 / 604)
+    if (f32_two_rows(W, cols, rows)) return go(std::integral_constant<int, 2>{}, std::integral_constant<int, 4>{});
+    if (rows <= 8) return go(std::integral_constant<int, 8>{}, std::integral_constant<int, 4>{});
+    return go(std::integral_constant<int, 8>{}, std::integral_constant<int, 1>{});
 }
 
 // ---------------------------------------------------------------------------------

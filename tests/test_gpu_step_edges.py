@@ -244,3 +244,29 @@ def test_projections_on_both_sides_of_the_streaming_rule(H, rows):
         assert torch.equal(a, b[:, :a.shape[1]]), mat
     want = x.double() @ w["wlm"].double().t()
     assert ((got["above", 4].double() - want).abs() <= 2e-4 + 1e-5 * want.abs()).all()
+
+
+@pytest.mark.parametrize("hidden,ffn,batch", [(256, 688, 3), (256, 688, 95), (256, 688, 96), (512, 1024, 17), (1024, 1000, 9), (1024, 1000, 2),
+                                              (2048, 4104, 5), (4096, 300, 1)])
+def test_f32_step_on_both_sides_of_its_rules(H, hidden, ffn, batch):
+    """The norm inside the projections or in a launch of its own, two or eight rows a wave, one or four steps along k in flight:
+    row counts that leave ragged groups of two and eight, against the oracle."""
+    shape = dataclasses.replace(wl.TINY, name="f32", n_layers=1, hidden=hidden, ffn=ffn, vocab=1100)
+    work = wl.make_workload("cfg1", shape=shape, dtype="f32", batch=batch, seed=990 + batch)
+    rng = np.random.default_rng(batch)
+    work.seq_lens = rng.integers(1, 30, size=batch).astype(np.int32)
+    work.page_tables, work.n_pages = wl.deal_page_tables(work.seq_lens, rng)
+    case = H.GpuCase(work)
+    ref = H.run_oracle(case, list(range(batch)))
+    case.logits.fill_(float("nan"))
+    case.step(flags=sun.SUN_VALIDATE)
+    H.check_logits(case.logits.cpu().numpy(), ref["logits"], "f32")
+    H.check_next_tokens(case.next.cpu().numpy(), ref["logits"], 1e-4)
+
+
+def test_f32_step_refuses_a_hidden_width_its_norm_does_not_hold(H):
+    """More than 16384 columns are refused, as in the bf16 step."""
+    shape = dataclasses.replace(wl.TINY, name="too_wide", n_layers=1, hidden=16392, ffn=128, vocab=64)
+    case = H.GpuCase(wl.make_workload("cfg1", shape=shape, dtype="f32", batch=1, seed=995))
+    with pytest.raises(sun.SunError):
+        case.step()
