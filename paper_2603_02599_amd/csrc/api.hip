@@ -1336,7 +1336,14 @@ int sun_linear(const sun_weights* weights_, int layer, int mat, int batch, const
     const Mat& M = mat == 4 ? W.lm : mat == 0 ? W.layers[layer].qkv : mat == 1 ? W.layers[layer].o
                                  : mat == 2 ? W.layers[layer].gu : W.layers[layer].down;
     if (c.act_dtype == SUN_F32) {
-        SUN_HIP_CHECK(launch_proj_f32(M, x, batch, nullptr, 0.f, mat == 2 ? F32_SWIGLU : F32_STORE, out, st));
+        if (mat == 2) {   // the output may lie over the input: then by way of the workspace
+            const size_t out_bytes = (size_t)batch * c.ffn * 4;
+            const bool apart = (uintptr_t)out + out_bytes <= (uintptr_t)x || (uintptr_t)x + (size_t)batch * M.K * 4 <= (uintptr_t)out;
+            SUN_HIP_CHECK(launch_proj_f32(M, x, batch, nullptr, 0.f, F32_SWIGLU, apart ? out : ws.u32, st));
+            if (!apart) SUN_HIP_CHECK(hipMemcpyAsync(out, ws.u32, out_bytes, hipMemcpyDeviceToDevice, st));
+        } else {
+            SUN_HIP_CHECK(launch_proj_f32(M, x, batch, nullptr, 0.f, F32_STORE, out, st));
+        }
         return SUN_OK;
     }
     // the tiled input goes to the buffer the step uses for this projection's input

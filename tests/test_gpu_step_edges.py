@@ -270,3 +270,22 @@ def test_f32_step_refuses_a_hidden_width_its_norm_does_not_hold(H):
     case = H.GpuCase(wl.make_workload("cfg1", shape=shape, dtype="f32", batch=1, seed=995))
     with pytest.raises(sun.SunError):
         case.step()
+
+
+@pytest.mark.parametrize("shift", [0, 64, -64])
+def test_f32_gate_up_may_write_over_its_input(H, shift):
+    """Gate/up with the output over the input (the same start, or a part of it): the result of separate buffers."""
+    shape, batch = wl.TINY, 9
+    cfg = sun.make_cfg(shape, "f32")
+    W = sun.sun_weights_create(cfg, wl.make_weights(shape, "f32", H.DEV, 82))
+    ws = torch.empty(sun.sun_workspace_bytes(cfg, batch, 1), dtype=torch.uint8, device=H.DEV)
+    x = torch.randn((batch, shape.hidden), device=H.DEV, generator=torch.Generator(device=H.DEV).manual_seed(1))
+    want = torch.empty((batch, shape.ffn), device=H.DEV)
+    sun.sun_linear(W, 0, 2, x, want, ws)
+    buf = torch.zeros(batch * shape.ffn + 128, device=H.DEV)
+    at_x, at_out = 64, 64 + shift
+    xin, out = buf[at_x:at_x + x.numel()].view_as(x), buf[at_out:at_out + want.numel()].view_as(want)
+    xin.copy_(x)
+    sun.sun_linear(W, 0, 2, xin, out, ws)
+    torch.cuda.synchronize()
+    assert torch.equal(out, want)
