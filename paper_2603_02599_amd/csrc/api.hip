@@ -106,6 +106,7 @@ struct Workspace {
     float *a32, *u32, *qkv32;   // fp32 path
     float* qs;           // 4-bit path: (scale, integer sum) of every row and 128-wide group of the current activations
     float* part;
+    size_t part_floats;
     float* q;
     float* table;
     AttnPlan plan;
@@ -138,7 +139,8 @@ static Workspace carve(const sun_model_cfg& c, int batch, int max_pages, char* b
         w.aA = take(atile_bytes(ATile{mb}, QD));
         w.uA = take(atile_bytes(ATile{mb}, F));
         w.qs = (float*)take((size_t)(std::max(std::max(H, QD), F) / 128 + 1) * mb * 32 * 8);  // scale and integer sum per row and group
-        w.part = (float*)take(std::max((size_t)kMaxSplits * batch * std::max(Nqkv, H), (size_t)kMaxSplitsWide * batch * 2 * F) * 4);
+        w.part_floats = std::max((size_t)kMaxSplits * batch * std::max(Nqkv, H), (size_t)kMaxSplitsWide * batch * 2 * F);
+        w.part = (float*)take(w.part_floats * 4);
     } else {
         w.a32 = (float*)take((size_t)batch * std::max(QD, H) * 4);  // attention's output; before and after it a normed input
         w.u32 = (float*)take((size_t)batch * F * 4);
@@ -158,7 +160,35 @@ static Workspace carve(const sun_model_cfg& c, int batch, int max_pages, char* b
     return w;
 }
 
-// Device memory of a prefill block of more than kMaxBatchTile rows (bf16): no decode plan, logits of one row.
+static void mat_dims(const sun_model_cfg& c, int which, int& N, int& K) {
+    const int H = c.hidden, QD = c.n_q_heads * c.head_dim, KD = c.n_kv_heads * c.head_dim;
+    switch (which) {
+    case 0: N = QD + 2 * KD; K = H; break;
+    case 1: N = H; K = QD; break;
+    case 2: N = 2 * c.ffn; K = H; break;
+    case 3: N = H; K = c.ffn; break;
+    default: N = c.vocab; K = H; break;
+    }
+}
+
+// Slabs that the projections of a prefill block of up to `rows` rows fill.  Within a class of row tiles the split along k does not
+// grow with the rows (the slabs are what they cost), so each class asks for at most the split of its fewest rows.
+static size_t block_slab_floats(const sun_model_cfg& c, int rows) {
+    size_t most = 0;
+    for (int which : {0, 1, 3}) {
+        Mat m;
+        m.kind = MAT_BF16_PACKED;
+        mat_dims(c, which, m.N, m.K);
+        for (int done = kMaxBatchTile; done < rows; done += 256)
+            most = std::max(most, (size_t)proj_pick_splits(m, done + 1, kMaxSplitsBlock) * std::min(rows, done + 256) * m.N);
+    }
+    return most;
+}
+
+// Device memory of a prefill block of more than kMaxBatchTile rows (bf16): no decode plan, logits of one row.  Three places are
+// used twice in a layer: the q/k/v input is done with before attention's output is written, and that before the gate/up input;
+// q before the down projection's input; the projections' slabs of q/k/v before attention's split keys, and those before the
+// slabs of the O projection.
 static Workspace carve_block(const sun_model_cfg& c, int rows, char* base) {
     Workspace w{};
     size_t off = 0;
@@ -167,17 +197,16 @@ static Workspace carve_block(const sun_model_cfg& c, int rows, char* base) {
         off += align_up(n);
         return (void*)p;
     };
-    const int H = c.hidden, QD = c.n_q_heads * c.head_dim, F = c.ffn, Nqkv = QD + 2 * c.n_kv_heads * c.head_dim;
+    const int H = c.hidden, QD = c.n_q_heads * c.head_dim, F = c.ffn;
     const ATile t = atile_for_rows(rows);
     w.x = (float*)take((size_t)rows * H * 4);
-    w.q = (float*)take((size_t)rows * QD * 4);
     w.table = (float*)take((size_t)rows * c.head_dim * 4);
-    w.hA = take(atile_bytes(t, H));
-    w.aA = take(atile_bytes(t, QD));
-    w.uA = take(atile_bytes(t, F));
-    w.part = (float*)take((size_t)kMaxSplitsBlock * rows * std::max(Nqkv, H) * 4);
+    w.hA = w.aA = take(atile_bytes(t, std::max(H, QD)));
+    w.uA = take(std::max(atile_bytes(t, F), (size_t)rows * QD * 4));
+    w.q = (float*)w.uA;
     w.plan.max_chunks = std::max(rows, 32768 / c.n_q_heads);   // no fewer than attn_prefill_splits() asks for at any rows
-    w.plan.partial = (float*)take((size_t)w.plan.max_chunks * c.n_q_heads * (c.head_dim + 2) * 4);
+    w.part_floats = std::max(block_slab_floats(c, rows), (size_t)w.plan.max_chunks * c.n_q_heads * (c.head_dim + 2));
+    w.part = w.plan.partial = (float*)take(w.part_floats * 4);
     w.logits = (float*)take((size_t)c.vocab * 4);
     w.amax_val = (float*)take((size_t)kArgmaxParts * 4);
     w.amax_idx = (int32_t*)take((size_t)kArgmaxParts * 4);
@@ -375,17 +404,6 @@ int sun_kv_pool_model_tokens(const sun_kv_pool* pool_, int model_id, int64_t* to
 }
 
 // ---------------------------------------------------------------- weights
-static void mat_dims(const sun_model_cfg& c, int which, int& N, int& K) {
-    const int H = c.hidden, QD = c.n_q_heads * c.head_dim, KD = c.n_kv_heads * c.head_dim;
-    switch (which) {
-    case 0: N = QD + 2 * KD; K = H; break;
-    case 1: N = H; K = QD; break;
-    case 2: N = 2 * c.ffn; K = H; break;
-    case 3: N = H; K = c.ffn; break;
-    default: N = c.vocab; K = H; break;
-    }
-}
-
 size_t sun_weights_pack_bytes(const sun_model_cfg* cfg) {
     if (!cfg || cfg->act_dtype != SUN_BF16) return 0;
     size_t tot = 0;
@@ -1089,7 +1107,11 @@ static int prefill_block(KvPool& pool, const Weights& W, const Workspace& ws, in
                          const int32_t* page_table, int max_pages, bool head, float* logits, int32_t* next, bool prof,
                          hipStream_t st) {
     const sun_model_cfg& c = W.cfg;
-    const int H = c.hidden, max_splits = rows > kMaxBatchTile ? kMaxSplitsBlock : kMaxSplits;
+    const int H = c.hidden;
+    const auto splits = [&](const Mat& m) {   // never more slabs than there is room for
+        const size_t room = ws.part_floats / ((size_t)rows * m.N);
+        return proj_pick_splits(m, rows, (int)std::min<size_t>(rows > kMaxBatchTile ? kMaxSplitsBlock : kMaxSplits, room));
+    };
     const int key_splits = std::max(1, std::min(attn_prefill_splits(c, rows, first), ws.plan.max_chunks / rows));
     {
         ProfScope p(prof, 7, st);
@@ -1102,7 +1124,7 @@ static int prefill_block(KvPool& pool, const Weights& W, const Workspace& ws, in
             ProfScope p(prof, 7, st);
             SUN_HIP_CHECK(launch_residual_norm(c, ws.x, ws.part, down_parts, rows, L.g1, rows, nullptr, ws.hA, nullptr, st));
         }
-        const int sq = proj_pick_splits(L.qkv, rows, max_splits);
+        const int sq = splits(L.qkv);
         {
             ProfScope p(prof, 2, st);
             SUN_HIP_CHECK(launch_proj(ProjLaunch{&L.qkv, ws.hA, nullptr, rows, EPI_STORE, sq, ws.part, L.qkv.N, rows}, st));
@@ -1116,7 +1138,7 @@ static int prefill_block(KvPool& pool, const Weights& W, const Workspace& ws, in
             ProfScope p(prof, 0, st);
             SUN_HIP_CHECK(launch_attn_prefill(pool, l, ws.q, page_table, first, rows, key_splits, ws.plan.partial, ws.aA, st));
         }
-        const int so = proj_pick_splits(L.o, rows, max_splits);
+        const int so = splits(L.o);
         {
             ProfScope p(prof, 3, st);
             SUN_HIP_CHECK(launch_proj(ProjLaunch{&L.o, ws.aA, nullptr, rows, EPI_STORE, so, ws.part, H, rows}, st));
@@ -1137,7 +1159,7 @@ static int prefill_block(KvPool& pool, const Weights& W, const Workspace& ws, in
             ProfScope p(prof, 7, st);
             SUN_HIP_CHECK(launch_swiglu_tile(ws.part, sg, rows, rows, c.ffn, ws.uA, nullptr, st));
         }
-        down_parts = proj_pick_splits(L.down, rows, max_splits);
+        down_parts = splits(L.down);
         {
             ProfScope p(prof, 5, st);
             SUN_HIP_CHECK(launch_proj(ProjLaunch{&L.down, ws.uA, nullptr, rows, EPI_STORE, down_parts, ws.part, H, rows}, st));

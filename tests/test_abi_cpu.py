@@ -253,3 +253,20 @@ def test_binding_fails_loudly_without_the_library(monkeypatch):
     monkeypatch.setattr(sun, "LIB_PATH", "/nonexistent/libsun.so")
     with pytest.raises(FileNotFoundError):
         sun.lib()
+
+
+def test_prefill_scratch_of_a_long_prompt(lib):
+    """A bf16 prefill takes longer blocks where it is given room, and asks for no more than its launches fill: for the 8B
+    and 14B shapes that is what 256 rows of a decode step take.  A buffer that serves a longer prompt serves a shorter one."""
+    for shape in (wl.LLAMA_8B, wl.QWEN_14B):
+        cfg = sun.make_cfg(shape, "bf16")
+        of_256 = sun.sun_prefill_workspace_bytes(cfg, 256, 64)
+        assert [sun.sun_prefill_workspace_bytes(cfg, n, 64) for n in (257, 700, 1024, 1536, 2048, 3000, 100000)] == 7 * [of_256]
+    for shape in (wl.SMALL128, wl.SMALL_G5, wl.TINY_Q):
+        cfg = sun.make_cfg(shape, "bf16")
+        sizes = [sun.sun_prefill_workspace_bytes(cfg, n, 64) for n in range(1, 2049)]
+        assert sizes == sorted(sizes)
+        # the residual rows, q, rotary table, two tiles and at most three slabs
+        row = 4 * (shape.hidden + shape.q_dim + shape.head_dim) + 4 * (max(shape.hidden, shape.q_dim) + shape.ffn) + \
+            12 * max(shape.hidden, shape.q_dim + 2 * shape.kv_dim)
+        assert sizes[-1] <= 2048 * row + 4 * 32768 * (shape.head_dim + 2) + 4 * shape.vocab + 4096
