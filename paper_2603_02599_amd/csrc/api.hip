@@ -1062,7 +1062,7 @@ int sun_decode_serve(sun_kv_pool* pool_, const sun_weights* weights_, int slots,
 }
 
 // ---------------------------------------------------------------- prefill
-// Extra device memory of a prefill behind the step's workspace: per-row page tables, lengths,
+// Extra device memory of an fp32 prefill behind the step's workspace: per-row page tables, lengths,
 // model ids and next tokens of one block of rows.
 struct PrefillExtra {
     int32_t *tables, *lens, *ids, *next;
@@ -1095,8 +1095,9 @@ static int prefill_block_rows(int n_tokens, int most) {
 size_t sun_prefill_workspace_bytes(const sun_model_cfg* cfg, int n_tokens, int max_pages) {
     if (!cfg || n_tokens < 1 || max_pages < 1 || check_cfg(cfg) != SUN_OK) return 0;
     const int rows = std::min(n_tokens, kMaxBatchTile);
-    const size_t least = carve(*cfg, rows, max_pages, nullptr).bytes + carve_prefill(rows, max_pages, nullptr).bytes;
-    if (cfg->act_dtype != SUN_BF16 || n_tokens <= kMaxBatchTile) return least;
+    const size_t least = carve(*cfg, rows, max_pages, nullptr).bytes;
+    if (cfg->act_dtype != SUN_BF16) return least + carve_prefill(rows, max_pages, nullptr).bytes;
+    if (n_tokens <= kMaxBatchTile) return least;
     return std::max(least, carve_block(*cfg, prefill_block_rows(n_tokens, kMaxPrefillTile), nullptr).bytes);
 }
 
@@ -1202,8 +1203,9 @@ int sun_prefill(sun_kv_pool* pool_, const sun_weights* weights_, int n_tokens, c
     const int rows_max = std::min(n_tokens, kMaxBatchTile);
     const size_t step_bytes = carve(c, rows_max, max_pages, nullptr).bytes;
     const PrefillExtra ex = carve_prefill(rows_max, max_pages, (char*)workspace + step_bytes);
-    if (step_bytes + ex.bytes > workspace_bytes)
-        return fail(SUN_ERR_WORKSPACE, "workspace has %zu bytes, prefill needs %zu", workspace_bytes, step_bytes + ex.bytes);
+    const size_t need = step_bytes + (c.act_dtype == SUN_BF16 ? 0 : ex.bytes);
+    if (need > workspace_bytes)
+        return fail(SUN_ERR_WORKSPACE, "workspace has %zu bytes, prefill needs %zu", workspace_bytes, need);
     hipStream_t st = (hipStream_t)stream;
     if (flags & SUN_VALIDATE) {
         const int vrc = guarded([&]() -> int {

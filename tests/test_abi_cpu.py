@@ -270,3 +270,9 @@ def test_prefill_scratch_of_a_long_prompt(lib):
         row = 4 * (shape.hidden + shape.q_dim + shape.head_dim) + 4 * (max(shape.hidden, shape.q_dim) + shape.ffn) + \
             12 * max(shape.hidden, shape.q_dim + 2 * shape.kv_dim)
         assert sizes[-1] <= 2048 * row + 4 * 32768 * (shape.head_dim + 2) + 4 * shape.vocab + 4096
+    # in blocks of up to 256 rows it takes what a decode step of as many requests takes; fp32 adds a page table per row
+    for n in (1, 77, 256):
+        cfg = sun.make_cfg(wl.SMALL128, "bf16")
+        assert sun.sun_prefill_workspace_bytes(cfg, n, 300) == sun.sun_workspace_bytes(cfg, n, 300)
+        cfg = sun.make_cfg(wl.TINY, "f32")
+        assert sun.sun_prefill_workspace_bytes(cfg, n, 300) >= sun.sun_workspace_bytes(cfg, n, 300) + n * 300 * 4
