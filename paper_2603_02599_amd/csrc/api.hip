@@ -150,7 +150,6 @@ static Workspace carve(const sun_model_cfg& c, int batch, int max_pages, char* b
     w.plan.max_chunks = (int)std::min<size_t>(mc, 0x7fffffff);
     w.plan.chunk_off = (int32_t*)take((size_t)(batch + 1) * 4);
     w.plan.full_off = (int32_t*)take((size_t)(batch + 1) * 4);
-    w.plan.small_off = (int32_t*)take((size_t)(batch + 1) * 4);
     w.plan.records = (int32_t*)take(mc * c.n_kv_heads * 24 * 4);
     w.plan.partial = (float*)take(mc * c.n_q_heads * (c.head_dim + 2) * 4);
     w.logits = (float*)take((size_t)batch * c.vocab * 4);
@@ -1306,7 +1305,6 @@ static Workspace carve_attention(const sun_model_cfg& c, int batch, int max_page
     w.plan.max_chunks = (int)std::min<size_t>(mc, 0x7fffffff);
     w.plan.chunk_off = (int32_t*)take((size_t)(batch + 1) * 4);
     w.plan.full_off = (int32_t*)take((size_t)(batch + 1) * 4);
-    w.plan.small_off = (int32_t*)take((size_t)(batch + 1) * 4);
     w.plan.records = (int32_t*)take(mc * c.n_kv_heads * 24 * 4);
     w.plan.partial = (float*)take(mc * c.n_q_heads * (c.head_dim + 2) * 4);
     w.bytes = off;

@@ -50,7 +50,7 @@ size_t attn_max_chunks(int batch, int max_pages, int Hkv) {
 struct PlanArgs {
     const int32_t* n_or_len;
     const int32_t* page_tables;
-    int32_t *chunk_off, *full_off, *small_off, *records;
+    int32_t *chunk_off, *full_off, *records;
     int len_plus, batch, max_pages, n_pages, Hkv;
 };
 
@@ -106,7 +106,6 @@ __device__ __forceinline__ void attn_plan_block(const PlanArgs& a, int block, in
     if (block == 0)
         for (int r = tid; r <= a.batch; r += 256) {
             a.full_off[r] = f_off[r];
-            a.small_off[r] = s_off[r];
             a.chunk_off[r] = f_off[r] + s_off[r];
         }
     const int total_full = f_off[a.batch] * a.Hkv, total = total_full + s_off[a.batch] * a.Hkv;
@@ -143,7 +142,7 @@ static PlanArgs plan_args(const AttnPlan& plan, const int32_t* n_or_len, int len
                           int max_pages, int n_pages, int Hkv, int& blocks) {
     const long long items = (long long)plan.max_chunks * Hkv;
     blocks = (int)max(1LL, min((items + 15) / 16, 1024LL));
-    return PlanArgs{n_or_len, page_tables, plan.chunk_off, plan.full_off, plan.small_off, plan.records, len_plus, batch,
+    return PlanArgs{n_or_len, page_tables, plan.chunk_off, plan.full_off, plan.records, len_plus, batch,
                     max_pages, n_pages, Hkv};
 }
 
