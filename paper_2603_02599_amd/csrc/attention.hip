@@ -614,11 +614,12 @@ struct CombineArgs {
 
 // A workgroup merges 128 columns of a request: one head of 128 dims or two of 64, each wave for itself.  Chunks are added in
 // token order under a running maximum that moves once per eight chunks.  Bound by the latency of the partials, which the
-// split kernel has just written: 64 chunks' maxima and sums are read at once, a lane per chunk, and their weights and the
-// eights' rescaling factors computed there, so that the outputs' loads depend on nothing but each other's order and sixteen
-// of them are in flight per thread.  With the outputs'
-// loads of a round behind the rescaling of the one before (24 loads a round): 8B shape, 16 / 256 requests 6.4 -> 5.3 /
-// 21.7 -> 17.6 us, 14B shape, 24 requests of 17 k tokens 24.4 -> 17.0.
+// split kernel has just written.  Up to eight chunks every thread reads all of them at once.  Beyond that 64 chunks' maxima and
+// sums are read at once, a lane per chunk, and their weights and the eights' rescaling factors computed there, so that the
+// outputs' loads depend on nothing but each other's order and sixteen of them are in flight per thread.  With eight
+// chunks a round throughout, each round's loads behind the rescaling of the one before: 8B shape, 16 / 256 requests 6.4 -> 5.3 /
+// 21.7 -> 17.0 us, 14B shape, 24 requests of 17 k tokens 24.4 -> 17.0; a lane per chunk throughout: 1000 requests of up to
+// 400 tokens 48 instead of 37.
 __global__ __launch_bounds__(128) void attn_combine_kernel(CombineArgs a) {
     const int b = blockIdx.y, col = blockIdx.x * 128 + threadIdx.x, lane = threadIdx.x & 63;
     const int h = col / a.D, j = col % a.D;   // a wave's 64 columns are of one head
@@ -627,39 +628,59 @@ __global__ __launch_bounds__(128) void attn_combine_kernel(CombineArgs a) {
     const size_t stride = (size_t)a.Hq * (a.D + 2);
     const float* p = a.partial + (size_t)c0 * stride + (size_t)h * (a.D + 2);
     float M = -INFINITY, num = 0.f, den = 0.f;
-    for (int cb = 0; cb < n; cb += 64) {
-        const int c = cb + lane, cnt = min(n - cb, 64);
-        const float m = c < n ? p[c * stride + a.D] : -INFINITY, l = c < n ? p[c * stride + a.D + 1] : 0.f;
-        float top = m;                        // maximum up to the end of the lane's eight
+    if (n <= 8) {                             // one group: every thread reads all of it
+        float m8[8], l8[8], o8[8];
 #pragma unroll
-        for (int o = 1; o < 8; o <<= 1) top = fmaxf(top, __shfl_xor(top, o));
-#pragma unroll
-        for (int o = 8; o < 64; o <<= 1) {
-            const float t = __shfl_up(top, o);
-            if (lane >= o) top = fmaxf(top, t);
+        for (int i = 0; i < 8; ++i) {
+            const float* pc = p + min(i, n - 1) * stride;
+            m8[i] = pc[a.D];
+            l8[i] = pc[a.D + 1];
+            o8[i] = pc[j];
         }
-        top = fmaxf(top, M);
-        float prev = __shfl_up(top, 8);       // and up to its start
-        if (lane < 8) prev = M;
-        const float w = c < n ? exp2f(m - top) : 0.f, sc = exp2f(prev - top);
-        M = __shfl(top, 63);
-        const float* pj = p + (size_t)cb * stride + j;
-        for (int k0 = 0; k0 < cnt; k0 += 16) {
-            float o[16];
 #pragma unroll
-            for (int i = 0; i < 16; ++i) o[i] = pj[min(k0 + i, cnt - 1) * stride];
+        for (int i = 0; i < 8; ++i) M = fmaxf(M, m8[i]);
 #pragma unroll
-            for (int i = 0; i < 16; ++i)
-                if (k0 + i < cnt) {
-                    if (i % 8 == 0) {
-                        const float s = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(sc), k0 + i));
-                        num *= s;
-                        den *= s;
+        for (int i = 0; i < 8; ++i)
+            if (i < n) {
+                const float w = exp2f(m8[i] - M);
+                den = fmaf(w, l8[i], den);
+                num = fmaf(w, o8[i], num);
+            }
+    } else {
+        for (int cb = 0; cb < n; cb += 64) {
+            const int c = cb + lane, cnt = min(n - cb, 64);
+            const float m = c < n ? p[c * stride + a.D] : -INFINITY, l = c < n ? p[c * stride + a.D + 1] : 0.f;
+            float top = m;                        // maximum up to the end of the lane's eight
+#pragma unroll
+            for (int s = 1; s < 8; s <<= 1) top = fmaxf(top, __shfl_xor(top, s));
+#pragma unroll
+            for (int s = 8; s < 64; s <<= 1) {
+                const float t = __shfl_up(top, s);
+                if (lane >= s) top = fmaxf(top, t);
+            }
+            top = fmaxf(top, M);
+            float prev = __shfl_up(top, 8);       // and up to its start
+            if (lane < 8) prev = M;
+            const float w = c < n ? exp2f(m - top) : 0.f, sc = exp2f(prev - top);
+            M = __shfl(top, 63);
+            const float* pj = p + (size_t)cb * stride + j;
+            for (int k0 = 0; k0 < cnt; k0 += 16) {
+                float o[16];
+#pragma unroll
+                for (int i = 0; i < 16; ++i) o[i] = pj[min(k0 + i, cnt - 1) * stride];
+#pragma unroll
+                for (int i = 0; i < 16; ++i)
+                    if (k0 + i < cnt) {
+                        if (i % 8 == 0) {
+                            const float s = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(sc), k0 + i));
+                            num *= s;
+                            den *= s;
+                        }
+                        const float wk = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(w), k0 + i));
+                        den = fmaf(wk, __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(l), k0 + i)), den);
+                        num = fmaf(wk, o[i], num);
                     }
-                    const float wk = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(w), k0 + i));
-                    den = fmaf(wk, __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(l), k0 + i)), den);
-                    num = fmaf(wk, o[i], num);
-                }
+            }
         }
     }
     const float v = num / den;
