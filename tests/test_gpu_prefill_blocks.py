@@ -127,3 +127,102 @@ def test_vocabulary_projection_on_both_sides_of_the_wide_rule(H, hidden, vocab, 
     torch.cuda.synchronize()
     want = x.double() @ w["wlm"].double().t()
     assert ((out.double() - want).abs() <= 2e-4 + 1e-5 * want.abs()).all()
+
+
+def _expect(H, case, shape, toks, before):
+    st, table = H.layout_strides(case.lay), case.work.page_tables[0]
+    logits, K, V = H.orc.full_forward(H.orc.make_cfg(shape), case.oracle_params(), toks, round_kv=True, want_kv=True)
+    pool = before.copy()
+    H.orc.kv_ingest(pool, st, H.orc.bf16_bits(K), H.orc.bf16_bits(V), 0, table)
+    return logits, pool, _written_mask(H, st, before.size, shape.n_layers, shape.n_kv_heads, shape.head_dim, table, 0, len(toks))
+
+
+@pytest.mark.parametrize("shape,T,cuts", [(wl.SMALL128, 2400, [203]), (wl.SMALL_G5, 1536, [])],
+                         ids=["blocks-of-1280-and-917-behind-203-keys", "g5-shares-of-14-14-12-stages"])
+def test_prefill_in_several_wide_blocks(H, shape, T, cuts):
+    """Two blocks of more than 256 rows in one call, the second at a workspace layout of its own and behind the first one's
+    keys, off a page and a tile boundary; and a split along k whose last share is shorter."""
+    H.say(f"wide blocks {shape.name} T={T} cuts={cuts}")
+    case, rng = _one_request_case(H, shape, "bf16", T, seed=760 + T)
+    toks = rng.integers(0, shape.vocab, size=T).astype(np.int32)
+    before = H.to_np(case.pool_mem).copy()
+    logits, expect, mask = _expect(H, case, shape, toks, before)
+    for a, b in zip([0] + cuts, cuts + [T]):
+        got, nxt = _prefill(case, toks[a:b], a, 1)
+        H.check_logits(got[None], logits[b - 1][None], "bf16")
+        H.check_next_tokens(np.array([nxt]), logits[b - 1][None], 2e-2)
+    H.check_appended_kv(H.to_np(case.pool_mem).copy(), expect, before, mask, "bf16", abs_tol=PREFILL_ABS_TOL, max_off_frac=0.6)
+
+
+def test_prefill_in_the_blocks_that_a_middle_sized_workspace_holds(H):
+    """1600 tokens in one block, and in the least workspace in blocks of 1024 and 576 rows."""
+    T = 1600
+    shape = dataclasses.replace(wl.SMALL128, name="small_wide_down", n_layers=1, hidden=1024, ffn=4096)
+    case, rng = _one_request_case(H, shape, "bf16", T, seed=770)
+    toks = rng.integers(0, shape.vocab, size=T).astype(np.int32)
+    before = H.to_np(case.pool_mem).copy()
+    logits, expect, mask = _expect(H, case, shape, toks, before)
+    d_tok, row = torch.from_numpy(toks).cuda(), case.tables[0].contiguous()
+    full, least = (sun.sun_prefill_workspace_bytes(case.cfg, n, row.numel()) for n in (T, 256))
+    assert least < full
+    for nbytes in (full, full - 256, least):
+        case.pool_mem.copy_(torch.from_numpy(before.view(np.int16)).view(torch.bfloat16))
+        got = torch.full((shape.vocab,), float("nan"), device="cuda")
+        sun.sun_prefill(case.pool, case.weights, d_tok, row, 0, 0, got, None, torch.empty(nbytes, dtype=torch.uint8, device="cuda"),
+                        flags=sun.SUN_VALIDATE)
+        torch.cuda.synchronize()
+        H.check_logits(got.cpu().numpy()[None], logits[T - 1][None], "bf16")
+        H.check_appended_kv(H.to_np(case.pool_mem).copy(), expect, before, mask, "bf16", abs_tol=PREFILL_ABS_TOL, max_off_frac=0.6)
+
+
+@pytest.mark.parametrize("value", [float("nan"), float("inf")])
+@pytest.mark.parametrize("first,bad_at,rows", [(43, 40, 20), (1003, 1000, 40), (1003, 100, 40), (1003, 1000, 300)],
+                         ids=["one-split-same-tile", "split-keys-same-tile", "split-keys-earlier-tile", "a-wide-block"])
+def test_a_value_that_is_not_finite_reaches_the_rows_that_see_it(H, value, first, bad_at, rows):
+    """A cached position with a finite K and a V that is not finite, in the 32 keys of the block's first rows (whose products
+    leave it out and mark the rows instead) or before them: every row of the block sees it, so all of a row's entries
+    after the first layer and the logits are not numbers; the first layer's entries are those of the clean cache bit for bit."""
+    shape = wl.SMALL128
+    T = first + rows
+    case, rng = _one_request_case(H, shape, "bf16", T, seed=780 + bad_at + rows)
+    toks = rng.integers(0, shape.vocab, size=T).astype(np.int32)
+    _prefill(case, toks[:first], 0, 0)
+    cached = case.pool_mem.clone()
+    clean, _ = _prefill(case, toks[first:], first, 0)
+    ok = H.to_np(case.pool_mem).copy()
+    case.pool_mem.copy_(cached)
+    st, table = H.layout_strides(case.lay), case.work.page_tables[0]
+    at = int(st["v_off"]) + int(table[bad_at // 16]) * int(st["v_page"]) + (bad_at % 16) * int(st["v_token"])   # layer 0, head 0
+    case.pool_mem[at + 7 * int(st["v_dim"])] = value
+    got, _ = _prefill(case, toks[first:], first, 0)
+    after = H.to_np(case.pool_mem).copy()
+    new = _written_mask(H, st, after.size, shape.n_layers, shape.n_kv_heads, shape.head_dim, table, first, rows)
+    deeper = np.zeros(after.size, bool)
+    deeper[int(st["k_layer"]):] = True
+    assert np.isfinite(clean).all() and np.isnan(got).all()
+    assert np.array_equal(after[new & ~deeper], ok[new & ~deeper])
+    assert np.isnan((after[new & deeper].astype(np.uint32) << 16).view(np.float32)).all()
+
+
+@pytest.mark.parametrize("first,rows", [(0, 37), (0, 300), (45, 9), (1003, 40)])
+def test_slots_past_the_prompt_may_hold_anything(H, first, rows):
+    """K and V of the positions behind the prompt, in its last page and the table's following ones, are not numbers: the same
+    logits and entries bit for bit."""
+    shape = wl.SMALL128
+    T = first + rows
+    case, rng = _one_request_case(H, shape, "bf16", T, seed=790 + T, extra=70)
+    toks = rng.integers(0, shape.vocab, size=T).astype(np.int32)
+    st, table = H.layout_strides(case.lay), case.work.page_tables[0]
+    sizes = (case.pool_mem.numel(), shape.n_layers, shape.n_kv_heads, shape.head_dim, table)
+    behind = torch.from_numpy(_written_mask(H, st, *sizes, T, 70)).cuda()
+    own = _written_mask(H, st, *sizes, 0, T)
+    if first:
+        _prefill(case, toks[:first], 0, 0)
+    cached, got = case.pool_mem.clone(), []
+    for fill in (0.0, float("nan")):
+        case.pool_mem.copy_(cached)
+        case.pool_mem[behind] = fill
+        logits, _ = _prefill(case, toks[first:], first, 0)
+        got.append((logits, H.to_np(case.pool_mem).copy()[own]))
+    assert np.isfinite(got[0][0]).all()
+    assert np.array_equal(got[0][0], got[1][0]) and np.array_equal(got[0][1], got[1][1])
