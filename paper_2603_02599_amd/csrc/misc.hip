@@ -421,13 +421,18 @@ hipError_t launch_argmax(const float* logits, int batch, int vocab, float* part_
 // pool keeps it transposed ([dim][token]).  Only the positions of the source are written, so a chunk can
 // be appended to a partly filled page.  A page id outside the pool skips the page.
 //
-// Bound by HBM: every byte is read once and written once.  A cache larger than what the L2s of the chip hold (32 MB) streams
-// past them (32 layers x 4096 tokens of 8 heads, 537 MB in and out: 189 us through the caches, 169 us streamed, 6.4 TB/s
-// read plus written; 24.3 -> 21.7 us for a hand-over of 25 us).  A smaller one is a launch and its latency, and what it
-// leaves in the caches the next step reads: through them (0.5 to 8.4 MB 7.4 us, streamed 7.6).  Two heads to a workgroup
-// (a source run of 512 bytes a token) is slower, 175 us for the 537 MB: half the workgroups, each with twice the work
-// around its one barrier.
-constexpr size_t kIngestStreamBytes = 32u << 20;  // bytes of the source, from which the launch streams
+// Bound by HBM: every byte is read once and written once.  A source larger than what the L2s of the chip hold (32 MB) is read with
+// streaming loads, and one larger than the memory-side cache (256 MB) is written past the caches as well.  Below that the source
+// is often still in the memory-side cache, having just been received, and stores that stream cost more than they save.
+// Plain / loads streamed / loads and stores streamed (us), a source that has just been written, then one that no cache holds,
+// destination cold: 36 MB 16.3 / 15.4 / 17.8, 24.5 / 18.5 / 19.2; 134 MB 43.6 / 44.5 / 57.3, 76 / 55 / 54; 268 MB 100 / 83 / 97,
+// 129 / 103 / 101; 537 MB (32 layers x 4096 tokens) 211 / 186 / 197, 235 / 209 / 196, and one such hand-over after the other
+// 189 / - / 169 (6.4 TB/s read plus written).  Only where source and
+// destination both are those of the call before does the plain one win (36 MB 18.8 / 20.9 / 20.5).  Up to 8.4 MB a launch and its latency, and what it leaves in the caches the next step
+// reads: plain 7.4, streamed 7.6.  Two heads to a workgroup (a source run of 512 bytes a token) is slower, 175 us for the 537 MB:
+// half the workgroups, each with twice the work around its one barrier.
+constexpr size_t kIngestStreamBytes = 32u << 20;   // bytes of the source, above which its loads stream
+constexpr size_t kIngestThroughBytes = 256u << 20; // and its stores
 
 template <bool STREAM, typename T>
 __device__ __forceinline__ T ingest_load(const T* p) {
@@ -450,7 +455,7 @@ struct IngestArgs {
     int n_tokens, first_pos, Hkv, D, n_pages;
 };
 
-template <bool STREAM>
+template <bool LOADS, bool STORES>
 __global__ __launch_bounds__(256) void kv_ingest_kernel(IngestArgs a) {
     __shared__ uint16_t tile[kPageTokens][128 + 8];
     const int lp = a.first_pos / kPageTokens + blockIdx.x, h = blockIdx.y, l = blockIdx.z, tid = threadIdx.x;
@@ -465,9 +470,9 @@ __global__ __launch_bounds__(256) void kv_ingest_kernel(IngestArgs a) {
         const int s = idx / cpt, c = idx % cpt;
         if (s < s_lo || s >= s_hi) continue;
         const size_t so = (((size_t)l * a.n_tokens + (p0 + s - a.first_pos)) * a.Hkv + h) * D + c * 8;
-        const u32x4 k = ingest_load<STREAM>(reinterpret_cast<const u32x4*>(a.k_src + so));
-        const u32x4 v = ingest_load<STREAM>(reinterpret_cast<const u32x4*>(a.v_src + so));
-        ingest_store<STREAM>(k, reinterpret_cast<u32x4*>(kd + s * D + c * 8));
+        const u32x4 k = ingest_load<LOADS>(reinterpret_cast<const u32x4*>(a.k_src + so));
+        const u32x4 v = ingest_load<LOADS>(reinterpret_cast<const u32x4*>(a.v_src + so));
+        ingest_store<STORES>(k, reinterpret_cast<u32x4*>(kd + s * D + c * 8));
         *reinterpret_cast<u32x4*>(&tile[s][c * 8]) = v;
     }
     __syncthreads();
@@ -481,7 +486,7 @@ __global__ __launch_bounds__(256) void kv_ingest_kernel(IngestArgs a) {
             u32x4 o;
 #pragma unroll
             for (int j = 0; j < 4; ++j) o[j] = (uint32_t)e[2 * j] | ((uint32_t)e[2 * j + 1] << 16);
-            ingest_store<STREAM>(o, reinterpret_cast<u32x4*>(vd + dim * kPageTokens + s0));
+            ingest_store<STORES>(o, reinterpret_cast<u32x4*>(vd + dim * kPageTokens + s0));
         } else {
             for (int j = 0; j < 8; ++j)
                 if (s0 + j >= s_lo && s0 + j < s_hi) vd[dim * kPageTokens + s0 + j] = tile[s0 + j][dim];
@@ -512,8 +517,9 @@ hipError_t launch_kv_ingest(const KvPool& pool, const void* k_src, const void* v
     const int pages = (first_pos + n_tokens - 1) / kPageTokens - first_pos / kPageTokens + 1;
     const size_t bytes = (size_t)2 * c.n_layers * n_tokens * c.n_kv_heads * c.head_dim * 2;
     const dim3 grid(pages, c.n_kv_heads, c.n_layers);
-    if (bytes > kIngestStreamBytes) hipLaunchKernelGGL(kv_ingest_kernel<true>, grid, dim3(256), 0, st, a);
-    else hipLaunchKernelGGL(kv_ingest_kernel<false>, grid, dim3(256), 0, st, a);
+    if (bytes > kIngestThroughBytes) hipLaunchKernelGGL((kv_ingest_kernel<true, true>), grid, dim3(256), 0, st, a);
+    else if (bytes > kIngestStreamBytes) hipLaunchKernelGGL((kv_ingest_kernel<true, false>), grid, dim3(256), 0, st, a);
+    else hipLaunchKernelGGL((kv_ingest_kernel<false, false>), grid, dim3(256), 0, st, a);
     return hipGetLastError();
 }
 

@@ -289,3 +289,21 @@ def test_f32_gate_up_may_write_over_its_input(H, shift):
     sun.sun_linear(W, 0, 2, xin, out, ws)
     torch.cuda.synchronize()
     assert torch.equal(out, want)
+
+
+@pytest.mark.parametrize("tokens,first", [(4096, 0), (4097, 3)], ids=["stores-through-the-caches", "stores-streamed"])
+def test_ingest_on_both_sides_of_the_rule_for_its_stores(H, tokens, first):
+    """Above 256 MB of source (64 KB a token here) the stores stream as well: the pool bit for bit as the oracle's."""
+    shape = dataclasses.replace(wl.LLAMA_8B, name="ingest", n_layers=16)
+    cfg = sun.make_cfg(shape, "bf16")
+    n_pages = (tokens + first + 15) // 16 + 1
+    mem = torch.zeros(sun.sun_kv_pool_bytes(cfg, n_pages) // 2, dtype=torch.bfloat16, device="cuda")
+    pool = sun.sun_kv_pool_create(cfg, mem, 16, 1)
+    host = H.to_np(mem).copy()
+    row = np.random.default_rng(tokens).permutation(n_pages).astype(np.int32)
+    k = torch.randn((16, tokens, shape.n_kv_heads, shape.head_dim), device="cuda").to(torch.bfloat16)
+    v = torch.randn_like(k)
+    sun.sun_kv_pool_ingest(pool, 0, k, v, first, torch.from_numpy(row).cuda(), flags=sun.SUN_VALIDATE)
+    H.orc.kv_ingest(host, H.layout_strides(pool.layout()), H.to_np(k), H.to_np(v), first, row)
+    torch.cuda.synchronize()
+    assert np.array_equal(H.to_np(mem), host)
