@@ -1,7 +1,7 @@
 """GPU parity of sun_prefill (the prefill module of Eq. 2) against the oracle's causal forward, through the
 C ABI.  The oracle side is the definition: a forward over the whole prompt with no cache (pinned on the CPU
-against a library implementation of the same architecture); the GPU side runs the prompt through the decode
-step's kernels in blocks of rows.  The cache it leaves in the pool, the first-token logits, and the decode
+against a library implementation of the same architecture); the GPU side runs the prompt in blocks of rows (in fp32
+through the decode step's kernels).  The cache it leaves in the pool, the first-token logits, and the decode
 steps that follow must all agree with the oracle.
 
 Cache entries in fp32: as for one step, an entry may differ from the oracle's bf16 rounding by one bf16 ulp.
