@@ -434,8 +434,9 @@ size_t sun_prefill_workspace_bytes(const sun_model_cfg* cfg, int n_tokens, int m
  * tokens at positions first_pos .. first_pos + n_tokens - 1.  It writes the K/V of those positions
  * into the request's pages in every layer (the prompt part C_X of Eq. 4) and returns the
  * distribution of the first generated token.  Positions 0 .. first_pos - 1 must already be cached
- * (first_pos > 0 continues a prompt that was prefilled in pieces); the result does not depend on
- * how a prompt is cut into pieces.
+ * (first_pos > 0 continues a prompt that was prefilled in pieces).  How a prompt is cut into pieces, and
+ * the block lengths that a workspace allows, change the order of some sums: results agree up to
+ * rounding, a stored bf16 entry up to its neighbour.
  *
  * SUN_BF16: the prompt is taken in blocks of up to 2048 positions (shorter ones if the workspace was sized for fewer
  * tokens); the K/V of a block are in the pool before its attention, in which the block's rows share what they read of
@@ -449,7 +450,8 @@ size_t sun_prefill_workspace_bytes(const sun_model_cfg* cfg, int n_tokens, int m
  *   logits_out  dev fp32 [vocab] or NULL: logits after the last prompt token
  *   next_token_out dev int32 [1] or NULL: their greedy argmax
  *   workspace   dev, 256-byte aligned, >= sun_prefill_workspace_bytes(cfg, n_tokens, max_pages) (SUN_BF16: one of
- *               sun_prefill_workspace_bytes(cfg, 256, max_pages) bytes serves any longer prompt, more slowly)
+ *               sun_prefill_workspace_bytes(cfg, 256, max_pages) bytes serves any longer prompt, in shorter blocks
+ *               where that is the smaller of the two)
  * `weights` must come from sun_weights_create (the prefill side stays in full precision, also
  * when decode is quantised: Section 3.3) and have the pool's shape.
  * Errors: SUN_ERR_NULL, SUN_ERR_SHAPE (also for 4-bit weights), SUN_ERR_MODEL_ID, SUN_ERR_SEQ_LEN (n_tokens < 1,

@@ -427,10 +427,10 @@ hipError_t launch_argmax(const float* logits, int batch, int vocab, float* part_
 // Plain / loads streamed / loads and stores streamed (us), a source that has just been written, then one that no cache holds,
 // destination cold: 36 MB 16.3 / 15.4 / 17.8, 24.5 / 18.5 / 19.2; 134 MB 43.6 / 44.5 / 57.3, 76 / 55 / 54; 268 MB 100 / 83 / 97,
 // 129 / 103 / 101; 537 MB (32 layers x 4096 tokens) 211 / 186 / 197, 235 / 209 / 196, and one such hand-over after the other
-// 189 / - / 169 (6.4 TB/s read plus written).  Only where source and
-// destination both are those of the call before does the plain one win (36 MB 18.8 / 20.9 / 20.5).  Up to 8.4 MB a launch and its latency, and what it leaves in the caches the next step
-// reads: plain 7.4, streamed 7.6.  Two heads to a workgroup (a source run of 512 bytes a token) is slower, 175 us for the 537 MB:
-// half the workgroups, each with twice the work around its one barrier.
+// 189 / - / 169 (6.4 TB/s read plus written).  Only where source and destination both are those of the call before does the
+// plain one win (36 MB 18.8 / 20.9 / 20.5).  Up to 8.4 MB a launch and its latency, and what it leaves in the caches the next
+// step reads: plain 7.4, streamed 7.6.  Two heads to a workgroup (a source run of 512 bytes a token) is slower, 175 us for the
+// 537 MB: half the workgroups, each with twice the work around its one barrier.
 constexpr size_t kIngestStreamBytes = 32u << 20;   // bytes of the source, above which its loads stream
 constexpr size_t kIngestThroughBytes = 256u << 20; // and its stores
 

@@ -428,9 +428,9 @@ void proj_tall_kernel(ProjArgs a) {
 // slots, two stages ahead, without passing through registers.  The requests leave between the matrix instructions,
 // where the memory pipeline's back pressure is covered: all of a stage's requests at its start cost 10 %.
 // Larger tiles than the kernel above because what limits there is the traffic from L2 into the compute units:
-// 24 bytes per cycle here against 47.  Measured, 28 672 x 4096, both planes counted: 1024 rows 369 us = 1.30 PFLOP/s,
-// 2048 rows 721 us = 1.33 (four / eight launches of the 128 x 256 kernel: 505 / 1010 us; the instructions alone, no
-// loads: 322 / 591; the same code on zeros, which draw less power and leave the clock up: 294 / 583).
+// 24 bytes per cycle here against 47.  Measured, 28 672 x 4096, both planes counted: 1024 rows 384 us on average in a prefill (368
+// the shortest) = 1.25 PFLOP/s, 2048 rows 729 (713) = 1.32 (four / eight launches of the 128 x 256 kernel: 505 / 1010 us; the
+// instructions alone, no loads: 322 / 591; the same code on zeros, which draw less power and leave the clock up: 294 / 583).
 // Measured and left out: 128 x 256 tiles in this scheme (1024 rows 430 us; at 256 rows no faster than the kernel
 // above), four or five slots, a deeper ring for the weights than for the activations, streaming loads for the
 // weights (the row tiles share them through L2: 775 us), a rotated start along k, other workgroup orders.
@@ -852,7 +852,7 @@ struct ProjTiling {
     int mb, mtiles;
 };
 static ProjTiling proj_tiling(const Mat& W, int rows) {
-    const int mbr = atile_for_rows(rows).MB;  // 32-row blocks of the activation tiling: 1, 2, 4 or 8
+    const int mbr = atile_for_rows(rows).MB;  // 32-row blocks of the activation tiling: 1, 2, 4 or a multiple of 8
     if (W.kind == MAT_W4_PACKED) return ProjTiling{2, (rows + 31) / 32};  // no tile without a row
     if (mbr <= 2) return ProjTiling{2 * mbr, 1};
     return ProjTiling{8, mbr / 4};
@@ -908,13 +908,14 @@ static ProjShape proj_pick(const Mat& W, int rows, int max_splits) {
 
 // Which kernel multiplies more than 128 rows (bf16).  256 x 256 tiles want whole rounds of 256 workgroups without a
 // split along k: a prefill block (rows > 256) and a vocabulary projection have them.  A batch's other projections do not: the
-// 128 x 256 tiles of the tall kernel (8B shape, 256 rows: o, q/k/v, down, gate/up 27 / 34 / 63 / 123 us) beat the wide kernel,
+// 128 x 256 tiles of the tall kernel (8B shape, 256 rows: o, q/k/v, down, gate/up 24 / 32 / 60 / 115 us) beat the wide kernel,
 // split finer, by 27 to 40 %.
 // Columns that just exceed one round pay a second one, and more so the shorter k is: there the strip kernel stays (128-row tiles,
 // two workgroups on a compute unit).  Strip -> wide kernel at 256 rows (us): hidden 1024 with 66 048 / 80 000 / 84 000 / 98 304
-// columns 92 -> 98 / 96 -> 99 / 106 -> 100 / 120 -> 109, hidden 2048 with 66 048 / 72 032 / 76 000 / 98 304
-// 175 -> 185 / 186 -> 186 / 190 -> 187 / 242 -> 201,
-// hidden 4096 with 65 568 / 80 000 / 128 256 359 -> 350 / 403 -> 374 / 635 -> 458, one whole round (65 536) 311 -> 233.
+// columns 92 -> 98 / 96 -> 99 / 106 -> 100 / 120 -> 109, hidden 2048 with 66 048 / 72 032 /
+// 76 000 / 98 304 175 -> 185 / 186 -> 186 / 190 -> 187 / 242 -> 201, hidden 4096 with 65 568 / 80 000 / 128 256 359 -> 350 / 403 ->
+// 374 / 635 -> 458, one whole round (65 536) against the tall kernel 311 -> 233; each with the
+// tiling of its input (the last 458 are 400 in a step).
 static bool use_wide(const Mat& W, int rows) {
     if (W.kind != MAT_BF16_PACKED) return false;
     const int tiles = (W.N / 32 + 7) / 8;
