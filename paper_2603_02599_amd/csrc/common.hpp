@@ -133,21 +133,18 @@ __device__ __forceinline__ u32x4_s load_stream(const u32x4_s* p) { return __buil
 
 // 16 bytes a lane from memory straight into LDS: lane i's, at base + lane_bytes, land at lds_byte + 16 i.  No register
 // holds the data and the compiler does not know of the request: whoever reads the place waits for it by hand (vmcnt,
-// then the workgroup's barrier).  base and lds_byte are the same for the whole wave.  A vector memory instruction may read a
-// scalar register that a vector instruction (a lane read, say) wrote only five wait states later, and the compiler inserts
-// none in front of assembly; a scalar copy of base carries no such delay and fills the wait state that m0 wants.
+// then the workgroup's barrier).  base and lds_byte are the same for the whole wave.  base has to come out of scalar
+// instructions: a scalar register that a vector instruction (a lane read, say) wrote may be read by a vector memory instruction
+// five wait states later, which the compiler does not insert in front of assembly (the compiled kernels are checked for it by
+// a test; a scalar copy here or longer waits cost 1 to 2 % of a 4-bit step of few requests).
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"   // m0 is a reserved register: it is overwritten here, and nobody is promised its value
 __device__ __forceinline__ void lds_dma16(const void* base, uint32_t lane_bytes, uint32_t lds_byte) {
-    uint64_t copy;
-    asm volatile("s_mov_b32 m0, %1\n\ts_mov_b64 %0, %3\n\tglobal_load_lds_dwordx4 %2, %0"
-                 : "=&s"(copy) : "s"(lds_byte), "v"(lane_bytes), "s"(base) : "memory", "m0");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_byte), "v"(lane_bytes), "s"(base) : "memory", "m0");
 }
 // The same with 4 bytes a lane: lane i's land at lds_byte + 4 i.
 __device__ __forceinline__ void lds_dma4(const void* base, uint32_t lane_bytes, uint32_t lds_byte) {
-    uint64_t copy;
-    asm volatile("s_mov_b32 m0, %1\n\ts_mov_b64 %0, %3\n\tglobal_load_lds_dword %2, %0"
-                 : "=&s"(copy) : "s"(lds_byte), "v"(lane_bytes), "s"(base) : "memory", "m0");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(lds_byte), "v"(lane_bytes), "s"(base) : "memory", "m0");
 }
 #pragma clang diagnostic pop
 // Read-only data of the launch at an address that is the same for the whole wave, through the scalar cache.

@@ -36,14 +36,6 @@ PROBE = r"""
 using namespace sun;
 typedef __attribute__((address_space(3))) unsigned lds_t;
 typedef __attribute__((address_space(1))) const void* global_t;
-__global__ void probe_base(const unsigned* where, unsigned* out) {
-    __shared__ unsigned buf[512];
-    const int lane = threadIdx.x & 63;
-    const unsigned lo = __builtin_amdgcn_readfirstlane(where[lane * 2]), hi = __builtin_amdgcn_readfirstlane(where[lane * 2 + 1]);
-    REQUEST((const void*)((uint64_t)hi << 32 | lo), lane * 4, (uint32_t)(uintptr_t)(lds_t*)buf);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    out[lane] = buf[lane];
-}
 __global__ void probe_m0(const unsigned* a, const unsigned* b, unsigned* out) {
     __shared__ unsigned buf[1024];
     const int lane = threadIdx.x & 63;
@@ -58,29 +50,70 @@ __global__ void probe_m0(const unsigned* a, const unsigned* b, unsigned* out) {
 
 
 @pytest.mark.parametrize("request_fn", ["lds_dma4", "lds_dma16"])
-def test_requests_into_lds_are_safe_by_themselves(tmp_path, request_fn):
-    """The statement's base may come from a lane read right before it: a vector memory instruction reads a scalar register that
-    a scalar instruction wrote, or five wait states lie between the vector instruction that wrote it and the read.  And
-    the statement overwrites m0: code around it that uses m0 has to set it again."""
+def test_a_request_into_lds_owns_m0(tmp_path, request_fn):
+    """The statement overwrites m0: code around it that uses m0 has to set it again."""
     src = tmp_path / "probe.hip"
     src.write_text(PROBE.replace('"common.hpp"', f'"{CSRC}/common.hpp"').replace("REQUEST", request_fn))
-    k = assembly(src, tmp_path / "probe.s")
-    code = next(v for n, v in k.items() if "probe_base" in n)
-    at = next(i for i, s in enumerate(code) if s.startswith("global_load_lds"))
-    base = re.search(r"s\[(\d+):(\d+)\]", code[at]).groups()
-    states, writer = 0, None
-    for s in reversed(code[:at]):
-        if re.match(rf"(v_readfirstlane_b32 s({base[0]}|{base[1]})|s_\w+ s\[{base[0]}:{base[1]}\]),", s):
-            writer = s
-            break
-        states += int(s.split()[1]) + 1 if s.startswith("s_nop") else 1
-    assert writer and (writer.startswith("s_") or states >= 5), (writer, states)
-    code = next(v for n, v in k.items() if "probe_m0" in n)
+    code = next(v for n, v in assembly(src, tmp_path / "probe.s").items() if "probe_m0" in n)
     uses = [i for i, s in enumerate(code) if s.startswith("global_load_lds")]
     sets = [i for i, s in enumerate(code) if re.match(r"s_\w+ m0\b", s)]
     assert len(uses) == 3
     for a, b in zip([-1] + uses, uses):
         assert any(a < i < b for i in sets), "a request without m0 of its own"
+
+
+def registers(operand):
+    m = re.fullmatch(r"s\[(\d+):(\d+)\]|s(\d+)", operand)
+    return set() if not m else {int(m[3])} if m[3] else set(range(int(m[1]), int(m[2]) + 1))
+
+
+def late_writers(code):
+    """Requests into LDS whose base a vector instruction wrote fewer than five wait states before, on any path."""
+    label = {s[:-1]: i for i, s in enumerate(code) if s.endswith(":")}
+    before = [[] for _ in code]
+    for i, s in enumerate(code):
+        if s.startswith(("s_branch", "s_cbranch")):
+            before[label[s.split()[1]]].append(i)
+        if i + 1 < len(code) and not s.startswith(("s_branch", "s_endpgm")):
+            before[i + 1].append(i)
+    found = []
+    for i, s in enumerate(code):
+        if not s.startswith("global_load_lds"):
+            continue
+        base = registers(re.split(r"[ ,]+", s)[2])
+        assert len(base) == 2, s
+        todo = [(p, 0, frozenset(base)) for p in before[i]]
+        while todo:
+            j, states, need = todo.pop()
+            t = code[j]
+            if not t.endswith(":"):
+                operands = re.split(r"[ ,]+", t)[1:]
+                written = operands[:2] if "_co_" in t.split()[0] else operands[:1]   # a carry is the second result
+                if t.startswith("v_") and any(need & registers(o) for o in written):
+                    found.append((t, s, states))
+                    continue
+                if t.startswith("s_") and operands:
+                    need = need - registers(operands[0])
+                states += int(operands[0]) + 1 if t.startswith("s_nop") else 1
+            if need and states < 5:
+                todo += [(p, states, need) for p in before[j]]
+    return found
+
+
+@pytest.mark.parametrize("source", ["proj.hip", "attention.hip"])
+def test_requests_into_lds_read_a_base_that_is_there(source, projection_code, attention_code):
+    """Five wait states lie between a vector instruction that writes a scalar register and a vector memory instruction that
+    reads it; in front of assembly the compiler inserts none, so the kernels' requests have to take their base from
+    scalar instructions (or far enough from a lane read)."""
+    code = projection_code if source == "proj.hip" else attention_code
+    requests = sum(s.startswith("global_load_lds") for v in code.values() for s in v)
+    assert requests >= 10
+    for name, v in code.items():
+        assert not late_writers(v), name
+    # the reading itself: a lane read right before a request is noticed, one five states earlier is not
+    assert late_writers(["v_readfirstlane_b32 s5, v1", "s_mov_b32 m0, s2", "s_nop 0", "global_load_lds_dword v0, s[4:5]"])
+    assert not late_writers(["v_readfirstlane_b32 s5, v1", "s_mov_b32 m0, s2", "s_nop 3", "global_load_lds_dword v0, s[4:5]"])
+    assert not late_writers(["v_readfirstlane_b32 s5, v1", "s_mov_b64 s[4:5], s[6:7]", "global_load_lds_dword v0, s[4:5]"])
 
 
 def fewest_loads_between_waits(code, wait):
@@ -135,3 +168,8 @@ def test_the_4_bit_kernel_waits_for_the_stage_it_reads(projection_code, waves):
 @pytest.fixture(scope="module")
 def projection_code(tmp_path_factory):
     return assembly(os.path.join(CSRC, "proj.hip"), tmp_path_factory.mktemp("asm") / "proj.s")
+
+
+@pytest.fixture(scope="module")
+def attention_code(tmp_path_factory):
+    return assembly(os.path.join(CSRC, "attention.hip"), tmp_path_factory.mktemp("asm") / "attention.s")
