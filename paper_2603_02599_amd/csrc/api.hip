@@ -779,14 +779,21 @@ static int step_impl(sun_kv_pool* pool_, const sun_weights* weights_, bool want_
     const int H = c.hidden;
     const ChunkHint hint = chunks_from_host(seq_lens_host, 1, batch, max_pages, c.n_kv_heads);
     float* logits = logits_out ? logits_out : ws.logits;
+    // All layers of a small batch in one launch, in the place of the activation tiles and slabs that the single launches use.  Under
+    // SUN_PROFILE every operation is a launch of its own, which is what is timed; under capture as well, since a
+    // recorded launch would not be kept apart from others like it on replay.
+    const LayersScratch scratch{ws.hA, bf ? (size_t)((char*)(ws.part + ws.part_floats) - (char*)ws.hA) : 0};
+    const bool one_launch = bf && !prof && layers_usable(W, batch, scratch, st);
 
     {
         ProfScope p(prof, 7, st);
         SUN_HIP_CHECK(launch_step_begin(c, W.embed, token_ids, seq_lens, batch, ws.x, ws.table, ws.plan, page_tables, max_pages,
-                                        (int)pool.lay.n_pages, st));
+                                        (int)pool.lay.n_pages, one_launch ? layers_zero(scratch, W) : LayersZero{}, st));
     }
     int down_parts = 0;
-    for (int l = 0; l < c.n_layers; ++l) {
+    if (one_launch)
+        SUN_HIP_CHECK(launch_layers(pool, W, batch, ws.x, ws.table, ws.plan, page_tables, max_pages, seq_lens, hint.total, hint.full, scratch, st));
+    for (int l = 0; l < c.n_layers && !one_launch; ++l) {
         const LayerW& L = W.layers[l];
         const float* attn_q = ws.q;
         if (bf) {

@@ -18,17 +18,13 @@
 // ~13 HBM bytes per CU-clock the vector ALUs cannot also convert, multiply and
 // reduce 256 bf16 values per token for several query heads; the kernel stays HBM
 // bound.  An fp32 vector-ALU variant serves the fp32 parity configuration.
+#include "attn_items.hpp"
 #include "kernels.hpp"
 #include "rows.hpp"
 
 namespace sun {
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-
-constexpr int CH = kAttnChunk;
-constexpr float kLog2e = 1.4426950408889634f;
-constexpr int kRecInts = 24;  // ints per item record
-constexpr int kTopUp = CH / kAttnSmall;  // small chunks that stand for one full chunk in a wave's item list
 
 size_t attn_max_chunks(int batch, int max_pages, int Hkv) {
     // An upper bound for every batch size up to `batch` (a workspace sized for a larger batch serves a smaller
@@ -44,7 +40,8 @@ size_t attn_max_chunks(int batch, int max_pages, int Hkv) {
 // ---------------------------------------------------------------------------------
 // Items of all full chunks come first, ordered (request, kv head, chunk), then the items of all small chunks in the same
 // order.  Record: the chunk's page ids (clamped into the pool, -1 where the chunk has no page), then request, kv head,
-// first and one-past-last token, and the chunk's slot in the partial array (chunks of a request in token order).
+// first and one-past-last token, the chunk's slot in the partial array (chunks of a request in token order), and whether it
+// holds the request's last token.
 // Every workgroup sums up the chunk counts of all requests for itself (at most 1024 of them, four a thread), so that no
 // launch has to come first; workgroup 0 stores the prefix sums for the kernels that follow.
 struct PlanArgs {
@@ -130,7 +127,7 @@ __device__ __forceinline__ void attn_plan_block(const PlanArgs& a, int block, in
         int32_t* rec = a.records + (size_t)item * kRecInts;
         rec[slot] = slot < npages ? min(max(a.page_tables[(size_t)req * a.max_pages + t0 / kPageTokens + slot], 0), a.n_pages - 1) : -1;
         if (slot < 8) {
-            const int vals[8] = {req, head, t0, t1, f_off[req] + s_off[req] + (is_full ? cj : nfull + cj), 0, 0, 0};
+            const int vals[8] = {req, head, t0, t1, f_off[req] + s_off[req] + (is_full ? cj : nfull + cj), t1 == n, 0, 0};
             rec[16 + slot] = vals[slot];
         }
     }
@@ -158,52 +155,21 @@ hipError_t launch_attn_plan(const AttnPlan& plan, const int32_t* n_or_len, int l
 // ---------------- first launch of a decode step ----------------
 // What depends on the step's inputs alone, in one launch instead of four (each costs 3 to 5 us beside its work):
 // workgroups 0 .. batch - 1 gather a row's embedding and its rotary table, the others make the attention plan.
-__global__ __launch_bounds__(256) void step_begin_kernel(EmbedRope e, PlanArgs a) {
+__global__ __launch_bounds__(256) void step_begin_kernel(EmbedRope e, PlanArgs a, LayersZero z) {
+    if (blockIdx.x == gridDim.x - 1)
+        for (int i = threadIdx.x; i < z.n; i += 256) z.p[i] = 0;
     if ((int)blockIdx.x < a.batch) embed_rope_row(e, blockIdx.x);
     else attn_plan_block(a, blockIdx.x - a.batch, gridDim.x - a.batch);
 }
 
 hipError_t launch_step_begin(const sun_model_cfg& cfg, const void* embed, const int32_t* tokens, const int32_t* seq_lens, int batch,
                              float* x, float* table, const AttnPlan& plan, const int32_t* page_tables, int max_pages,
-                             int n_pages, hipStream_t st) {
+                             int n_pages, LayersZero zero, hipStream_t st) {
     if (batch > 1024) return hipErrorInvalidValue;
     int blocks;
     const PlanArgs a = plan_args(plan, seq_lens, 1, batch, page_tables, max_pages, n_pages, cfg.n_kv_heads, blocks);
-    hipLaunchKernelGGL(step_begin_kernel, dim3(batch + blocks), dim3(256), 0, st, make_embed_rope(cfg, embed, tokens, seq_lens, 0, x, table), a);
+    hipLaunchKernelGGL(step_begin_kernel, dim3(batch + blocks), dim3(256), 0, st, make_embed_rope(cfg, embed, tokens, seq_lens, 0, x, table), a, zero);
     return hipGetLastError();
-}
-
-struct AttnArgs {
-    const uint16_t* kbase;  // pool base + k_off + layer * k_layer
-    const uint16_t* vbase;
-    int64_t k_page, k_head, v_page, v_head;
-    const float* q;         // [batch, Hq*D]
-    const int32_t* page_tables;
-    const int32_t* n_or_len;
-    const int32_t* chunk_off;
-    const int32_t* full_off;
-    const int32_t* records;
-    float* partial;
-    int len_plus, max_pages, batch, Hq, Hkv, n_pages;
-    int n_full_items, total_items;  // item counts when the host knows the lengths, else -1: read from the plan
-    float qscale;           // log2(e) / sqrt(D)
-};
-
-__device__ __forceinline__ uint32_t bf16_pair_hi(float a, float b, float& ra, float& rb) {
-    const uint32_t ha = f32_to_bf16_bits(a), hb = f32_to_bf16_bits(b);
-    ra = a - __uint_as_float(ha << 16);
-    rb = b - __uint_as_float(hb << 16);
-    return ha | (hb << 16);
-}
-
-// bf16 hi/lo split of two fp32 values with the hardware converter (round to nearest even)
-__device__ __forceinline__ void split_pair(float x0, float x1, uint32_t& hi, uint32_t& lo) {
-    typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
-    typedef float fl2 __attribute__((ext_vector_type(2)));
-    const bf2 h = __builtin_convertvector(fl2{x0, x1}, bf2);
-    hi = __builtin_bit_cast(uint32_t, h);
-    const bf2 l = __builtin_convertvector(fl2{x0 - bf16_lo(hi), x1 - bf16_hi(hi)}, bf2);
-    lo = __builtin_bit_cast(uint32_t, l);
 }
 
 // ---------------------------------------------------------------------------------
@@ -211,238 +177,8 @@ __device__ __forceinline__ void split_pair(float x0, float x1, uint32_t& hi, uin
 // ---------------------------------------------------------------------------------
 template <int D, int G>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_split_kernel(AttnArgs a) {
-    constexpr int NS = D / 32;  // dim slices of a QK MFMA
-    constexpr int NB = D / 16;  // dim blocks of a PV MFMA
-    const int lane = threadIdx.x & 63;
-    const int c16 = lane & 15, kq = lane >> 4;
-    // One workgroup of 8 waves per compute unit.  Items are dealt to workgroups statically: full
-    // chunks (all of one size) round-robin; the workgroups that got one full chunk fewer are
-    // topped up with a block of kTopUp small chunks, the remaining small chunks go round-robin.
-    // Inside a workgroup the waves take the list's entries in order through a counter in LDS, so
-    // they run out of work within one small chunk of each other however unevenly the hardware
-    // serves them.  Which wave computes an item has no effect on its value.
     __shared__ int list_cursor;
-    if (threadIdx.x == 0) list_cursor = 0;
-    __syncthreads();
-    const int n_full = a.n_full_items >= 0 ? a.n_full_items : a.full_off[a.batch] * a.Hkv;
-    const int total_items = a.total_items >= 0 ? a.total_items : a.chunk_off[a.batch] * a.Hkv;
-    const int n_small = total_items - n_full;
-    const int wg = blockIdx.x, nwg = gridDim.x;
-    const int fq = n_full / nwg, fr = n_full % nwg;
-    auto next_item = [&]() -> int {  // next unclaimed entry of this workgroup's list, total_items when it is over
-        int c = 0;
-        if (lane == 0) c = atomicAdd(&list_cursor, 1);
-        c = __builtin_amdgcn_readfirstlane(c);
-        const int mine_full = fq + (wg < fr ? 1 : 0);
-        if (c < mine_full) return wg + c * nwg;
-        c -= mine_full;
-        const int top = wg >= fr ? min(max(n_small - kTopUp * (wg - fr), 0), kTopUp) : 0;
-        if (c < top) return n_full + kTopUp * (wg - fr) + c;
-        c -= top;
-        const long long j = (long long)kTopUp * (nwg - fr) + wg + (long long)c * nwg;
-        return j < n_small ? n_full + (int)j : total_items;
-    };
-    int item = next_item();
-    if (item >= total_items) return;
-    int item_n = next_item();
-
-    // K operand rows: MFMA row i of tile 0 <-> page (i>>3), token 8*((i>>2)&1) + (i&3); tile 1: +4
-    const int k_psel = c16 >> 3, k_tok = 8 * ((c16 >> 2) & 1) + (c16 & 3);
-    const int64_t k_lane_off = (int64_t)k_tok * D + kq * 8;
-    // V^T operand: lane (dim c16 of a 16-dim block, token octet kq): page (kq>>1), tokens 8*(kq&1)..+7
-    const int v_psel = kq >> 1;
-    const int64_t v_lane_off = (int64_t)c16 * kPageTokens + 8 * (kq & 1);
-
-    auto load_rec = [&](int it) { return lane < kRecInts ? a.records[(size_t)it * kRecInts + lane] : 0; };
-    u32x4 kr[2][NS], vr[NB];  // K and V^T operand registers of one 32-token page pair
-    auto load_k = [&](int recv, int head, int pp) {
-        const int pA = __builtin_amdgcn_readlane(recv, 2 * pp);
-        int pB = __builtin_amdgcn_readlane(recv, 2 * pp + 1);
-        if (pB < 0) pB = pA;
-        const uint16_t* kp = a.kbase + head * a.k_head + (int64_t)(k_psel ? pB : pA) * a.k_page + k_lane_off;
-#pragma unroll
-        for (int s = 0; s < NS; ++s) {
-            kr[0][s] = *reinterpret_cast<const u32x4*>(kp + s * 32);
-            kr[1][s] = *reinterpret_cast<const u32x4*>(kp + 4 * D + s * 32);
-        }
-    };
-    // V^T is requested with streaming loads (every instruction reads two runs of 512 contiguous bytes, which
-    // such loads move 10 % faster than cached ones and without displacing what the neighbouring kernels exchange
-    // through the caches); K with plain loads: an instruction of K reads 64 bytes of each of 16 token rows, half a
-    // cache line at a time, and streaming loads are slower than cached ones on that pattern (measured with a
-    // read-only kernel: 6.7 against 6.1 TB/s on contiguous kilobytes, 5.95 against 6.2 on the K pattern)
-    auto load_v = [&](int recv, int head, int pp) {
-        const int pA = __builtin_amdgcn_readlane(recv, 2 * pp);
-        int pB = __builtin_amdgcn_readlane(recv, 2 * pp + 1);
-        if (pB < 0) pB = pA;
-        const uint16_t* vp = a.vbase + head * a.v_head + (int64_t)(v_psel ? pB : pA) * a.v_page + v_lane_off;
-#pragma unroll
-        for (int b = 0; b < NB; ++b) vr[b] = load_stream(reinterpret_cast<const u32x4*>(vp + b * 16 * kPageTokens));
-    };
-
-    bf16x8 qhi[NS], qlo[NS];
-    // q as MFMA B operand: lane (head g = c16, dim octet kq) per 32-dim slice, hi + lo bf16
-    auto load_q = [&](int req, int head) {
-        const float* qp = a.q + ((size_t)req * a.Hq + head * G + (c16 < G ? c16 : 0)) * D;
-#pragma unroll
-        for (int s = 0; s < NS; ++s) {
-            u32x4 h, l;
-            const f32x4 v0 = *reinterpret_cast<const f32x4*>(qp + s * 32 + kq * 8);
-            const f32x4 v1 = *reinterpret_cast<const f32x4*>(qp + s * 32 + kq * 8 + 4);
-            float x[8] = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
-#pragma unroll
-            for (int p = 0; p < 4; ++p) {
-                const float xa = c16 < G ? x[2 * p] * a.qscale : 0.f;
-                const float xb = c16 < G ? x[2 * p + 1] * a.qscale : 0.f;
-                float ra, rb;
-                h[p] = bf16_pair_hi(xa, xb, ra, rb);
-                l[p] = pack_bf16(ra, rb);
-            }
-            qhi[s] = __builtin_bit_cast(bf16x8, h);
-            qlo[s] = __builtin_bit_cast(bf16x8, l);
-        }
-    };
-
-    // current item state (wave-uniform scalars) and accumulators
-    int rec = load_rec(item);
-    int req = __builtin_amdgcn_readlane(rec, 16), head = __builtin_amdgcn_readlane(rec, 17);
-    int t0 = __builtin_amdgcn_readlane(rec, 18), t1 = __builtin_amdgcn_readlane(rec, 19);
-    int cidx = __builtin_amdgcn_readlane(rec, 20);
-    int npairs = ((t1 - t0 + kPageTokens - 1) / kPageTokens + 1) / 2, pp = 0;
-    load_k(rec, head, 0);
-    load_v(rec, head, 0);
-    int rec_n = load_rec(item_n < total_items ? item_n : item);
-    load_q(req, head);
-    int head_n = __builtin_amdgcn_readlane(rec_n, 17);
-
-    f32x4 O[NB];
-#pragma unroll
-    for (int b = 0; b < NB; ++b) O[b] = f32x4{0.f, 0.f, 0.f, 0.f};
-    float m_run = -INFINITY, l_run = 0.f;
-
-    // One pipeline step = one 32-token page pair.  On entry K of the pair has been requested
-    // earlier and V is still in flight.  K of the following pair (of this item or of the wave's
-    // next item) is requested as soon as the score MFMAs have consumed the K registers, V of the
-    // following pair right after the output MFMAs.  Returns false when the wave's range is done.
-    auto step = [&]() -> bool {
-        f32x4 sx = {0.f, 0.f, 0.f, 0.f}, sy = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int s = 0; s < NS; ++s) {
-            const bf16x8 kx = __builtin_bit_cast(bf16x8, kr[0][s]), ky = __builtin_bit_cast(bf16x8, kr[1][s]);
-            sx = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kx, qhi[s], sx, 0, 0, 0);
-            sy = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ky, qhi[s], sy, 0, 0, 0);
-            sx = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kx, qlo[s], sx, 0, 0, 0);
-            sy = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ky, qlo[s], sy, 0, 0, 0);
-        }
-        // The following pair is requested unconditionally (branch-free, so that the K and V
-        // requests can stay in flight across each other); past the end of the wave's range it
-        // re-reads a valid pair that is never used.
-        const bool more_pairs = pp + 1 < npairs;
-        const int nrec = more_pairs ? rec : rec_n, nhead = more_pairs ? head : head_n, npp = more_pairs ? pp + 1 : 0;
-        load_k(nrec, nhead, npp);
-
-        // this lane: head c16, tokens tb + r (tile X) and tb + 4 + r (tile Y)
-        const int tb = t0 + pp * 32 + (kq >> 1) * 16 + 8 * (kq & 1);
-        float mloc = -INFINITY;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            sx[r] = (tb + r < t1) ? sx[r] : -INFINITY;
-            sy[r] = (tb + 4 + r < t1) ? sy[r] : -INFINITY;
-            mloc = fmaxf(mloc, fmaxf(sx[r], sy[r]));
-        }
-        mloc = fmaxf(mloc, __shfl_xor(mloc, 16));
-        mloc = fmaxf(mloc, __shfl_xor(mloc, 32));
-        const float m_new = fmaxf(m_run, mloc);
-        const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
-        m_run = m_new;
-        float p[8], psum = 0.f;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            p[r] = __builtin_amdgcn_exp2f(sx[r] - m_new);
-            p[4 + r] = __builtin_amdgcn_exp2f(sy[r] - m_new);
-        }
-#pragma unroll
-        for (int e = 0; e < 8; ++e) psum += p[e];
-        l_run = l_run * alpha + psum;
-        u32x4 ph, pl;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            uint32_t hi, lo;
-            split_pair(p[2 * e], p[2 * e + 1], hi, lo);
-            ph[e] = hi;
-            pl[e] = lo;
-        }
-        const bf16x8 phi = __builtin_bit_cast(bf16x8, ph), plo = __builtin_bit_cast(bf16x8, pl);
-        // rescale O only when some head's running maximum moved (rare after the first pairs);
-        // row (head) 4*kq + r of the output tile needs alpha of lane (head)
-        if (__any(alpha != 1.f)) {
-            float al[4];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) al[r] = __shfl(alpha, 4 * kq + r);
-#pragma unroll
-            for (int b = 0; b < NB; ++b)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) O[b][r] *= al[r];
-        }
-        // pool slots past the end of the cache may hold anything: zero their V
-        if (t0 + pp * 32 + 32 > t1) {
-            const int vt = t0 + pp * 32 + (kq >> 1) * 16 + 8 * (kq & 1);
-            uint32_t msk[4];
-#pragma unroll
-            for (int w = 0; w < 4; ++w)
-                msk[w] = (vt + 2 * w < t1 ? 0x0000ffffu : 0u) | (vt + 2 * w + 1 < t1 ? 0xffff0000u : 0u);
-#pragma unroll
-            for (int b = 0; b < NB; ++b)
-#pragma unroll
-                for (int w = 0; w < 4; ++w) vr[b][w] &= msk[w];
-        }
-#pragma unroll
-        for (int b = 0; b < NB; ++b) {
-            const bf16x8 vt8 = __builtin_bit_cast(bf16x8, vr[b]);
-            O[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(phi, vt8, O[b], 0, 0, 0);
-            O[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(plo, vt8, O[b], 0, 0, 0);
-        }
-        load_v(nrec, nhead, npp);
-        if (++pp < npairs) return true;
-
-        float l_tot = l_run + __shfl_xor(l_run, 16);
-        l_tot += __shfl_xor(l_tot, 32);
-        float* pbase = a.partial + ((size_t)cidx * a.Hq + head * G) * (D + 2);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int g = 4 * kq + r;
-            if (g < G) {
-#pragma unroll
-                for (int b = 0; b < NB; ++b) pbase[(size_t)g * (D + 2) + b * 16 + c16] = O[b][r];
-            }
-        }
-        if (kq == 0 && c16 < G) {
-            pbase[(size_t)c16 * (D + 2) + D] = m_run;
-            pbase[(size_t)c16 * (D + 2) + D + 1] = l_tot;
-        }
-        if (item_n >= total_items) return false;
-        item = item_n;
-        item_n = next_item();
-        rec = rec_n;
-        req = __builtin_amdgcn_readlane(rec, 16);
-        head = __builtin_amdgcn_readlane(rec, 17);
-        t0 = __builtin_amdgcn_readlane(rec, 18);
-        t1 = __builtin_amdgcn_readlane(rec, 19);
-        cidx = __builtin_amdgcn_readlane(rec, 20);
-        npairs = ((t1 - t0 + kPageTokens - 1) / kPageTokens + 1) / 2;
-        pp = 0;
-        rec_n = load_rec(item_n < total_items ? item_n : item);
-        load_q(req, head);  // also drains every outstanding request before the steady state resumes
-        head_n = __builtin_amdgcn_readlane(rec_n, 17);
-#pragma unroll
-        for (int b = 0; b < NB; ++b) O[b] = f32x4{0.f, 0.f, 0.f, 0.f};
-        m_run = -INFINITY;
-        l_run = 0.f;
-        return true;
-    };
-
-    while (step()) {
-    }
+    attn_split_items<D, G, false>(a, blockIdx.x, gridDim.x, &list_cursor, [] {});
 }
 
 // ---------------------------------------------------------------------------------
@@ -554,28 +290,7 @@ hipError_t launch_attn_split(const KvPool& pool, int layer, const AttnPlan& plan
     const sun_kv_layout& L = pool.lay;
     const int D = c.head_dim, G = c.n_q_heads / c.n_kv_heads;
     if (L.k_dim != 1 || L.k_token != D || L.v_token != 1 || L.v_dim != kPageTokens) return hipErrorInvalidValue;
-    AttnArgs a{};
-    a.kbase = pool.base + L.k_off + (int64_t)layer * L.k_layer;
-    a.vbase = pool.base + L.v_off + (int64_t)layer * L.v_layer;
-    a.k_page = L.k_page;
-    a.k_head = L.k_head;
-    a.v_page = L.v_page;
-    a.v_head = L.v_head;
-    a.q = q;
-    a.page_tables = page_tables;
-    a.n_or_len = n_or_len;
-    a.chunk_off = plan.chunk_off;
-    a.full_off = plan.full_off;
-    a.records = plan.records;
-    a.partial = plan.partial;
-    a.len_plus = len_plus;
-    a.max_pages = max_pages;
-    a.batch = batch;
-    a.Hq = c.n_q_heads;
-    a.Hkv = c.n_kv_heads;
-    a.n_pages = (int)L.n_pages;
-    a.qscale = kLog2e / sqrtf((float)D);
-    a.n_full_items = a.total_items = -1;
+    AttnArgs a = make_attn_args(pool, layer, plan, q, page_tables, max_pages, n_or_len, len_plus, batch);
     const long long chunks = total_chunks_hint >= 0 ? total_chunks_hint : plan.max_chunks;
     const long long items = chunks * c.n_kv_heads;
     if (f32_exact) {

@@ -152,6 +152,24 @@ __device__ __forceinline__ int32_t load_uniform(const int32_t* p) {
     return *(const __attribute__((address_space(4))) int32_t*)(uintptr_t)p;
 }
 
+// ---- data that workgroups of one launch hand to one another ----
+// Stores that go through to memory and loads that do not take what this XCD's caches hold (each of the eight XCDs has an L2 of
+// its own).  A store has arrived when vmcnt says so; no cache has to be written back or invalidated as a whole.
+__device__ __forceinline__ void st_agent(float* p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ void st_agent(uint32_t* p, uint32_t v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ void st_agent(uint16_t* p, uint16_t v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ float ld_agent(const float* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ uint32_t ld_agent(const uint32_t* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+// two floats, eight bytes aligned
+__device__ __forceinline__ void st_agent2(float* p, float a, float b) {
+    __hip_atomic_store((unsigned long long*)p, (unsigned long long)__float_as_uint(a) | (unsigned long long)__float_as_uint(b) << 32,
+                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ float2 ld_agent2(const float* p) {
+    const unsigned long long v = __hip_atomic_load((const unsigned long long*)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return float2{__uint_as_float((uint32_t)v), __uint_as_float((uint32_t)(v >> 32))};
+}
+
 // ---- wave reductions (all lanes receive the result; fixed order => deterministic) ----
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll

@@ -58,9 +58,14 @@ size_t attn_max_chunks(int batch, int max_pages, int Hkv);
 hipError_t launch_attn_plan(const AttnPlan& plan, const int32_t* n_or_len, int len_plus, int batch,
                             const int32_t* page_tables, int max_pages, int n_pages, int Hkv, hipStream_t st);
 // First launch of a decode step: launch_embed_rope and launch_attn_plan (n_tokens = seq_lens + 1) together.
+// Counters of the launch that runs all layers start at zero.
+struct LayersZero {
+    uint32_t* p;
+    int n;
+};
 hipError_t launch_step_begin(const sun_model_cfg& cfg, const void* embed, const int32_t* tokens, const int32_t* seq_lens, int batch,
                              float* x, float* table, const AttnPlan& plan, const int32_t* page_tables, int max_pages,
-                             int n_pages, hipStream_t st);
+                             int n_pages, LayersZero zero, hipStream_t st);
 // n_tokens(i) = n_or_len[i] + len_plus.  q fp32 [batch, Hq*d].  The chunk counts of the batch (all chunks, full
 // chunks) when the host knows the lengths, else < 0.
 hipError_t launch_attn_split(const KvPool& pool, int layer, const AttnPlan& plan, const float* q,
@@ -78,6 +83,25 @@ hipError_t launch_attn_prefill(const KvPool& pool, int layer, const float* q, co
                                int splits, float* partial, void* out_tiled, hipStream_t st);
 // how many splits the block wants
 int attn_prefill_splits(const sun_model_cfg& c, int rows, int first);
+
+// ---------------- all layers of a small batch in one launch (layers.hip) ----------------
+constexpr int kLayersRows = 16;    // rows of such a step at most; measured in layers.hip
+constexpr int kLayersRowsW4 = 8;   // with 4-bit weights
+struct LayersScratch {
+    void* p;
+    size_t bytes;
+};
+bool layers_usable(const Weights& W, int rows, const LayersScratch& scratch, hipStream_t st);
+LayersZero layers_zero(const LayersScratch& scratch, const Weights& W);
+// x: the embedding on entry, the residual stream behind the last layer on return.  Behind launch_step_begin with
+// layers_zero() of the same scratch.
+hipError_t launch_layers(const KvPool& pool, const Weights& W, int rows, float* x, const float* table, const AttnPlan& plan,
+                         const int32_t* page_tables, int max_pages, const int32_t* seq_lens, int total_chunks_hint, int full_chunks_hint,
+                         const LayersScratch& scratch, hipStream_t st);
+
+// Workgroups of a kernel (one per compute unit, at most `most`) that a cooperative launch on the device keeps resident; 0: none.
+int resident_grid(const void* kernel, int threads, int most, int dev);
+bool is_capturing(hipStream_t st);   // or cannot tell
 
 // ---------------- everything else (misc.hip) ----------------
 
