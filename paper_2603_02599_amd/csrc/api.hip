@@ -751,7 +751,7 @@ static int step_impl(sun_kv_pool* pool_, const sun_weights* weights_, bool want_
                      const int32_t* token_ids, const int32_t* page_tables, int max_pages, const int32_t* seq_lens,
                      const int32_t* seq_lens_host, const int32_t* model_ids, float* logits_out,
                      int32_t* next_tokens_out, void* workspace, size_t workspace_bytes, void* stream, unsigned flags,
-                     bool with_head = true) {
+                     bool prefill = false, bool with_head = true) {
     if (!pool_ || !weights_) return fail(SUN_ERR_NULL, "pool or weights is NULL");
     if (!token_ids || !page_tables || !seq_lens || !model_ids || !next_tokens_out || !workspace)
         return fail(SUN_ERR_NULL, "a required device pointer is NULL");
@@ -783,6 +783,8 @@ static int step_impl(sun_kv_pool* pool_, const sun_weights* weights_, bool want_
     // SUN_PROFILE every operation is a launch of its own, which is what is timed; under capture as well, since a
     // recorded launch would not be kept apart from others like it on replay.
     const LayersScratch scratch{ws.hA, bf ? (size_t)((char*)(ws.part + ws.part_floats) - (char*)ws.hA) : 0};
+    // under SUN_PROFILE the attention is timed by its own launches
+    const bool short_f32 = !bf && !prof && !prefill && attn_short_f32(c, max_pages);
     const bool one_launch = bf && !prof && layers_usable(W, batch, scratch, st);
 
     {
@@ -816,15 +818,18 @@ static int step_impl(sun_kv_pool* pool_, const sun_weights* weights_, bool want_
         } else {
             ProfScope p(prof, 7, st);
             SUN_HIP_CHECK(f32_norm_proj(c, L.qkv, ws, L.g1, batch, F32_STORE, ws.qkv32, st));
-            SUN_HIP_CHECK(launch_rope_append(pool, l, ws.qkv32, 1, batch, ws.table, seq_lens, 0, page_tables, max_pages,
-                                             batch, ws.q, L.qn, L.kn, L.bq, L.bk, L.bv, st));
+            if (short_f32)
+                SUN_HIP_CHECK(launch_attn_short_f32(pool, l, ws.qkv32, ws.table, seq_lens, page_tables, max_pages, batch, L, ws.a32, st));
+            else
+                SUN_HIP_CHECK(launch_rope_append(pool, l, ws.qkv32, 1, batch, ws.table, seq_lens, 0, page_tables, max_pages,
+                                                 batch, ws.q, L.qn, L.kn, L.bq, L.bk, L.bv, st));
         }
-        {
+        if (!short_f32) {
             ProfScope p(prof, 0, st);
             SUN_HIP_CHECK(launch_attn_split(pool, l, ws.plan, attn_q, page_tables, max_pages, seq_lens, 1, batch, hint.total,
                                             hint.full, !bf, st));
         }
-        {
+        if (!short_f32) {
             ProfScope p(prof, 1, st);
             SUN_HIP_CHECK(launch_attn_combine(c, ws.plan, batch, bf ? nullptr : ws.a32, bf ? ws.aA : nullptr,
                                               (bf && W.quant) ? ws.qs : nullptr, st));
@@ -1262,7 +1267,7 @@ int sun_prefill(sun_kv_pool* pool_, const sun_weights* weights_, int n_tokens, c
         const bool last_block = done + rows == n_tokens;
         SUN_HIP_CHECK(launch_prefill_rows(page_table, max_pages, first_pos + done, model_id, rows, ex.tables, ex.lens, ex.ids, st));
         const int rc = step_impl(pool_, weights_, false, rows, token_ids + done, ex.tables, max_pages, ex.lens, nullptr,
-                                 ex.ids, nullptr, ex.next, workspace, step_bytes, stream, step_flags,
+                                 ex.ids, nullptr, ex.next, workspace, step_bytes, stream, step_flags, true,
                                  last_block && (logits_out || next_token_out));
         if (rc != SUN_OK) return rc;
         if (last_block) {

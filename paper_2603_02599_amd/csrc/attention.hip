@@ -271,6 +271,202 @@ __global__ __launch_bounds__(256) void attn_split_f32_kernel(AttnArgs a, int G) 
     }
 }
 
+// ---------------------------------------------------------------------------------
+// fp32, short tables: rotation, append, attention over all chunks and their merge in one launch
+// ---------------------------------------------------------------------------------
+// Bound by latency like the launches it replaces (rope_append_kernel, attn_split_f32_kernel, attn_combine_kernel: three of
+// a layer's seven): a workgroup per request and KV head takes the new position's heads out of the q/k/v product, appends K
+// and V, walks the request's chunks (a wave per chunk and query head, partial results in LDS) and merges them.  Every sum has
+// the order it has there, so the results are theirs bit for bit.  Tiny configuration, three launches -> this (us a step): 8 requests of 16 /
+// 100 / 250 / 500 / 900 cached tokens 78.7 / 79.2 / 82.2 / 83.4 / 83.4 -> 68.7 / 71.4 / 76.6 / 86.2 / 106.7, 48 of 250 105 -> 100,
+// 200 of 250 160 -> 146: a request is a few workgroups', so tables beyond kShortTokens stay with the launches that spread it.
+// Not for a prefill block, where a row attends to entries that other rows of the launch append.
+constexpr int kShortPart = (kShortTokens / kAttnSmall) * 8 * 130;   // floats of LDS for partial results: chunks, query heads, dims + 2
+
+struct ShortArgs {
+    const float *qkv, *table, *bq, *bk, *bv, *qn, *kn;   // biases and head-norm gains may be NULL
+    const int32_t *seq_lens, *page_tables;
+    uint16_t *kbase, *vbase;                             // of the layer
+    int64_t k_page, k_head, v_page, v_head;
+    float* out;                                          // [batch, Hq * D]
+    int batch, Hq, Hkv, max_pages, n_pages;
+    float eps, qscale;
+};
+
+template <int D>
+__global__ __launch_bounds__(512) void attn_short_f32_kernel(ShortArgs a) {
+    constexpr int W = 8, half = D / 2;
+    __shared__ __attribute__((aligned(16))) float qs[8 * D], sc[W][CH], part[kShortPart];
+    __shared__ __attribute__((aligned(16))) uint16_t kv[2][D];   // the new entry
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, kh = blockIdx.x, b = blockIdx.y, G = a.Hq / a.Hkv;
+    // lengths and page ids are validated on the host under SUN_VALIDATE; clamp so bad input cannot fault
+    const int L = min(max(a.seq_lens[b], 0), a.max_pages * kPageTokens - 1), n = L + 1;
+    const int32_t* pt = a.page_tables + (size_t)b * a.max_pages;
+    const auto page_of = [&](int p) { return min(max(pt[p], 0), a.n_pages - 1); };
+    uint16_t *kb = a.kbase + (int64_t)kh * a.k_head, *vb = a.vbase + (int64_t)kh * a.v_head;
+    for (int t = wave; t < G + 2; t += W) {                 // a wave per head; lane j holds elements j and j + D / 2
+        const int hh = t < G ? kh * G + t : t == G ? a.Hq + kh : a.Hq + a.Hkv + kh, j = lane;
+        const bool act = j < half;
+        const float* src = a.qkv + ((size_t)b * (a.Hq + 2 * a.Hkv) + hh) * D;
+        float lo = 0.f, hi = 0.f;
+        if (act) {
+            lo += src[j];
+            hi += src[j + half];
+        }
+        if (a.bq && act) {
+            const float* bias = t < G ? a.bq : t == G ? a.bk : a.bv;
+            const int h0 = (t < G ? hh : kh) * D;
+            lo += bias[h0 + j];
+            hi += bias[h0 + j + half];
+        }
+        if (a.qn && t <= G) {
+            const float ss = wave_sum(lo * lo + hi * hi);
+            const float r = 1.0f / sqrtf(ss / (float)D + a.eps);
+            if (act) {
+                const float* g = t < G ? a.qn : a.kn;
+                lo = lo * r * g[j];
+                hi = hi * r * g[j + half];
+            }
+        }
+        if (!act) continue;
+        if (t <= G) {
+            const float c = a.table[((size_t)b * half + j) * 2], sn = a.table[((size_t)b * half + j) * 2 + 1];
+            const float rl = lo * c - hi * sn, rh = hi * c + lo * sn;
+            lo = rl;
+            hi = rh;
+        }
+        if (t < G) {
+            qs[t * D + j] = lo;
+            qs[t * D + j + half] = hi;
+        } else {
+            const uint16_t l16 = f32_to_bf16_bits(lo), h16 = f32_to_bf16_bits(hi);
+            const int64_t page = page_of(L / kPageTokens), slot = L % kPageTokens;
+            kv[t - G][j] = l16;
+            kv[t - G][j + half] = h16;
+            if (t == G) {
+                kb[page * a.k_page + slot * D + j] = l16;
+                kb[page * a.k_page + slot * D + j + half] = h16;
+            } else {
+                vb[page * a.v_page + (int64_t)j * kPageTokens + slot] = l16;
+                vb[page * a.v_page + (int64_t)(j + half) * kPageTokens + slot] = h16;
+            }
+        }
+    }
+    int n_full, n_small, ch;
+    attn_chunking(n, a.batch, a.Hkv, n_full, n_small, ch);
+    const int nc = n_full + n_small;
+    __syncthreads();
+    for (int task = wave; task < nc * G; task += W) {       // a wave per chunk and query head
+        const int ci = task / G, g = task % G;
+        const int t0 = ci < n_full ? ci * ch : n_full * ch + (ci - n_full) * kAttnSmall, t1 = ci < n_full ? t0 + ch : min(n, t0 + kAttnSmall);
+        const int cnt = t1 - t0;
+        float* s = sc[wave];
+        float mx = -INFINITY;
+        for (int tt = lane; tt < cnt; tt += 64) {           // scores: lane <-> token; the new one's K comes from LDS
+            const int pos = t0 + tt;
+            const u32x4* kr = pos == L ? reinterpret_cast<const u32x4*>(kv[0])
+                                       : reinterpret_cast<const u32x4*>(kb + (int64_t)page_of(pos / kPageTokens) * a.k_page + (pos % kPageTokens) * D);
+            u32x4 kw[D / 8];
+#pragma unroll
+            for (int i = 0; i < D / 8; ++i) kw[i] = kr[i];
+            const f32x4* qg = reinterpret_cast<const f32x4*>(qs + g * D);
+            float acc = 0.f;
+#pragma unroll
+            for (int i = 0; i < D / 8; ++i) {
+                const f32x4 q0 = qg[2 * i], q1 = qg[2 * i + 1];
+#pragma unroll
+                for (int w = 0; w < 4; ++w) {
+                    acc = fmaf(w < 2 ? q0[2 * w] : q1[2 * w - 4], bf16_lo(kw[i][w]), acc);
+                    acc = fmaf(w < 2 ? q0[2 * w + 1] : q1[2 * w - 3], bf16_hi(kw[i][w]), acc);
+                }
+            }
+            const float v = acc * a.qscale;
+            s[tt] = v;
+            mx = fmaxf(mx, v);
+        }
+        mx = wave_max(mx);
+        float sum = 0.f;
+        for (int tt = lane; tt < cnt; tt += 64) {
+            const float p = exp2f(s[tt] - mx);
+            s[tt] = p;
+            sum += p;
+        }
+        sum = wave_sum(sum);
+        float* pb = part + task * (D + 2);
+        if (lane == 0) {
+            pb[D] = mx;
+            pb[D + 1] = sum;
+        }
+        __builtin_amdgcn_wave_barrier();                    // the lanes' scores are read by all of them; a wave's LDS accesses are in order
+        for (int j = lane; j < D; j += 64) {                // output: lane <-> dim
+            const float vnew = bf16_bits_to_f32(kv[1][j]);
+            float acc = 0.f;
+            for (int p0 = 0; p0 * kPageTokens < cnt; p0 += 4) {
+                u32x4 v[4][2];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int pg = min(p0 + i, (cnt - 1) / kPageTokens);
+                    const u32x4* vr = reinterpret_cast<const u32x4*>(vb + (int64_t)page_of(t0 / kPageTokens + pg) * a.v_page + j * kPageTokens);
+                    v[i][0] = vr[0];
+                    v[i][1] = vr[1];
+                }
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int e = 0; e < kPageTokens; ++e) {
+                        const int tt = (p0 + i) * kPageTokens + e;
+                        const uint32_t w = v[i][e >> 3][(e & 7) >> 1];
+                        const float vv = t0 + tt == L ? vnew : e & 1 ? bf16_hi(w) : bf16_lo(w);
+                        if (tt < cnt) acc = fmaf(s[tt], vv, acc);   // slots past the end may hold anything
+                    }
+            }
+            pb[j] = acc;
+        }
+    }
+    __syncthreads();
+    for (int i = tid; i < G * D; i += 512) {                // merged in chunk order, the maximum moves once per eight chunks
+        const int g = i / D, j = i % D;
+        float M = -INFINITY, num = 0.f, den = 0.f;
+        for (int c8 = 0; c8 < nc; c8 += 8) {
+            const int c9 = min(nc, c8 + 8);
+            float top = M;
+            for (int c = c8; c < c9; ++c) top = fmaxf(top, part[(c * G + g) * (D + 2) + D]);
+            const float s8 = exp2f(M - top);
+            num *= s8;
+            den *= s8;
+            M = top;
+            for (int c = c8; c < c9; ++c) {
+                const float* pb = part + (c * G + g) * (D + 2);
+                const float wk = exp2f(pb[D] - M);
+                den = fmaf(wk, pb[D + 1], den);
+                num = fmaf(wk, pb[j], num);
+            }
+        }
+        a.out[((size_t)b * a.Hq + kh * G + g) * D + j] = num / den;
+    }
+}
+
+bool attn_short_f32(const sun_model_cfg& c, int max_pages) {
+    // every chunk but a request's last covers at least kAttnSmall positions
+    return c.n_q_heads / c.n_kv_heads <= 8 && c.head_dim <= 128 && (long long)max_pages * kPageTokens <= kShortTokens;
+}
+
+hipError_t launch_attn_short_f32(const KvPool& pool, int layer, const float* qkv, const float* table, const int32_t* seq_lens, const int32_t* page_tables,
+                                 int max_pages, int batch, const LayerW& w, float* out, hipStream_t st) {
+    const sun_model_cfg& c = pool.cfg;
+    const sun_kv_layout& L = pool.lay;
+    if (!attn_short_f32(c, max_pages) || L.k_dim != 1 || L.k_token != c.head_dim || L.v_token != 1 || L.v_dim != kPageTokens) return hipErrorInvalidValue;
+    const auto f = [](bool on, const void* p) { return on ? (const float*)p : nullptr; };
+    const ShortArgs a{qkv, table, f(c.qkv_bias, w.bq), f(c.qkv_bias, w.bk), f(c.qkv_bias, w.bv), f(c.qk_norm, w.qn), f(c.qk_norm, w.kn), seq_lens, page_tables,
+                      pool.base + L.k_off + (int64_t)layer * L.k_layer, pool.base + L.v_off + (int64_t)layer * L.v_layer, L.k_page, L.k_head, L.v_page, L.v_head,
+                      out, batch, c.n_q_heads, c.n_kv_heads, max_pages, (int)L.n_pages, c.rms_eps, kLog2e / sqrtf((float)c.head_dim)};
+    const dim3 grid(c.n_kv_heads, batch);
+    if (c.head_dim == 64) hipLaunchKernelGGL(attn_short_f32_kernel<64>, grid, dim3(512), 0, st, a);
+    else if (c.head_dim == 128) hipLaunchKernelGGL(attn_short_f32_kernel<128>, grid, dim3(512), 0, st, a);
+    else return hipErrorInvalidValue;
+    return hipGetLastError();
+}
+
 template <int D>
 static hipError_t launch_split_d(const AttnArgs& a, int G, int grid, hipStream_t st) {
     switch (G) {

@@ -76,6 +76,13 @@ hipError_t launch_attn_split(const KvPool& pool, int layer, const AttnPlan& plan
 hipError_t launch_attn_combine(const sun_model_cfg& cfg, const AttnPlan& plan, int batch, float* out_f32,
                                void* out_tiled, float* qscale, hipStream_t st);
 
+// fp32, tables of at most kShortTokens positions: launch_rope_append, launch_attn_split and launch_attn_combine of a decode step in
+// one launch, bit for bit.  qkv [batch, (Hq + 2 Hkv) * d], out [batch, Hq * d].
+constexpr int kShortTokens = 384;
+bool attn_short_f32(const sun_model_cfg& c, int max_pages);
+hipError_t launch_attn_short_f32(const KvPool& pool, int layer, const float* qkv, const float* table, const int32_t* seq_lens, const int32_t* page_tables,
+                                 int max_pages, int batch, const LayerW& w, float* out, hipStream_t st);
+
 // Causal attention of `rows` consecutive positions first .. first + rows - 1 of one request over positions 0 .. its own;
 // K and V of all of them are in the pool.  q fp32 [rows, Hq*d], rotated; out: two-plane tile of the O projection.
 // splits > 1: the keys are split and merged again, partial is scratch of [rows][splits][Hq][d + 2] floats.

@@ -307,3 +307,31 @@ def test_ingest_on_both_sides_of_the_rule_for_its_stores(H, tokens, first):
     H.orc.kv_ingest(host, H.layout_strides(pool.layout()), H.to_np(k), H.to_np(v), first, row)
     torch.cuda.synchronize()
     assert np.array_equal(H.to_np(mem), host)
+
+
+SHORT = 384   # positions of the longest table whose attention is one launch
+
+
+@pytest.mark.parametrize("shape,lens,extra", [
+    (wl.TINY, [0], 0), (wl.TINY, [15, 16, 62, 63, 64, 127, 128, 255, 382], 0), (wl.TINY, [383], 0), (wl.TINY, [383, 5], 1),
+    (WIDE, [0, 63, 200, 383], 0), (wl.TINY_BIAS, [17, 64, 300], 0), (wl.TINY_QWEN, [17, 64, 300], 0), (wl.TINY, list(range(310, 375)), 0)],
+    ids=["empty", "edges", "whole", "beyond", "g8-d128", "bias", "head-norm", "65-full-chunks"])
+def test_short_tables_take_one_launch_for_attention(H, shape, lens, extra):
+    """Bit for bit what the separate launches give (SUN_PROFILE asks for them): logits and every slot of the cache."""
+    work = wl.make_workload("cfg1", shape=shape, dtype="f32", batch=len(lens), seed=980 + len(lens))
+    work.seq_lens = np.asarray(lens, np.int32)
+    work.page_tables, work.n_pages = wl.deal_page_tables(work.seq_lens, np.random.default_rng(3))
+    wide = np.full((len(lens), SHORT // 16 + extra), -1, np.int32)
+    wide[:, :work.page_tables.shape[1]] = work.page_tables
+    work.page_tables = wide
+    case = H.GpuCase(work)
+    pool0 = case.pool_mem.clone()
+    ref = H.run_oracle(case, list(range(len(lens))))
+    got = []
+    for flags in (0, sun.SUN_PROFILE):
+        case.pool_mem.copy_(pool0)
+        case.ws.fill_(0xFF)
+        case.step(flags=flags)
+        H.check_logits(case.logits.cpu().numpy(), ref["logits"], "f32")
+        got.append((case.logits.clone(), case.pool_mem.clone()))
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1].view(torch.int16), got[1][1].view(torch.int16))
