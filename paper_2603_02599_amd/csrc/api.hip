@@ -747,11 +747,19 @@ static hipError_t f32_norm_proj(const sun_model_cfg& c, const Mat& M, const Work
     return launch_proj_f32(M, ws.a32, batch, nullptr, 0.f, epilogue, out, st);
 }
 
+// What is different about a step that is part of something larger.
+struct StepKind {
+    bool prefill = false;       // a block of an fp32 prompt: rows attend to entries of one another
+    bool with_head = true;
+    bool begun = false;         // embedding rows and rotary table are in place, and nobody needs the attention plan
+    bool with_argmax = true;
+};
+
 static int step_impl(sun_kv_pool* pool_, const sun_weights* weights_, bool want_quant, int batch,
                      const int32_t* token_ids, const int32_t* page_tables, int max_pages, const int32_t* seq_lens,
                      const int32_t* seq_lens_host, const int32_t* model_ids, float* logits_out,
                      int32_t* next_tokens_out, void* workspace, size_t workspace_bytes, void* stream, unsigned flags,
-                     bool prefill = false, bool with_head = true) {
+                     StepKind kind = StepKind{}) {
     if (!pool_ || !weights_) return fail(SUN_ERR_NULL, "pool or weights is NULL");
     if (!token_ids || !page_tables || !seq_lens || !model_ids || !next_tokens_out || !workspace)
         return fail(SUN_ERR_NULL, "a required device pointer is NULL");
@@ -784,10 +792,10 @@ static int step_impl(sun_kv_pool* pool_, const sun_weights* weights_, bool want_
     // recorded launch would not be kept apart from others like it on replay.
     const LayersScratch scratch{ws.hA, bf ? (size_t)((char*)(ws.part + ws.part_floats) - (char*)ws.hA) : 0};
     // under SUN_PROFILE the attention is timed by its own launches
-    const bool short_f32 = !bf && !prof && !prefill && attn_short_f32(c, max_pages);
+    const bool short_f32 = !bf && !prof && !kind.prefill && attn_short_f32(c, max_pages);
     const bool one_launch = bf && !prof && layers_usable(W, batch, scratch, st);
 
-    {
+    if (!kind.begun) {
         ProfScope p(prof, 7, st);
         SUN_HIP_CHECK(launch_step_begin(c, W.embed, token_ids, seq_lens, batch, ws.x, ws.table, ws.plan, page_tables, max_pages,
                                         (int)pool.lay.n_pages, one_launch ? layers_zero(scratch, W) : LayersZero{}, st));
@@ -876,7 +884,7 @@ static int step_impl(sun_kv_pool* pool_, const sun_weights* weights_, bool want_
             SUN_HIP_CHECK(launch_proj_f32(L.down, ws.u32, batch, nullptr, 0.f, F32_ADD, ws.x, st));
         }
     }
-    if (!with_head) return SUN_OK;  // a caller that only wants the cache entries (all but the last prefill block)
+    if (!kind.with_head) return SUN_OK;  // a caller that only wants the cache entries (all but the last prefill block)
     if (bf) {
         ProfScope p(prof, 7, st);
         SUN_HIP_CHECK(launch_residual_norm(c, ws.x, ws.part, down_parts, batch, W.gf, batch, nullptr, ws.hA, nullptr, st));
@@ -890,7 +898,7 @@ static int step_impl(sun_kv_pool* pool_, const sun_weights* weights_, bool want_
             SUN_HIP_CHECK(f32_norm_proj(c, W.lm, ws, W.gf, batch, F32_STORE, logits, st));
         }
     }
-    {
+    if (kind.with_argmax) {
         ProfScope p(prof, 7, st);
         SUN_HIP_CHECK(launch_argmax(logits, batch, c.vocab, ws.amax_val, ws.amax_idx, next_tokens_out, st));
     }
@@ -949,15 +957,26 @@ int sun_decode_run(sun_kv_pool* pool_, const sun_weights* weights_, int batch, i
         });
         if (vrc != SUN_OK) return vrc;
     }
+    // small fp32 models: what lies between two steps is one launch
+    const sun_model_cfg& c = W.cfg;
+    const bool turns = c.act_dtype == SUN_F32 && !(flags & SUN_PROFILE) && batch <= kTurnRows && (long long)batch * c.vocab <= kTurnLogits &&
+                       attn_short_f32(c, max_pages);
     for (int s = 0; s < n_steps; ++s) {
         const bool last = s + 1 == n_steps;
+        int32_t* next = tokens_out + (size_t)s * batch;
         // only the first step can be validated from the host: later inputs exist on the device only
         const int rc = step_impl(pool_, weights_, W.quant, batch, token_ids, page_tables, max_pages, seq_lens, nullptr,
-                                 model_ids, last ? logits_out : nullptr, tokens_out + (size_t)s * batch, workspace,
-                                 workspace_bytes, stream, s == 0 ? flags : (flags & ~SUN_VALIDATE));
+                                 model_ids, last ? logits_out : nullptr, next, workspace, workspace_bytes, stream,
+                                 s == 0 ? flags : (flags & ~SUN_VALIDATE), StepKind{false, true, turns && s > 0, !turns});
         if (rc != SUN_OK) return rc;
-        SUN_HIP_CHECK(launch_advance(tokens_out + (size_t)s * batch, batch, max_pages, free_pages, n_free, token_ids,
-                                     page_tables, seq_lens, free_head, run_status, s == 0, (hipStream_t)stream));
+        if (turns) {
+            const Workspace ws = carve(c, batch, max_pages, (char*)workspace);
+            SUN_HIP_CHECK(launch_run_turn(c, W.embed, last && logits_out ? logits_out : ws.logits, batch, max_pages, free_pages, n_free, next, token_ids,
+                                          page_tables, seq_lens, free_head, run_status, s == 0, last, ws.x, ws.table, (hipStream_t)stream));
+        } else {
+            SUN_HIP_CHECK(launch_advance(next, batch, max_pages, free_pages, n_free, token_ids, page_tables, seq_lens, free_head, run_status,
+                                         s == 0, (hipStream_t)stream));
+        }
     }
     return SUN_OK;
 }
@@ -1267,8 +1286,8 @@ int sun_prefill(sun_kv_pool* pool_, const sun_weights* weights_, int n_tokens, c
         const bool last_block = done + rows == n_tokens;
         SUN_HIP_CHECK(launch_prefill_rows(page_table, max_pages, first_pos + done, model_id, rows, ex.tables, ex.lens, ex.ids, st));
         const int rc = step_impl(pool_, weights_, false, rows, token_ids + done, ex.tables, max_pages, ex.lens, nullptr,
-                                 ex.ids, nullptr, ex.next, workspace, step_bytes, stream, step_flags, true,
-                                 last_block && (logits_out || next_token_out));
+                                 ex.ids, nullptr, ex.next, workspace, step_bytes, stream, step_flags,
+                                 StepKind{true, last_block && (logits_out || next_token_out)});
         if (rc != SUN_OK) return rc;
         if (last_block) {
             const Workspace ws = carve(c, rows, max_pages, (char*)workspace);

@@ -128,6 +128,12 @@ hipError_t launch_kv_ingest(const KvPool& pool, const void* k_src, const void* v
 hipError_t launch_advance(const int32_t* next, int batch, int max_pages, const int32_t* free_pages, int n_free,
                           int32_t* token_ids, int32_t* page_tables, int32_t* seq_lens, int32_t* free_head,
                           int32_t* status, bool clear_status, hipStream_t st);
+// Between two steps of a run (fp32): launch_argmax, launch_advance and, unless it was the last step, the next step's embedding rows and
+// rotary table, in one launch.
+constexpr int kTurnRows = 64, kTurnLogits = 1 << 17;   // requests, and logits of all of them, at most
+hipError_t launch_run_turn(const sun_model_cfg& cfg, const void* embed, const float* logits, int batch, int max_pages, const int32_t* free_pages, int n_free,
+                           int32_t* next, int32_t* token_ids, int32_t* page_tables, int32_t* seq_lens, int32_t* free_head, int32_t* status,
+                           bool clear_status, bool last, float* x, float* table, hipStream_t st);
 // Per-row inputs of one block of a prefill: row r gets a copy of the request's page-table row, length
 // first_pos + r and the source-model id.
 hipError_t launch_prefill_rows(const int32_t* page_table, int max_pages, int first_pos, int model_id, int rows,

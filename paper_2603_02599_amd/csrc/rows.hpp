@@ -32,24 +32,32 @@ inline EmbedRope make_embed_rope(const sun_model_cfg& cfg, const void* embed, co
                                (double)cfg.rope_low_freq_factor, (double)cfg.rope_high_freq_factor}};
 }
 
+__device__ __forceinline__ double rope_theta(const EmbedRope& e, int j) {
+    double theta = pow(e.base, -2.0 * (double)j / (double)e.d);
+    if (e.rs.scaling == 1) {
+        const double wavelen = 2.0 * 3.14159265358979323846 / theta, orig = (double)e.rs.orig_max;
+        if (wavelen > orig / e.rs.low_freq) {
+            theta = theta / e.rs.factor;
+        } else if (wavelen >= orig / e.rs.high_freq) {
+            const double smooth = (orig / wavelen - e.rs.low_freq) / (e.rs.high_freq - e.rs.low_freq);
+            theta = (1.0 - smooth) * theta / e.rs.factor + smooth * theta;
+        }
+    }
+    return theta;
+}
+// cosine and sine of position * theta
+__device__ __forceinline__ float2 rope_pair(double theta, int position) {
+    const double ang = (double)position * theta;
+    return float2{(float)cos(ang), (float)sin(ang)};
+}
+
 // x[b] = E[token_b], and row b's cosines and sines; a workgroup of 256
 __device__ __forceinline__ void embed_rope_row(const EmbedRope& e, int b) {
     const int tid = threadIdx.x;
     if (tid < e.d / 2) {
-        const double pos = (double)(e.seq_lens ? e.seq_lens[b] : e.first_pos + b);
-        double theta = pow(e.base, -2.0 * (double)tid / (double)e.d);
-        if (e.rs.scaling == 1) {
-            const double wavelen = 2.0 * 3.14159265358979323846 / theta, orig = (double)e.rs.orig_max;
-            if (wavelen > orig / e.rs.low_freq) {
-                theta = theta / e.rs.factor;
-            } else if (wavelen >= orig / e.rs.high_freq) {
-                const double smooth = (orig / wavelen - e.rs.low_freq) / (e.rs.high_freq - e.rs.low_freq);
-                theta = (1.0 - smooth) * theta / e.rs.factor + smooth * theta;
-            }
-        }
-        const double ang = pos * theta;
-        e.table[((size_t)b * (e.d / 2) + tid) * 2] = (float)cos(ang);
-        e.table[((size_t)b * (e.d / 2) + tid) * 2 + 1] = (float)sin(ang);
+        const float2 cs = rope_pair(rope_theta(e, tid), e.seq_lens ? e.seq_lens[b] : e.first_pos + b);
+        e.table[((size_t)b * (e.d / 2) + tid) * 2] = cs.x;
+        e.table[((size_t)b * (e.d / 2) + tid) * 2 + 1] = cs.y;
     }
     const int tok = min(max(e.tokens[b], 0), e.V - 1);  // ids are validated on the host under SUN_VALIDATE; never fault here
     float* x = e.x + (size_t)b * e.H;

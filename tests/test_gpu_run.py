@@ -4,6 +4,8 @@ The GPU decodes freely for n steps.  The oracle then replays the same steps fed 
 (teacher forcing), so one legitimate near-tie cannot make every later step look wrong: at every step the
 GPU's token must be the oracle's argmax, or the runner-up of a documented near-tie.  Page tables, lengths,
 free-list head, status and every cache entry written during the run are compared as well."""
+import dataclasses
+
 import numpy as np
 import pytest
 import torch
@@ -120,3 +122,39 @@ def test_run_of_one_step_equals_the_step(H):
     torch.cuda.synchronize()
     assert torch.equal(out[0], nxt_step) and torch.equal(logits, logits_step) and torch.equal(case.pool_mem, pool_step)
     assert torch.equal(tok, nxt_step)
+
+
+ODD = dataclasses.replace(wl.TINY, name="odd", ffn=689, vocab=1031)
+
+
+@pytest.mark.parametrize("shape,batch,steps,spare,width", [
+    (wl.TINY, 1, 1, 2, 24), (wl.TINY, 1, 3, 2, 24), (ODD, 7, 5, 3, 24), (wl.TINY, 64, 18, 200, 24), (wl.TINY, 64, 18, 9, 3), (wl.TINY, 65, 3, 200, 24),
+    (wl.TINY_QWEN, 5, 20, 40, 24)], ids=["one-step", "one", "odd-vocab", "64", "64-no-pages", "65", "scaled-out"])
+def test_what_lies_between_two_steps_in_one_launch(H, shape, batch, steps, spare, width):
+    """The run with everything between two steps in one launch equals the run of separate launches (SUN_PROFILE asks for them) bit for
+    bit: tokens, logits, tables, lengths, free list, status and cache."""
+    rng = np.random.default_rng(batch)
+    work = wl.make_workload("cfg1", shape=shape, dtype="f32", batch=batch, seed=60 + batch)
+    work.seq_lens = rng.integers(0, 16 * min(width, 6) - 1, size=batch).astype(np.int32)
+    work.page_tables, used = wl.deal_page_tables(work.seq_lens, rng)
+    work.n_pages = used + spare
+    wide = np.full((batch, width), -1, np.int32)
+    wide[:, :work.page_tables.shape[1]] = work.page_tables
+    work.page_tables = wide
+    case = H.GpuCase(work)
+    pool0 = case.pool_mem.clone()
+    free = torch.arange(used, used + spare, dtype=torch.int32, device="cuda")
+    got = []
+    for flags in (0, sun.SUN_PROFILE):
+        case.pool_mem.copy_(pool0)
+        case.ws.fill_(0xFF)
+        tok, tab, ln = case.tokens.clone(), case.tables.clone(), case.lens.clone()
+        head = torch.zeros(1, dtype=torch.int32, device="cuda")
+        status = torch.full((1,), 9, dtype=torch.int32, device="cuda")
+        out = torch.full((steps, batch), -7, dtype=torch.int32, device="cuda")
+        logits = torch.full((batch, shape.vocab), float("nan"), device="cuda")
+        sun.sun_decode_run(case.pool, case.weights, steps, tok, tab, ln, case.ids, free, head, status, out, logits, case.ws, flags=flags)
+        torch.cuda.synchronize()
+        got.append((out, logits, tok, tab, ln, head, status, case.pool_mem.clone().view(torch.int16)))
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
