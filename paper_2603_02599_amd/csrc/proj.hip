@@ -431,14 +431,16 @@ void proj_tall_kernel(ProjArgs a) {
 // 24 bytes per cycle here against 47.  Measured, 28 672 x 4096, both planes counted: 1024 rows 384 us on average in a prefill (368
 // the shortest) = 1.25 PFLOP/s, 2048 rows 729 (713) = 1.32 (four / eight launches of the 128 x 256 kernel: 505 / 1010 us; the
 // instructions alone, no loads: 322 / 591; the same code on zeros, which draw less power and leave the clock up: 294 / 583).
+// CB: 32-column strips of a workgroup, eight or, where that makes whole rounds, fewer (wide_pick).
 // Measured and left out: 128 x 256 tiles in this scheme (1024 rows 430 us; at 256 rows no faster than the kernel
 // above), four or five slots, a deeper ring for the weights than for the activations, streaming loads for the
 // weights (the row tiles share them through L2: 775 us), a rotated start along k, other workgroup orders.
-template <int EPI>
+template <int EPI, int CB>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void proj_wide_kernel(ProjArgs a) {
-    constexpr int RB = 8, CB = 8;                       // row blocks and column strips of a workgroup
-    constexpr int AF = 2 * 2 * RB, WF = 2 * CB;         // operand fragments (1 KiB) of a stage: two k-steps
+    constexpr int RB = 8, CS = 8;                       // row blocks of a workgroup, and places for its column strips in a slot
+    constexpr int S0 = (CB + 1) / 2;                    // strips of the waves of column half 0; the others have CB - S0
+    constexpr int AF = 2 * 2 * RB, WF = 2 * CS;         // operand fragments (1 KiB) of a stage: two k-steps
     constexpr int STAGE_UNITS = (AF + WF) * 64;         // 16-byte units (48 KiB)
     constexpr int NBUF = 3;
     constexpr int WA = AF / 8, PER = WA + WF / 8;       // fragments a wave fetches per stage: four of A, two of W
@@ -446,7 +448,9 @@ void proj_wide_kernel(ProjArgs a) {
 
     const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int ch = wave & 1, rh = wave >> 1;            // column half, 64-row group
+    // column half, 64-row group; the two waves of a SIMD (w and w + 4) are of different halves, which may differ by a strip
+    const int ch = (wave ^ (wave >> 2)) & 1, rh = wave >> 1;
+    const bool short_half = CB % 2 && ch == 1;
     const int n_strips = a.N / 32;
     const int strip0 = blockIdx.x * CB;
     const int split = blockIdx.y;
@@ -468,10 +472,10 @@ void proj_wide_kernel(ProjArgs a) {
             src[i] = a.A + ((size_t)(s0 * 2 + ks) * (2 * a.mb_rows) + gb) * 64;
             dst[i] = lds0 + f * 1024;
         } else {
-            const int f = wave * (WF / 8) + (i - WA), ks = f / CB, blk = f % CB;
+            const int f = min(wave * (WF / 8) + (i - WA), 2 * CB - 1), ks = f / CB, blk = f % CB;   // past the last: that one again, the same bytes
             const int strip = min(strip0 + blk, n_strips - 1);  // past the last strip: any valid one, its result is dropped
             src[i] = a.W + ((size_t)strip * kch8 + s0 * 2 + ks) * 64;
-            dst[i] = lds0 + (AF + f) * 1024;
+            dst[i] = lds0 + (AF + ks * CS + blk) * 1024;
         }
     }
     const size_t step_a = (size_t)4 * a.mb_rows * 64, step_w = 128;  // units from one stage to the next
@@ -486,16 +490,16 @@ void proj_wide_kernel(ProjArgs a) {
         if (fill == NBUF * STAGE_UNITS * 16) fill = 0;
         ++fill_st;
     };
-    f32x16 acc[4][2];
+    f32x16 acc[S0][2];
 #pragma unroll
-    for (int s = 0; s < 4; ++s)
+    for (int s = 0; s < S0; ++s)
 #pragma unroll
         for (int m = 0; m < 2; ++m)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[s][m][r] = 0.f;
 
     struct Frags {
-        u32x4 a[2][2], w[4];
+        u32x4 a[2][2], w[S0];
     };
     int at = 0;                                         // ring slot that is read
     auto read = [&](Frags& f, int ks) {
@@ -505,19 +509,21 @@ void proj_wide_kernel(ProjArgs a) {
 #pragma unroll
             for (int m = 0; m < 2; ++m) f.a[pl][m] = p[(ks * 2 * RB + pl * RB + rh * 2 + m) * 64];
 #pragma unroll
-        for (int s = 0; s < 4; ++s) f.w[s] = p[(AF + ks * CB + ch * 4 + s) * 64];
+        for (int s = 0; s < S0; ++s) f.w[s] = p[(AF + ks * CS + ch * S0 + s) * 64];   // past a short half's strips: not used
     };
-    // 16 matrix instructions, the requests i0 .. i0 + 2 of the stage being fetched between them
+    // 4 S0 matrix instructions (16 for 256 columns), the requests i0 .. i0 + 2 of the stage being fetched between them
     auto mma = [&](const Frags& f, int i0) {
 #pragma unroll
         for (int pl = 0; pl < 2; ++pl)
 #pragma unroll
-            for (int s = 0; s < 4; ++s) {
+            for (int s = 0; s < S0; ++s) {
+                if (s + 1 < S0 || !short_half) {
 #pragma unroll
-                for (int m = 0; m < 2; ++m)
-                    acc[s][m] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, f.a[pl][m]),
-                                                                      __builtin_bit_cast(bf16x8, f.w[s]), acc[s][m], 0, 0, 0);
-                const int g = pl * 4 + s;
+                    for (int m = 0; m < 2; ++m)
+                        acc[s][m] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, f.a[pl][m]),
+                                                                          __builtin_bit_cast(bf16x8, f.w[s]), acc[s][m], 0, 0, 0);
+                }
+                const int g = pl * S0 + s;
                 if ((g & 1) && g < 6) {
                     __builtin_amdgcn_sched_barrier(0);
                     issue(i0 + (g >> 1));
@@ -556,7 +562,7 @@ void proj_wide_kernel(ProjArgs a) {
         }
     }
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");  // nothing is in flight into LDS any more
-    const int my_strip = strip0 + ch * 4;
+    const int my_strip = strip0 + ch * S0, my_end = min(n_strips, strip0 + (ch ? CB : S0));
     const int col = lane & 31, row0 = (mb_off + rh * 2) * 32;
     if constexpr (EPI == EPI_SWIGLU) {
         // The results leave as the tile the down projection reads: hi and lo plane, 16-byte units
@@ -564,13 +570,13 @@ void proj_wide_kernel(ProjArgs a) {
         uint16_t* sw = reinterpret_cast<uint16_t*>(lds_all) + (size_t)wave * (2 * 64 * 16);
         u32x4* tile = reinterpret_cast<u32x4*>(a.out);
 #pragma unroll
-        for (int s = 0; s < 4; ++s) {
+        for (int s = 0; s < S0; ++s) {
             const int nb = my_strip + s;
 #pragma unroll
             for (int m = 0; m < 2; ++m) swiglu_strip<64>(acc[s][m], sw, m * 32);
             __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): the wave's LDS writes have landed (no other wave reads them)
             __builtin_amdgcn_wave_barrier();
-            if (nb < n_strips) {
+            if (nb < my_end) {
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {    // 64 rows x 2 units x 2 planes = 256 units, 64 lanes
                     const int idx = i * 64 + lane;
@@ -584,9 +590,9 @@ void proj_wide_kernel(ProjArgs a) {
         }
     } else {
 #pragma unroll
-        for (int s = 0; s < 4; ++s) {
+        for (int s = 0; s < S0; ++s) {
             const int nb = my_strip + s;
-            if (nb >= n_strips) continue;
+            if (nb >= my_end) continue;
             float* o = a.out + (size_t)split * a.ld_rows * a.ldo + nb * 32 + col;
 #pragma unroll
             for (int m = 0; m < 2; ++m)
@@ -798,16 +804,26 @@ static hipError_t launch_proj_tall(const ProjArgs& a, int epilogue, int splits, 
     return hipGetLastError();
 }
 
-static hipError_t launch_proj_wide(const ProjArgs& a, int epilogue, int splits, hipStream_t st) {
-    dim3 grid((a.N / 32 + 7) / 8, splits, (a.rows + 255) / 256);
-    if (epilogue == EPI_SWIGLU) {
-        if (splits != 1) return hipErrorInvalidValue;
-        hipLaunchKernelGGL((proj_wide_kernel<EPI_SWIGLU>), grid, dim3(512), 0, st, a);
+static hipError_t launch_proj_wide(const ProjArgs& a, int epilogue, int cb, int splits, hipStream_t st) {
+    const auto go = [&](auto cbc) {
+        constexpr int CB = decltype(cbc)::value;
+        dim3 grid((a.N / 32 + CB - 1) / CB, splits, (a.rows + 255) / 256);
+        if (epilogue == EPI_SWIGLU) {
+            if (splits != 1) return hipErrorInvalidValue;
+            hipLaunchKernelGGL((proj_wide_kernel<EPI_SWIGLU, CB>), grid, dim3(512), 0, st, a);
+            return hipGetLastError();
+        }
+        if (epilogue != EPI_STORE) return hipErrorInvalidValue;
+        hipLaunchKernelGGL((proj_wide_kernel<EPI_STORE, CB>), grid, dim3(512), 0, st, a);
         return hipGetLastError();
+    };
+    switch (cb) {
+    case 5: return go(std::integral_constant<int, 5>{});
+    case 6: return go(std::integral_constant<int, 6>{});
+    case 7: return go(std::integral_constant<int, 7>{});
+    case 8: return go(std::integral_constant<int, 8>{});
     }
-    if (epilogue != EPI_STORE) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((proj_wide_kernel<EPI_STORE>), grid, dim3(512), 0, st, a);
-    return hipGetLastError();
+    return hipErrorInvalidValue;
 }
 
 // Split-K factor of the launch above 128 rows (bf16; workgroups of 128 rows x 256 columns).  All workgroups do
@@ -925,24 +941,33 @@ static bool use_tall(const Mat& W, int rows) {
     return W.kind == MAT_BF16_PACKED && rows > 128 && !use_wide(W, rows) && (W.N / 32 + 7) / 8 <= 256;
 }
 
-// Split-K factor of a wide launch: whole rounds of 256 workgroups cost stages x 0.95 us (2048 cycles of matrix
-// instructions) plus about 8 us each, a split the writing and reading of its slab.  With every unit busy on random data
-// the clock falls and a stage takes up to 1.4 us; that figure gives the same split for 45 of 48 launches of the 8B and
-// 14B shapes (q/k/v, o, down at 300 to 2048 rows).
-static int wide_pick_splits(const Mat& W, int rows, int max_splits) {
-    const int stages = W.K / 32;
-    const long long tiles = (long long)((W.N / 32 + 7) / 8) * ((rows + 255) / 256);
-    int best = 1;
+// Column strips of a workgroup and split-K factor of a wide launch.  A round of 256 workgroups costs 8 us and a stage time for each
+// of its stages, a split the writing and reading of its slab.  With every unit busy the matrix cores' power bounds a stage: 1.7 us
+// at eight strips, in proportion for fewer; a workgroup alone takes 0.95 us however few its strips are (loads and barrier), and a
+// round that is not full lies between the two.  So a partial last round costs less than a whole one, but narrower tiles that make whole
+// rounds still win.  Measured in prefills, eight strips -> picked (us): gate/up of the 8B shape at 1024 / 1536 rows 407 / 591 -> 396 /
+// 574 (seven), 14B shape at 1024 rows 490 -> 476 (seven), q/k/v at 1024 rows 105 -> 89 (six), at 1536 rows 142 in three slabs
+// -> 139 in one (five); o and down at 1024 rows stay (61 / 192; six strips 79 / 220).  The figures give the measured times of 28
+// launches to within 10 %.
+struct WideShape {
+    int cb, splits;
+};
+static WideShape wide_pick(const Mat& W, int rows, int max_splits, int only_splits = 0) {
+    const int stages = W.K / 32, strips = W.N / 32, row_tiles = (rows + 255) / 256;
+    WideShape best{8, max(1, only_splits)};
     double best_us = 0;
-    for (int s = 1; s <= max(1, min(max_splits, stages / 8)); ++s) {
-        const int sps = (stages + s - 1) / s;
-        if ((stages + sps - 1) / sps != s) continue;
-        const double us = (double)((tiles * s + 255) / 256) * (sps * 0.95 + 8.0) + (double)s * rows * W.N * 8e-6 / 5.0;
-        if (best_us == 0 || us < best_us) {
-            best_us = us;
-            best = s;
+    for (int cb = 8; cb >= 5; --cb)
+        for (int s = 1; s <= max(1, min(max_splits, stages / 8)); ++s) {
+            const int sps = (stages + s - 1) / s;
+            if (only_splits ? s != only_splits : (stages + sps - 1) / sps != s) continue;
+            const long long wgs = (long long)((strips + cb - 1) / cb) * row_tiles * s, rounds = (wgs + 255) / 256;
+            const double full = (double)wgs / (double)(rounds * 256), stage = 0.95 + (1.7 * cb / 8 - 0.95) * full;
+            const double us = (double)rounds * (sps * stage + 8.0) + (double)s * rows * W.N * 8e-6 / 5.0;
+            if (best_us == 0 || us < best_us) {
+                best_us = us;
+                best = WideShape{cb, s};
+            }
         }
-    }
     return best;
 }
 
@@ -958,7 +983,7 @@ bool proj_fuses_swiglu(const Mat& gu, int rows) {
 }
 
 int proj_pick_splits(const Mat& W, int rows, int max_splits) {
-    if (use_wide(W, rows)) return wide_pick_splits(W, rows, max_splits);
+    if (use_wide(W, rows)) return wide_pick(W, rows, max_splits).splits;
     if (use_tall(W, rows)) return tall_pick_splits(W, rows, max_splits);
     return proj_pick(W, rows, max_splits).splits;
 }
@@ -1041,7 +1066,8 @@ hipError_t launch_proj(const ProjLaunch& p, hipStream_t st) {
         const int stg = kch * 4, per = (stg + want - 1) / want;
         a.n_stages = stg;
         a.stages_per_split = per;
-        return launch_proj_wide(a, p.epilogue, (stg + per - 1) / per, st);
+        const int real_s = (stg + per - 1) / per;
+        return launch_proj_wide(a, p.epilogue, wide_pick(W, p.rows, real_s, real_s).cb, real_s, st);
     }
     if (use_tall(W, p.rows)) {
         const int want = p.epilogue == EPI_SWIGLU ? 1 : max(1, p.splits);

@@ -227,3 +227,11 @@ def test_slots_past_the_prompt_may_hold_anything(H, first, rows):
         got.append((logits, H.to_np(case.pool_mem).copy()[own]))
     assert np.isfinite(got[0][0]).all()
     assert np.array_equal(got[0][0], got[1][0]) and np.array_equal(got[0][1], got[1][1])
+
+
+@pytest.mark.parametrize("heads,ffn", [((64, 32), 7040), ((56, 28), 8192)], ids=["qkv-7-gate-up-6", "qkv-6-gate-up-7"])
+def test_column_tiles_of_other_widths(H, heads, ffn):
+    """Widths for which q/k/v and gate/up take workgroups of six and of seven 32-column strips (the last workgroup ragged), three row
+    tiles of which the last holds eight rows; o and down take five."""
+    shape = dataclasses.replace(wl.SMALL128, name="narrow", hidden=256, n_q_heads=heads[0], n_kv_heads=heads[1], ffn=ffn)
+    test_prefill_blocks_equal_the_causal_forward(H, shape, 520, [])
