@@ -431,11 +431,12 @@ void proj_tall_kernel(ProjArgs a) {
 // 24 bytes per cycle here against 47.  Measured, 28 672 x 4096, both planes counted: 1024 rows 384 us on average in a prefill (368
 // the shortest) = 1.25 PFLOP/s, 2048 rows 729 (713) = 1.32 (four / eight launches of the 128 x 256 kernel: 505 / 1010 us; the
 // instructions alone, no loads: 322 / 591; the same code on zeros, which draw less power and leave the clock up: 294 / 583).
-// CB: 32-column strips of a workgroup, eight or, where that makes whole rounds, fewer (wide_pick).
+// CB: 32-column strips of a workgroup, eight or, where that makes whole rounds, fewer (wide_pick).  RAGGED: row blocks without a row are
+// left out of the products (launch_proj_wide).
 // Measured and left out: 128 x 256 tiles in this scheme (1024 rows 430 us; at 256 rows no faster than the kernel
 // above), four or five slots, a deeper ring for the weights than for the activations, streaming loads for the
 // weights (the row tiles share them through L2: 775 us), a rotated start along k, other workgroup orders.
-template <int EPI, int CB>
+template <int EPI, int CB, bool RAGGED>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void proj_wide_kernel(ProjArgs a) {
     constexpr int RB = 8, CS = 8;                       // row blocks of a workgroup, and places for its column strips in a slot
@@ -451,6 +452,8 @@ void proj_wide_kernel(ProjArgs a) {
     // column half, 64-row group; the two waves of a SIMD (w and w + 4) are of different halves, which may differ by a strip
     const int ch = (wave ^ (wave >> 2)) & 1, rh = wave >> 1;
     const bool short_half = CB % 2 && ch == 1;
+    // row blocks of this wave that hold a row (none: 0 or less)
+    const int blocks = RAGGED ? min(2, (a.rows - ((int)blockIdx.z * RB + rh * 2) * 32 + 31) / 32) : 2;
     const int n_strips = a.N / 32;
     const int strip0 = blockIdx.x * CB;
     const int split = blockIdx.y;
@@ -517,10 +520,11 @@ void proj_wide_kernel(ProjArgs a) {
         for (int pl = 0; pl < 2; ++pl)
 #pragma unroll
             for (int s = 0; s < S0; ++s) {
-                if (s + 1 < S0 || !short_half) {
+                if ((s + 1 < S0 || !short_half) && (!RAGGED || blocks > 0)) {
 #pragma unroll
                     for (int m = 0; m < 2; ++m)
-                        acc[s][m] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, f.a[pl][m]),
+                        if (!RAGGED || m < blocks)
+                            acc[s][m] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, f.a[pl][m]),
                                                                           __builtin_bit_cast(bf16x8, f.w[s]), acc[s][m], 0, 0, 0);
                 }
                 const int g = pl * S0 + s;
@@ -808,13 +812,22 @@ static hipError_t launch_proj_wide(const ProjArgs& a, int epilogue, int cb, int 
     const auto go = [&](auto cbc) {
         constexpr int CB = decltype(cbc)::value;
         dim3 grid((a.N / 32 + CB - 1) / CB, splits, (a.rows + 255) / 256);
+        // Row blocks without a row cost no matrix instruction where they are an eighth of the launch or more; below that the branches
+        // cost more (4 layers of the 8B shape, left out: 260 / 400 / 800 (14B) tokens with 44 / 19 / 22 % of them 1864 / 1905 / 4311 ->
+        // 1677 / 1861 / 4154 us, 1100 / 1300 with 13 / 15 % 4181 / 5051 -> 4152 / 5014, 900 with 9 % 3419 -> 3435, 1200 (14B) with 5 %
+        // 5503 -> 5594, 1500 with 2 % 5170 -> 5298; a 4-bit step of 150 requests,
+        // whose vocabulary has three blocks of eight left out, 3288 -> 3228).
+        const int row_blocks = (a.rows + 31) / 32, launched = (a.rows + 255) / 256 * 8;
+        const bool ragged = (launched - row_blocks) * 8 >= launched;
         if (epilogue == EPI_SWIGLU) {
             if (splits != 1) return hipErrorInvalidValue;
-            hipLaunchKernelGGL((proj_wide_kernel<EPI_SWIGLU, CB>), grid, dim3(512), 0, st, a);
+            if (ragged) hipLaunchKernelGGL((proj_wide_kernel<EPI_SWIGLU, CB, true>), grid, dim3(512), 0, st, a);
+            else hipLaunchKernelGGL((proj_wide_kernel<EPI_SWIGLU, CB, false>), grid, dim3(512), 0, st, a);
             return hipGetLastError();
         }
         if (epilogue != EPI_STORE) return hipErrorInvalidValue;
-        hipLaunchKernelGGL((proj_wide_kernel<EPI_STORE, CB>), grid, dim3(512), 0, st, a);
+        if (ragged) hipLaunchKernelGGL((proj_wide_kernel<EPI_STORE, CB, true>), grid, dim3(512), 0, st, a);
+        else hipLaunchKernelGGL((proj_wide_kernel<EPI_STORE, CB, false>), grid, dim3(512), 0, st, a);
         return hipGetLastError();
     };
     switch (cb) {

@@ -235,3 +235,9 @@ def test_column_tiles_of_other_widths(H, heads, ffn):
     tiles of which the last holds eight rows; o and down take five."""
     shape = dataclasses.replace(wl.SMALL128, name="narrow", hidden=256, n_q_heads=heads[0], n_kv_heads=heads[1], ffn=ffn)
     test_prefill_blocks_equal_the_causal_forward(H, shape, 520, [])
+
+
+@pytest.mark.parametrize("rows", [160, 161, 193, 224, 225])
+def test_wide_vocabulary_projection_leaves_out_row_blocks(H, rows):
+    """Five to eight of the eight 32-row blocks of a tile hold rows: a wave with both of its blocks, with one, with none."""
+    test_wide_vocabulary_projection(H, rows)
