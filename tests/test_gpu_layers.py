@@ -3,6 +3,7 @@ each finishes and the largest taken, one row beyond it, lengths around chunk and
 column blocks than compute units, more layers than one launch takes, head norm, biases, both 4-bit layouts.  Against the oracle, and
 against a launch per operation (which SUN_PROFILE asks for)."""
 import dataclasses
+import threading
 
 import numpy as np
 import pytest
@@ -125,3 +126,35 @@ def test_under_capture_a_step_takes_a_launch_per_operation(H):
         torch.cuda.synchronize()
         assert torch.equal(case.logits, want)
         case.step()                       # an eager step between the replays
+
+
+def test_steps_on_two_streams_from_two_threads(H):
+    """Two such launches do not fit the chip together: they run one behind the other, each with counters in its own workspace."""
+    cases = [make_case(H, wl.SMALL128, EDGES[:8], seed=s) for s in (710, 720)]
+    pools = [c.pool_mem.clone() for c in cases]
+    want = []
+    for c in cases:
+        c.step()
+        torch.cuda.synchronize()
+        want.append(c.logits.clone())
+    got, streams = [[], []], [torch.cuda.Stream(), torch.cuda.Stream()]
+
+    def work(i):
+        with torch.cuda.stream(streams[i]):
+            for _ in range(10):
+                c = cases[i]
+                c.pool_mem.copy_(pools[i])
+                sun.sun_decode_step(c.pool, c.weights, c.tokens, c.tables, c.lens, c.ids, c.logits, c.next, c.ws, seq_lens_host=lens)
+                got[i].append(c.logits.clone())
+
+    lens = np.asarray(EDGES[:8], dtype=np.int32)
+    torch.cuda.synchronize()
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    torch.cuda.synchronize()
+    assert [len(g) for g in got] == [10, 10]
+    for w, g in zip(want, got):
+        assert all(torch.equal(w, x) for x in g)
