@@ -431,7 +431,7 @@ void proj_tall_kernel(ProjArgs a) {
 // 24 bytes per cycle here against 47.  Measured, 28 672 x 4096, both planes counted: 1024 rows 384 us on average in a prefill (368
 // the shortest) = 1.25 PFLOP/s, 2048 rows 729 (713) = 1.32 (four / eight launches of the 128 x 256 kernel: 505 / 1010 us; the
 // instructions alone, no loads: 322 / 591; the same code on zeros, which draw less power and leave the clock up: 294 / 583).
-// CB: 32-column strips of a workgroup, eight or, where that makes whole rounds, fewer (wide_pick).  RAGGED: row blocks without a row are
+// CB: 32-column strips of a workgroup, eight or, where that makes whole rounds, fewer (wide_pick_strips).  RAGGED: row blocks without a row are
 // left out of the products (launch_proj_wide).
 // Measured and left out: 128 x 256 tiles in this scheme (1024 rows 430 us; at 256 rows no faster than the kernel
 // above), four or five slots, a deeper ring for the weights than for the activations, streaming loads for the
@@ -954,32 +954,49 @@ static bool use_tall(const Mat& W, int rows) {
     return W.kind == MAT_BF16_PACKED && rows > 128 && !use_wide(W, rows) && (W.N / 32 + 7) / 8 <= 256;
 }
 
-// Column strips of a workgroup and split-K factor of a wide launch.  A round of 256 workgroups costs 8 us and a stage time for each
-// of its stages, a split the writing and reading of its slab.  With every unit busy the matrix cores' power bounds a stage: 1.7 us
-// at eight strips, in proportion for fewer; a workgroup alone takes 0.95 us however few its strips are (loads and barrier), and a
-// round that is not full lies between the two.  So a partial last round costs less than a whole one, but narrower tiles that make whole
-// rounds still win.  Measured in prefills, eight strips -> picked (us): gate/up of the 8B shape at 1024 / 1536 rows 407 / 591 -> 396 /
-// 574 (seven), 14B shape at 1024 rows 490 -> 476 (seven), q/k/v at 1024 rows 105 -> 89 (six), at 1536 rows 142 in three slabs
-// -> 139 in one (five); o and down at 1024 rows stay (61 / 192; six strips 79 / 220).  The figures give the measured times of 28
-// launches to within 10 %.
-struct WideShape {
-    int cb, splits;
-};
-static WideShape wide_pick(const Mat& W, int rows, int max_splits, int only_splits = 0) {
-    const int stages = W.K / 32, strips = W.N / 32, row_tiles = (rows + 255) / 256;
-    WideShape best{8, max(1, only_splits)};
+// Split-K factor of a wide launch: whole rounds of 256 workgroups of eight strips cost stages x 0.95 us (2048 cycles of matrix
+// instructions) plus about 8 us each, a split the writing and reading of its slab.  The factor sets the order of the sums, so
+// it does not follow the tile width below: chosen together with it, o at 1024 rows went from four slabs to two and with its norm from 91 to
+// 102 us, down at 768 / 1536 rows from 163 / 319 to 186 / 342 (8B shape), at 1024 rows from 251 to 268 (14B shape).
+static int wide_pick_splits(const Mat& W, int rows, int max_splits) {
+    const int stages = W.K / 32;
+    const long long tiles = (long long)((W.N / 32 + 7) / 8) * ((rows + 255) / 256);
+    int best = 1;
     double best_us = 0;
-    for (int cb = 8; cb >= 5; --cb)
-        for (int s = 1; s <= max(1, min(max_splits, stages / 8)); ++s) {
-            const int sps = (stages + s - 1) / s;
-            if (only_splits ? s != only_splits : (stages + sps - 1) / sps != s) continue;
-            const long long wgs = (long long)((strips + cb - 1) / cb) * row_tiles * s, rounds = (wgs + 255) / 256;
-            const double full = (double)wgs / (double)(rounds * 256), stage = 0.95 + (1.7 * cb / 8 - 0.95) * full;
-            const double us = (double)rounds * (sps * stage + 8.0) + (double)s * rows * W.N * 8e-6 / 5.0;
-            if (best_us == 0 || us < best_us) {
-                best_us = us;
-                best = WideShape{cb, s};
-            }
+    for (int s = 1; s <= max(1, min(max_splits, stages / 8)); ++s) {
+        const int sps = (stages + s - 1) / s;
+        if ((stages + sps - 1) / sps != s) continue;
+        const double us = (double)((tiles * s + 255) / 256) * (sps * 0.95 + 8.0) + (double)s * rows * W.N * 8e-6 / 5.0;
+        if (best_us == 0 || us < best_us) {
+            best_us = us;
+            best = s;
+        }
+    }
+    return best;
+}
+
+// Column strips of a workgroup, given the split.  A round of 256 workgroups costs 8 us and a stage time for each of its stages.  With
+// every unit busy the matrix cores' power bounds a stage: 1.7 us at eight strips, in proportion for fewer; a workgroup alone takes
+// 0.95 us however few its strips are (loads and barrier), and a round that is not full lies between the two.  So a partial last round
+// costs less than a whole one, but narrower tiles that make whole rounds still win.  Eight strips unless another number promises
+// more than a twentieth, which the model is off by itself.  Measured in prefills, eight strips -> picked (us): gate/up of the 8B shape
+// at 1024 / 1200 / 1792 rows 412 / 549 / 740 -> 404 / 481 / 706 (seven, six, five), q/k/v at 1024 / 1792 rows 105 / 175 -> 92 / 151 (six);
+// the launches beside them, eight strips on both sides, take 2 to 3 % longer (what a launch saves in time it draws in power).  All
+// kernels of two layers: 8B shape at 1024 / 1200 / 1792 rows 1987 / 2372 / 3239 -> 1945 / 2274 / 3156, 14B shape at 512 / 1024 rows
+// 1450 / 2393 -> 1423 / 2407.
+static int wide_pick_strips(const Mat& W, int rows, int splits) {
+    const int stages = W.K / 32, strips = W.N / 32, row_tiles = (rows + 255) / 256, sps = (stages + splits - 1) / splits;
+    const auto cost = [&](int cb) {
+        const long long wgs = (long long)((strips + cb - 1) / cb) * row_tiles * splits, rounds = (wgs + 255) / 256;
+        const double full = (double)wgs / (double)(rounds * 256), stage = 0.95 + (1.7 * cb / 8 - 0.95) * full;
+        return (double)rounds * (sps * stage + 8.0);
+    };
+    int best = 8;
+    double best_us = cost(8) * 0.95;
+    for (int cb = 7; cb >= 5; --cb)
+        if (const double us = cost(cb); us < best_us) {
+            best_us = us;
+            best = cb;
         }
     return best;
 }
@@ -996,7 +1013,7 @@ bool proj_fuses_swiglu(const Mat& gu, int rows) {
 }
 
 int proj_pick_splits(const Mat& W, int rows, int max_splits) {
-    if (use_wide(W, rows)) return wide_pick(W, rows, max_splits).splits;
+    if (use_wide(W, rows)) return wide_pick_splits(W, rows, max_splits);
     if (use_tall(W, rows)) return tall_pick_splits(W, rows, max_splits);
     return proj_pick(W, rows, max_splits).splits;
 }
@@ -1080,7 +1097,7 @@ hipError_t launch_proj(const ProjLaunch& p, hipStream_t st) {
         a.n_stages = stg;
         a.stages_per_split = per;
         const int real_s = (stg + per - 1) / per;
-        return launch_proj_wide(a, p.epilogue, wide_pick(W, p.rows, real_s, real_s).cb, real_s, st);
+        return launch_proj_wide(a, p.epilogue, wide_pick_strips(W, p.rows, real_s), real_s, st);
     }
     if (use_tall(W, p.rows)) {
         const int want = p.epilogue == EPI_SWIGLU ? 1 : max(1, p.splits);

@@ -229,12 +229,44 @@ def test_slots_past_the_prompt_may_hold_anything(H, first, rows):
     assert np.array_equal(got[0][0], got[1][0]) and np.array_equal(got[0][1], got[1][1])
 
 
-@pytest.mark.parametrize("heads,ffn", [((64, 32), 7040), ((56, 28), 8192)], ids=["qkv-7-gate-up-6", "qkv-6-gate-up-7"])
-def test_column_tiles_of_other_widths(H, heads, ffn):
-    """Widths for which q/k/v and gate/up take workgroups of six and of seven 32-column strips (the last workgroup ragged), three row
-    tiles of which the last holds eight rows; o and down take five."""
-    shape = dataclasses.replace(wl.SMALL128, name="narrow", hidden=256, n_q_heads=heads[0], n_kv_heads=heads[1], ffn=ffn)
+@pytest.mark.parametrize("hidden,heads,ffn", [(256, (64, 32), 7040), (256, (56, 28), 8192), (512, (72, 36), 16256), (512, (42, 42), 18816), (512, (52, 26), 13568)],
+                         ids=["qkv-8-gate-up-6", "qkv-6-gate-up-8", "qkv-7-gate-up-6", "qkv-6-gate-up-7", "qkv-5-gate-up-5"])
+def test_column_tiles_of_other_widths(H, hidden, heads, ffn):
+    """Widths for which q/k/v and gate/up take workgroups of five to eight 32-column strips (the last workgroup ragged), three row
+    tiles of which the last holds eight rows."""
+    shape = dataclasses.replace(wl.SMALL128, name="narrow", hidden=hidden, n_q_heads=heads[0], n_kv_heads=heads[1], ffn=ffn)
     test_prefill_blocks_equal_the_causal_forward(H, shape, 520, [])
+
+
+@pytest.mark.parametrize("rows,slabs", [(520, 3), (1024, 2), (1536, 3), (2048, 1)])
+def test_the_split_along_k_does_not_follow_the_tile_width(H, rows, slabs):
+    """How many slabs the sums of q/k/v (6144 x 4096) have, read from V: its weights are 2^30, then ones, then -2^30, and the inputs
+    ones, so that of each row's 4096 products those of the first slab are lost beside the 2^30 (64 is half of what it resolves there, a
+    matrix instruction adds 16) and those of the others stay.  The tiles are six or seven strips wide."""
+    shape = dataclasses.replace(wl.SHAPES["llama8b"], name="one_layer", n_layers=1, ffn=128, vocab=64)
+    cfg = sun.make_cfg(shape, "bf16")
+    w = wl.make_weights(shape, "bf16", H.DEV, 91)
+    w["embed"].fill_(1.0)
+    w["g1"][0].fill_(1.0)
+    w["wv"][0].fill_(1.0)
+    w["wv"][0][:, 0] = 2.0 ** 30
+    w["wv"][0][:, -1] = -(2.0 ** 30)
+    W = sun.sun_weights_create(cfg, w)
+    n_pages = (rows + 15) // 16
+    mem = torch.zeros(sun.sun_kv_pool_bytes(cfg, n_pages) // 2, dtype=torch.bfloat16, device=H.DEV)
+    pool = sun.sun_kv_pool_create(cfg, mem, 16, 1)
+    lay = pool.layout()
+    table = torch.arange(n_pages, dtype=torch.int32, device=H.DEV)
+    ws = torch.empty(sun.sun_prefill_workspace_bytes(cfg, rows, n_pages), dtype=torch.uint8, device=H.DEV)
+    logits, nxt = torch.empty(shape.vocab, device=H.DEV), torch.empty(1, dtype=torch.int32, device=H.DEV)
+    sun.sun_prefill(pool, W, torch.zeros(rows, dtype=torch.int32, device=H.DEV), table, 0, 0, logits, nxt, ws)
+    torch.cuda.synchronize()
+    v = mem.as_strided((n_pages, shape.n_kv_heads, shape.head_dim, 16), (lay.v_page, lay.v_head, lay.v_dim, lay.v_token), lay.v_off)
+    v = v.permute(0, 3, 1, 2).reshape(n_pages * 16, -1)[:rows].float()
+    stages = shape.hidden // 32
+    first = -(-stages // slabs) * 32
+    # the last slab and each sum with a slab behind the first round to a multiple of 64, V to 2^-9 of itself
+    assert float(v.min()) == float(v.max()) and abs(float(v[0, 0]) - (shape.hidden - first)) <= 32 * slabs + 8
 
 
 @pytest.mark.parametrize("rows", [160, 161, 193, 224, 225])
