@@ -178,7 +178,7 @@ hipError_t launch_step_begin(const sun_model_cfg& cfg, const void* embed, const 
 template <int D, int G>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_split_kernel(AttnArgs a) {
     __shared__ int list_cursor;
-    attn_split_items<D, G, false>(a, blockIdx.x, gridDim.x, &list_cursor, [] {});
+    attn_split_items<D, G, false>(a, blockIdx.x, gridDim.x, threadIdx.x & 63, &list_cursor, [] {});
 }
 
 // ---------------------------------------------------------------------------------

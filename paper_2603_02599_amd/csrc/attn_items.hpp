@@ -79,11 +79,10 @@ __device__ __forceinline__ void split_pair(float x0, float x1, uint32_t& hi, uin
 // before() (SHARED) is what to wait for before q and the newest entry of every request may be read; items without the newest
 // entry request their first K and V in front of it, except for wave 0's, which polls there.
 template <int D, int GT, bool SHARED, class Before>
-__device__ __forceinline__ void attn_split_items(const AttnArgs& a, int wg, int nwg, int* list_cursor, Before before) {
+__device__ __forceinline__ void attn_split_items(const AttnArgs& a, int wg, int nwg, int lane, int* list_cursor, Before before) {
     const int G = GT ? GT : a.Hq / a.Hkv;
     constexpr int NS = D / 32;  // dim slices of a QK MFMA
     constexpr int NB = D / 16;  // dim blocks of a PV MFMA
-    const int lane = threadIdx.x & 63;
     const int c16 = lane & 15, kq = lane >> 4;
     // One workgroup of 8 waves per compute unit.  Items are dealt to workgroups statically: full
     // chunks (all of one size) round-robin; the workgroups that got one full chunk fewer are

@@ -37,6 +37,7 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kWaves = 8;
+static_assert(kLayersRowsW4 <= kWaves && kLayersRows <= 2 * kWaves, "one row a wave with 4-bit weights, two otherwise");
 constexpr int kUnits = 256;         // work units a phase is cut into at most (one per compute unit)
 constexpr int kLayersPerLaunch = 48;
 constexpr int kBfRow = 512;         // bytes of 128 activations of one row: [32-wide step][plane][32] bf16
@@ -419,7 +420,7 @@ __device__ __forceinline__ void matrix_phase(const LayersArgs& a, const MatP& m,
         else __syncthreads();           // the unit before is done with LDS
         if (!wave) p.template prefetch<STREAM>(ring);
         unit_sums<W4, STREAM, CB>(p, ring, A, a.R, red);
-        if (a.R <= kWaves) unit_finish<W4, CB, NC, 1>(a, m, layer, u, red, flag, col, early, done);
+        if (W4 || a.R <= kWaves) unit_finish<W4, CB, NC, 1>(a, m, layer, u, red, flag, col, early, done);
         else unit_finish<W4, CB, NC, kLayersRows / kWaves>(a, m, layer, u, red, flag, col, early, done);
     }
 }
@@ -584,7 +585,9 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 
             at.kbase += l * a.rope.k_layer;
             at.vbase += l * a.rope.v_layer;
             at.q = a.q + (size_t)(l % a.ring) * a.q_step;
-            attn_split_items<128, 0, true>(at, blockIdx.x, gridDim.x, &cursor, wait);
+            // with 4-bit weights what depends on the lane does not fit beside the other phases' registers from layer to layer (741 -> 731 us
+            // at five requests; the bf16 kernel has the room and would lose 0.3 %)
+            attn_split_items<128, 0, true>(at, blockIdx.x, gridDim.x, W4 ? lane_here() : threadIdx.x & 63, &cursor, wait);
         }
         arrive();
         {

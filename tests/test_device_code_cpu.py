@@ -173,3 +173,12 @@ def projection_code(tmp_path_factory):
 @pytest.fixture(scope="module")
 def attention_code(tmp_path_factory):
     return assembly(os.path.join(CSRC, "attention.hip"), tmp_path_factory.mktemp("asm") / "attention.s")
+
+
+def test_the_kernel_of_all_layers_keeps_its_registers(tmp_path):
+    """It takes nearly the whole register file (one workgroup of eight waves a compute unit): what does not fit would go through
+    memory in every layer."""
+    kernels = {n: v for n, v in assembly(os.path.join(CSRC, "layers.hip"), tmp_path / "layers.s").items() if "layers_kernel" in n}
+    assert len(kernels) == 3
+    for name, code in kernels.items():
+        assert not any(s.startswith("scratch_") for s in code), name
