@@ -65,6 +65,9 @@ enum {
     SUN_SERVE_RESET = 4u /* sun_decode_serve only: before the first iteration make every row idle
                             and admit from the queue */
 };
+/* For tests, or'ed into the flags of a step, a run or a serve call: a wait inside the one launch of a small batch (see
+ * sun_decode_step) gives up after n polls, 0 <= n <= 65534, instead of after half a minute. */
+#define SUN_WAIT_POLLS(n) (((unsigned)(n) + 1u) << 16)
 
 /*
  * Decoder shape (pre-norm Llama-style block: RMSNorm, GQA attention with rotary
@@ -287,6 +290,9 @@ size_t sun_workspace_bytes(const sun_model_cfg* cfg, int max_batch, int max_page
  * layers in one cooperative launch, except under SUN_PROFILE and while the stream is captured, where every
  * operation is a launch of its own.  The two sum in different orders: results agree up to fp32
  * rounding and, where a new cache entry falls on the other side of it, bf16 rounding.
+ * That launch needs every compute unit: it starts as other work leaves them, and where some are held for half a minute it
+ * gives up.  The step then has no result: next_tokens_out is -1 and all logits are not-a-numbers.  Cache entries
+ * at the new positions are right or not written, nothing else has changed, and the call can be repeated.
  * Errors: SUN_ERR_NULL, SUN_ERR_SHAPE (batch < 1, or a pool / weights pair of
  * different shape), SUN_ERR_WORKSPACE; under SUN_VALIDATE also SUN_ERR_TOKEN,
  * SUN_ERR_SEQ_LEN, SUN_ERR_PAGE_RANGE, SUN_ERR_MODEL_ID.
@@ -322,7 +328,9 @@ int sun_qdecode_step(sun_kv_pool* pool, const sun_weights* weights, int batch,
  * token at the same position, over its own earlier entry there, and the tokens it produces are not a
  * continuation of its sequence; bit 0 (list empty) or bit 1 (table full) of *run_status is set and the
  * caller must discard that request's outputs from the step it was starved in (sun_decode_serve avoids
- * the situation by reserving pages at admission).  *run_status is cleared at the start of the run.
+ * the situation by reserving pages at admission).  A step without a result (see sun_decode_step) leaves every request as it
+ * is: its row of tokens_out is -1, bit 2 of *run_status is set, and the next step of the run is that step again, so a run
+ * that has met one ends that much earlier in its sequences.  *run_status is cleared at the start of the run.
  *
  *   token_ids   dev int32 [batch]             in: y_{t-1}; out: the last generated token
  *   page_tables dev int32 [batch, max_pages]  in/out
@@ -383,7 +391,8 @@ int sun_decode_run(sun_kv_pool* pool, const sun_weights* weights, int batch, int
  *     until pages come back.  A budget that would run past the table (max_pages * 16
  *     positions) is cut to fit and status bit 1 is set.
  * Status bit 0: step 3 found the ring empty (possible only if rows were placed by hand without
- * enough pages; the row then keeps its length, as in sun_decode_run).
+ * enough pages; the row then keeps its length, as in sun_decode_run).  Status bit 2: a step had no result (see
+ * sun_decode_step); its rows of tokens_out and req_out are -1, steps 1 to 3 are left out and the next iteration is that step again.
  */
 typedef struct sun_serve_state {
     int32_t* token_ids;

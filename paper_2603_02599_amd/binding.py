@@ -16,6 +16,13 @@ LIB_PATH = os.environ.get("SUN_LIB_PATH", os.path.join(_HERE, "libsun.so"))  # o
 
 SUN_F32, SUN_BF16 = 0, 1
 SUN_VALIDATE, SUN_PROFILE, SUN_SERVE_RESET = 1, 2, 4
+
+
+def SUN_WAIT_POLLS(n: int) -> int:
+    """Step flag for tests: a wait inside the launch of a small batch gives up after n polls."""
+    return (n + 1) << 16
+
+
 STATUS = {0: "SUN_OK", 1: "SUN_ERR_NULL", 2: "SUN_ERR_SHAPE", 3: "SUN_ERR_POOL_SIZE", 4: "SUN_ERR_WORKSPACE",
           5: "SUN_ERR_PAGE_RANGE", 6: "SUN_ERR_SEQ_LEN", 7: "SUN_ERR_MODEL_ID", 8: "SUN_ERR_HIP", 9: "SUN_ERR_TOKEN"}
 PROFILE_KINDS = ("attn_split", "attn_combine", "qkv_proj", "o_proj", "gate_up_proj", "down_proj", "lm_head", "other")

@@ -10,6 +10,7 @@
 #include <new>
 #include <vector>
 
+#include "grid.hpp"
 #include "kernels.hpp"
 
 namespace sun {
@@ -747,6 +748,9 @@ static hipError_t f32_norm_proj(const sun_model_cfg& c, const Mat& M, const Work
     return launch_proj_f32(M, ws.a32, batch, nullptr, 0.f, epilogue, out, st);
 }
 
+// polls of a wait inside the launch of all layers: the default, or what SUN_WAIT_POLLS asks for
+static unsigned wait_polls(unsigned flags) { return flags >> 16 ? (flags >> 16) - 1 : kSpinLimit; }
+
 // What is different about a step that is part of something larger.
 struct StepKind {
     bool prefill = false;       // a block of an fp32 prompt: rows attend to entries of one another
@@ -794,15 +798,16 @@ static int step_impl(sun_kv_pool* pool_, const sun_weights* weights_, bool want_
     // under SUN_PROFILE the attention is timed by its own launches
     const bool short_f32 = !bf && !prof && !kind.prefill && attn_short_f32(c, max_pages);
     const bool one_launch = bf && !prof && layers_usable(W, batch, scratch, st);
+    const uint32_t* lost = one_launch ? layers_lost(ws.plan) : nullptr;
 
     if (!kind.begun) {
         ProfScope p(prof, 7, st);
         SUN_HIP_CHECK(launch_step_begin(c, W.embed, token_ids, seq_lens, batch, ws.x, ws.table, ws.plan, page_tables, max_pages,
-                                        (int)pool.lay.n_pages, one_launch ? layers_zero(scratch, W) : LayersZero{}, st));
+                                        (int)pool.lay.n_pages, one_launch ? layers_zero(scratch, W, ws.plan) : LayersZero{}, st));
     }
     int down_parts = 0;
     if (one_launch)
-        SUN_HIP_CHECK(launch_layers(pool, W, batch, ws.x, ws.table, ws.plan, page_tables, max_pages, seq_lens, hint.total, hint.full, scratch, st));
+        SUN_HIP_CHECK(launch_layers(pool, W, batch, ws.x, ws.table, ws.plan, page_tables, max_pages, seq_lens, hint.total, hint.full, scratch, wait_polls(flags), st));
     for (int l = 0; l < c.n_layers && !one_launch; ++l) {
         const LayerW& L = W.layers[l];
         const float* attn_q = ws.q;
@@ -887,7 +892,7 @@ static int step_impl(sun_kv_pool* pool_, const sun_weights* weights_, bool want_
     if (!kind.with_head) return SUN_OK;  // a caller that only wants the cache entries (all but the last prefill block)
     if (bf) {
         ProfScope p(prof, 7, st);
-        SUN_HIP_CHECK(launch_residual_norm(c, ws.x, ws.part, down_parts, batch, W.gf, batch, nullptr, ws.hA, nullptr, st));
+        SUN_HIP_CHECK(launch_residual_norm(c, ws.x, ws.part, down_parts, batch, W.gf, batch, nullptr, ws.hA, nullptr, st, lost));
     }
     {
         ProfScope p(prof, 6, st);
@@ -900,7 +905,7 @@ static int step_impl(sun_kv_pool* pool_, const sun_weights* weights_, bool want_
     }
     if (kind.with_argmax) {
         ProfScope p(prof, 7, st);
-        SUN_HIP_CHECK(launch_argmax(logits, batch, c.vocab, ws.amax_val, ws.amax_idx, next_tokens_out, st));
+        SUN_HIP_CHECK(launch_argmax(logits, batch, c.vocab, ws.amax_val, ws.amax_idx, next_tokens_out, lost, st));
     }
     return SUN_OK;
 }
@@ -1080,7 +1085,7 @@ int sun_decode_serve(sun_kv_pool* pool_, const sun_weights* weights_, int slots,
                 s.w_tables, s.w_lens, s.w_model, s.w_budget, s.ring, s.counters, s.n_wait, s.ring_cap, s.idle_page,
                 s.eos_id, slots, max_pages};
     if (reset) SUN_HIP_CHECK(launch_serve(a, nullptr, nullptr, nullptr, true, false, st));
-    const unsigned step_flags = flags & SUN_PROFILE;
+    const unsigned step_flags = flags & (SUN_PROFILE | ~0xffffu);
     for (int i = 0; i < n_steps; ++i) {
         const bool last = i + 1 == n_steps;
         const int rc = step_impl(pool_, weights_, W.quant, slots, s.token_ids, s.page_tables, max_pages, s.seq_lens, nullptr,
@@ -1208,7 +1213,7 @@ static int prefill_block(KvPool& pool, const Weights& W, const Workspace& ws, in
         SUN_HIP_CHECK(launch_proj(ProjLaunch{&W.lm, ws.hA, nullptr, 1, EPI_STORE, 1, out, c.vocab, 1}, st));
     }
     ProfScope p(prof, 7, st);
-    if (next) SUN_HIP_CHECK(launch_argmax(out, 1, c.vocab, ws.amax_val, ws.amax_idx, next, st));
+    if (next) SUN_HIP_CHECK(launch_argmax(out, 1, c.vocab, ws.amax_val, ws.amax_idx, next, nullptr, st));
     return SUN_OK;
 }
 

@@ -157,7 +157,10 @@ hipError_t launch_attn_plan(const AttnPlan& plan, const int32_t* n_or_len, int l
 // workgroups 0 .. batch - 1 gather a row's embedding and its rotary table, the others make the attention plan.
 __global__ __launch_bounds__(256) void step_begin_kernel(EmbedRope e, PlanArgs a, LayersZero z) {
     if (blockIdx.x == gridDim.x - 1)
-        for (int i = threadIdx.x; i < z.n; i += 256) z.p[i] = 0;
+        for (int i = threadIdx.x; i <= z.n; i += 256) {
+            if (i < z.n) z.p[i] = 0;
+            else if (z.lost) *z.lost = 0;
+        }
     if ((int)blockIdx.x < a.batch) embed_rope_row(e, blockIdx.x);
     else attn_plan_block(a, blockIdx.x - a.batch, gridDim.x - a.batch);
 }

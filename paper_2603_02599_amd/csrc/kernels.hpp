@@ -58,10 +58,11 @@ size_t attn_max_chunks(int batch, int max_pages, int Hkv);
 hipError_t launch_attn_plan(const AttnPlan& plan, const int32_t* n_or_len, int len_plus, int batch,
                             const int32_t* page_tables, int max_pages, int n_pages, int Hkv, hipStream_t st);
 // First launch of a decode step: launch_embed_rope and launch_attn_plan (n_tokens = seq_lens + 1) together.
-// Counters of the launch that runs all layers start at zero.
+// Counters of the launch that runs all layers, and its word that says it was given up, start at zero.
 struct LayersZero {
     uint32_t* p;
     int n;
+    uint32_t* lost;
 };
 hipError_t launch_step_begin(const sun_model_cfg& cfg, const void* embed, const int32_t* tokens, const int32_t* seq_lens, int batch,
                              float* x, float* table, const AttnPlan& plan, const int32_t* page_tables, int max_pages,
@@ -99,12 +100,18 @@ struct LayersScratch {
     size_t bytes;
 };
 bool layers_usable(const Weights& W, int rows, const LayersScratch& scratch, hipStream_t st);
-LayersZero layers_zero(const LayersScratch& scratch, const Weights& W);
-// x: the embedding on entry, the residual stream behind the last layer on return.  Behind launch_step_begin with
+// A launch that was given up says so in a word of the plan's first array, behind the prefix sums of so few rows and within the 256 bytes
+// that the array's place is rounded up to; it outlives the step's other scratch.
+constexpr int kLostAt = 32;
+static_assert(kLayersRows + 1 <= kLostAt && kLostAt < 64, "a place of its own");
+inline uint32_t* layers_lost(const AttnPlan& plan) { return (uint32_t*)plan.chunk_off + kLostAt; }
+LayersZero layers_zero(const LayersScratch& scratch, const Weights& W, const AttnPlan& plan);
+// x: the embedding on entry, the residual stream behind the last layer on return, or nothing of use where the launch was given up (after
+// `polls` polls of one wait in vain); cache entries that it has appended by then are right.  Behind launch_step_begin with
 // layers_zero() of the same scratch.
 hipError_t launch_layers(const KvPool& pool, const Weights& W, int rows, float* x, const float* table, const AttnPlan& plan,
                          const int32_t* page_tables, int max_pages, const int32_t* seq_lens, int total_chunks_hint, int full_chunks_hint,
-                         const LayersScratch& scratch, hipStream_t st);
+                         const LayersScratch& scratch, unsigned polls, hipStream_t st);
 
 // Workgroups of a kernel (one per compute unit, at most `most`) that a cooperative launch on the device keeps resident; 0: none.
 int resident_grid(const void* kernel, int threads, int most, int dev);
@@ -117,14 +124,16 @@ hipError_t launch_embed_rope(const sun_model_cfg& cfg, const void* embed, const 
                              int first_pos, int rows, float* x, float* table, hipStream_t st);
 // x[b] += sum_s partial[s][b] (s ascending; nparts may be 0); then h = rmsnorm(x; g).
 // h_f32 (fp32 gains): row-major.  Else h_tiled (bf16 gains): two-plane tiled bf16; with qscale given the fixed-point tile of a 4-bit projection instead, and qscale
-// receives its (scale, integer sum) pairs.
+// receives its (scale, integer sum) pairs.  lost (may be NULL): where *lost is not 0, h is not-a-numbers.
 hipError_t launch_residual_norm(const sun_model_cfg& cfg, float* x, const float* partial, int nparts, int ld_rows,
-                                const void* gain, int batch, float* h_f32, void* h_tiled, float* qscale, hipStream_t st);
+                                const void* gain, int batch, float* h_f32, void* h_tiled, float* qscale, hipStream_t st,
+                                const uint32_t* lost = nullptr);
 // k_src, v_src: bf16 [n_layers][n_tokens][Hkv][d]; token t lands at position first_pos + t of the request whose
 // page-table row is given.
 hipError_t launch_kv_ingest(const KvPool& pool, const void* k_src, const void* v_src, int n_tokens, int first_pos,
                             const int32_t* page_table, hipStream_t st);
-// Between two steps of a run: token feedback, length + 1, page allocation in request order.
+// Between two steps of a run: token feedback, length + 1, page allocation in request order.  A request without a token (next < 0)
+// stays as it is, status bit 2.
 hipError_t launch_advance(const int32_t* next, int batch, int max_pages, const int32_t* free_pages, int n_free,
                           int32_t* token_ids, int32_t* page_tables, int32_t* seq_lens, int32_t* free_head,
                           int32_t* status, bool clear_status, hipStream_t st);
@@ -163,9 +172,9 @@ hipError_t launch_hbm_read_probe(const void* src, long long n_blocks, int block_
                                  bool stream, uint32_t* sink, hipStream_t st);
 constexpr int kArgmaxParts = 16;    // slices of a logits row searched by separate workgroups
 constexpr int kArgmaxOne = 4096;    // a row of at most this many logits is searched by one
-// part_val / part_idx: scratch [batch][kArgmaxParts]
+// part_val / part_idx: scratch [batch][kArgmaxParts].  lost (may be NULL): where *lost is not 0 there are no tokens, next = -1.
 hipError_t launch_argmax(const float* logits, int batch, int vocab, float* part_val, int32_t* part_idx, int32_t* next,
-                         hipStream_t st);
+                         const uint32_t* lost, hipStream_t st);
 // fp32 [rows, K] -> two-plane tiled bf16, or fixed-point tile + qscale
 hipError_t launch_tile_rows(const float* x, int rows, int K, void* tiled, float* qscale, hipStream_t st);
 // out[b][n] = sum_s partial[s][b][n]

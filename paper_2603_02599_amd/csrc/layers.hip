@@ -72,7 +72,8 @@ struct LayersArgs {
     float* x;
     float *ssq1, *ssq2;             // [hidden / 128][kLayersRows] sums of squares of the residual stream
     float* slab;
-    uint32_t* counters;
+    alignas(32) uint32_t *counters, *lost;   // what a wait reads, side by side
+    uint32_t polls;
     char *t1, *ta, *t2, *tu;        // activation tiles of layer 0 and their steps; `ring` layers have their own
     float* q;
     size_t h_step, a_step, u_step, q_step;
@@ -161,6 +162,12 @@ __device__ __forceinline__ float row_squares(const LayersArgs& a, const float* s
 __device__ __forceinline__ float row_rinv(const LayersArgs& a, float squares) {
     return 1.0f / sqrtf(wave_sum(squares) / (float)a.H + a.eps);
 }
+
+struct Shared {
+    int cursor;                     // of attention's item list
+    int last;                       // this workgroup was the last of a column block to arrive
+    int given_up;                   // it has stopped waiting for the others (grid_wait)
+};
 
 // ---------------- matrix products ----------------
 // A unit: the products of up to 16 rows with a block of CB columns over a part of k.  Each wave takes some columns and a share of
@@ -327,9 +334,9 @@ __device__ __forceinline__ void unit_sums(const Part<W4, CB>& p, Ring<W4>& ring,
 }
 
 // What happens to a unit's sums, NR rows a wave.  With a split along k the workgroup that is the last of a block to arrive adds the
-// slabs up, in their order.
+// slabs up, in their order.  False where the wait in front of the phase was given up.
 template <bool W4, int CB, int NC, int NR, class Col, class Early, class Done>
-__device__ __forceinline__ void unit_finish(const LayersArgs& a, const MatP& m, int layer, int u, const float* red, int* flag, Col col, Early early,
+__device__ __forceinline__ bool unit_finish(const LayersArgs& a, const MatP& m, int layer, int u, const float* red, Shared& sh, Col col, Early early,
                                             Done done) {
     constexpr int KW = Part<W4, CB>::KW, LDR = CB + 4;
     const int lane = lane_here(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), R = a.R;
@@ -345,6 +352,7 @@ __device__ __forceinline__ void unit_finish(const LayersArgs& a, const MatP& m, 
         for (int i = 0; i < NR; ++i) in[i] = early(blk, row[i]);
     }
     __syncthreads();
+    const int gone = lds_word(&sh.given_up);
     if (mine) {
 #pragma unroll
         for (int i = 0; i < NR; ++i)
@@ -356,6 +364,7 @@ __device__ __forceinline__ void unit_finish(const LayersArgs& a, const MatP& m, 
                 v[i][c] = t;
             }
     }
+    if (__builtin_amdgcn_readfirstlane(gone)) return false;   // before the first store: others may still read what lies there
     if (m.S > 1) {
         float* sl = a.slab + (size_t)blk * R * CB;
         const size_t step = (size_t)m.nblk * R * CB;
@@ -371,11 +380,11 @@ __device__ __forceinline__ void unit_finish(const LayersArgs& a, const MatP& m, 
         __syncthreads();
         if (threadIdx.x == 0) {
             const uint32_t before_me = __hip_atomic_fetch_add(m.arrived + blk, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            *flag = before_me + 1 == (uint32_t)m.S * (layer + 1);
+            sh.last = before_me + 1 == (uint32_t)m.S * (layer + 1);
         }
         __syncthreads();
         asm volatile("" ::: "memory");
-        if (!*(volatile int*)flag || !mine) return;
+        if (!lds_word(&sh.last) || !mine) return true;
 #pragma unroll
         for (int i = 0; i < NR; ++i)
 #pragma unroll
@@ -403,15 +412,19 @@ __device__ __forceinline__ void unit_finish(const LayersArgs& a, const MatP& m, 
         for (int i = 0; i < NR; ++i)
             if (wave + i * kWaves < R) done(blk, row[i], in[i], v[i]);
     }
+    return true;
 }
 
-// A phase: all units of one matrix.  wait() is the barrier in front of it, col(lane, i) names the NC columns of the block that a lane
-// finishes, early(blk, row) loads what done(blk, row, early's result, sums) wants beside the sums.
+// A phase: all units of one matrix, false where the launch is to be left.  wait() is the barrier in front of it, col(lane, i) names the NC
+// columns of the block that a lane finishes, early(blk, row) loads what done(blk, row, early's result, sums) wants beside the sums.
 template <bool W4, bool STREAM, int CB, int NC, class Wait, class Col, class Early, class Done>
-__device__ __forceinline__ void matrix_phase(const LayersArgs& a, const MatP& m, int layer, const char* A, float* red, int* flag, Wait wait, Col col,
+__device__ __forceinline__ bool matrix_phase(const LayersArgs& a, const MatP& m, int layer, const char* A, float* red, Shared& sh, Wait wait, Col col,
                                              Early early, Done done) {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), units = m.nblk * m.S;
-    if ((int)blockIdx.x >= units) wait();
+    if ((int)blockIdx.x >= units) {
+        wait();
+        return !__builtin_amdgcn_readfirstlane(lds_word(&sh.given_up));
+    }
     for (int u = blockIdx.x; u < units; u += gridDim.x) {
         const Part<W4, CB> p(m, layer, u, a.s_only);
         Ring<W4> ring;
@@ -420,9 +433,12 @@ __device__ __forceinline__ void matrix_phase(const LayersArgs& a, const MatP& m,
         else __syncthreads();           // the unit before is done with LDS
         if (!wave) p.template prefetch<STREAM>(ring);
         unit_sums<W4, STREAM, CB>(p, ring, A, a.R, red);
-        if (W4 || a.R <= kWaves) unit_finish<W4, CB, NC, 1>(a, m, layer, u, red, flag, col, early, done);
-        else unit_finish<W4, CB, NC, kLayersRows / kWaves>(a, m, layer, u, red, flag, col, early, done);
+        bool ok;
+        if (W4 || a.R <= kWaves) ok = unit_finish<W4, CB, NC, 1>(a, m, layer, u, red, sh, col, early, done);
+        else ok = unit_finish<W4, CB, NC, kLayersRows / kWaves>(a, m, layer, u, red, sh, col, early, done);
+        if (!ok) return false;
     }
+    return true;
 }
 
 // ---------------- the other phases ----------------
@@ -539,16 +555,20 @@ __device__ __forceinline__ const LayersArgs& args_here() { return kernel_args<La
 template <bool W4, bool STREAM>
 __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void layers_kernel(LayersArgs) {
     __shared__ float red[kWaves * 16 * 132];
-    __shared__ int cursor, flag, dead;
+    __shared__ Shared sh;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    if (threadIdx.x == 0) dead = 0;
+    if (threadIdx.x == 0) sh.given_up = 0;
     __syncthreads();
     uint32_t times;
     const auto arrive = [&]() {
-        grid_arrive(args_here().counters);
+        grid_arrive(args_here().counters, &sh.given_up);
         ++times;
     };
-    const auto wait = [&]() { grid_wait(args_here().counters, times, &dead); };
+    const auto wait_for = [&](bool fresh) {
+        const LayersArgs& a = args_here();
+        grid_wait(a.counters, a.lost, times, a.polls, &sh.given_up, fresh);
+    };
+    const auto wait = [&]() { wait_for(false); };
     int l, l1;
     {
         const LayersArgs& a = args_here();
@@ -569,14 +589,15 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 
         {   // q/k/v: a block is one head
             const LayersArgs& a = args_here();
             const bool again = l >= a.ring && l % a.ring == 0;   // the tiles of the last `ring` layers are written a second time
-            const auto wait_fresh = [&]() { grid_wait(args_here().counters, times, &dead, again); };
-            matrix_phase<W4, STREAM, 128, 2>(a, a.qkv, l, a.t1 + (size_t)(l % a.ring) * a.h_step, red, &flag, wait_fresh, [](int lane, int c) { return lane + 64 * c; },
+            const auto wait_fresh = [&]() { wait_for(again); };
+            if (!matrix_phase<W4, STREAM, 128, 2>(a, a.qkv, l, a.t1 + (size_t)(l % a.ring) * a.h_step, red, sh, wait_fresh, [](int lane, int c) { return lane + 64 * c; },
                                              [&](int, int row) { return rope_in(args_here(), row); },
                                              [&](int blk, int row, const RopeIn& in, const float (&v)[2]) {
                                                  const LayersArgs& b = args_here();
                                                  const float ri = row_rinv(b, in.squares);
                                                  rope_row(b, l, blk, row, in, v[0] * ri, v[1] * ri);
-                                             });
+                                             }))
+                break;
         }
         arrive();
         {
@@ -587,7 +608,7 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 
             at.q = a.q + (size_t)(l % a.ring) * a.q_step;
             // with 4-bit weights what depends on the lane does not fit beside the other phases' registers from layer to layer (741 -> 731 us
             // at five requests; the bf16 kernel has the room and would lose 0.3 %)
-            attn_split_items<128, 0, true>(at, blockIdx.x, gridDim.x, W4 ? lane_here() : threadIdx.x & 63, &cursor, wait);
+            attn_split_items<128, 0, true>(at, blockIdx.x, gridDim.x, W4 ? lane_here() : threadIdx.x & 63, &sh.cursor, wait);
         }
         arrive();
         {
@@ -607,7 +628,7 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 
         arrive();
         {
             const LayersArgs& a = args_here();
-            matrix_phase<W4, STREAM, 128, 2>(a, a.o, l, a.ta + (size_t)(l % a.ring) * a.a_step, red, &flag, wait, pair,
+            if (!matrix_phase<W4, STREAM, 128, 2>(a, a.o, l, a.ta + (size_t)(l % a.ring) * a.a_step, red, sh, wait, pair,
                                              [&](int blk, int row) {
                                                  const LayersArgs& b = args_here();
                                                  return residual_in(b, blk, row, b.lp[l - b.l0].g2);
@@ -615,13 +636,14 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 
                                              [&](int blk, int row, const ResidualIn& in, const float (&v)[2]) {
                                                  const LayersArgs& b = args_here();
                                                  residual_row<W4>(b, blk, row, in.x, in.gains, true, v[0], v[1], b.ssq2, true, b.t2 + (size_t)(l % b.ring) * b.h_step);
-                                             });
+                                             }))
+                break;
         }
         arrive();
         {
             const LayersArgs& a = args_here();
             if constexpr (W4) {   // a block is a group of the down projection: 128 gate and 128 up columns, 16 and 16 in turn
-                matrix_phase<W4, STREAM, kGuBlock, 4>(a, a.gu, l, a.t2 + (size_t)(l % a.ring) * a.h_step, red, &flag, wait,
+                if (!matrix_phase<W4, STREAM, kGuBlock, 4>(a, a.gu, l, a.t2 + (size_t)(l % a.ring) * a.h_step, red, sh, wait,
                                                    [](int lane, int c) { return (lane >> 3) * 32 + (2 * lane & 15) + (c >> 1) * 16 + (c & 1); },
                                                    [&](int, int row) {
                                                        const LayersArgs& b = args_here();
@@ -632,9 +654,10 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 
                                                        const float ri = row_rinv(b, squares), g0 = v[0] * ri, g1 = v[1] * ri;
                                                        store_tile128<true>(b.tu + (size_t)(l % b.ring) * b.u_step, b.R, blk, row, g0 / (1.f + __expf(-g0)) * (v[2] * ri),
                                                                            g1 / (1.f + __expf(-g1)) * (v[3] * ri));
-                                                   });
+                                                   }))
+                    break;
             } else {              // 64 gate and 64 up columns
-                matrix_phase<W4, STREAM, kGuBlock, 2>(a, a.gu, l, a.t2 + (size_t)(l % a.ring) * a.h_step, red, &flag, wait,
+                if (!matrix_phase<W4, STREAM, kGuBlock, 2>(a, a.gu, l, a.t2 + (size_t)(l % a.ring) * a.h_step, red, sh, wait,
                                                     [](int lane, int c) { return (lane >> 4) * 32 + (lane & 15) + c * 16; },
                                                     [&](int, int row) {
                                                         const LayersArgs& b = args_here();
@@ -644,13 +667,14 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 
                                                         const LayersArgs& b = args_here();
                                                         const float ri = row_rinv(b, squares), g = v[0] * ri;
                                                         store_tile64(b.tu + (size_t)(l % b.ring) * b.u_step, b.R, blk >> 1, blk & 1, row, g / (1.f + __expf(-g)) * (v[1] * ri));
-                                                    });
+                                                    }))
+                    break;
             }
         }
         arrive();
         {
             const LayersArgs& a = args_here();
-            matrix_phase<W4, STREAM, 128, 2>(a, a.down, l, a.tu + (size_t)(l % a.ring) * a.u_step, red, &flag, wait, pair,
+            if (!matrix_phase<W4, STREAM, 128, 2>(a, a.down, l, a.tu + (size_t)(l % a.ring) * a.u_step, red, sh, wait, pair,
                                              [&](int blk, int row) {
                                                  const LayersArgs& b = args_here();
                                                  return residual_in(b, blk, row, l + 1 == b.n_layers ? nullptr : l + 1 < b.l1 ? b.lp[l + 1 - b.l0].g1 : b.g1_next);
@@ -658,14 +682,15 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 
                                              [&](int blk, int row, const ResidualIn& in, const float (&v)[2]) {
                                                  const LayersArgs& b = args_here();
                                                  residual_row<W4>(b, blk, row, in.x, in.gains, true, v[0], v[1], b.ssq1, l + 1 < b.n_layers, b.t1 + (size_t)((l + 1) % b.ring) * b.h_step);
-                                             });
+                                             }))
+                break;
         }
         arrive();
     }
-    if (dead) {   // some workgroup never came: no result rather than a wrong one
-        const LayersArgs& a = args_here();
-        for (int i = threadIdx.x; i < a.R * a.H; i += kWaves * 64) st_agent(a.x + i, NAN);
-    }
+    // Where a wait was given up the workgroup has left in the phase behind it, or, from attention's and the merge's, in the o projection, and
+    // nobody passes the wait behind that one.  So all that it can have spoilt are partials and tiles of its own items, which at
+    // most the merge and the o projection of this layer read: never a cache entry, which comes out of q/k/v.  x is left as
+    // it is, others may still read it; the next launch makes not-a-numbers of it.
 }
 
 // ---------------- host side ----------------
@@ -761,11 +786,13 @@ bool layers_usable(const Weights& W, int rows, const LayersScratch& scratch, hip
     return layers_grid(layers_fn(W.quant, W.layers[0].qkv.stream)) > 0;
 }
 
-LayersZero layers_zero(const LayersScratch& scratch, const Weights& W) { return LayersZero{(uint32_t*)scratch.p, (int)n_counters(W.cfg)}; }
+LayersZero layers_zero(const LayersScratch& scratch, const Weights& W, const AttnPlan& plan) {
+    return LayersZero{(uint32_t*)scratch.p, (int)n_counters(W.cfg), layers_lost(plan)};
+}
 
 hipError_t launch_layers(const KvPool& pool, const Weights& W, int rows, float* x, const float* table, const AttnPlan& plan,
                          const int32_t* page_tables, int max_pages, const int32_t* seq_lens, int total_chunks_hint, int full_chunks_hint,
-                         const LayersScratch& scratch, hipStream_t st) {
+                         const LayersScratch& scratch, unsigned polls, hipStream_t st) {
     const sun_model_cfg& c = W.cfg;
     const sun_kv_layout& P = pool.lay;
     const LayersLayout L = layers_layout(c, rows, W.quant, scratch.bytes);
@@ -803,6 +830,8 @@ hipError_t launch_layers(const KvPool& pool, const Weights& W, int rows, float* 
     a.ssq2 = (float*)(base + L.ssq2);
     a.slab = (float*)(base + L.slab);
     a.counters = (uint32_t*)base;
+    a.lost = layers_lost(plan);
+    a.polls = polls;
     a.ring = L.ring;
     a.t1 = base + L.t1;
     a.ta = base + L.ta;

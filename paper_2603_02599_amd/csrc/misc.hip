@@ -39,6 +39,7 @@ struct NormArgs {
     float* h_f32;    // F32 only: row-major
     uint16_t* h_tiled;
     float2* qscale;  // not NULL: h_tiled is the fixed-point tile of a 4-bit projection, and this its scales and sums
+    const uint32_t* lost;
     int nparts, ld_rows, H, mb;
     float eps;
 };
@@ -49,6 +50,7 @@ template <bool F32>
 __global__ __launch_bounds__(1024) void residual_norm_kernel(NormArgs a) {
     __shared__ float red[16];
     const int b = blockIdx.x, tid = threadIdx.x, H = a.H, nunits = H / 8, nthreads = blockDim.x;
+    const uint32_t lost = a.lost ? *a.lost : 0u;
     float* xr = a.x + (size_t)b * H;
     float v[2][8];
     float ss = 0.f;
@@ -92,7 +94,7 @@ __global__ __launch_bounds__(1024) void residual_norm_kernel(NormArgs a) {
     __syncthreads();
     float tot = 0.f;
     for (int w = 0; w < nthreads / 64; ++w) tot += red[w];
-    const float rinv = 1.0f / sqrtf(tot / (float)H + a.eps);
+    const float rinv = lost ? NAN : 1.0f / sqrtf(tot / (float)H + a.eps);
 #pragma unroll
     for (int it = 0; it < 2; ++it) {
         const int u = tid + it * nthreads;
@@ -132,7 +134,7 @@ __global__ __launch_bounds__(1024) void residual_norm_kernel(NormArgs a) {
 }
 
 hipError_t launch_residual_norm(const sun_model_cfg& cfg, float* x, const float* partial, int nparts, int ld_rows,
-                                const void* gain, int batch, float* h_f32, void* h_tiled, float* qscale, hipStream_t st) {
+                                const void* gain, int batch, float* h_f32, void* h_tiled, float* qscale, hipStream_t st, const uint32_t* lost) {
     NormArgs a{};
     a.x = x;
     a.partial = partial;
@@ -140,6 +142,7 @@ hipError_t launch_residual_norm(const sun_model_cfg& cfg, float* x, const float*
     a.h_f32 = h_f32;
     a.h_tiled = (uint16_t*)h_tiled;
     a.qscale = (float2*)qscale;
+    a.lost = lost;
     a.nparts = nparts;
     a.ld_rows = ld_rows;
     a.H = cfg.hidden;
@@ -381,12 +384,12 @@ __device__ __forceinline__ Best block_best(const float* row, int j0, int j1, boo
 
 __global__ __launch_bounds__(256) void argmax_part_kernel(const float* __restrict__ logits, int V, int per, int vec,
                                                           float* __restrict__ pval, int32_t* __restrict__ pidx,
-                                                          int32_t* __restrict__ next) {
+                                                          int32_t* __restrict__ next, const uint32_t* __restrict__ lost) {
     const int b = blockIdx.y, part = blockIdx.x;
     const Best r = block_best(logits + (size_t)b * V, min(V, part * per), min(V, (part + 1) * per), vec != 0);
     if (threadIdx.x != 0) return;
     if (next) {
-        next[b] = r.i == 0x7fffffff ? 0 : r.i;
+        next[b] = lost && *lost ? -1 : r.i == 0x7fffffff ? 0 : r.i;
     } else {
         pval[(size_t)b * kArgmaxParts + part] = r.v;
         pidx[(size_t)b * kArgmaxParts + part] = r.i;
@@ -394,24 +397,24 @@ __global__ __launch_bounds__(256) void argmax_part_kernel(const float* __restric
 }
 
 __global__ __launch_bounds__(256) void argmax_pick_kernel(const float* __restrict__ pval, const int32_t* __restrict__ pidx,
-                                                          int batch, int32_t* __restrict__ next) {
+                                                          int batch, int32_t* __restrict__ next, const uint32_t* __restrict__ lost) {
     static_assert(kArgmaxParts <= 64, "a lane per slice");
     const int b = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
     if (b >= batch) return;
     Best r{-INFINITY, 0x7fffffff};
     if (lane < kArgmaxParts) r = Best{pval[(size_t)b * kArgmaxParts + lane], pidx[(size_t)b * kArgmaxParts + lane]};
     r = wave_best(r);
-    if (lane == 0) next[b] = r.i == 0x7fffffff ? 0 : r.i;
+    if (lane == 0) next[b] = lost && *lost ? -1 : r.i == 0x7fffffff ? 0 : r.i;
 }
 
 hipError_t launch_argmax(const float* logits, int batch, int vocab, float* part_val, int32_t* part_idx, int32_t* next,
-                         hipStream_t st) {
+                         const uint32_t* lost, hipStream_t st) {
     const bool one = vocab <= kArgmaxOne;
     const int per = one ? vocab : ((vocab + kArgmaxParts - 1) / kArgmaxParts + 3) / 4 * 4;
     const int vec = (uintptr_t)logits % 16 == 0 && vocab % 4 == 0;
     hipLaunchKernelGGL(argmax_part_kernel, dim3(one ? 1 : kArgmaxParts, batch), dim3(256), 0, st, logits, vocab, per, vec, part_val,
-                       part_idx, one ? next : nullptr);
-    if (!one) hipLaunchKernelGGL(argmax_pick_kernel, dim3((batch + 3) / 4), dim3(256), 0, st, part_val, part_idx, batch, next);
+                       part_idx, one ? next : nullptr, lost);
+    if (!one) hipLaunchKernelGGL(argmax_pick_kernel, dim3((batch + 3) / 4), dim3(256), 0, st, part_val, part_idx, batch, next, lost);
     return hipGetLastError();
 }
 
@@ -547,7 +550,7 @@ hipError_t launch_prefill_rows(const int32_t* page_table, int max_pages, int fir
 // position opens a page its table does not have yet, it takes the next unused entry of the free
 // list; requests are served in index order (an exclusive scan over the requests that need a page).
 // A request that finds the list empty, or whose table is full, keeps its length and re-decodes the
-// same position; status bit 0 / bit 1 records that.
+// same position; status bit 0 / bit 1 records that.  A request that got no token (next < 0) stays as it is, bit 2.
 __global__ __launch_bounds__(1024) void advance_kernel(const int32_t* __restrict__ next, int batch, int max_pages,
                                                        const int32_t* __restrict__ free_pages, int n_free,
                                                        int32_t* __restrict__ token_ids, int32_t* __restrict__ page_tables,
@@ -557,8 +560,9 @@ __global__ __launch_bounds__(1024) void advance_kernel(const int32_t* __restrict
     const int t = threadIdx.x;
     if (clear_status && t == 0) *status = 0;  // ordered before the atomicOr below by the barriers in between
     int new_len = 0, slot_page = 0, wants = 0, full = 0;
-    if (t < batch) {
-        token_ids[t] = next[t];
+    const int token = t < batch ? next[t] : -1;
+    if (token >= 0) {
+        token_ids[t] = token;
         new_len = seq_lens[t] + 1;
         slot_page = new_len / kPageTokens;
         full = slot_page >= max_pages;
@@ -576,7 +580,9 @@ __global__ __launch_bounds__(1024) void advance_kernel(const int32_t* __restrict
     const int rank = scan[t] - wants;  // requests before this one that take a page
     int flags = 0;
     if (t < batch) {
-        if (full) {
+        if (token < 0) {
+            flags = 4;
+        } else if (full) {
             flags = 2;
         } else if (wants && head + rank >= n_free) {
             flags = 1;
@@ -753,12 +759,14 @@ __global__ __launch_bounds__(kServeThreads) void serve_kernel(ServeArgs a, const
     bool clear = row && do_reset;  // rows to be written as idle
     if (do_advance) {
         const int tok = row ? next[t] : 0;
+        const bool lost = tok < 0;   // a step without a result: the rows stay as they are
         if (row) {
             tokens_out[t] = occ ? tok : -1;
-            req_out[t] = req;
+            req_out[t] = lost ? -1 : req;
         }
+        if (lost) status |= 4;
         bool fin = false;
-        if (occ) {
+        if (occ && !lost) {
             left -= 1;
             generated = 1;
             fin = left == 0 || tok == a.eos_id;
@@ -788,7 +796,7 @@ __global__ __launch_bounds__(kServeThreads) void serve_kernel(ServeArgs a, const
         tail += give_total;
         __syncthreads();  // the ring entries written above may be taken below
         // advance the others
-        const bool cont = occ && !fin;
+        const bool cont = occ && !fin && !lost;
         const int new_len = len + 1, col = new_len / kPageTokens;
         const int wants = cont && col < a.max_pages && new_len % kPageTokens == 0 && tab[col] < 0;
         int want_total;

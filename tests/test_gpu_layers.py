@@ -27,10 +27,11 @@ def H():
     return gpu_harness
 
 
-def make_case(H, shape, lens, quant=None, seed=700):
+def make_case(H, shape, lens, quant=None, seed=700, spare=0):
     work = wl.make_workload("cfg1", shape=shape, dtype="bf16", batch=len(lens), seed=seed + len(lens))
     work.seq_lens = np.asarray(lens, dtype=np.int32)
     work.page_tables, work.n_pages = wl.deal_page_tables(work.seq_lens, np.random.default_rng(seed))
+    work.n_pages += spare
     return H.GpuCase(work, quant_mode=quant)
 
 
@@ -158,3 +159,92 @@ def test_steps_on_two_streams_from_two_threads(H):
     assert [len(g) for g in got] == [10, 10]
     for w, g in zip(want, got):
         assert all(torch.equal(w, x) for x in g)
+
+
+def bits(t):
+    return t.clone().view(torch.int16)
+
+
+@pytest.mark.parametrize("shape,quant", [(wl.SMALL128, None), (wl.SMALL128, "asym"), (DEEP, None)], ids=["small", "small-w4", "two-launches"])
+def test_a_wait_that_gives_up_is_reported(H, shape, quant):
+    """The wait made to give up after few polls, which some workgroups then do and some do not: either the step is the usual one, or it has no
+    result (next -1, logits not-a-numbers) and every cache entry is the old one or the right one; the next step on the same
+    workspace is the usual one again."""
+    case = make_case(H, shape, EDGES[2:8], quant)
+    pool0 = case.pool_mem.clone()
+    case.step()
+    torch.cuda.synchronize()
+    logits, nxt, pool = case.logits.clone(), case.next.clone(), bits(case.pool_mem)
+    for polls in (0, 1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 20, 24, 32, 48, 64, 0):
+        case.pool_mem.copy_(pool0)
+        case.logits.fill_(7.0)
+        case.next.fill_(-7)
+        case.step(flags=sun.SUN_WAIT_POLLS(polls))
+        torch.cuda.synchronize()
+        lost = bool((case.next == -1).all())
+        assert lost or torch.equal(case.next, nxt)
+        assert lost or polls > 0
+        assert bool(torch.isnan(case.logits).all()) if lost else torch.equal(case.logits, logits)
+        after = bits(case.pool_mem)
+        assert bool(((after == pool) | (after == bits(pool0))).all())
+        case.pool_mem.copy_(pool0)
+        case.step()
+        torch.cuda.synchronize()
+        assert torch.equal(case.logits, logits) and torch.equal(case.next, nxt) and torch.equal(bits(case.pool_mem), pool)
+
+
+@pytest.mark.parametrize("polls", [0, 4, 20])
+def test_a_run_goes_on_behind_a_step_without_a_result(H, polls):
+    lens0, steps = [3, 15, 60, 100], 6
+    case = make_case(H, wl.SMALL128, lens0, seed=730, spare=6)
+    pool0, got = case.pool_mem.clone(), []
+    for flags in (0, sun.SUN_WAIT_POLLS(polls)):
+        case.pool_mem.copy_(pool0)
+        tok, tab, ln = case.tokens.clone(), torch.full((4, 12), -1, dtype=torch.int32, device=H.DEV), case.lens.clone()
+        tab[:, :case.tables.shape[1]] = case.tables
+        free = torch.arange(case.work.n_pages - 6, case.work.n_pages, dtype=torch.int32, device=H.DEV)
+        start = (tok.clone(), tab.clone(), ln.clone())
+        head, status = torch.zeros(1, dtype=torch.int32, device=H.DEV), torch.full((1,), 9, dtype=torch.int32, device=H.DEV)
+        out = torch.full((steps, 4), -7, dtype=torch.int32, device=H.DEV)
+        ws = torch.empty(sun.sun_workspace_bytes(case.cfg, 4, 12), dtype=torch.uint8, device=H.DEV)
+        sun.sun_decode_run(case.pool, case.weights, steps, tok, tab, ln, case.ids, free, head, status, out, case.logits, ws, flags=flags)
+        torch.cuda.synchronize()
+        got.append((out.cpu(), int(status), ln.cpu(), tok.cpu(), tab.cpu(), int(head), bits(case.pool_mem)))
+    (want, ok, *_), (out, status, ln, tok, tab, head, pool) = got
+    lost = (out == -1).all(1)
+    done = int((~lost).sum())
+    assert ok & 4 == 0 and bool((want >= 0).all())
+    assert torch.equal(out[~lost], want[:done]) and bool(((out == -1).any(1) == lost).all())
+    assert (status & 4 != 0) == bool(lost.any())
+    if polls == 0:
+        assert done == 0 and head == 0
+        for a, b in zip((tok, tab, ln), start):
+            assert torch.equal(a, b.cpu())
+    assert bool(((pool == got[0][6]) | (pool == bits(pool0))).all())
+
+
+def test_serving_goes_on_behind_steps_without_a_result(H):
+    from test_gpu_serve import _Setup
+    S = _Setup(H, wl.SMALL128, "bf16", 4, [5, 30, 64, 1, 17], [4, 7, 3, 5, 6], 12, 8, seed=21)
+    got = []
+    for lose in (False, True):
+        S.case.pool_mem.copy_(torch.from_numpy(S.before.view(np.int16)).cuda().view(torch.bfloat16))
+        state = sun.ServeTensors(S.slots, S.cols, S.waiting, S.ring, S.n_pages, S.idle)
+        ws = torch.empty(sun.sun_serve_workspace_bytes(S.case.cfg, S.slots, S.cols), dtype=torch.uint8, device=H.DEV)
+
+        def serve(n, flags):
+            toks, reqs = (torch.full((n, S.slots), -7, dtype=torch.int32, device=H.DEV) for _ in range(2))
+            sun.sun_decode_serve(S.case.pool, S.case.weights, n, state, toks, reqs, S.case.logits, ws, flags=flags)
+            torch.cuda.synchronize()
+            return toks, reqs
+        if lose:
+            toks, reqs = serve(3, sun.SUN_SERVE_RESET | sun.SUN_WAIT_POLLS(0))
+            assert bool((toks == -1).all()) and bool((reqs == -1).all())
+            c = state.counters.cpu().numpy()
+            assert c[3] == 4 and c[4] == 0 and c[6] == 0 and c[7] == 3
+        toks, reqs = serve(6, 0 if lose else sun.SUN_SERVE_RESET)
+        got.append((toks, reqs, state.seq_lens.clone(), state.page_tables.clone(), state.counters.clone(), bits(S.case.pool_mem)))
+    for i in (0, 1, 2, 3, 5):
+        assert torch.equal(got[0][i], got[1][i])
+    a, b = (g[4].cpu().numpy() for g in got[:2])
+    assert list(a[[0, 1, 2, 4, 5, 6]]) == list(b[[0, 1, 2, 4, 5, 6]]) and b[3] == a[3] | 4 and b[7] == a[7] + 3
