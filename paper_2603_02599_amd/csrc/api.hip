@@ -964,7 +964,7 @@ int sun_decode_run(sun_kv_pool* pool_, const sun_weights* weights_, int batch, i
     }
     // small fp32 models: what lies between two steps is one launch
     const sun_model_cfg& c = W.cfg;
-    const bool turns = c.act_dtype == SUN_F32 && !(flags & SUN_PROFILE) && batch <= kTurnRows && (long long)batch * c.vocab <= kTurnLogits &&
+    const bool turns = c.act_dtype == SUN_F32 && !(flags & SUN_PROFILE) && batch <= kTurnRows && c.vocab <= kTurnVocab && (long long)batch * c.vocab <= kTurnLogits &&
                        attn_short_f32(c, max_pages);
     for (int s = 0; s < n_steps; ++s) {
         const bool last = s + 1 == n_steps;

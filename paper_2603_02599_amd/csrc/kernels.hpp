@@ -139,7 +139,7 @@ hipError_t launch_advance(const int32_t* next, int batch, int max_pages, const i
                           int32_t* status, bool clear_status, hipStream_t st);
 // Between two steps of a run (fp32): launch_argmax, launch_advance and, unless it was the last step, the next step's embedding rows and
 // rotary table, in one launch.
-constexpr int kTurnRows = 64, kTurnLogits = 1 << 17;   // requests, and logits of all of them, at most
+constexpr int kTurnRows = 64, kTurnVocab = 1 << 15, kTurnLogits = 1 << 17;   // requests, logits of one and of all of them, at most
 hipError_t launch_run_turn(const sun_model_cfg& cfg, const void* embed, const float* logits, int batch, int max_pages, const int32_t* free_pages, int n_free,
                            int32_t* next, int32_t* token_ids, int32_t* page_tables, int32_t* seq_lens, int32_t* free_head, int32_t* status,
                            bool clear_status, bool last, float* x, float* table, hipStream_t st);

@@ -611,6 +611,8 @@ hipError_t launch_advance(const int32_t* next, int batch, int max_pages, const i
 // token and gathers its embedding; one more keeps the books, for which no token is needed, and then makes the rotary tables of
 // the new positions (the frequencies while it waits for the lengths).  Tiny configuration, three launches -> this (us a step): 1 / 8 / 48 requests 64.9 / 68.7 /
 // 94.9 -> 62.5 / 66.3 / 89.6, the run of 16 steps with 8 requests 1141 -> 1034 us; all of it in one workgroup: 63.6 / 66.6 / 97.3.
+// A row is searched by one workgroup, so long ones stay with the launches that search them by sixteen: one request of 4096 / 16 384 / 32 768 /
+// 65 536 / 131 072 logits 66.8 / 72.9 / 86.3 / 100.7 / 114.8 -> 61.5 / 68.6 / 81.8 / 100.8 / 121.6, hence kTurnVocab.
 struct TurnArgs {
     EmbedRope e;                    // x, table
     const float* logits;

@@ -125,11 +125,13 @@ def test_run_of_one_step_equals_the_step(H):
 
 
 ODD = dataclasses.replace(wl.TINY, name="odd", ffn=689, vocab=1031)
+LONG_ROW, PAST_ROW = (dataclasses.replace(wl.TINY, name=f"vocab{v}", vocab=v) for v in (32767, 32772))   # either side of the longest row
 
 
 @pytest.mark.parametrize("shape,batch,steps,spare,width", [
     (wl.TINY, 1, 1, 2, 24), (wl.TINY, 1, 3, 2, 24), (ODD, 7, 5, 3, 24), (wl.TINY, 64, 18, 200, 24), (wl.TINY, 64, 18, 9, 3), (wl.TINY, 65, 3, 200, 24),
-    (wl.TINY_QWEN, 5, 20, 40, 24)], ids=["one-step", "one", "odd-vocab", "64", "64-no-pages", "65", "scaled-out"])
+    (wl.TINY_QWEN, 5, 20, 40, 24), (LONG_ROW, 4, 3, 2, 24), (PAST_ROW, 3, 3, 2, 24)],
+    ids=["one-step", "one", "odd-vocab", "64", "64-no-pages", "65", "scaled-out", "long-row", "past-row"])
 def test_what_lies_between_two_steps_in_one_launch(H, shape, batch, steps, spare, width):
     """The run with everything between two steps in one launch equals the run of separate launches (SUN_PROFILE asks for them) bit for
     bit: tokens, logits, tables, lengths, free list, status and cache."""
