@@ -747,8 +747,14 @@ static LayersLayout layers_layout(const sun_model_cfg& c, int rows, bool w4, siz
     return L;
 }
 
+// The cooperative launch costs about 26 us more than it saves outside the layers, and a layer saves, at the narrowest widths that were
+// timed (hidden 1024; wider ones two or three times that), 19 us at one row down to 4 at 16 (bf16), 11 at one row down to 4 at 8
+// (4-bit): few layers are faster with a launch per operation.  Hidden 1024, launch per operation -> this (us): one layer 12 / 16
+// requests 80 -> 97 / 81 -> 101, 4-bit 5 / 8 75 -> 94 / 76 -> 97; two layers one request 126 -> 117, 4-bit 117 -> 120; four at 12 / 16
+// 240 -> 233 / 244 -> 255, 4-bit at 5 218 -> 211; eight 473 -> 419 / 480 -> 469, 4-bit at 8 411 -> 395.
 static bool layers_shape(const Weights& W, int rows) {
-    return W.cfg.act_dtype == SUN_BF16 && W.cfg.head_dim == 128 && rows <= (W.quant ? kLayersRowsW4 : kLayersRows);
+    return W.cfg.act_dtype == SUN_BF16 && W.cfg.head_dim == 128 && rows <= (W.quant ? kLayersRowsW4 : kLayersRows) &&
+           W.cfg.n_layers * ((W.quant ? 12 : 20) - rows) >= 26;
 }
 
 int resident_grid(const void* kernel, int threads, int most, int dev) {
