@@ -334,9 +334,9 @@ __device__ __forceinline__ void unit_sums(const Part<W4, CB>& p, Ring<W4>& ring,
 }
 
 // What happens to a unit's sums, NR rows a wave.  With a split along k the workgroup that is the last of a block to arrive adds the
-// slabs up, in their order.  False where the wait in front of the phase was given up.
+// slabs up, in their order.
 template <bool W4, int CB, int NC, int NR, class Col, class Early, class Done>
-__device__ __forceinline__ bool unit_finish(const LayersArgs& a, const MatP& m, int layer, int u, const float* red, Shared& sh, Col col, Early early,
+__device__ __forceinline__ void unit_finish(const LayersArgs& a, const MatP& m, int layer, int u, const float* red, Shared& sh, Col col, Early early,
                                             Done done) {
     constexpr int KW = Part<W4, CB>::KW, LDR = CB + 4;
     const int lane = lane_here(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), R = a.R;
@@ -352,7 +352,6 @@ __device__ __forceinline__ bool unit_finish(const LayersArgs& a, const MatP& m, 
         for (int i = 0; i < NR; ++i) in[i] = early(blk, row[i]);
     }
     __syncthreads();
-    const int gone = lds_word(&sh.given_up);
     if (mine) {
 #pragma unroll
         for (int i = 0; i < NR; ++i)
@@ -364,7 +363,6 @@ __device__ __forceinline__ bool unit_finish(const LayersArgs& a, const MatP& m, 
                 v[i][c] = t;
             }
     }
-    if (__builtin_amdgcn_readfirstlane(gone)) return false;   // before the first store: others may still read what lies there
     if (m.S > 1) {
         float* sl = a.slab + (size_t)blk * R * CB;
         const size_t step = (size_t)m.nblk * R * CB;
@@ -384,7 +382,7 @@ __device__ __forceinline__ bool unit_finish(const LayersArgs& a, const MatP& m, 
         }
         __syncthreads();
         asm volatile("" ::: "memory");
-        if (!lds_word(&sh.last) || !mine) return true;
+        if (!lds_word(&sh.last) || !mine) return;
 #pragma unroll
         for (int i = 0; i < NR; ++i)
 #pragma unroll
@@ -412,7 +410,6 @@ __device__ __forceinline__ bool unit_finish(const LayersArgs& a, const MatP& m, 
         for (int i = 0; i < NR; ++i)
             if (wave + i * kWaves < R) done(blk, row[i], in[i], v[i]);
     }
-    return true;
 }
 
 // A phase: all units of one matrix, false where the launch is to be left.  wait() is the barrier in front of it, col(lane, i) names the NC
@@ -432,11 +429,11 @@ __device__ __forceinline__ bool matrix_phase(const LayersArgs& a, const MatP& m,
         if (u == (int)blockIdx.x) wait();
         else __syncthreads();           // the unit before is done with LDS
         if (!wave) p.template prefetch<STREAM>(ring);
+        const int gone = lds_word(&sh.given_up);
         unit_sums<W4, STREAM, CB>(p, ring, A, a.R, red);
-        bool ok;
-        if (W4 || a.R <= kWaves) ok = unit_finish<W4, CB, NC, 1>(a, m, layer, u, red, sh, col, early, done);
-        else ok = unit_finish<W4, CB, NC, kLayersRows / kWaves>(a, m, layer, u, red, sh, col, early, done);
-        if (!ok) return false;
+        if (__builtin_amdgcn_readfirstlane(gone)) return false;   // before the first store: others may still read what lies there
+        if (W4 || a.R <= kWaves) unit_finish<W4, CB, NC, 1>(a, m, layer, u, red, sh, col, early, done);
+        else unit_finish<W4, CB, NC, kLayersRows / kWaves>(a, m, layer, u, red, sh, col, early, done);
     }
     return true;
 }
