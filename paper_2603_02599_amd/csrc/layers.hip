@@ -767,26 +767,28 @@ bool is_capturing(hipStream_t st) {
     return hipStreamIsCapturing(st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone;
 }
 
-static int layers_grid(const void* kernel) {
+constexpr int kVariants = 3;
+static int layers_variant(const Weights& W) { return W.quant ? 2 : W.layers[0].qkv.stream; }
+static const void* layers_fn(int variant) {
+    return variant == 2 ? (const void*)layers_kernel<true, false> : variant == 1 ? (const void*)layers_kernel<false, true> : (const void*)layers_kernel<false, false>;
+}
+
+static int layers_grid(int variant) {
     constexpr int kDevices = 64;
-    static std::atomic<int> known[kDevices];          // grid + 1 of a device
+    static std::atomic<int> known[kVariants][kDevices];   // grid + 1 of a kernel on a device
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kDevices) return 0;
-    int g = known[dev].load(std::memory_order_relaxed);
+    int g = known[variant][dev].load(std::memory_order_relaxed);
     if (g == 0) {
-        g = resident_grid(kernel, kWaves * 64, kUnits, dev) + 1;
-        known[dev].store(g, std::memory_order_relaxed);
+        g = resident_grid(layers_fn(variant), kWaves * 64, kUnits, dev) + 1;
+        known[variant][dev].store(g, std::memory_order_relaxed);
     }
     return g - 1;
 }
 
-static const void* layers_fn(bool w4, bool stream) {
-    return w4 ? (const void*)layers_kernel<true, false> : stream ? (const void*)layers_kernel<false, true> : (const void*)layers_kernel<false, false>;
-}
-
 bool layers_usable(const Weights& W, int rows, const LayersScratch& scratch, hipStream_t st) {
     if (!layers_shape(W, rows) || layers_layout(W.cfg, rows, W.quant, scratch.bytes).ring < 1 || is_capturing(st)) return false;
-    return layers_grid(layers_fn(W.quant, W.layers[0].qkv.stream)) > 0;
+    return layers_grid(layers_variant(W)) > 0;
 }
 
 LayersZero layers_zero(const LayersScratch& scratch, const Weights& W, const AttnPlan& plan) {
@@ -850,8 +852,8 @@ hipError_t launch_layers(const KvPool& pool, const Weights& W, int rows, float* 
     a.H = c.hidden;
     a.s_only = w4 && W.layers[0].qkv.s_only;
     a.eps = c.rms_eps;
-    const void* fn = layers_fn(w4, W.layers[0].qkv.stream);
-    const int grid = layers_grid(fn);
+    const void* fn = layers_fn(layers_variant(W));
+    const int grid = layers_grid(layers_variant(W));
     if (grid < 1) return hipErrorNotSupported;
     for (int l0 = 0; l0 < c.n_layers; l0 += kLayersPerLaunch) {
         a.l0 = l0;
