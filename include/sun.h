@@ -287,7 +287,8 @@ size_t sun_workspace_bytes(const sun_model_cfg* cfg, int max_batch, int max_page
  * pages may be shared read-only).  Outputs are valid after the stream is
  * synchronised.  With flags = 0 device array contents are not checked.
  * With SUN_BF16 and head_dim 128 a step of up to 16 requests (8 with 4-bit weights) runs all its
- * layers in one cooperative launch (seven or more of them always, fewer where they pay), except under SUN_PROFILE and while the stream is captured, where every
+ * layers in one cooperative launch (seven or more of them always, fewer where that pays).  Under
+ * SUN_PROFILE, while the stream is captured and on a stream that may not use all compute units every
  * operation is a launch of its own.  The two sum in different orders: results agree up to fp32
  * rounding and, where a new cache entry falls on the other side of it, bf16 rounding.
  * That launch needs every compute unit: it starts as other work leaves them, and where some are held for half a minute it

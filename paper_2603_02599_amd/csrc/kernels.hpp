@@ -116,6 +116,7 @@ hipError_t launch_layers(const KvPool& pool, const Weights& W, int rows, float* 
 // Workgroups of a kernel (one per compute unit, at most `most`) that a cooperative launch on the device keeps resident; 0: none.
 int resident_grid(const void* kernel, int threads, int most, int dev);
 bool is_capturing(hipStream_t st);   // or cannot tell
+bool has_all_units(hipStream_t st);  // not confined to some of the compute units (false if it cannot tell)
 
 // ---------------- everything else (misc.hip) ----------------
 

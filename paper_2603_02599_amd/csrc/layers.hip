@@ -767,6 +767,17 @@ bool is_capturing(hipStream_t st) {
     return hipStreamIsCapturing(st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone;
 }
 
+// Whether a stream's work may run on all compute units: a workgroup that needs a unit which its stream may not use never comes.
+bool has_all_units(hipStream_t st) {
+    int dev = 0, cus = 0;
+    uint32_t mask[32] = {};                               // 0.5 us a call
+    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus > 32 * 32) return false;
+    if (hipExtStreamGetCUMask(st, (cus + 31) / 32, mask) != hipSuccess) return false;
+    for (int i = 0; i < cus; ++i)
+        if (!(mask[i / 32] >> (i % 32) & 1)) return false;
+    return true;
+}
+
 constexpr int kVariants = 3;
 static int layers_variant(const Weights& W) { return W.quant ? 2 : W.layers[0].qkv.stream; }
 static const void* layers_fn(int variant) {
@@ -788,7 +799,7 @@ static int layers_grid(int variant) {
 
 bool layers_usable(const Weights& W, int rows, const LayersScratch& scratch, hipStream_t st) {
     if (!layers_shape(W, rows) || layers_layout(W.cfg, rows, W.quant, scratch.bytes).ring < 1 || is_capturing(st)) return false;
-    return layers_grid(layers_variant(W)) > 0;
+    return has_all_units(st) && layers_grid(layers_variant(W)) > 0;
 }
 
 LayersZero layers_zero(const LayersScratch& scratch, const Weights& W, const AttnPlan& plan) {

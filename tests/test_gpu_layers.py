@@ -2,6 +2,7 @@
 each finishes and the largest taken, one row beyond it, lengths around chunk and page boundaries, matrices with fewer
 column blocks than compute units, more layers than one launch takes, head norm, biases, both 4-bit layouts.  Against the oracle, and
 against a launch per operation (which SUN_PROFILE asks for)."""
+import ctypes
 import dataclasses
 import threading
 
@@ -154,6 +155,31 @@ def test_under_capture_a_step_takes_a_launch_per_operation(H):
         torch.cuda.synchronize()
         assert torch.equal(case.logits, want)
         case.step()                       # an eager step between the replays
+
+
+@pytest.mark.parametrize("words,one", [([0xFFFFFFFF] * 8, True), ([0xFFFFFFFF] * 4 + [0] * 4, False), ([0xFFFFFFFE] + [0xFFFFFFFF] * 7, False)],
+                         ids=["all", "half", "all-but-one"])
+def test_a_stream_confined_to_some_compute_units_takes_a_launch_per_operation(H, words, one):
+    """The launch needs a workgroup on every compute unit, which such a stream cannot give it."""
+    case = make_case(H, SMALL, [5, 100, 300])
+    pool0 = case.pool_mem.clone()
+    case.step(flags=0 if one else sun.SUN_PROFILE)
+    want, pool = case.logits.clone(), bits(case.pool_mem)
+    case.pool_mem.copy_(pool0)
+    case.logits.fill_(float("nan"))
+    lens = case.lens.cpu().numpy()
+    torch.cuda.synchronize()
+    hip, stream = ctypes.CDLL("libamdhip64.so"), ctypes.c_void_p()
+    hip.hipExtStreamCreateWithCUMask.argtypes = [ctypes.POINTER(ctypes.c_void_p), ctypes.c_uint32, ctypes.POINTER(ctypes.c_uint32)]
+    hip.hipStreamSynchronize.argtypes = hip.hipStreamDestroy.argtypes = [ctypes.c_void_p]
+    assert hip.hipExtStreamCreateWithCUMask(ctypes.byref(stream), 8, (ctypes.c_uint32 * 8)(*words)) == 0
+    try:
+        sun.sun_decode_step(case.pool, case.weights, case.tokens, case.tables, case.lens, case.ids, case.logits, case.next, case.ws,
+                            seq_lens_host=lens, stream=stream.value)
+        assert hip.hipStreamSynchronize(stream) == 0
+        assert torch.equal(case.logits, want) and torch.equal(bits(case.pool_mem), pool)
+    finally:
+        hip.hipStreamDestroy(stream)
 
 
 def test_steps_on_two_streams_from_two_threads(H):
