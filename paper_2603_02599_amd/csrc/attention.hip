@@ -282,7 +282,11 @@ __global__ __launch_bounds__(256) void attn_split_f32_kernel(AttnArgs a, int G) 
 // and V, walks the request's chunks (a wave per chunk and query head, partial results in LDS) and merges them.  Every sum has
 // the order it has there, so the results are theirs bit for bit.  Tiny configuration, three launches -> this (us a step): 8 requests of 16 /
 // 100 / 250 / 500 / 900 cached tokens 78.7 / 79.2 / 82.2 / 83.4 / 83.4 -> 68.7 / 71.4 / 76.6 / 86.2 / 106.7, 48 of 250 105 -> 100,
-// 200 of 250 160 -> 146: a request is a few workgroups', so tables beyond kShortTokens stay with the launches that spread it.
+// 200 of 250 160 -> 146: a request is a few workgroups', so longer tables stay with the launches that spread it.  How long depends on a
+// workgroup's share, chunks x query heads x dims at 64 positions a chunk.  One request, two KV heads, hidden 512, tables of 64 / 128 / 192 /
+// 256 / 384 positions: 2 query heads of 128 each 86 / 87 / 87 / 88 / 92 -> 76 / 78 / 82 / 85 / 103, 4 of 64 82 / 83 / 85 / 85 / 85 -> 71 / 74 / 81 /
+// 85 / 94, 8 of 64 98 / 97 / 98 / 100 / 98 -> 83 / 90 / 99 / 113 / 130, 4 of 128 101 / 102 / 104 / 104 / 104 -> 88 / 93 / 109 / 113 / 133, 8 of 128
+// 131 / 133 / 134 / 133 / 134 -> 110 / 130 / 151 / 171 / 212 (32 requests the same way); hence kShortShare.
 // Not for a prefill block, where a row attends to entries that other rows of the launch append.
 constexpr int kShortPart = (kShortTokens / kAttnSmall) * 8 * 130;   // floats of LDS for partial results: chunks, query heads, dims + 2
 
@@ -451,7 +455,9 @@ __global__ __launch_bounds__(512) void attn_short_f32_kernel(ShortArgs a) {
 
 bool attn_short_f32(const sun_model_cfg& c, int max_pages) {
     // every chunk but a request's last covers at least kAttnSmall positions
-    return c.n_q_heads / c.n_kv_heads <= 8 && c.head_dim <= 128 && (long long)max_pages * kPageTokens <= kShortTokens;
+    const long long positions = (long long)max_pages * kPageTokens, chunks = (positions + kAttnSmall - 1) / kAttnSmall;
+    return c.n_q_heads / c.n_kv_heads <= 8 && c.head_dim <= 128 && positions <= kShortTokens &&
+           chunks * (c.n_q_heads / c.n_kv_heads) * c.head_dim <= kShortShare;
 }
 
 hipError_t launch_attn_short_f32(const KvPool& pool, int layer, const float* qkv, const float* table, const int32_t* seq_lens, const int32_t* page_tables,

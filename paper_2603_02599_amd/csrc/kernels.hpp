@@ -77,9 +77,9 @@ hipError_t launch_attn_split(const KvPool& pool, int layer, const AttnPlan& plan
 hipError_t launch_attn_combine(const sun_model_cfg& cfg, const AttnPlan& plan, int batch, float* out_f32,
                                void* out_tiled, float* qscale, hipStream_t st);
 
-// fp32, tables of at most kShortTokens positions: launch_rope_append, launch_attn_split and launch_attn_combine of a decode step in
+// fp32, tables of at most kShortTokens positions (fewer with many or wide query heads): launch_rope_append, launch_attn_split and launch_attn_combine of a decode step in
 // one launch, bit for bit.  qkv [batch, (Hq + 2 Hkv) * d], out [batch, Hq * d].
-constexpr int kShortTokens = 384;
+constexpr int kShortTokens = 384, kShortShare = 1024;   // chunks x query heads of a KV head x dims; measured in attention.hip
 bool attn_short_f32(const sun_model_cfg& c, int max_pages);
 hipError_t launch_attn_short_f32(const KvPool& pool, int layer, const float* qkv, const float* table, const int32_t* seq_lens, const int32_t* page_tables,
                                  int max_pages, int batch, const LayerW& w, float* out, hipStream_t st);

@@ -309,13 +309,18 @@ def test_ingest_on_both_sides_of_the_rule_for_its_stores(H, tokens, first):
     assert np.array_equal(H.to_np(mem), host)
 
 
-SHORT = 384   # positions of the longest table whose attention is one launch
+SHORT = 384   # positions of the longest table whose attention is one launch; many or wide query heads make it shorter
+G4, G2_D128, G1_D128 = (dataclasses.replace(wl.TINY, name=n, n_q_heads=q, n_kv_heads=2, head_dim=d)
+                        for n, q, d in (("g4", 8, 64), ("g2_d128", 4, 128), ("g1_d128", 2, 128)))
 
 
 @pytest.mark.parametrize("shape,lens,extra", [
     (wl.TINY, [0], 0), (wl.TINY, [15, 16, 62, 63, 64, 127, 128, 255, 382], 0), (wl.TINY, [383], 0), (wl.TINY, [383, 5], 1),
-    (WIDE, [0, 63, 200, 383], 0), (wl.TINY_BIAS, [17, 64, 300], 0), (wl.TINY_QWEN, [17, 64, 300], 0), (wl.TINY, list(range(310, 375)), 0)],
-    ids=["empty", "edges", "whole", "beyond", "g8-d128", "bias", "head-norm", "65-full-chunks"])
+    (WIDE, [0, 63, 200, 383], 0), (wl.TINY_BIAS, [17, 64, 300], 0), (wl.TINY_QWEN, [17, 64, 300], 0), (wl.TINY, list(range(310, 375)), 0),
+    (WIDE, [0, 15, 62, 63], -20), (WIDE, [0, 63, 64, 79], -19), (G4, [0, 63, 191, 255], -8), (G4, [0, 63, 256, 271], -7),
+    (G2_D128, [5, 127, 255], -8), (G1_D128, [0, 64, 383], 0)],
+    ids=["empty", "edges", "whole", "beyond", "g8-d128-beyond", "bias", "head-norm", "65-full-chunks", "g8-d128", "g8-d128-one-page-more", "g4-d64",
+         "g4-d64-one-page-more", "g2-d128", "g1-d128"])
 def test_short_tables_take_one_launch_for_attention(H, shape, lens, extra):
     """Bit for bit what the separate launches give (SUN_PROFILE asks for them): logits and every slot of the cache."""
     work = wl.make_workload("cfg1", shape=shape, dtype="f32", batch=len(lens), seed=980 + len(lens))
