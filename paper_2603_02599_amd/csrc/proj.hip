@@ -816,9 +816,10 @@ static hipError_t launch_proj_wide(const ProjArgs& a, int epilogue, int cb, int 
         // cost more (4 layers of the 8B shape, left out: 260 / 400 / 800 (14B) tokens with 44 / 19 / 22 % of them 1864 / 1905 / 4311 ->
         // 1677 / 1861 / 4154 us, 1100 / 1300 with 13 / 15 % 4181 / 5051 -> 4152 / 5014, 900 with 9 % 3419 -> 3435, 1200 (14B) with 5 %
         // 5503 -> 5594, 1500 with 2 % 5170 -> 5298; a 4-bit step of 150 requests,
-        // whose vocabulary has three blocks of eight left out, 3288 -> 3228).
+        // whose vocabulary has three blocks of eight left out, 3288 -> 3228).  In the one row tile of a vocabulary a single block of
+        // eight is not enough (200 rows, vocabulary 65 536 of hidden 4096 / 128 256 of hidden 1024: 200 / 114 -> 213 / 118 us).
         const int row_blocks = (a.rows + 31) / 32, launched = (a.rows + 255) / 256 * 8;
-        const bool ragged = (launched - row_blocks) * 8 >= launched;
+        const bool ragged = (launched - row_blocks) * (launched == 8 ? 4 : 8) >= launched;
         if (epilogue == EPI_SWIGLU) {
             if (splits != 1) return hipErrorInvalidValue;
             if (ragged) hipLaunchKernelGGL((proj_wide_kernel<EPI_SWIGLU, CB, true>), grid, dim3(512), 0, st, a);
@@ -983,9 +984,11 @@ static int wide_pick_splits(const Mat& W, int rows, int max_splits) {
 // at 1024 / 1200 / 1792 rows 412 / 549 / 740 -> 404 / 481 / 706 (seven, six, five), q/k/v at 1024 / 1792 rows 105 / 175 -> 92 / 151 (six);
 // the launches beside them, eight strips on both sides, take 2 to 3 % longer (what a launch saves in time it draws in power).  All
 // kernels of two layers: 8B shape at 1024 / 1200 / 1792 rows 1987 / 2372 / 3239 -> 1945 / 2274 / 3156, 14B shape at 512 / 1024 rows
-// 1450 / 2393 -> 1423 / 2407.
+// 1450 / 2393 -> 1423 / 2407.  One row tile (a vocabulary above 128 rows) takes eight: no two workgroups share a column's weights there, and
+// seven strips, which the figures promise 6 % for, took 664 / 693 us instead of 640 / 674 (152 064 x 5120 at 200 / 256 rows).
 static int wide_pick_strips(const Mat& W, int rows, int splits) {
     const int stages = W.K / 32, strips = W.N / 32, row_tiles = (rows + 255) / 256, sps = (stages + splits - 1) / splits;
+    if (row_tiles == 1) return 8;
     const auto cost = [&](int cb) {
         const long long wgs = (long long)((strips + cb - 1) / cb) * row_tiles * splits, rounds = (wgs + 255) / 256;
         const double full = (double)wgs / (double)(rounds * 256), stage = 0.95 + (1.7 * cb / 8 - 0.95) * full;

@@ -269,7 +269,7 @@ def test_the_split_along_k_does_not_follow_the_tile_width(H, rows, slabs):
     assert float(v.min()) == float(v.max()) and abs(float(v[0, 0]) - (shape.hidden - first)) <= 32 * slabs + 8
 
 
-@pytest.mark.parametrize("rows", [160, 161, 193, 224, 225])
+@pytest.mark.parametrize("rows", [129, 160, 161, 192, 193, 224, 225])
 def test_wide_vocabulary_projection_leaves_out_row_blocks(H, rows):
     """Five to eight of the eight 32-row blocks of a tile hold rows: a wave with both of its blocks, with one, with none."""
     test_wide_vocabulary_projection(H, rows)
