@@ -441,7 +441,7 @@ def main():
                           "steps": args.steps, "warmup": args.warmup, "ms_per_step": ms, "higher_is_better": True,
                           "dtype": "bf16", "data": "synthetic",
                           "config": {"workload": f"one prompt of {n} tokens, {shape.name} shape, shuffled pages, "
-                                                 "through the decode step's kernels in blocks of 256 rows"}}))
+                                                 "in blocks of up to 2048 rows"}}))
         return
     if args.sweep_step_times:
         from paper_2603_02599_amd import workloads as wl

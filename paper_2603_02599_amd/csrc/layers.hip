@@ -6,11 +6,11 @@
 //   q/k/v -> attention -> merge -> o -> gate/up -> down
 // are separated by a barrier over the grid (2.6 us from the last arrival's stores to the next phase's loads), in front of which
 // every wave but one requests its first weights.  Bound by the weight stream in the long phases (gate/up 6.6 to 7 TB/s) and by
-// chains of small loads and stores around them.  Step of 8 layers of the 8B shape, launch per operation -> this (us): bf16 at 1 /
-// 16 requests 1156 -> 905 / 1340 -> 1199, 4-bit at 5 834 -> 746.  Four layers at 1 / 2 / 8 / 12 / 16 requests: bf16 650 -> 553 /
-// 687 -> 575 / 701 -> 620 / 712 -> 646 / 697 -> 633, 4-bit 491 -> 445 / 508 -> 454 / 527 -> 502 / 549 -> 552 / 524 -> 553;
-// eight layers of hidden 2048 at 1 / 8 / 16 requests: bf16 586 -> 407 / 612 -> 470 / 635 -> 554, 4-bit 474 -> 372 / 505 -> 464 /
-// 540 -> 586.  Hence kLayersRows and kLayersRowsW4.
+// chains of small loads and stores around them.  Steps of 8 layers, launch per operation -> this (us), 1 / 8 / 16 requests of 200 to 1200
+// cached tokens: 8B shape bf16 1154 -> 923 / 1185 -> 1010 / 1217 -> 1106, 4-bit at 1 / 4 / 8 817 -> 678 / 835 -> 728 / 837 -> 771; hidden
+// 2048, ffn 8192 bf16 644 -> 441 / 666 -> 523 / 697 -> 650, 4-bit at 1 / 8 510 -> 400 / 538 -> 500; hidden 1024 440 -> 303 / 476 -> 370 /
+// 494 -> 475, 403 -> 316 / 430 -> 405.  4-bit at 12 / 16 requests (4 layers, 8B shape, two rows a wave) 549 -> 552 / 524 -> 553.  Hence
+// kLayersRows and kLayersRowsW4.
 //
 // Hand-over between workgroups.  Data that another workgroup reads in the same launch is stored through to memory (st_agent),
 // and its storer waits for vmcnt before it counts itself as arrived.  Readers either pass their caches by (ld_agent: the residual
@@ -694,7 +694,10 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 
 static size_t up256(size_t v) { return (v + 255) / 256 * 256; }
 
 // Column blocks and split along k.  As many units as there are workgroups at most; every wave that shares k gets a step.
-// A row's sums depend on the matrix alone.
+// A row's sums depend on the matrix alone.  Widths whose blocks fill the chip badly lose part of the gain, not all of it (4 layers, launch
+// per operation -> this, us): 296 gate/up blocks on 256 workgroups (hidden 3584, ffn 18 944) at 1 / 16 requests 577 -> 489 / 593 -> 591;
+// 136 of 4-bit weights (hidden 5120, ffn 17 408) at 1 / 8 468 -> 399 / 473 -> 434, bf16 at 1 / 16 724 -> 644 / 747 -> 746; 14B shape 847 ->
+// 697 / 886 -> 780, 4-bit 613 -> 554 / 634 -> 600; hidden 8192, ffn 28 672 1351 -> 1258 / 1376 -> 1346, 4-bit 706 -> 607 / 740 -> 655.
 static void cut(MatP& m, int N, int K, int cb, bool w4) {
     m.K = K;
     m.nblk = N / cb;
