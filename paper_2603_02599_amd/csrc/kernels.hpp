@@ -125,7 +125,7 @@ hipError_t launch_embed_rope(const sun_model_cfg& cfg, const void* embed, const 
                              int first_pos, int rows, float* x, float* table, hipStream_t st);
 // x[b] += sum_s partial[s][b] (s ascending; nparts may be 0); then h = rmsnorm(x; g).
 // h_f32 (fp32 gains): row-major.  Else h_tiled (bf16 gains): two-plane tiled bf16; with qscale given the fixed-point tile of a 4-bit projection instead, and qscale
-// receives its (scale, integer sum) pairs.  lost (may be NULL): where *lost is not 0, h is not-a-numbers.
+// receives its (scale, integer sum) pairs.  lost (may be NULL; not with h_f32): where *lost is not 0, h is not-a-numbers.
 hipError_t launch_residual_norm(const sun_model_cfg& cfg, float* x, const float* partial, int nparts, int ld_rows,
                                 const void* gain, int batch, float* h_f32, void* h_tiled, float* qscale, hipStream_t st,
                                 const uint32_t* lost = nullptr);

@@ -46,11 +46,13 @@ struct NormArgs {
 
 // One 8-element unit per thread and pass (up to two passes, i.e. hidden <= 16 * blockDim), all
 // slab loads of a unit independent of one another so that they are in flight together.
-template <bool F32>
+// LOST: behind the launch of all layers, which may have been given up.
+template <bool F32, bool LOST>
 __global__ __launch_bounds__(1024) void residual_norm_kernel(NormArgs a) {
     __shared__ float red[16];
     const int b = blockIdx.x, tid = threadIdx.x, H = a.H, nunits = H / 8, nthreads = blockDim.x;
-    const uint32_t lost = a.lost ? *a.lost : 0u;
+    uint32_t lost = 0u;
+    if constexpr (LOST) lost = *a.lost;
     float* xr = a.x + (size_t)b * H;
     float v[2][8];
     float ss = 0.f;
@@ -151,8 +153,9 @@ hipError_t launch_residual_norm(const sun_model_cfg& cfg, float* x, const float*
     if (cfg.hidden % 8 || cfg.hidden > 16 * 1024) return hipErrorInvalidValue;
     const int units = cfg.hidden / 8;
     const int threads = units <= 1024 ? (units + 63) / 64 * 64 : ((units + 1) / 2 + 63) / 64 * 64;
-    if (h_f32) hipLaunchKernelGGL(residual_norm_kernel<true>, dim3(batch), dim3(threads), 0, st, a);
-    else hipLaunchKernelGGL(residual_norm_kernel<false>, dim3(batch), dim3(threads), 0, st, a);
+    if (h_f32) hipLaunchKernelGGL((residual_norm_kernel<true, false>), dim3(batch), dim3(threads), 0, st, a);
+    else if (lost) hipLaunchKernelGGL((residual_norm_kernel<false, true>), dim3(batch), dim3(threads), 0, st, a);
+    else hipLaunchKernelGGL((residual_norm_kernel<false, false>), dim3(batch), dim3(threads), 0, st, a);
     return hipGetLastError();
 }
 
