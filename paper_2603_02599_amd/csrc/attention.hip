@@ -570,19 +570,10 @@ __global__ __launch_bounds__(128) void attn_combine_kernel(CombineArgs a) {
         for (int cb = 0; cb < n; cb += 64) {
             const int c = cb + lane, cnt = min(n - cb, 64);
             const float m = c < n ? p[c * stride + a.D] : -INFINITY, l = c < n ? p[c * stride + a.D + 1] : 0.f;
-            float top = m;                        // maximum up to the end of the lane's eight
-#pragma unroll
-            for (int s = 1; s < 8; s <<= 1) top = fmaxf(top, __shfl_xor(top, s));
-#pragma unroll
-            for (int s = 8; s < 64; s <<= 1) {
-                const float t = __shfl_up(top, s);
-                if (lane >= s) top = fmaxf(top, t);
-            }
-            top = fmaxf(top, M);
-            float prev = __shfl_up(top, 8);       // and up to its start
-            if (lane < 8) prev = M;
+            float prev;                           // maximum up to the start and to the end of the lane's eight
+            const float top = wave_octet_max(m, M, prev);
             const float w = c < n ? exp2f(m - top) : 0.f, sc = exp2f(prev - top);
-            M = __shfl(top, 63);
+            M = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(top), 63));
             const float* pj = p + (size_t)cb * stride + j;
             for (int k0 = 0; k0 < cnt; k0 += 16) {
                 float o[16];
@@ -625,8 +616,7 @@ __global__ __launch_bounds__(128) void attn_combine_kernel(CombineArgs a) {
         tile[qtile_unit(ATile{a.out_mb}, 0, b, col >> 4) * 16 + (col & 15)] = (uint8_t)(hq & 255);
         tile[qtile_unit(ATile{a.out_mb}, 1, b, col >> 4) * 16 + (col & 15)] = (uint8_t)(l & 255);
         int sum = xi;
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
+        sum = wave_sum(sum);
         if ((threadIdx.x & 63) == 0) red_sum[threadIdx.x >> 6] = sum;
         __syncthreads();
         if (threadIdx.x == 0)
@@ -815,7 +805,7 @@ void attn_prefill_kernel(PrefillAttnArgs a) {
             float mloc = S[0];
 #pragma unroll
             for (int r = 1; r < 16; ++r) mloc = fmaxf(mloc, S[r]);
-            mloc = fmaxf(mloc, __shfl_xor(mloc, 32));
+            mloc = fmaxf(mloc, lane_xor<32>(mloc));
             // a split may begin behind a row's last key: all its scores are masked then, and its weights have to be zeros
             const float m_new = fmaxf(m_run, mloc), m_use = m_new == -INFINITY ? 0.f : m_new;
             const float alpha = __builtin_amdgcn_exp2f(m_run - m_use);
@@ -890,7 +880,7 @@ void attn_prefill_kernel(PrefillAttnArgs a) {
         at = at + 1 == NBUF ? 0 : at + 1;
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // nothing is in flight into LDS when the workgroup ends
-    const float l_tot = poisoned ? __builtin_nanf("") : l_run + __shfl_xor(l_run, 32);
+    const float l_sum = l_run + lane_xor<32>(l_run), l_tot = poisoned ? __builtin_nanf("") : l_sum;
     if (row >= a.rows) return;
     if (a.partial) {
         float* o = a.partial + (((size_t)row * gridDim.z + blockIdx.z) * a.Hq + hq) * (D + 2);

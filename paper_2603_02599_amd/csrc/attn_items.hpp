@@ -238,8 +238,8 @@ __device__ __forceinline__ void attn_split_items(const AttnArgs& a, int wg, int 
             sy[r] = (tb + 4 + r < t1) ? sy[r] : -INFINITY;
             mloc = fmaxf(mloc, fmaxf(sx[r], sy[r]));
         }
-        mloc = fmaxf(mloc, __shfl_xor(mloc, 16));
-        mloc = fmaxf(mloc, __shfl_xor(mloc, 32));
+        mloc = fmaxf(mloc, lane_xor<16>(mloc));
+        mloc = fmaxf(mloc, lane_xor<32>(mloc));
         const float m_new = fmaxf(m_run, mloc);
         const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
         m_run = m_new;
@@ -295,8 +295,8 @@ __device__ __forceinline__ void attn_split_items(const AttnArgs& a, int wg, int 
             if (++pp < npairs) return;
         }
 
-        float l_tot = l_run + __shfl_xor(l_run, 16);
-        l_tot += __shfl_xor(l_tot, 32);
+        float l_tot = l_run + lane_xor<16>(l_run);
+        l_tot += lane_xor<32>(l_tot);
         float* pbase = a.partial + ((size_t)cidx * a.Hq + head * G) * (D + 2);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {

@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
 #include <vector>
 
 #include "../../include/sun.h"
@@ -170,16 +171,93 @@ __device__ __forceinline__ float2 ld_agent2(const float* p) {
     return float2{__uint_as_float((uint32_t)v), __uint_as_float((uint32_t)(v >> 32))};
 }
 
-// ---- wave reductions (all lanes receive the result; fixed order => deterministic) ----
+// ---- lanes of a wave reading one another ----
+// The vector ALU moves a value within a row of 16 lanes while it computes (DPP) and exchanges rows in one instruction, some 10
+// cycles a step where a shuffle through LDS takes 60 to 100; an all-lane sum is six steps in a row and ends most of the step's small
+// kernels.  Against shuffles, the same bits: tiny fp32 run of 16 steps 1034 -> 967 us, 8 layers of the 8B shape, 4 bits, 5 requests 735 -> 726,
+// 32 layers at 64 requests 8076 -> 8008.  All lanes have to be active.
+template <int CTRL, class T>
+__device__ __forceinline__ T lane_dpp(T v) {
+    static_assert(sizeof(T) == 4, "a register");
+    return __builtin_bit_cast(T, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true));
+}
+// the 16-lane rows (O = 16) or 32-lane halves (O = 32) of a and b with the odd ones of a and the even ones of b exchanged
+template <int O, class T>
+__device__ __forceinline__ void swap_rows(T& a, T& b) {
+    static_assert(sizeof(T) == 4 && (O == 16 || O == 32), "");
+    uint32_t x = __builtin_bit_cast(uint32_t, a), y = __builtin_bit_cast(uint32_t, b);
+    if constexpr (O == 32) {
+        const auto r = __builtin_amdgcn_permlane32_swap(x, y, false, false);
+        x = r[0];
+        y = r[1];
+    } else {
+        const auto r = __builtin_amdgcn_permlane16_swap(x, y, false, false);
+        x = r[0];
+        y = r[1];
+    }
+    a = __builtin_bit_cast(T, x);
+    b = __builtin_bit_cast(T, y);
+}
+// lane l gets lane l ^ O's
+template <int O, class T>
+__device__ __forceinline__ T lane_xor(T v) {
+    if constexpr (O == 1) return lane_dpp<0xB1>(v);                       // lanes 1 0 3 2 of every four
+    else if constexpr (O == 2) return lane_dpp<0x4E>(v);                  // lanes 2 3 0 1
+    else if constexpr (O == 4) return lane_dpp<0x1B>(lane_dpp<0x141>(v)); // l ^ 7 of every eight, then l ^ 3
+    else if constexpr (O == 8) return lane_dpp<0x128>(v);                 // rotated by eight of sixteen
+    else {
+        T a = v, b = v;
+        swap_rows<O>(a, b);
+        return threadIdx.x & O ? a : b;
+    }
+}
+// f over all lanes, in the order of a butterfly over lane bits 5 .. 0 (fixed => deterministic); f commutes.  Behind the step
+// over bit 3 a row repeats after eight lanes, so a rotation by four reads what lane l ^ 4 holds, and so on.
+template <class T, class F>
+__device__ __forceinline__ T wave_all(T v, F f) {
+    T a = v, b = v;
+    swap_rows<32>(a, b);
+    v = f(a, b);
+    a = b = v;
+    swap_rows<16>(a, b);
+    v = f(a, b);
+    v = f(v, lane_dpp<0x128>(v));
+    v = f(v, lane_dpp<0x124>(v));
+    v = f(v, lane_dpp<0x122>(v));
+    return f(v, lane_dpp<0x121>(v));
+}
 __device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-    return v;
+    return wave_all(v, [](float a, float b) { return a + b; });
+}
+__device__ __forceinline__ int wave_sum(int v) {
+    return wave_all(v, [](int a, int b) { return a + b; });
 }
 __device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
-    return v;
+    return wave_all(v, [](float a, float b) { return fmaxf(a, b); });
+}
+
+// Maxima over eight lanes at a time and up to there: a lane gets the largest of `start` and all m up to the end of its eight lanes;
+// before, the same up to their start.
+__device__ __forceinline__ float wave_octet_max(float m, float start, float& before) {
+    const auto moved = [](float old, float v, auto ctrl, auto rows, auto banks) {   // lanes that nothing moves to keep old
+        return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, old), __builtin_bit_cast(int, v), decltype(ctrl)::value,
+                                                                     decltype(rows)::value, decltype(banks)::value, false));
+    };
+    typedef std::integral_constant<int, 0x118> Right8;    // within a row of 16 lanes
+    typedef std::integral_constant<int, 0x142> NextRow;   // a row's last lane to the row behind it
+    typedef std::integral_constant<int, 0x143> UpperHalf; // lane 31 to rows 2 and 3
+    typedef std::integral_constant<int, 0xf> All;
+    const float none = -INFINITY;
+    float top = fmaxf(m, lane_xor<1>(m));
+    top = fmaxf(top, lane_xor<2>(top));
+    top = fmaxf(top, lane_dpp<0x141>(top));               // mirrored within eight lanes: the other four
+    top = fmaxf(top, moved(none, top, Right8{}, All{}, All{}));
+    top = fmaxf(top, moved(none, top, NextRow{}, std::integral_constant<int, 0xa>{}, All{}));
+    top = fmaxf(top, moved(none, top, UpperHalf{}, std::integral_constant<int, 0xc>{}, All{}));
+    top = fmaxf(top, start);
+    before = moved(start, top, NextRow{}, std::integral_constant<int, 0xe>{}, std::integral_constant<int, 0x3>{});
+    before = moved(before, top, Right8{}, All{}, std::integral_constant<int, 0xc>{});
+    return top;
 }
 
 // Packed weights of a model from which they are streamed past the caches: the memory-side cache's 256 MB, in which those of a

@@ -102,13 +102,11 @@ __device__ __forceinline__ void store_tile128(char* tile, int R, int chunk, int 
         const uint32_t lo = (uint32_t)(l0 & 255) | (uint32_t)(l1 & 255) << 8;
         const uint32_t hi = (uint32_t)(((x0 - l0) >> 8) & 255) | (uint32_t)(((x1 - l1) >> 8) & 255) << 8;
         // four columns of a plane per lane: even lanes the high plane's, odd lanes the low plane's
-        const uint32_t got = __shfl_xor(lane & 1 ? hi : lo, 1);
+        const uint32_t got = lane_xor<1>(lane & 1 ? hi : lo);
         const uint32_t v = lane & 1 ? (got | lo << 16) : (hi | got << 16);
         const int c = 4 * (lane >> 1), half = c >> 6, s = (c >> 4) & 3;
         st_agent((uint32_t*)(p + (((s & 1) * 2 + (lane & 1)) * 4 + half * 2 + (s >> 1)) * 16 + (c & 15)), v);
-        int sum = x0 + x1;
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
+        const int sum = wave_sum(x0 + x1);
         if (lane == 0) st_agent2((float*)(p + 256), am / kQMax, __int_as_float(sum));
     }
 }
@@ -118,7 +116,7 @@ __device__ __forceinline__ void store_tile64(char* tile, int R, int chunk, int u
     const int lane = lane_here();
     uint16_t lo;
     const uint16_t hi = split_bf16(y, lo);
-    const uint32_t got = __shfl_xor((uint32_t)(lane & 1 ? hi : lo), 1);
+    const uint32_t got = lane_xor<1>((uint32_t)(lane & 1 ? hi : lo));
     const uint32_t v = lane & 1 ? (got | (uint32_t)lo << 16) : ((uint32_t)hi | got << 16);
     const int c = upper * 64 + (lane & ~1);
     st_agent((uint32_t*)(tile + ((size_t)chunk * R + row) * kBfRow + (c >> 5) * 128 + (lane & 1) * 64 + (c & 31) * 2), v);
@@ -510,19 +508,10 @@ __device__ __forceinline__ void merge_row(const AttnArgs& a, int b, int h, int c
 #pragma unroll
         for (int i = 0; i < B; ++i) ov[i] = ld_agent2(pj + (size_t)min(i, cnt - 1) * stride);
         const float m = c < n ? ml.x : -INFINITY, l = c < n ? ml.y : 0.f;
-        float top = m;                        // maximum up to the end of the lane's eight
-#pragma unroll
-        for (int s = 1; s < 8; s <<= 1) top = fmaxf(top, __shfl_xor(top, s));
-#pragma unroll
-        for (int s = 8; s < 64; s <<= 1) {
-            const float t = __shfl_up(top, s);
-            if (lane >= s) top = fmaxf(top, t);
-        }
-        top = fmaxf(top, M);
-        float prev = __shfl_up(top, 8);       // and up to its start
-        if (lane < 8) prev = M;
+        float prev;                           // maximum up to the start and to the end of the lane's eight
+        const float top = wave_octet_max(m, M, prev);
         const float w = c < n ? exp2f(m - top) : 0.f, sc = exp2f(prev - top);
-        M = __shfl(top, 63);
+        M = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(top), 63));
         for (int k0 = 0; k0 < cnt; k0 += B) {
             if (k0) {
 #pragma unroll

@@ -18,15 +18,15 @@ __device__ __forceinline__ void qtile_group16(uint8_t* tile, float2* qscale, ATi
     float am = 0.f;
 #pragma unroll
     for (int e = 0; e < 8; ++e) am = fmaxf(am, fabsf(y[e]));
-    am = fmaxf(am, __shfl_xor(am, 1));
-    am = fmaxf(am, __shfl_xor(am, 2));
-    am = fmaxf(am, __shfl_xor(am, 4));
-    am = fmaxf(am, __shfl_xor(am, 8));
+    am = fmaxf(am, lane_xor<1>(am));
+    am = fmaxf(am, lane_xor<2>(am));
+    am = fmaxf(am, lane_xor<4>(am));
+    am = fmaxf(am, lane_xor<8>(am));
     int sum = live ? qtile_store8(tile, t, b, u, y, qtile_inv(am)) : 0;
-    sum += __shfl_xor(sum, 1);
-    sum += __shfl_xor(sum, 2);
-    sum += __shfl_xor(sum, 4);
-    sum += __shfl_xor(sum, 8);
+    sum += lane_xor<1>(sum);
+    sum += lane_xor<2>(sum);
+    sum += lane_xor<4>(sum);
+    sum += lane_xor<8>(sum);
     if (live && (threadIdx.x & 15) == 0) qscale[(size_t)(u >> 4) * (t.MB * 32) + b] = float2{am / kQMax, __int_as_float(sum)};
 }
 
@@ -348,8 +348,18 @@ __device__ __forceinline__ void better(Best& a, float v, int i) {
     if (v > a.v || (v == a.v && i < a.i)) a = Best{v, i};
 }
 __device__ __forceinline__ Best wave_best(Best a) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) better(a, __shfl_xor(a.v, o), __shfl_xor(a.i, o));
+    const auto exchange = [&](auto o) {
+        Best b = a;
+        swap_rows<decltype(o)::value>(a.v, b.v);
+        swap_rows<decltype(o)::value>(a.i, b.i);
+        better(a, b.v, b.i);
+    };
+    exchange(std::integral_constant<int, 32>{});
+    exchange(std::integral_constant<int, 16>{});
+    better(a, lane_xor<8>(a.v), lane_xor<8>(a.i));
+    better(a, lane_xor<4>(a.v), lane_xor<4>(a.i));
+    better(a, lane_xor<2>(a.v), lane_xor<2>(a.i));
+    better(a, lane_xor<1>(a.v), lane_xor<1>(a.i));
     return a;
 }
 // logits j0 .. j1 - 1 of a row by a workgroup of 256; the result is in thread 0

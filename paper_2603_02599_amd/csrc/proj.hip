@@ -62,7 +62,7 @@ __device__ __forceinline__ void swiglu_strip(const f32x16& acc, uint16_t* sw, in
     const bool up_lane = col >= 16;
 #pragma unroll
     for (int r = 0; r < 16; r += 2) {
-        const float got = __shfl_xor(up_lane ? acc[r] : acc[r + 1], 16);
+        const float got = lane_xor<16>(up_lane ? acc[r] : acc[r + 1]);
         const float g = up_lane ? got : acc[r], up = up_lane ? acc[r + 1] : got;
         const float y = g / (1.f + __expf(-g)) * up;
         const uint16_t hi = f32_to_bf16_bits(y);
@@ -1129,25 +1129,30 @@ struct F32Mat {
     float eps;
 };
 
-// Eight sums over the wave at once: three exchanges halve what a lane holds (4 + 2 + 1 shuffles), three more finish the
-// one it is left with, instead of six shuffles per sum.  Each is summed in the order of wave_sum.  Lane bits 5, 4, 3 name
+// Eight sums over the wave at once: three exchanges halve what a lane holds (4 + 2 + 1 values), three more finish the
+// one it is left with, instead of six per sum.  Each is summed in the order of wave_sum.  Lane bits 5, 4, 3 name
 // the sum a lane ends up with.
 template <int O, int C>
 __device__ __forceinline__ void wave_fold(float (&v)[8]) {
-    const bool up = threadIdx.x & O;
 #pragma unroll
     for (int j = 0; j < C; ++j) {
-        const float give = up ? v[j] : v[j + C], keep = up ? v[j + C] : v[j];
-        v[j] = keep + __shfl_xor(give, O);
+        if constexpr (O >= 16) {
+            swap_rows<O>(v[j], v[j + C]);
+            v[j] += v[j + C];
+        } else {
+            const bool up = threadIdx.x & O;
+            const float give = up ? v[j] : v[j + C], keep = up ? v[j + C] : v[j];
+            v[j] = keep + lane_xor<O>(give);
+        }
     }
 }
 __device__ __forceinline__ float wave_sum8(float (&v)[8]) {
     wave_fold<32, 4>(v);
     wave_fold<16, 2>(v);
     wave_fold<8, 1>(v);
-    float t = v[0] + __shfl_xor(v[0], 4);
-    t += __shfl_xor(t, 2);
-    return t + __shfl_xor(t, 1);
+    float t = v[0] + lane_xor<4>(v[0]);
+    t += lane_xor<2>(t);
+    return t + lane_xor<1>(t);
 }
 
 // the sum of row j's lanes, in lanes 8 j .. 8 j + 7
