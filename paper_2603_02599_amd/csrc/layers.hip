@@ -7,10 +7,11 @@
 // are separated by a barrier over the grid (2.6 us from the last arrival's stores to the next phase's loads), in front of which
 // every wave but one requests its first weights.  Bound by the weight stream in the long phases (gate/up 6.6 to 7 TB/s) and by
 // chains of small loads and stores around them.  Steps of 8 layers, launch per operation -> this (us), 1 / 8 / 16 requests of 200 to 1200
-// cached tokens: 8B shape bf16 1154 -> 923 / 1185 -> 1010 / 1217 -> 1106, 4-bit at 1 / 4 / 8 817 -> 678 / 835 -> 728 / 837 -> 771; hidden
-// 2048, ffn 8192 bf16 644 -> 441 / 666 -> 523 / 697 -> 650, 4-bit at 1 / 8 510 -> 400 / 538 -> 500; hidden 1024 440 -> 303 / 476 -> 370 /
-// 494 -> 475, 403 -> 316 / 430 -> 405.  4-bit at 12 / 16 requests (4 layers, 8B shape, two rows a wave) 549 -> 552 / 524 -> 553.  Hence
-// kLayersRows and kLayersRowsW4.
+// cached tokens: 8B shape bf16 1154 -> 923 / 1185 -> 1010 / 1217 -> 1106, 4-bit at 1 / 4 / 8 817 -> 620 / 835 -> 666 / 837 -> 696; hidden
+// 2048, ffn 8192 bf16 644 -> 441 / 666 -> 523 / 697 -> 650, 4-bit at 1 / 8 510 -> 360 / 538 -> 433; hidden 1024 440 -> 303 / 476 -> 370 /
+// 494 -> 475, 403 -> 290 / 430 -> 339.  Eight rows are what an operand of the 4-bit products holds beside their low planes; with
+// two rows a wave and operands of 16 4-bit steps at 12 / 16 requests (4 layers, 8B shape) took 549 -> 552 / 524 -> 553.  Hence kLayersRows and
+// kLayersRowsW4.
 //
 // Hand-over between workgroups.  Data that another workgroup reads in the same launch is stored through to memory (st_agent),
 // and its storer waits for vmcnt before it counts itself as arrived.  Readers either pass their caches by (ld_agent: the residual
@@ -38,10 +39,12 @@ typedef int i32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kWaves = 8;
 static_assert(kLayersRowsW4 <= kWaves && kLayersRows <= 2 * kWaves, "one row a wave with 4-bit weights, two otherwise");
+constexpr int kBlock = 128;        // columns of a block
 constexpr int kUnits = 256;         // work units a phase is cut into at most (one per compute unit)
 constexpr int kLayersPerLaunch = 48;
 constexpr int kBfRow = 512;         // bytes of 128 activations of one row: [32-wide step][plane][32] bf16
 constexpr int kQRow = 384;          // the same as 16-bit fixed point: [step of 64][plane][octet of 16] int8, then (scale, sum)
+constexpr int kQHalf = 256;         // each step of 64 with a scale of its own: [plane][octet of 16] int8, then (scale, sum)
 
 struct LayerPtrs {
     const void *g1, *g2, *qn, *kn, *bq, *bk, *bv;
@@ -122,6 +125,21 @@ __device__ __forceinline__ void store_tile64(char* tile, int R, int chunk, int u
     st_agent((uint32_t*)(tile + ((size_t)chunk * R + row) * kBfRow + (c >> 5) * 128 + (lane & 1) * 64 + (c & 31) * 2), v);
 }
 
+// The same as 16-bit fixed point, one from each lane: one step of a chunk, with its own scale.
+__device__ __forceinline__ void store_qhalf(char* tile, int R, int chunk, int step, int row, float y) {
+    const int lane = lane_here();
+    char* p = tile + (((size_t)chunk * R + row) * 2 + step) * kQHalf;
+    const float am = wave_max(fabsf(y));
+    const int x = (int)rintf(y * qtile_inv(am)), l = ((x + 128) & 255) - 128;
+    const uint32_t mine = (uint32_t)(((x - l) >> 8) & 255) | (uint32_t)(l & 255) << 16;
+    const uint32_t next = lane_xor<1>(mine), two = lane & 1 ? next | mine << 8 : mine | next << 8;   // planes of two lanes, of four
+    const uint32_t more = lane_xor<2>(two), a = lane & 2 ? more : two, b = lane & 2 ? two : more;
+    if ((lane & 3) < 2)
+        st_agent((uint32_t*)(p + (lane & 1) * 64 + (lane & 48) + (lane & 12)), lane & 1 ? a >> 16 | (b & 0xffff0000u) : (a & 0xffffu) | b << 16);
+    const int sum = wave_sum(x);
+    if (lane == 0) st_agent2((float*)(p + 128), am / kQMax, __int_as_float(sum));
+}
+
 // 128 columns of one row of the residual stream: x += add; the row's sum of squares over them; x * gain as the next
 // projection's input (the norm's 1 / rms is a factor of the row that the projection applies to its result).
 template <bool W4>
@@ -176,7 +194,14 @@ struct Shared {
 // Requested earlier, behind the products by waves that take no part in what follows them, they cost more than they gained (8B
 // shape, 1 / 16 requests bf16, 5 requests 4-bit: 1054 / 1489 / 946 us a step): a phase ends with a chain of small loads and
 // stores (slabs, arrivals, the residual stream), and under the weights' traffic each of them takes 3 us instead of 1.
-// Arrivals counted by wave instead of by workgroup: 938 / 1329 / 835.
+// Arrivals counted by wave instead of by workgroup: 938 / 1329 / 835.  A block's rows finished by all its workgroups, each polling
+// for the others, instead of by the last to arrive: 909 / 1275 / 785 against 903 / 1193 / 726, the polls hold up the arrivals.
+//
+// 4-bit weights: the vector ALU is busiest (widening the codes, scales and zero points of every sum), so high and low planes of eight rows
+// share a 16-row operand: half the matrix instructions, loads of activations and sums to scale.  Gate/up is not split along k, its
+// blocks are every other strip, the columns of one 64-wide step of the down projection's groups, which has its own scale (finer
+// than a scale per group, so nothing is lost): slabs and an arrival less, twice the sums to scale in the down projection.  8 layers
+// of the 8B shape, 5 requests: 726 -> 678 us (a layer's gate/up 20.7 -> 15.5, down 10.6 -> 10.0).
 template <bool W4>
 struct Ring {
     static constexpr int PD = 4, NS = W4 ? 4 : 8;   // steps and 16-column strips
@@ -184,8 +209,8 @@ struct Ring {
     uint32_t sz[W4 ? PD : 1][W4 ? NS : 1];
 };
 
-// this wave's part of unit u
-template <bool W4, int CB>
+// this wave's part of unit u.  ALT: a block is every other strip of 32 columns.
+template <bool W4, int CB, bool ALT>
 struct Part {
     static constexpr int CW = W4 ? CB / 64 : 1, KW = kWaves / CW, AHEAD = Ring<W4>::PD;
     const char *W, *SZ;             // the same for the whole wave; a lane's part of an address has 32 bits
@@ -202,13 +227,16 @@ struct Part {
         const int k0 = steps * split / m.S, n = steps * (split + 1) / m.S - k0;
         a0 = k0 + n * kw / KW;
         a1 = k0 + n * (kw + 1) / KW;
+        const int s0 = ALT ? (blk >> 1) * (CB / 16) + (blk & 1) + cw * 4 : blk * (CB / 32) + cw * 2;
         strip = (size_t)kch * (W4 ? 2048 : 8192);
-        W = m.w + (size_t)layer * m.w_step + (size_t)(blk * (CB / 32) + cw * 2) * strip;
+        W = m.w + (size_t)layer * m.w_step + s0 * strip;
+        if (ALT) strip *= 2;
         if constexpr (W4) {
             w_lane = ((o & 1) * 64 + (o >> 1) * 32 + n16) * 16;
             s_lane = n16 * 4;
             sz_strip = (size_t)(s_only ? (kch + 1) >> 1 : kch) * 128;
-            SZ = m.sz + (size_t)layer * m.sz_step + (size_t)(blk * (CB / 32) + cw * 2) * sz_strip;
+            SZ = m.sz + (size_t)layer * m.sz_step + s0 * sz_strip;
+            if (ALT) sz_strip *= 2;
         } else {
             w_lane = (o * 64 + n16) * 16;
         }
@@ -234,60 +262,71 @@ struct Part {
     }
 };
 
-// activations of one step: the fragments of a 16-row operand, and with 4-bit weights the rows' (scale, sum) pairs
-template <bool W4>
+// Activations of one step.  bf16: a 16-row operand for each plane.  4-bit: eight rows at most, so the operand's rows 0 to 7 are the rows'
+// high planes and 8 to 15 their low planes, one for each 64 along k; with it the (scale, sum) pairs of the two rows that a lane finishes
+// (HALF: for each 64 along k).
+template <bool W4, bool HALF>
 struct Acts {
-    u32x4 f[W4 ? 4 : 2];
-    float2 sx[W4 ? 4 : 1];
+    u32x4 f[2];
+    float2 sx[HALF ? 2 : 1][W4 ? 2 : 1];
 };
 
-template <bool W4, bool STREAM, int CB>
-__device__ __forceinline__ void unit_sums(const Part<W4, CB>& p, Ring<W4>& ring, const char* A, int R, float* red) {
-    constexpr int NS = Ring<W4>::NS, PD = Ring<W4>::PD, PA = W4 ? 2 : PD, LDR = CB + 4;   // activations PA steps ahead
+template <bool W4, bool STREAM, int CB, bool ALT, bool HALF>
+__device__ __forceinline__ void unit_sums(const Part<W4, CB, ALT>& p, Ring<W4>& ring, const char* A, int R, float* red) {
+    constexpr int NS = Ring<W4>::NS, PD = Ring<W4>::PD, PA = PD, LDR = CB + 4;   // activations PA steps ahead
+    constexpr int NV = W4 ? 2 : 4, ROW = !W4 ? kBfRow : HALF ? 2 * kQHalf : kQRow;
     const int lane = lane_here(), n16 = lane & 15, o = lane >> 4, a0 = p.a0, a1 = p.a1;
-    const uint32_t a_lane = min(n16, R - 1) * (W4 ? kQRow : kBfRow) + o * 16;
-    uint32_t x_lane[4];
+    const uint32_t a_lane = W4 ? min(n16 & 7, R - 1) * ROW + (n16 >> 3) * 64 + o * 16 : min(n16, R - 1) * ROW + o * 16;
+    const auto row = [&](int i) { return W4 ? 4 * (o & 1) + 2 * i + (o >> 1) : 4 * o + i; };   // of this lane's i-th sum
+    uint32_t x_lane[2];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) x_lane[r] = min(4 * o + r, R - 1) * kQRow + 256;
-    Acts<W4> ar[PA];
+    for (int i = 0; i < 2; ++i) x_lane[i] = min(row(i), R - 1) * ROW + (HALF ? 128 : 256);
+    Acts<W4, HALF> ar[PA];
     const auto load_a = [&](int slot, int ks) {
         if constexpr (W4) {
-            const char* q = A + (size_t)ks * R * kQRow;
+            const char* q = A + (size_t)ks * R * ROW;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) ar[slot % PA].f[i] = *(const u32x4*)(q + i * 64 + a_lane);
+            for (int m = 0; m < 2; ++m) ar[slot % PA].f[m] = *(const u32x4*)(q + m * (HALF ? kQHalf : 128) + a_lane);
 #pragma unroll
-            for (int r = 0; r < 4; ++r) ar[slot % PA].sx[r] = *(const float2*)(q + x_lane[r]);
+            for (int m = 0; m < (HALF ? 2 : 1); ++m)
+#pragma unroll
+                for (int i = 0; i < 2; ++i) ar[slot % PA].sx[m][i] = *(const float2*)(q + m * kQHalf + x_lane[i]);
         } else {
             const char* q = A + (size_t)(ks >> 2) * R * kBfRow + (ks & 3) * 128 + a_lane;
             ar[slot % PA].f[0] = *(const u32x4*)q;
             ar[slot % PA].f[1] = *(const u32x4*)(q + 64);
         }
     };
-    f32x4 acc[NS];
+    typedef float Sums __attribute__((ext_vector_type(NV)));
+    Sums acc[NS];
 #pragma unroll
-    for (int s = 0; s < NS; ++s) acc[s] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int s = 0; s < NS; ++s) acc[s] = Sums(0.f);
     const auto compute = [&](int slot, int ks) {
         if constexpr (W4) {   // the arithmetic of proj_w4_kernel
 #pragma unroll
             for (int s = 0; s < NS; ++s) {
-                i32x4 ih = {0, 0, 0, 0}, il = {0, 0, 0, 0};
-#pragma unroll
-                for (int m = 0; m < 2; ++m) {
-                    const uint32_t wa = ring.w[slot][s][2 * m], wb = ring.w[slot][s][2 * m + 1];
-                    const i32x4 b = {(int)(wa & 0x0F0F0F0Fu), (int)((wa >> 4) & 0x0F0F0F0Fu), (int)(wb & 0x0F0F0F0Fu),
-                                     (int)((wb >> 4) & 0x0F0F0F0Fu)};
-                    ih = __builtin_amdgcn_mfma_i32_16x16x64_i8(__builtin_bit_cast(i32x4, ar[slot % PA].f[2 * m]), b, ih, 0, 0, 0);
-                    il = __builtin_amdgcn_mfma_i32_16x16x64_i8(__builtin_bit_cast(i32x4, ar[slot % PA].f[2 * m + 1]), b, il, 0, 0, 0);
-                }
                 // scale-only layout: this group's half of the dword; the zero point is 8 everywhere
                 const uint32_t szg = p.s_only ? (((ring.sz[slot][s] >> (16 * (ks & 1))) & 0xffffu) | 0x48000000u) : ring.sz[slot][s];
                 const __half2 h2 = __builtin_bit_cast(__half2, szg);
                 const float sc = __low2float(h2);
                 const int nzi = -(int)__high2float(h2);
+                i32x4 d = {0, 0, 0, 0};   // lanes 0 to 31: sums of the high plane, rows 4 o + r; the others: those rows' of the low plane
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int tot = (ih[r] << 8) + il[r] + __mul24(nzi, __float_as_int(ar[slot % PA].sx[r].y));
-                    acc[s][r] = fmaf((float)tot, sc * ar[slot % PA].sx[r].x, acc[s][r]);
+                for (int m = 0; m < 2; ++m) {
+                    const uint32_t wa = ring.w[slot][s][2 * m], wb = ring.w[slot][s][2 * m + 1];
+                    const i32x4 b = {(int)(wa & 0x0F0F0F0Fu), (int)((wa >> 4) & 0x0F0F0F0Fu), (int)(wb & 0x0F0F0F0Fu),
+                                     (int)((wb >> 4) & 0x0F0F0F0Fu)};
+                    d = __builtin_amdgcn_mfma_i32_16x16x64_i8(__builtin_bit_cast(i32x4, ar[slot % PA].f[m]), b, d, 0, 0, 0);
+                    if (!HALF && m == 0) continue;
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) {
+                        int hi = d[2 * i], lo = d[2 * i + 1];
+                        swap_rows<32>(hi, lo);   // both planes of row 2 i in the lower lanes, of row 2 i + 1 in the upper ones
+                        const float2 sx = ar[slot % PA].sx[HALF ? m : 0][i];
+                        const int tot = (hi << 8) + lo + __mul24(nzi, __float_as_int(sx.y));
+                        acc[s][i] = fmaf((float)tot, sc * sx.x, acc[s][i]);
+                    }
+                    if (HALF) d = i32x4{0, 0, 0, 0};
                 }
             }
         } else {
@@ -324,19 +363,19 @@ __device__ __forceinline__ void unit_sums(const Part<W4, CB>& p, Ring<W4>& ring,
             }
     }
 #pragma unroll
-    for (int r = 0; r < 4; ++r)
-        if (4 * o + r < R) {
+    for (int i = 0; i < NV; ++i)
+        if (row(i) < R) {
 #pragma unroll
-            for (int s = 0; s < NS; ++s) red[(p.kw * 16 + 4 * o + r) * LDR + p.cw * 64 + s * 16 + n16] = acc[s][r];
+            for (int s = 0; s < NS; ++s) red[(p.kw * 16 + row(i)) * LDR + p.cw * 64 + s * 16 + n16] = acc[s][i];
         }
 }
 
 // What happens to a unit's sums, NR rows a wave.  With a split along k the workgroup that is the last of a block to arrive adds the
 // slabs up, in their order.
-template <bool W4, int CB, int NC, int NR, class Col, class Early, class Done>
+template <int KW, int CB, int NC, int NR, class Col, class Early, class Done>
 __device__ __forceinline__ void unit_finish(const LayersArgs& a, const MatP& m, int layer, int u, const float* red, Shared& sh, Col col, Early early,
                                             Done done) {
-    constexpr int KW = Part<W4, CB>::KW, LDR = CB + 4;
+    constexpr int LDR = CB + 4;
     const int lane = lane_here(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), R = a.R;
     const int blk = u % m.nblk, split = u / m.nblk;
     const bool mine = wave < R;
@@ -369,7 +408,7 @@ __device__ __forceinline__ void unit_finish(const LayersArgs& a, const MatP& m, 
             for (int i = 0; i < NR; ++i)
                 if (wave + i * kWaves < R) {
 #pragma unroll
-                    for (int c = 0; c < NC; ++c) st_agent(sl + split * step + row[i] * CB + col(lane, c), v[i][c]);
+                    for (int c = 0; c < NC; c += 2) st_agent2(sl + split * step + row[i] * CB + lane * NC + c, v[i][c], v[i][c + 1]);
                 }
             asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
         }
@@ -386,20 +425,20 @@ __device__ __forceinline__ void unit_finish(const LayersArgs& a, const MatP& m, 
 #pragma unroll
             for (int c = 0; c < NC; ++c) v[i][c] = 0.f;
         for (int s0 = 0; s0 < m.S; s0 += 8) {
-            float t[NR][8][NC];
+            float2 t[NR][8][NC / 2];
 #pragma unroll
             for (int i = 0; i < NR; ++i)
 #pragma unroll
                 for (int s = 0; s < 8; ++s)
 #pragma unroll
-                    for (int c = 0; c < NC; ++c) t[i][s][c] = ld_agent(sl + min(s0 + s, m.S - 1) * step + row[i] * CB + col(lane, c));
+                    for (int c = 0; c < NC; c += 2) t[i][s][c / 2] = ld_agent2(sl + min(s0 + s, m.S - 1) * step + row[i] * CB + lane * NC + c);
 #pragma unroll
             for (int i = 0; i < NR; ++i)
 #pragma unroll
                 for (int s = 0; s < 8; ++s)
                     if (s0 + s < m.S) {
 #pragma unroll
-                        for (int c = 0; c < NC; ++c) v[i][c] += t[i][s][c];
+                        for (int c = 0; c < NC; ++c) v[i][c] += c & 1 ? t[i][s][c / 2].y : t[i][s][c / 2].x;
                     }
         }
     }
@@ -412,26 +451,27 @@ __device__ __forceinline__ void unit_finish(const LayersArgs& a, const MatP& m, 
 
 // A phase: all units of one matrix, false where the launch is to be left.  wait() is the barrier in front of it, col(lane, i) names the NC
 // columns of the block that a lane finishes, early(blk, row) loads what done(blk, row, early's result, sums) wants beside the sums.
-template <bool W4, bool STREAM, int CB, int NC, class Wait, class Col, class Early, class Done>
+template <bool W4, bool STREAM, int NC, bool ALT, bool HALF, class Wait, class Col, class Early, class Done>
 __device__ __forceinline__ bool matrix_phase(const LayersArgs& a, const MatP& m, int layer, const char* A, float* red, Shared& sh, Wait wait, Col col,
                                              Early early, Done done) {
+    constexpr int CB = kBlock;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), units = m.nblk * m.S;
     if ((int)blockIdx.x >= units) {
         wait();
         return !__builtin_amdgcn_readfirstlane(lds_word(&sh.given_up));
     }
     for (int u = blockIdx.x; u < units; u += gridDim.x) {
-        const Part<W4, CB> p(m, layer, u, a.s_only);
+        const Part<W4, CB, ALT> p(m, layer, u, a.s_only);
         Ring<W4> ring;
         if (wave) p.template prefetch<STREAM>(ring);
         if (u == (int)blockIdx.x) wait();
         else __syncthreads();           // the unit before is done with LDS
         if (!wave) p.template prefetch<STREAM>(ring);
         const int gone = lds_word(&sh.given_up);
-        unit_sums<W4, STREAM, CB>(p, ring, A, a.R, red);
+        unit_sums<W4, STREAM, CB, ALT, HALF>(p, ring, A, a.R, red);
         if (__builtin_amdgcn_readfirstlane(gone)) return false;   // before the first store: others may still read what lies there
-        if (W4 || a.R <= kWaves) unit_finish<W4, CB, NC, 1>(a, m, layer, u, red, sh, col, early, done);
-        else unit_finish<W4, CB, NC, kLayersRows / kWaves>(a, m, layer, u, red, sh, col, early, done);
+        if (W4 || a.R <= kWaves) unit_finish<Part<W4, CB, ALT>::KW, CB, NC, 1>(a, m, layer, u, red, sh, col, early, done);
+        else unit_finish<Part<W4, CB, ALT>::KW, CB, NC, kLayersRows / kWaves>(a, m, layer, u, red, sh, col, early, done);
     }
     return true;
 }
@@ -569,14 +609,13 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 
             arrive();
         }
     }
-    constexpr int kGuBlock = W4 ? 256 : 128;   // gate/up columns of a block
     const auto pair = [](int lane, int c) { return 2 * lane + c; };
     for (; l < l1; ++l) {
         {   // q/k/v: a block is one head
             const LayersArgs& a = args_here();
             const bool again = l >= a.ring && l % a.ring == 0;   // the tiles of the last `ring` layers are written a second time
             const auto wait_fresh = [&]() { wait_for(again); };
-            if (!matrix_phase<W4, STREAM, 128, 2>(a, a.qkv, l, a.t1 + (size_t)(l % a.ring) * a.h_step, red, sh, wait_fresh, [](int lane, int c) { return lane + 64 * c; },
+            if (!matrix_phase<W4, STREAM, 2, false, false>(a, a.qkv, l, a.t1 + (size_t)(l % a.ring) * a.h_step, red, sh, wait_fresh, [](int lane, int c) { return lane + 64 * c; },
                                              [&](int, int row) { return rope_in(args_here(), row); },
                                              [&](int blk, int row, const RopeIn& in, const float (&v)[2]) {
                                                  const LayersArgs& b = args_here();
@@ -614,7 +653,7 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 
         arrive();
         {
             const LayersArgs& a = args_here();
-            if (!matrix_phase<W4, STREAM, 128, 2>(a, a.o, l, a.ta + (size_t)(l % a.ring) * a.a_step, red, sh, wait, pair,
+            if (!matrix_phase<W4, STREAM, 2, false, false>(a, a.o, l, a.ta + (size_t)(l % a.ring) * a.a_step, red, sh, wait, pair,
                                              [&](int blk, int row) {
                                                  const LayersArgs& b = args_here();
                                                  return residual_in(b, blk, row, b.lp[l - b.l0].g2);
@@ -628,39 +667,26 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 
         arrive();
         {
             const LayersArgs& a = args_here();
-            if constexpr (W4) {   // a block is a group of the down projection: 128 gate and 128 up columns, 16 and 16 in turn
-                if (!matrix_phase<W4, STREAM, kGuBlock, 4>(a, a.gu, l, a.t2 + (size_t)(l % a.ring) * a.h_step, red, sh, wait,
-                                                   [](int lane, int c) { return (lane >> 3) * 32 + (2 * lane & 15) + (c >> 1) * 16 + (c & 1); },
-                                                   [&](int, int row) {
-                                                       const LayersArgs& b = args_here();
-                                                       return row_squares(b, b.ssq2, row);
-                                                   },
-                                                   [&](int blk, int row, float squares, const float (&v)[4]) {
-                                                       const LayersArgs& b = args_here();
-                                                       const float ri = row_rinv(b, squares), g0 = v[0] * ri, g1 = v[1] * ri;
-                                                       store_tile128<true>(b.tu + (size_t)(l % b.ring) * b.u_step, b.R, blk, row, g0 / (1.f + __expf(-g0)) * (v[2] * ri),
-                                                                           g1 / (1.f + __expf(-g1)) * (v[3] * ri));
-                                                   }))
-                    break;
-            } else {              // 64 gate and 64 up columns
-                if (!matrix_phase<W4, STREAM, kGuBlock, 2>(a, a.gu, l, a.t2 + (size_t)(l % a.ring) * a.h_step, red, sh, wait,
-                                                    [](int lane, int c) { return (lane >> 4) * 32 + (lane & 15) + c * 16; },
-                                                    [&](int, int row) {
-                                                        const LayersArgs& b = args_here();
-                                                        return row_squares(b, b.ssq2, row);
-                                                    },
-                                                    [&](int blk, int row, float squares, const float (&v)[2]) {
-                                                        const LayersArgs& b = args_here();
-                                                        const float ri = row_rinv(b, squares), g = v[0] * ri;
-                                                        store_tile64(b.tu + (size_t)(l % b.ring) * b.u_step, b.R, blk >> 1, blk & 1, row, g / (1.f + __expf(-g)) * (v[1] * ri));
-                                                    }))
-                    break;
-            }
+            // A block: 64 gate and 64 up columns, 16 and 16 in turn; with 4-bit weights those of one step of the down projection's groups
+            if (!matrix_phase<W4, STREAM, 2, W4, false>(a, a.gu, l, a.t2 + (size_t)(l % a.ring) * a.h_step, red, sh, wait,
+                                                        [](int lane, int c) { return (lane >> 4) * 32 + (lane & 15) + c * 16; },
+                                                        [&](int, int row) {
+                                                            const LayersArgs& b = args_here();
+                                                            return row_squares(b, b.ssq2, row);
+                                                        },
+                                                        [&](int blk, int row, float squares, const float (&v)[2]) {
+                                                            const LayersArgs& b = args_here();
+                                                            const float ri = row_rinv(b, squares), g = v[0] * ri, y = g / (1.f + __expf(-g)) * (v[1] * ri);
+                                                            char* t = b.tu + (size_t)(l % b.ring) * b.u_step;
+                                                            if constexpr (W4) store_qhalf(t, b.R, blk >> 1, blk & 1, row, y);
+                                                            else store_tile64(t, b.R, blk >> 1, blk & 1, row, y);
+                                                        }))
+                break;
         }
         arrive();
         {
             const LayersArgs& a = args_here();
-            if (!matrix_phase<W4, STREAM, 128, 2>(a, a.down, l, a.tu + (size_t)(l % a.ring) * a.u_step, red, sh, wait, pair,
+            if (!matrix_phase<W4, STREAM, 2, false, W4>(a, a.down, l, a.tu + (size_t)(l % a.ring) * a.u_step, red, sh, wait, pair,
                                              [&](int blk, int row) {
                                                  const LayersArgs& b = args_here();
                                                  return residual_in(b, blk, row, l + 1 == b.n_layers ? nullptr : l + 1 < b.l1 ? b.lp[l + 1 - b.l0].g1 : b.g1_next);
@@ -685,12 +711,13 @@ static size_t up256(size_t v) { return (v + 255) / 256 * 256; }
 // Column blocks and split along k.  As many units as there are workgroups at most; every wave that shares k gets a step.
 // A row's sums depend on the matrix alone.  Widths whose blocks fill the chip badly lose part of the gain, not all of it (4 layers, launch
 // per operation -> this, us): 296 gate/up blocks on 256 workgroups (hidden 3584, ffn 18 944) at 1 / 16 requests 577 -> 489 / 593 -> 591;
-// 136 of 4-bit weights (hidden 5120, ffn 17 408) at 1 / 8 468 -> 399 / 473 -> 434, bf16 at 1 / 16 724 -> 644 / 747 -> 746; 14B shape 847 ->
+// 272 of 4-bit weights (hidden 5120, ffn 17 408) at 1 / 8 468 -> 399 / 473 -> 434 (136 of twice the columns;
+// on longer requests those 395 / 467, these 382 / 459), bf16 at 1 / 16 724 -> 644 / 747 -> 746; 14B shape 847 ->
 // 697 / 886 -> 780, 4-bit 613 -> 554 / 634 -> 600; hidden 8192, ffn 28 672 1351 -> 1258 / 1376 -> 1346, 4-bit 706 -> 607 / 740 -> 655.
-static void cut(MatP& m, int N, int K, int cb, bool w4) {
+static void cut(MatP& m, int N, int K, bool w4) {
     m.K = K;
-    m.nblk = N / cb;
-    m.S = max(1, min(kUnits / m.nblk, w4 ? K / (128 * (kWaves / (cb / 64))) : K / (32 * kWaves)));
+    m.nblk = N / kBlock;
+    m.S = max(1, min(kUnits / m.nblk, w4 ? K / (128 * (kWaves / (kBlock / 64))) : K / (32 * kWaves)));
 }
 
 static size_t n_counters(const sun_model_cfg& c) {
@@ -718,13 +745,13 @@ static LayersLayout layers_layout(const sun_model_cfg& c, int rows, bool w4, siz
     size_t slab = 0;
     for (int i = 0; i < 4; ++i) {
         MatP m{};
-        cut(m, Ns[i], Ks[i], w4 && i == 2 ? 256 : 128, w4);
+        cut(m, Ns[i], Ks[i], w4);
         if (m.S > 1) slab = max(slab, (size_t)m.S * rows * Ns[i] * 4);
     }
     L.slab = take(slab);
     L.h_step = up256((size_t)c.hidden / 128 * rows * row);
     L.a_step = up256(QD / 128 * rows * row);
-    L.u_step = up256((size_t)c.ffn / 128 * rows * row);
+    L.u_step = up256((size_t)c.ffn / 128 * rows * (w4 ? 2 * kQHalf : kBfRow));
     L.q_step = up256(QD * rows * 4);
     const size_t layer = 2 * L.h_step + L.a_step + L.u_step + L.q_step;
     L.ring = (int)min((size_t)c.n_layers, bytes > off ? (bytes - off) / layer : 0);
@@ -809,22 +836,22 @@ hipError_t launch_layers(const KvPool& pool, const Weights& W, int rows, float* 
     const bool w4 = W.quant;
     LayersArgs a{};
     uint32_t* arrived = (uint32_t*)base + kCounters * 32;
-    const auto mat = [&](const Mat LayerW::*which, int cb) {
+    const auto mat = [&](const Mat LayerW::*which) {
         const Mat &m0 = W.layers[0].*which, &m1 = W.layers[c.n_layers > 1 ? 1 : 0].*which;
         MatP m{};
         m.w = (const char*)m0.w;
         m.w_step = (const char*)m1.w - (const char*)m0.w;   // the packed layers lie one like the other
         m.sz = (const char*)m0.sz;
         m.sz_step = w4 ? (const char*)m1.sz - (const char*)m0.sz : 0;
-        cut(m, m0.N, m0.K, cb, w4);
+        cut(m, m0.N, m0.K, w4);
         m.arrived = arrived;
         arrived += m.nblk;
         return m;
     };
-    a.qkv = mat(&LayerW::qkv, 128);
-    a.o = mat(&LayerW::o, 128);
-    a.gu = mat(&LayerW::gu, w4 ? 256 : 128);
-    a.down = mat(&LayerW::down, 128);
+    a.qkv = mat(&LayerW::qkv);
+    a.o = mat(&LayerW::o);
+    a.gu = mat(&LayerW::gu);
+    a.down = mat(&LayerW::down);
     a.attn = make_attn_args(pool, 0, plan, nullptr, page_tables, max_pages, seq_lens, 1, rows);
     if (total_chunks_hint >= 0 && full_chunks_hint >= 0) {
         a.attn.n_full_items = full_chunks_hint * c.n_kv_heads;
