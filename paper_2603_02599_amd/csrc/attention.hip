@@ -184,6 +184,30 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     attn_split_items<D, G, false>(a, blockIdx.x, gridDim.x, threadIdx.x & 63, &list_cursor, [] {});
 }
 
+// One dim's share of a page: acc + p[0] v[0] + ... in the order of the tokens, the first `count` of them (slots past the end may hold
+// anything), vnew in the place of token `fresh`.  All but the last page of a chunk take the sixteen without a question; with
+// one asked at every token, and its p read from LDS behind it, 64 tokens took 3 us.
+__device__ __forceinline__ float page_dot(float acc, const float* p, const u32x4 (&v)[2], int count, int fresh, float vnew) {
+    f32x4 q[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) q[i] = reinterpret_cast<const f32x4*>(p)[i];
+    const auto value = [&](int e) {
+        const uint32_t w = v[e >> 3][(e & 7) >> 1];
+        return e & 1 ? bf16_hi(w) : bf16_lo(w);
+    };
+    if (count >= kPageTokens && fresh >= kPageTokens) {
+#pragma unroll
+        for (int e = 0; e < kPageTokens; ++e) acc = fmaf(q[e >> 2][e & 3], value(e), acc);
+    } else {
+#pragma unroll
+        for (int e = 0; e < kPageTokens; ++e) {
+            const float more = fmaf(q[e >> 2][e & 3], e == fresh ? vnew : value(e), acc);
+            acc = e < count ? more : acc;
+        }
+    }
+    return acc;
+}
+
 // ---------------------------------------------------------------------------------
 // split kernel, fp32 vector-ALU variant (parity configuration); a workgroup of four waves per item
 // ---------------------------------------------------------------------------------
@@ -261,13 +285,10 @@ __global__ __launch_bounds__(256) void attn_split_f32_kernel(AttnArgs a, int G) 
                         v[i][1] = vr[1];
                     }
 #pragma unroll
-                    for (int i = 0; i < 4; ++i)
-#pragma unroll
-                        for (int e = 0; e < kPageTokens; ++e) {
-                            const int tt = (p0 + i) * kPageTokens + e;
-                            const uint32_t w = v[i][e >> 3][(e & 7) >> 1];
-                            if (tt < cnt) acc = fmaf(sc[g][tt], e & 1 ? bf16_hi(w) : bf16_lo(w), acc);  // slots past the end may hold anything
-                        }
+                    for (int i = 0; i < 4; ++i) {
+                        const int from = (p0 + i) * kPageTokens;
+                        if (from < cnt) acc = page_dot(acc, &sc[g][from], v[i], cnt - from, kPageTokens, 0.f);
+                    }
                 }
                 pbase[(size_t)g * (D + 2) + j] = acc;
             }
@@ -278,7 +299,8 @@ __global__ __launch_bounds__(256) void attn_split_f32_kernel(AttnArgs a, int G) 
 // fp32, short tables: rotation, append, attention over all chunks and their merge in one launch
 // ---------------------------------------------------------------------------------
 // Bound by latency like the launches it replaces (rope_append_kernel, attn_split_f32_kernel, attn_combine_kernel: three of
-// a layer's seven): a workgroup per request and KV head takes the new position's heads out of the q/k/v product, appends K
+// a layer's seven); with a wave's first keys and values requested in front of everything else (page_dot has the other half) a launch
+// of the tiny configuration takes 6.4 us where it took 8.8.  A workgroup per request and KV head takes the new position's heads out of the q/k/v product, appends K
 // and V, walks the request's chunks (a wave per chunk and query head, partial results in LDS) and merges them.  Every sum has
 // the order it has there, so the results are theirs bit for bit.  Tiny configuration, three launches -> this (us a step): 8 requests of 16 /
 // 100 / 250 / 500 / 900 cached tokens 78.7 / 79.2 / 82.2 / 83.4 / 83.4 -> 68.7 / 71.4 / 76.6 / 86.2 / 106.7, 48 of 250 105 -> 100,
@@ -311,6 +333,33 @@ __global__ __launch_bounds__(512) void attn_short_f32_kernel(ShortArgs a) {
     const int32_t* pt = a.page_tables + (size_t)b * a.max_pages;
     const auto page_of = [&](int p) { return min(max(pt[p], 0), a.n_pages - 1); };
     uint16_t *kb = a.kbase + (int64_t)kh * a.k_head, *vb = a.vbase + (int64_t)kh * a.v_head;
+    int n_full, n_small, ch;
+    attn_chunking(n, a.batch, a.Hkv, n_full, n_small, ch);
+    const int nc = n_full + n_small;
+    // a wave's first keys and values depend on the tables alone: they are requested in front of the new position's heads
+    const auto chunk_from = [&](int ci) { return ci < n_full ? ci * ch : n_full * ch + (ci - n_full) * kAttnSmall; };
+    const auto chunk_to = [&](int ci) { return ci < n_full ? (ci + 1) * ch : min(n, chunk_from(ci) + kAttnSmall); };
+    const auto load_k = [&](u32x4 (&kw)[D / 8], int pos) {
+        const u32x4* kr = reinterpret_cast<const u32x4*>(kb + (int64_t)page_of(pos / kPageTokens) * a.k_page + (pos % kPageTokens) * D);
+#pragma unroll
+        for (int i = 0; i < D / 8; ++i) kw[i] = kr[i];
+    };
+    const auto load_v = [&](u32x4 (&v)[4][2], int t0, int t1, int p0, int j) {   // four pages; past the chunk the last one again
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int pg = min(p0 + i, (t1 - t0 - 1) / kPageTokens);
+            const u32x4* vr = reinterpret_cast<const u32x4*>(vb + (int64_t)page_of(t0 / kPageTokens + pg) * a.v_page + j * kPageTokens);
+            v[i][0] = vr[0];
+            v[i][1] = vr[1];
+        }
+    };
+    constexpr bool EARLY = D <= 64;   // twice the registers do not fit
+    u32x4 k_first[D / 8], v_first[4][2];
+    if (EARLY && wave < nc * G) {
+        const int t0 = chunk_from(wave / G), t1 = chunk_to(wave / G);
+        load_k(k_first, min(t0 + lane, t1 - 1));
+        load_v(v_first, t0, t1, 0, lane);
+    }
     for (int t = wave; t < G + 2; t += W) {                 // a wave per head; lane j holds elements j and j + D / 2
         const int hh = t < G ? kh * G + t : t == G ? a.Hq + kh : a.Hq + a.Hkv + kh, j = lane;
         const bool act = j < half;
@@ -359,23 +408,25 @@ __global__ __launch_bounds__(512) void attn_short_f32_kernel(ShortArgs a) {
             }
         }
     }
-    int n_full, n_small, ch;
-    attn_chunking(n, a.batch, a.Hkv, n_full, n_small, ch);
-    const int nc = n_full + n_small;
     __syncthreads();
     for (int task = wave; task < nc * G; task += W) {       // a wave per chunk and query head
         const int ci = task / G, g = task % G;
-        const int t0 = ci < n_full ? ci * ch : n_full * ch + (ci - n_full) * kAttnSmall, t1 = ci < n_full ? t0 + ch : min(n, t0 + kAttnSmall);
-        const int cnt = t1 - t0;
+        const int t0 = chunk_from(ci), t1 = chunk_to(ci), cnt = t1 - t0;
         float* s = sc[wave];
         float mx = -INFINITY;
         for (int tt = lane; tt < cnt; tt += 64) {           // scores: lane <-> token; the new one's K comes from LDS
             const int pos = t0 + tt;
-            const u32x4* kr = pos == L ? reinterpret_cast<const u32x4*>(kv[0])
-                                       : reinterpret_cast<const u32x4*>(kb + (int64_t)page_of(pos / kPageTokens) * a.k_page + (pos % kPageTokens) * D);
             u32x4 kw[D / 8];
+            if (EARLY && task == wave && tt == lane) {
 #pragma unroll
-            for (int i = 0; i < D / 8; ++i) kw[i] = kr[i];
+                for (int i = 0; i < D / 8; ++i) kw[i] = k_first[i];
+            } else {
+                load_k(kw, pos);
+            }
+            if (pos == L) {
+#pragma unroll
+                for (int i = 0; i < D / 8; ++i) kw[i] = reinterpret_cast<const u32x4*>(kv[0])[i];
+            }
             const f32x4* qg = reinterpret_cast<const f32x4*>(qs + g * D);
             float acc = 0.f;
 #pragma unroll
@@ -410,22 +461,20 @@ __global__ __launch_bounds__(512) void attn_short_f32_kernel(ShortArgs a) {
             float acc = 0.f;
             for (int p0 = 0; p0 * kPageTokens < cnt; p0 += 4) {
                 u32x4 v[4][2];
+                if (EARLY && task == wave && !p0 && j == lane) {
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int pg = min(p0 + i, (cnt - 1) / kPageTokens);
-                    const u32x4* vr = reinterpret_cast<const u32x4*>(vb + (int64_t)page_of(t0 / kPageTokens + pg) * a.v_page + j * kPageTokens);
-                    v[i][0] = vr[0];
-                    v[i][1] = vr[1];
+                    for (int i = 0; i < 4; ++i) {
+                        v[i][0] = v_first[i][0];
+                        v[i][1] = v_first[i][1];
+                    }
+                } else {
+                    load_v(v, t0, t1, p0, j);
                 }
 #pragma unroll
-                for (int i = 0; i < 4; ++i)
-#pragma unroll
-                    for (int e = 0; e < kPageTokens; ++e) {
-                        const int tt = (p0 + i) * kPageTokens + e;
-                        const uint32_t w = v[i][e >> 3][(e & 7) >> 1];
-                        const float vv = t0 + tt == L ? vnew : e & 1 ? bf16_hi(w) : bf16_lo(w);
-                        if (tt < cnt) acc = fmaf(s[tt], vv, acc);   // slots past the end may hold anything
-                    }
+                for (int i = 0; i < 4; ++i) {
+                    const int from = (p0 + i) * kPageTokens;
+                    if (from < cnt) acc = page_dot(acc, s + from, v[i], cnt - from, L - t0 - from, vnew);
+                }
             }
             pb[j] = acc;
         }

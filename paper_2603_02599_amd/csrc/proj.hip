@@ -1166,7 +1166,8 @@ __device__ __forceinline__ float wave_rows(float (&v)[2]) {
 // along: the norm in front (f32_fuses_norm; each wave sums its rows' squares for itself), the residual sum or SwiGLU behind.  The
 // loads of UN steps along k are in flight together; the sums keep the order of one step at a time (lane l adds k = l, l + 64,
 // ... and the lanes meet in a butterfly), the norm's that of a workgroup with a thread per eight columns.  Tiny
-// configuration, 8 requests: 5.3 us a launch against 6.4 of the bare products, and 18 launches a step instead of 29.
+// configuration, 8 requests: 5.3 us a launch against 6.4 of the bare products, and 18 launches a step instead of 29; with the first
+// weights and the value that is added to requested in front of the rows 4.0 to 4.9 (a run of 16 steps 967 -> 927 us).
 // BT rows a wave: 8 or 2 (f32_two_rows; the sums are the same ones).
 template <int BT, int UN, bool NORM, int EPI>
 __global__ __launch_bounds__(256) void proj_f32_kernel(F32Mat m, const float* __restrict__ x, int nrows, float* out) {
@@ -1191,6 +1192,35 @@ __global__ __launch_bounds__(256) void proj_f32_kernel(F32Mat m, const float* __
     const float* row[BT];
 #pragma unroll
     for (int j = 0; j < BT; ++j) row[j] = x + (size_t)min(b0 + j, nrows - 1) * K;
+    const int ng = K / kGroup;
+    float wv[UN][NC], gv[UN];
+    const auto load_w = [&](int k0) {
+#pragma unroll
+        for (int i = 0; i < UN; ++i) {
+            const int k = min(k0 + i * 64, K - 1);  // past the end: valid, not added
+#pragma unroll
+            for (int c = 0; c < NC; ++c) {
+                if (m.quant) {
+                    const uint8_t byte = m.q[src[c]][(size_t)r[c] * (K / 2) + (k >> 1)];
+                    const float code = (float)((k & 1) ? (byte >> 4) : (byte & 15));
+                    const size_t g = (size_t)r[c] * ng + k / kGroup;
+                    const float zf = m.z[src[c]] ? __half2float(__ushort_as_half(m.z[src[c]][g])) : 8.f;
+                    const float sf = __half2float(__ushort_as_half(m.s[src[c]][g]));
+                    wv[i][c] = (code - zf) * sf;  // exact: 5-bit integer times an 11-bit significand
+                } else {
+                    wv[i][c] = m.w[src[c]][(size_t)r[c] * K + k];
+                }
+            }
+            if constexpr (NORM) gv[i] = m.gain[k];
+        }
+    };
+    // what does not wait for the rows is requested in front of them: the first weights and the value that is added to
+    load_w(lane);
+    const int b = b0 + (lane >> 3);
+    const bool mine = lane < BT * 8 && (lane & 7) == 0 && b < nrows;
+    float* o = out + (size_t)min(b, nrows - 1) * n_out + n;
+    float before = 0.f;
+    if constexpr (EPI == F32_ADD) before = *o;
     float rinv[BT];
     if constexpr (NORM) {  // the rows' sums of squares: eight columns a lane, 512 a round, a round's sum as one wave of a workgroup
         float tot = 0.f;
@@ -1216,29 +1246,13 @@ __global__ __launch_bounds__(256) void proj_f32_kernel(F32Mat m, const float* __
     for (int c = 0; c < NC; ++c)
 #pragma unroll
         for (int j = 0; j < BT; ++j) acc[c][j] = 0.f;
-    const int ng = K / kGroup;
     for (int k0 = lane; k0 < K; k0 += 64 * UN) {
-        float wv[UN][NC], xv[UN][BT], gv[UN];
+        float xv[UN][BT];
+        if (k0 >= 64 * UN) load_w(k0);
 #pragma unroll
-        for (int i = 0; i < UN; ++i) {
-            const int k = min(k0 + i * 64, K - 1);  // past the end: valid, not added
+        for (int i = 0; i < UN; ++i)
 #pragma unroll
-            for (int c = 0; c < NC; ++c) {
-                if (m.quant) {
-                    const uint8_t byte = m.q[src[c]][(size_t)r[c] * (K / 2) + (k >> 1)];
-                    const float code = (float)((k & 1) ? (byte >> 4) : (byte & 15));
-                    const size_t g = (size_t)r[c] * ng + k / kGroup;
-                    const float zf = m.z[src[c]] ? __half2float(__ushort_as_half(m.z[src[c]][g])) : 8.f;
-                    const float sf = __half2float(__ushort_as_half(m.s[src[c]][g]));
-                    wv[i][c] = (code - zf) * sf;  // exact: 5-bit integer times an 11-bit significand
-                } else {
-                    wv[i][c] = m.w[src[c]][(size_t)r[c] * K + k];
-                }
-            }
-            if constexpr (NORM) gv[i] = m.gain[k];
-#pragma unroll
-            for (int j = 0; j < BT; ++j) xv[i][j] = row[j][k];
-        }
+            for (int j = 0; j < BT; ++j) xv[i][j] = row[j][min(k0 + i * 64, K - 1)];
 #pragma unroll
         for (int i = 0; i < UN; ++i)
             if (k0 + i * 64 < K) {
@@ -1254,11 +1268,9 @@ __global__ __launch_bounds__(256) void proj_f32_kernel(F32Mat m, const float* __
     float v[NC];
 #pragma unroll
     for (int c = 0; c < NC; ++c) v[c] = wave_rows(acc[c]);
-    const int b = b0 + (lane >> 3);
-    if (lane >= BT * 8 || (lane & 7) != 0 || b >= nrows) return;
-    float* o = out + (size_t)b * n_out + n;
+    if (!mine) return;
     if constexpr (EPI == F32_SWIGLU) *o = v[0] / (1.0f + expf(-v[0])) * v[1];
-    else if constexpr (EPI == F32_ADD) *o += v[0];
+    else if constexpr (EPI == F32_ADD) *o = before + v[0];
     else *o = v[0];
 }
 
