@@ -83,6 +83,7 @@ __device__ __forceinline__ void attn_split_items(const AttnArgs& a, int wg, int 
     const int G = GT ? GT : a.Hq / a.Hkv;
     constexpr int NS = D / 32;  // dim slices of a QK MFMA
     constexpr int NB = D / 16;  // dim blocks of a PV MFMA
+    constexpr bool QUADS = NS == 4;  // K through load_stream and turn_k
     const int c16 = lane & 15, kq = lane >> 4;
     // One workgroup of 8 waves per compute unit.  Items are dealt to workgroups statically: full
     // chunks (all of one size) round-robin; the workgroups that got one full chunk fewer are
@@ -127,18 +128,32 @@ __device__ __forceinline__ void attn_split_items(const AttnArgs& a, int wg, int 
         const int pA = __builtin_amdgcn_readlane(recv, 2 * pp);
         int pB = __builtin_amdgcn_readlane(recv, 2 * pp + 1);
         if (pB < 0) pB = pA;
-        const uint16_t* kp = a.kbase + head * a.k_head + (int64_t)(k_psel ? pB : pA) * a.k_page + k_lane_off;
+        const uint16_t* kh = a.kbase + head * a.k_head;
+        if constexpr (QUADS) {
+            const uint16_t* kp = kh + (int64_t)(lane & 8 ? pB : pA) * a.k_page + ((lane >> 2) & 1) * 8 * D + kq * 32 + (lane & 3) * 8;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                kr[0][r] = load_stream(reinterpret_cast<const u32x4_s*>(kp + r * D));
+                kr[1][r] = load_stream(reinterpret_cast<const u32x4_s*>(kp + (4 + r) * D));
+            }
+            return;
+        }
+        const uint16_t* kp = kh + (int64_t)(k_psel ? pB : pA) * a.k_page + k_lane_off;
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
             kr[0][s] = *reinterpret_cast<const u32x4_s*>(kp + s * 32);
             kr[1][s] = *reinterpret_cast<const u32x4_s*>(kp + 4 * D + s * 32);
         }
     };
-    // V^T is requested with streaming loads (every instruction reads two runs of 512 contiguous bytes, which
+    // V^T is requested with streaming loads: every instruction reads two runs of 512 contiguous bytes, which
     // such loads move 10 % faster than cached ones and without displacing what the neighbouring kernels exchange
-    // through the caches); K with plain loads: an instruction of K reads 64 bytes of each of 16 token rows, half a
-    // cache line at a time, and streaming loads are slower than cached ones on that pattern (measured with a
-    // read-only kernel: 6.7 against 6.1 TB/s on contiguous kilobytes, 5.95 against 6.2 on the K pattern)
+    // through the caches.  On half cache lines they are slower than cached ones (a read-only kernel: 6.7 against 6.1 TB/s on
+    // contiguous kilobytes, 5.95 against 6.2 on 64 bytes of each of 16 rows), which is what K's operand is in the cache's layout: lane
+    // (token, eight dims).  So K of 128 dims is read in whole token rows instead, four lanes side by side on 64 bytes,
+    // register r the tokens 8 half + r (+ 4), and turn_k exchanges register and lane of four: behind it register s holds dims 32 kq + 8 s of the
+    // lane's token.  Streamed so, against cached loads of the operand as it lies (us, 8 layers of the 8B shape, one process
+    // in turn): 64 requests 2216 -> 2198, 150 (4-bit) 3176 -> 3120, 256 5355 -> 5235, 14B shape with 24 long requests 3352 -> 3357; read so without
+    // streaming 2221 / 3174 / 5354 / 3360, the operand as it lies streamed 2275 / 3316 / 5735 / 3509 (2242 / 3269 / 5641 / 3345 beside them).
     auto load_v = [&](int recv, int head, int pp) {
         const int pA = __builtin_amdgcn_readlane(recv, 2 * pp);
         int pB = __builtin_amdgcn_readlane(recv, 2 * pp + 1);
@@ -148,15 +163,39 @@ __device__ __forceinline__ void attn_split_items(const AttnArgs& a, int wg, int 
         for (int b = 0; b < NB; ++b) vr[b] = load_stream(reinterpret_cast<const u32x4_s*>(vp + b * 16 * kPageTokens));
     };
 
+    auto turn_k = [&]() {
+        if constexpr (QUADS) {
+            const bool b0 = lane & 1, b1 = lane & 2;
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int w = 0; w < 4; ++w) {
+                    uint32_t x[4];
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) {
+                        const uint32_t lo = kr[t][j][w], hi = kr[t][j + 2][w], up = lane_xor<2>(hi), down = lane_xor<2>(lo);
+                        x[j] = b1 ? up : lo;
+                        x[j + 2] = b1 ? hi : down;
+                    }
+#pragma unroll
+                    for (int j = 0; j < 4; j += 2) {
+                        const uint32_t up = lane_xor<1>(x[j + 1]), down = lane_xor<1>(x[j]);
+                        kr[t][j][w] = b0 ? up : x[j];
+                        kr[t][j + 1][w] = b0 ? x[j + 1] : down;
+                    }
+                }
+        }
+    };
     bf16x8 qhi[NS], qlo[NS];
-    // q as MFMA B operand: lane (head g = c16, dim octet kq) per 32-dim slice, hi + lo bf16
+    // q as MFMA B operand: lane (head g = c16, dim octet kq) per 32-dim slice, hi + lo bf16; with QUADS slice s is dims 8 s .. + 7
+    // of every 32
     auto load_q = [&](int req, int head) {
         const float* qp = a.q + ((size_t)req * a.Hq + head * G + (c16 < G ? c16 : 0)) * D;
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
             u32x4_s h, l;
-            const f32x4 v0 = *reinterpret_cast<const f32x4*>(qp + s * 32 + kq * 8);
-            const f32x4 v1 = *reinterpret_cast<const f32x4*>(qp + s * 32 + kq * 8 + 4);
+            const f32x4 v0 = *reinterpret_cast<const f32x4*>(qp + (QUADS ? kq * 32 + s * 8 : s * 32 + kq * 8));
+            const f32x4 v1 = *reinterpret_cast<const f32x4*>(qp + (QUADS ? kq * 32 + s * 8 : s * 32 + kq * 8) + 4);
             float x[8] = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
 #pragma unroll
             for (int p = 0; p < 4; ++p) {
@@ -215,6 +254,7 @@ __device__ __forceinline__ void attn_split_items(const AttnArgs& a, int wg, int 
     auto step = [&](auto is_last) {
         constexpr bool LAST = decltype(is_last)::value;
         f32x4 sx = {0.f, 0.f, 0.f, 0.f}, sy = {0.f, 0.f, 0.f, 0.f};
+        turn_k();
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
             const bf16x8 kx = __builtin_bit_cast(bf16x8, kr[0][s]), ky = __builtin_bit_cast(bf16x8, kr[1][s]);
