@@ -761,9 +761,10 @@ void attn_prefill_kernel(PrefillAttnArgs a) {
             u32x4 hi, lo;
 #pragma unroll
             for (int p = 0; p < 4; ++p) {
-                float ra, rb;
-                hi[p] = bf16_pair_hi(x[2 * p] * a.qscale, x[2 * p + 1] * a.qscale, ra, rb);
-                lo[p] = pack_bf16(ra, rb);
+                uint32_t ph, pl;
+                split_pair(x[2 * p] * a.qscale, x[2 * p + 1] * a.qscale, ph, pl);
+                hi[p] = ph;
+                lo[p] = pl;
             }
             qhi[s] = __builtin_bit_cast(bf16x8, hi);
             qlo[s] = __builtin_bit_cast(bf16x8, lo);

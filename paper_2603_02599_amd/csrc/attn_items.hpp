@@ -57,21 +57,10 @@ inline AttnArgs make_attn_args(const KvPool& pool, int layer, const AttnPlan& pl
     return a;
 }
 
-__device__ __forceinline__ uint32_t bf16_pair_hi(float a, float b, float& ra, float& rb) {
-    const uint32_t ha = f32_to_bf16_bits(a), hb = f32_to_bf16_bits(b);
-    ra = a - __uint_as_float(ha << 16);
-    rb = b - __uint_as_float(hb << 16);
-    return ha | (hb << 16);
-}
-
-// bf16 hi/lo split of two fp32 values with the hardware converter (round to nearest even)
+// hi and lo bf16 of two fp32 values
 __device__ __forceinline__ void split_pair(float x0, float x1, uint32_t& hi, uint32_t& lo) {
-    typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
-    typedef float fl2 __attribute__((ext_vector_type(2)));
-    const bf2 h = __builtin_convertvector(fl2{x0, x1}, bf2);
-    hi = __builtin_bit_cast(uint32_t, h);
-    const bf2 l = __builtin_convertvector(fl2{x0 - bf16_lo(hi), x1 - bf16_hi(hi)}, bf2);
-    lo = __builtin_bit_cast(uint32_t, l);
+    hi = pack_bf16(x0, x1);
+    lo = pack_bf16(x0 - bf16_lo(hi), x1 - bf16_hi(hi));
 }
 
 // The items of workgroup wg out of nwg, by its eight waves.  GT: query heads per KV head, 0: taken from the arguments.
@@ -191,19 +180,20 @@ __device__ __forceinline__ void attn_split_items(const AttnArgs& a, int wg, int 
     // of every 32
     auto load_q = [&](int req, int head) {
         const float* qp = a.q + ((size_t)req * a.Hq + head * G + (c16 < G ? c16 : 0)) * D;
+        f32x4 q[NS][2];
+#pragma unroll
+        for (int s = 0; s < NS; ++s)
+#pragma unroll
+            for (int i = 0; i < 2; ++i) q[s][i] = *reinterpret_cast<const f32x4*>(qp + (QUADS ? kq * 32 + s * 8 : s * 32 + kq * 8) + 4 * i);
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
             u32x4_s h, l;
-            const f32x4 v0 = *reinterpret_cast<const f32x4*>(qp + (QUADS ? kq * 32 + s * 8 : s * 32 + kq * 8));
-            const f32x4 v1 = *reinterpret_cast<const f32x4*>(qp + (QUADS ? kq * 32 + s * 8 : s * 32 + kq * 8) + 4);
-            float x[8] = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
 #pragma unroll
-            for (int p = 0; p < 4; ++p) {
-                const float xa = c16 < G ? x[2 * p] * a.qscale : 0.f;
-                const float xb = c16 < G ? x[2 * p + 1] * a.qscale : 0.f;
-                float ra, rb;
-                h[p] = bf16_pair_hi(xa, xb, ra, rb);
-                l[p] = pack_bf16(ra, rb);
+            for (int p = 0; p < 4; ++p) {   // with the hardware's converter: rounded by hand, a change of item took 0.3 to 0.8 % of a step longer
+                uint32_t hi, lo;
+                split_pair(c16 < G ? q[s][p >> 1][2 * (p & 1)] * a.qscale : 0.f, c16 < G ? q[s][p >> 1][2 * (p & 1) + 1] * a.qscale : 0.f, hi, lo);
+                h[p] = hi;
+                l[p] = lo;
             }
             qhi[s] = __builtin_bit_cast(bf16x8, h);
             qlo[s] = __builtin_bit_cast(bf16x8, l);

@@ -43,18 +43,18 @@ constexpr int kGroup = 128;         // quantisation group along K (Appendix A.1)
 constexpr int kMaxBatchTile = 256;  // rows of a decode batch
 constexpr int kMaxPrefillTile = 2048;  // rows of a prefill block (bf16 projections only)
 
-// ---- bf16 <-> f32 (round to nearest even) ----
-__device__ __forceinline__ uint16_t f32_to_bf16_bits(float f) {
-    uint32_t u = __float_as_uint(f);
-    if ((u & 0x7fffffffu) > 0x7f800000u) return 0x7fc0;
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return (uint16_t)(u >> 16);
-}
+// ---- bf16 <-> f32 (round to nearest even, by the hardware's converter: one instruction for two values) ----
+// The bits of every value are those of rounding by hand (all 2^32 compared; a NaN stays one but keeps its sign and payload's upper bits),
+// which took six instructions a value in the kernels' tails: 8 layers of the 8B shape at 16 / 150 (4-bit) requests 1181 / 3068 ->
+// 1165 / 3048 us, 5 requests 4-bit 678 -> 667, prefill of 1024 tokens 6528 -> 6461.
+typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+typedef float f32x2_t __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint16_t f32_to_bf16_bits(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
 __device__ __forceinline__ float bf16_bits_to_f32(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
 __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
-    return (uint32_t)f32_to_bf16_bits(lo) | ((uint32_t)f32_to_bf16_bits(hi) << 16);
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2_t{lo, hi}, bf16x2_t));
 }
 
 // ---- projection activations: "fragment-tiled" two-plane bf16 layout ----
