@@ -328,14 +328,20 @@ __device__ __forceinline__ void attn_split_items(const AttnArgs& a, int wg, int 
         float l_tot = l_run + lane_xor<16>(l_run);
         l_tot += lane_xor<32>(l_tot);
         float* pbase = a.partial + ((size_t)cidx * a.Hq + head * G) * (D + 2);
+        // Rows of 16 lanes hold heads 4 kq + r, 16 dims of each register's block: the first four heads' and the next four's
+        // rows of four blocks are exchanged into one register, 64 dims of a head that a wave stores together.
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int g = 4 * kq + r;
-            if (g < G) {
+        for (int r = 0; r < 4; ++r)
 #pragma unroll
-                for (int b = 0; b < NB; ++b) put(pbase + (size_t)g * (D + 2) + b * 16 + c16, O[b][r]);
+            for (int b = 0; b < NB; b += 4) {
+                float x[4] = {O[b][r], O[b + 1][r], O[b + 2][r], O[b + 3][r]};
+                swap_rows<16>(x[0], x[1]);   // rows 0 and 1 of x[0]: head r's of blocks b and b + 1, of x[1]: head 4 + r's
+                swap_rows<16>(x[2], x[3]);
+                swap_rows<32>(x[0], x[2]);
+                swap_rows<32>(x[1], x[3]);
+                if (r < G) put(pbase + (size_t)r * (D + 2) + b * 16 + lane, x[0]);
+                if (4 + r < G) put(pbase + (size_t)(4 + r) * (D + 2) + b * 16 + lane, x[1]);
             }
-        }
         if (kq == 0 && c16 < G) {
             put(pbase + (size_t)c16 * (D + 2) + D, m_run);
             put(pbase + (size_t)c16 * (D + 2) + D + 1, l_tot);
