@@ -887,11 +887,17 @@ static ProjTiling proj_tiling(const Mat& W, int rows) {
     if (mbr <= 2) return ProjTiling{2 * mbr, 1};
     return ProjTiling{8, mbr / 4};
 }
+// Beside its strips a workgroup costs what it takes to start and end (six strip stages).  A vocabulary of more than two rounds whatever the wave
+// count is bound otherwise: every round streams beside the last one's end, and what counts is the activation tile that each workgroup
+// stages again, about two strips' worth.  152 064 x 5120, five -> seven waves: step of 24 / 64 requests 1076 -> 1065 / 1374 -> 1355 us (six
+// 1093 / 1385); 128 256 x 4096 at 8 / 32 / 64 rows with four waves (picked by either) / five / six / seven 988 / 1013 / 995 / 1006, 1210 / 1231 / 1210 / 1215, 1380 /
+// 1416 / 1378 / 1389.
+constexpr int kVocabStrips = 7 * 512;
 static long long proj_cost(int strips, int kch, int mtiles, int nw, int s) {
     const int cps = chunks_per_split(kch, s), real_s = (kch + cps - 1) / cps;
     const long long wgs = (long long)((strips + nw - 1) / nw) * real_s * mtiles;
     const long long rounds = (wgs + 255) / 256;
-    return rounds * ((long long)nw * cps + 6) * 16 + real_s;  // ties: fewer splits
+    return rounds * ((long long)nw * cps + (strips >= kVocabStrips ? 2 * cps : 6)) * 16 + real_s;  // ties: fewer splits
 }
 // 4-bit weights with more than one 32-row tile: several workgroups share a compute unit (16 waves at 128
 // registers), so the launch wants two to four times 256 workgroups rather than exactly 256.  Four waves per
