@@ -175,6 +175,18 @@ def test_widths_of_the_8b_shape(H, lens, layers, quant):
     check_against_oracle(H, case, rows, extracted, quant)
 
 
+@pytest.mark.parametrize("lens", [[40], EDGES[4:11], EDGES[6:14]], ids=lambda v: f"{len(v)}rows")
+def test_more_4_bit_gate_up_blocks_than_workgroups(H, lens):
+    """272 blocks of every other strip, so that sixteen workgroups finish two; one row, seven, and the eight whose planes fill an operand."""
+    shape = dataclasses.replace(DEEP_W4, name="wide_ffn", n_layers=7, ffn=17408)
+    case = make_case(H, shape, lens, "asym")
+    assert takes_one_launch(case)
+    rows = sorted({0, len(lens) // 2, len(lens) - 1})
+    extracted = H.case_extract_pool(case, rows)
+    case.step()
+    check_against_oracle(H, case, rows, extracted, "asym")
+
+
 def test_under_capture_a_step_takes_a_launch_per_operation(H):
     case = make_case(H, SMALL, [5, 100, 300])
     pool0 = case.pool_mem.clone()

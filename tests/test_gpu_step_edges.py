@@ -246,6 +246,24 @@ def test_projections_on_both_sides_of_the_streaming_rule(H, rows):
     assert ((got["above", 4].double() - want).abs() <= 2e-4 + 1e-5 * want.abs()).all()
 
 
+@pytest.mark.parametrize("rows", [1, 33])
+@pytest.mark.parametrize("vocab", [114656, 114688, 120000, 152064])
+def test_vocabulary_projection_on_both_sides_of_the_rule_for_its_waves(H, vocab, rows):
+    """From 3584 strips of 32 columns on (more than two rounds of workgroups of seven waves) the waves are chosen by another cost: four below
+    it, seven, five and seven here, with a ragged last workgroup.  Against float64 (about 1e-6 of a logit from the sums; the bound of the other projections)."""
+    shape = dataclasses.replace(wl.SMALL128, name="vocab", n_layers=1, hidden=256, vocab=vocab)
+    cfg = sun.make_cfg(shape, "bf16")
+    w = wl.make_weights(shape, "bf16", H.DEV, 83)
+    W = sun.sun_weights_create(cfg, w)
+    x = torch.randn((rows, 256), device=H.DEV, generator=torch.Generator(device=H.DEV).manual_seed(rows))
+    out = torch.full((rows, vocab), float("nan"), device=H.DEV)
+    ws = torch.empty(sun.sun_workspace_bytes(cfg, rows, 1), dtype=torch.uint8, device=H.DEV)
+    sun.sun_linear(W, 0, 4, x, out, ws)
+    torch.cuda.synchronize()
+    want = x.double() @ w["wlm"].double().t()
+    assert ((out.double() - want).abs() <= 2e-4 + 1e-5 * want.abs()).all()
+
+
 @pytest.mark.parametrize("hidden,ffn,batch", [(256, 688, 3), (256, 688, 95), (256, 688, 96), (512, 1024, 17), (1024, 1000, 9), (1024, 1000, 2),
                                               (2048, 4104, 5), (4096, 300, 1)])
 def test_f32_step_on_both_sides_of_its_rules(H, hidden, ffn, batch):
