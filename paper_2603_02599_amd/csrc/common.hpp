@@ -126,7 +126,7 @@ __device__ __forceinline__ int qtile_store8(uint8_t* tile, ATile t, int b, int k
 // 1 / sx for a group whose largest magnitude is amax (an all-zero group maps to zeros with sx = 0)
 __device__ __forceinline__ float qtile_inv(float amax) { return amax > 0.f ? kQMax / amax : 0.f; }
 
-// 16-byte load of data that is read once and never again by this launch (the cached V of the attention kernel):
+// 16-byte load of data that is read once and never again by this launch (the cached K and V of the attention kernel):
 // streamed past the caches (the "nt" form of the load), which also leaves what the neighbouring kernels exchange
 // in place.  Pays where an instruction reads long contiguous runs; see the attention kernel.
 typedef uint32_t u32x4_s __attribute__((ext_vector_type(4)));
