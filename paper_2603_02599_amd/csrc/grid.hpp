@@ -4,7 +4,13 @@
 
 namespace sun {
 
-constexpr int kCounters = 16;       // arrivals are spread over this many counters, 128 bytes apart
+// Arrivals are spread over this many counters, 128 bytes apart: what arrives on one counter is added up one after the other, and wave 0
+// looks at all of them with one load, so a counter per lane is the most.  8 layers of the 8B shape with 4 / 8 / 16 / 32 / 64 counters, us:
+// one request 961 / 928 / 908 / 889 / 884, five with 4-bit weights 762 / 716 / 686 / 668 / 663, sixteen 1261 / 1218 / 1180 / 1169 / 1163.
+// A flag per workgroup, stored without an add and looked at four a lane (64 lines as here, or 16): 902 and 964, 680 and 730, 1179 and
+// 1219.  A pause of 64 cycles between two looks: no difference.
+constexpr int kCounters = 64;
+static_assert(kCounters <= 64, "wave 0 polls one counter a lane");
 constexpr uint32_t kSpinLimit = 1u << 25;  // polls (about a microsecond each) before a workgroup stops waiting
 
 // The kernel's arguments, read again where they are used: all of them kept in registers across the phases do not fit.

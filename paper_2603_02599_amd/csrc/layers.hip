@@ -42,6 +42,10 @@ static_assert(kLayersRowsW4 <= kWaves && kLayersRows <= 2 * kWaves, "one row a w
 constexpr int kBlock = 128;        // columns of a block
 constexpr int kUnits = 256;         // work units a phase is cut into at most (one per compute unit)
 constexpr int kLayersPerLaunch = 48;
+// Words between the counters of two blocks' arrivals: side by side, 32 blocks' arrivals are on one line and are added one after the
+// other.  8 layers of the 8B shape, 1 / 8 / 32 words apart: five 4-bit requests 663 / 655 / 656 us, one bf16 request 883 / 881 / 882, sixteen
+// 1165 / 1165 / 1166; step_begin_kernel clears them all.
+constexpr int kApart = 8;
 constexpr int kBfRow = 512;         // bytes of 128 activations of one row: [32-wide step][plane][32] bf16
 constexpr int kQRow = 384;          // the same as 16-bit fixed point: [step of 64][plane][octet of 16] int8, then (scale, sum)
 constexpr int kQHalf = 256;         // each step of 64 with a scale of its own: [plane][octet of 16] int8, then (scale, sum)
@@ -63,7 +67,7 @@ struct MatP {
     const char* sz;
     size_t w_step, sz_step;         // from one layer to the next
     int K, S, nblk;                 // split along k, column blocks
-    uint32_t* arrived;              // [nblk]
+    uint32_t* arrived;              // [nblk][kApart]
 };
 
 struct LayersArgs {
@@ -414,7 +418,7 @@ __device__ __forceinline__ void unit_finish(const LayersArgs& a, const MatP& m, 
         }
         __syncthreads();
         if (threadIdx.x == 0) {
-            const uint32_t before_me = __hip_atomic_fetch_add(m.arrived + blk, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const uint32_t before_me = __hip_atomic_fetch_add(m.arrived + blk * kApart, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             sh.last = before_me + 1 == (uint32_t)m.S * (layer + 1);
         }
         __syncthreads();
@@ -721,7 +725,7 @@ static void cut(MatP& m, int N, int K, bool w4) {
 }
 
 static size_t n_counters(const sun_model_cfg& c) {
-    return kCounters * 32 + c.n_q_heads + 2 * c.n_kv_heads + 2 * (c.hidden / 128) + c.ffn / 64;
+    return kCounters * 32 + kApart * (c.n_q_heads + 2 * c.n_kv_heads + 2 * (c.hidden / 128) + c.ffn / 64);
 }
 
 struct LayersLayout {
@@ -845,7 +849,7 @@ hipError_t launch_layers(const KvPool& pool, const Weights& W, int rows, float* 
         m.sz_step = w4 ? (const char*)m1.sz - (const char*)m0.sz : 0;
         cut(m, m0.N, m0.K, w4);
         m.arrived = arrived;
-        arrived += m.nblk;
+        arrived += m.nblk * kApart;
         return m;
     };
     a.qkv = mat(&LayerW::qkv);
