@@ -4,12 +4,12 @@
 // boundary (a launch costs 4 to 5 us beside its work), the first requests' latency, the drain.  Here one workgroup per
 // compute unit stays for the whole stack and the phases of a layer
 //   q/k/v -> attention -> merge -> o -> gate/up -> down
-// are separated by a barrier over the grid (2.6 us from the last arrival's stores to the next phase's loads), in front of which
+// are separated by a barrier over the grid (2.6 us from the last arrival's stores to the next phase's loads on 16 counters, 0.5 less on 64), in front of which
 // every wave but one requests its first weights.  Bound by the weight stream in the long phases (gate/up 6.6 to 7 TB/s) and by
 // chains of small loads and stores around them.  Steps of 8 layers, launch per operation -> this (us), 1 / 8 / 16 requests of 200 to 1200
-// cached tokens: 8B shape bf16 1154 -> 923 / 1185 -> 1010 / 1217 -> 1106, 4-bit at 1 / 4 / 8 817 -> 620 / 835 -> 666 / 837 -> 696; hidden
-// 2048, ffn 8192 bf16 644 -> 441 / 666 -> 523 / 697 -> 650, 4-bit at 1 / 8 510 -> 360 / 538 -> 433; hidden 1024 440 -> 303 / 476 -> 370 /
-// 494 -> 475, 403 -> 290 / 430 -> 339.  Eight rows are what an operand of the 4-bit products holds beside their low planes; with
+// cached tokens: 8B shape bf16 1154 -> 879 / 1185 -> 968 / 1217 -> 1077, 4-bit at 1 / 4 / 8 817 -> 607 / 835 -> 640 / 837 -> 675; hidden
+// 2048, ffn 8192 bf16 644 -> 400 / 666 -> 457 / 697 -> 566, 4-bit at 1 / 8 510 -> 332 / 538 -> 384; hidden 1024 440 -> 283 / 476 -> 328 /
+// 494 -> 403, 403 -> 282 / 430 -> 333.  Eight rows are what an operand of the 4-bit products holds beside their low planes; with
 // two rows a wave and operands of 16 4-bit steps at 12 / 16 requests (4 layers, 8B shape) took 549 -> 552 / 524 -> 553.  Hence kLayersRows and
 // kLayersRowsW4.
 //
@@ -716,7 +716,7 @@ static size_t up256(size_t v) { return (v + 255) / 256 * 256; }
 // A row's sums depend on the matrix alone.  Widths whose blocks fill the chip badly lose part of the gain, not all of it (4 layers, launch
 // per operation -> this, us): 296 gate/up blocks on 256 workgroups (hidden 3584, ffn 18 944) at 1 / 16 requests 577 -> 489 / 593 -> 591;
 // 272 of 4-bit weights (hidden 5120, ffn 17 408) at 1 / 8 468 -> 399 / 473 -> 434 (136 of twice the columns;
-// on longer requests those 395 / 467, these 382 / 459), bf16 at 1 / 16 724 -> 644 / 747 -> 746; 14B shape 847 ->
+// on longer requests those 395 / 467, these 375 / 449), bf16 at 1 / 16 724 -> 644 / 747 -> 746; 14B shape 847 ->
 // 697 / 886 -> 780, 4-bit 613 -> 554 / 634 -> 600; hidden 8192, ffn 28 672 1351 -> 1258 / 1376 -> 1346, 4-bit 706 -> 607 / 740 -> 655.
 static void cut(MatP& m, int N, int K, bool w4) {
     m.K = K;
@@ -771,7 +771,8 @@ static LayersLayout layers_layout(const sun_model_cfg& c, int rows, bool w4, siz
 // timed (hidden 1024; wider ones two or three times that), 19 us at one row down to 4 at 16 (bf16), 11 at one row down to 4 at 8
 // (4-bit): few layers are faster with a launch per operation.  Hidden 1024, launch per operation -> this (us): one layer 12 / 16
 // requests 80 -> 97 / 81 -> 101, 4-bit 5 / 8 75 -> 94 / 76 -> 97; two layers one request 126 -> 117, 4-bit 117 -> 120; four at 12 / 16
-// 240 -> 233 / 244 -> 255, 4-bit at 5 218 -> 211; eight 473 -> 419 / 480 -> 469, 4-bit at 8 411 -> 395.
+// 240 -> 233 / 244 -> 255, 4-bit at 5 218 -> 211; eight 473 -> 419 / 480 -> 469, 4-bit at 8 411 -> 395 (all with the barrier's arrivals on 16
+// counters; on 64 eight layers take 403 at 16 requests).
 static bool layers_shape(const Weights& W, int rows) {
     return W.cfg.act_dtype == SUN_BF16 && W.cfg.head_dim == 128 && rows <= (W.quant ? kLayersRowsW4 : kLayersRows) &&
            W.cfg.n_layers * ((W.quant ? 12 : 20) - rows) >= 26;
