@@ -641,6 +641,7 @@ int sun_qweights_create(const sun_model_cfg* cfg, const sun_qweight_ptrs* d, int
     {   // lm_head stays dense (Appendix A.1)
         Mat& m = w->lm;
         mat_dims(c, 4, m.N, m.K);
+        m.vocab = true;
         const void* src[3] = {d->wlm, nullptr, nullptr};
         const int rows[3] = {c.vocab, 0, 0};
         if (bf) {

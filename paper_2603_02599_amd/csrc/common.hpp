@@ -284,6 +284,7 @@ struct Mat {
                                // s_only, the fp16 scales alone, two groups per dword (zero point 8 everywhere)
     bool s_only = false;
     bool stream = false;       // BF16_PACKED: the model's weights together exceed kStreamWeightBytes
+    bool vocab = false;        // the vocabulary projection
     // W4_LOGICAL (fp32 activations): logical arrays, up to two stacked sources (gate, up)
     const uint8_t* q[3] = {nullptr, nullptr, nullptr};
     const uint16_t* s[3] = {nullptr, nullptr, nullptr};

@@ -856,7 +856,7 @@ static int tall_pick_splits(const Mat& W, int rows, int max_splits) {
     return best;
 }
 
-static int chunks_per_split(int kch, int splits) { return (kch + splits - 1) / splits; }
+static constexpr int chunks_per_split(int kch, int splits) { return (kch + splits - 1) / splits; }
 
 // Waves per workgroup (each wave owns 32 columns) and split-K factor.  A compute unit's share of
 // the HBM bandwidth does not grow with the number of workgroups it hosts, so the launch is only
@@ -887,17 +887,12 @@ static ProjTiling proj_tiling(const Mat& W, int rows) {
     if (mbr <= 2) return ProjTiling{2 * mbr, 1};
     return ProjTiling{8, mbr / 4};
 }
-// Beside its strips a workgroup costs what it takes to start and end (six strip stages).  A vocabulary of more than two rounds whatever the wave
-// count is bound otherwise: every round streams beside the last one's end, and what counts is the activation tile that each workgroup
-// stages again, about two strips' worth.  152 064 x 5120, five -> seven waves: step of 24 / 64 requests 1076 -> 1065 / 1374 -> 1355 us (six
-// 1093 / 1385); 128 256 x 4096 at 8 / 32 / 64 rows with four waves (picked by either) / five / six / seven 988 / 1013 / 995 / 1006, 1210 / 1231 / 1210 / 1215, 1380 /
-// 1416 / 1378 / 1389.
-constexpr int kVocabStrips = 7 * 512;
-static long long proj_cost(int strips, int kch, int mtiles, int nw, int s) {
+// Beside its strips a workgroup costs what it takes to start and end (six strip stages).
+static constexpr long long proj_cost(int strips, int kch, int mtiles, int nw, int s, int ends = 6) {
     const int cps = chunks_per_split(kch, s), real_s = (kch + cps - 1) / cps;
     const long long wgs = (long long)((strips + nw - 1) / nw) * real_s * mtiles;
     const long long rounds = (wgs + 255) / 256;
-    return rounds * ((long long)nw * cps + (strips >= kVocabStrips ? 2 * cps : 6)) * 16 + real_s;  // ties: fewer splits
+    return rounds * ((long long)nw * cps + ends) * 16 + real_s;  // ties: fewer splits
 }
 // 4-bit weights with more than one 32-row tile: several workgroups share a compute unit (16 waves at 128
 // registers), so the launch wants two to four times 256 workgroups rather than exactly 256.  Four waves per
@@ -1027,22 +1022,28 @@ int proj_pick_splits(const Mat& W, int rows, int max_splits) {
     return proj_pick(W, rows, max_splits).splits;
 }
 
+static constexpr int waves_by_cost(int strips, int kch, int mtiles, int most, int splits, int ends = 6) {
+    int best = 4;
+    for (int nw = 5; nw <= most; ++nw)
+        if (proj_cost(strips, kch, mtiles, nw, splits, ends) < proj_cost(strips, kch, mtiles, best, splits, ends)) best = nw;
+    return best;
+}
+// The vocabulary (one matrix, never split).  From two rounds of workgroups of seven waves on it is bound otherwise than by starts and ends: every round
+// streams beside the last one's end, and what counts is the activation tile that each workgroup stages again, about two strips' worth.
+// Waves by starts and ends -> by the tile, us of the projection at 1 / 32 / 64 rows: 128 256 x 256 six -> four 20.6 / 23.7 / 26.5 -> 15.4 / 18.1 / 22.9;
+// 152 064 five -> seven x 1024 62.8 / 73.2 / 82.5 -> 58.6 / 70.7 / 78.1, x 4096 212 / 240 / 280 -> 205 / 235 / 251, x 5120 262 / 296 / 346 -> 252 / 288 /
+// 307; 256 000 x 2048 four -> seven 188 / 220 / 233 -> 184 / 213 / 225.  128 256 x 4096 (four by either) with five / six / seven is 2 to 20 % slower.
+static constexpr int vocab_waves(int strips, int kch) { return waves_by_cost(strips, kch, 1, 7, 1, strips >= 7 * 512 ? 2 * kch : 6); }
+static_assert(vocab_waves(4008, 2) == 4 && vocab_waves(4752, 8) == 7 && vocab_waves(4752, 40) == 7 && vocab_waves(8000, 16) == 7, "by the tile");
+
 // the wave count that goes with a given split factor
 static int proj_pick_waves(const Mat& W, int rows, int splits) {
     const int strips = W.N / 32, kch = W.K / 128;
     const ProjTiling t = proj_tiling(W, rows);
     const int mtiles = t.mtiles;
     if (W.kind == MAT_W4_PACKED && mtiles >= 2) return W.N / 32 >= 512 && mtiles <= 2 ? 7 : 4;
-    int best = 4;
-    long long best_cost = -1;
-    for (int nw = 4; nw <= (t.mb <= 4 ? 7 : 4); ++nw) {
-        const long long c = proj_cost(strips, kch, mtiles, nw, splits);
-        if (best_cost < 0 || c < best_cost) {
-            best_cost = c;
-            best = nw;
-        }
-    }
-    return best;
+    if (W.vocab && t.mb <= 4) return vocab_waves(strips, kch);
+    return waves_by_cost(strips, kch, mtiles, t.mb <= 4 ? 7 : 4, splits);
 }
 
 template <int MB, int KS>

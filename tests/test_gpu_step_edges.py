@@ -264,6 +264,33 @@ def test_vocabulary_projection_on_both_sides_of_the_rule_for_its_waves(H, vocab,
     assert ((out.double() - want).abs() <= 2e-4 + 1e-5 * want.abs()).all()
 
 
+@pytest.mark.parametrize("rows", [1, 32])
+@pytest.mark.parametrize("ffn", [57344, 58368, 65536])
+def test_wide_4_bit_gate_up_is_not_split_along_k(H, ffn, rows):
+    """The rule for a vocabulary's waves does not reach a gate/up pair as wide as a vocabulary, whose split along k sets the order of its
+    sums.  An up column's 16 groups add up to 15 * 2^22, about 1 each, -15 * 2^22: 1 is lost beside the first (fp32 resolves 4 there), so one
+    slab sums to what the first was rounded by, 2 at most, and what a second one holds (by that rule 58 368 and 65 536 columns have two and
+    three) stays, 4 or more.  The gate is 16."""
+    shape = dataclasses.replace(wl.SMALL128, name="gate_up", n_layers=1, hidden=2048, n_q_heads=2, n_kv_heads=1, ffn=ffn, vocab=64)
+    cfg = sun.make_cfg(shape, "bf16")
+    w = wl.make_weights(shape, "bf16", H.DEV, 84)
+
+    def codes(n, k, scales):   # code 15, zero point 0
+        s = torch.tensor(scales, dtype=torch.float16, device=H.DEV)[None].expand(n, k // 128).contiguous()
+        return torch.full((n, k // 2), 0xFF, dtype=torch.uint8, device=H.DEV), s, torch.zeros_like(s)
+
+    dims = {"wq": (256, 2048), "wk": (128, 2048), "wv": (128, 2048), "wo": (2048, 256), "wg": (ffn, 2048), "wu": (ffn, 2048), "wd": (2048, ffn)}
+    one = 1 / (15 * 128)
+    quant = {k: [codes(n, c, [one] * (c // 128))] for k, (n, c) in dims.items()}
+    quant["wu"] = [codes(ffn, 2048, [2.0 ** 15] + [one] * 14 + [-(2.0 ** 15)])]
+    W = sun.sun_qweights_create(cfg, w, quant)
+    x = torch.ones((rows, shape.hidden), device=H.DEV)
+    out = torch.full((rows, ffn), float("nan"), device=H.DEV)
+    sun.sun_linear(W, 0, 2, x, out, torch.empty(sun.sun_workspace_bytes(cfg, rows, 1), dtype=torch.uint8, device=H.DEV))
+    torch.cuda.synchronize()
+    assert float(out.abs().max()) <= 16 * 2.1
+
+
 @pytest.mark.parametrize("hidden,ffn,batch", [(256, 688, 3), (256, 688, 95), (256, 688, 96), (512, 1024, 17), (1024, 1000, 9), (1024, 1000, 2),
                                               (2048, 4104, 5), (4096, 300, 1)])
 def test_f32_step_on_both_sides_of_its_rules(H, hidden, ffn, batch):
