@@ -450,13 +450,14 @@ void sun_weights_destroy(sun_weights* w) {
     delete p;
 }
 
-static void mark_streamed(Weights& w, size_t packed_bytes) {
+static void mark_matrices(Weights& w, size_t packed_bytes) {
     const bool stream = packed_bytes > kStreamWeightBytes;
     for (int l = 0; l < w.cfg.n_layers; ++l) {
         LayerW& L = w.layers[l];
         L.qkv.stream = L.o.stream = L.gu.stream = L.down.stream = stream;
     }
     w.lm.stream = stream;
+    w.lm.vocab = true;
 }
 
 static int check_ptr_arrays(const void* const* const arrs[], int n_arrs, int n_layers) {
@@ -538,7 +539,7 @@ int sun_weights_create(const sun_model_cfg* cfg, const sun_weight_ptrs* d, void*
         pack(L.down, 3, d->wd[l], nullptr, nullptr, c.hidden, 0, 0, 1, 0);
     }
     pack(w->lm, 4, d->wlm, nullptr, nullptr, c.vocab, 0, 0, 1, 0);
-    mark_streamed(*w, off);
+    mark_matrices(*w, off);
     if (e == hipSuccess && bf) e = hipStreamSynchronize(st);
     if (e != hipSuccess) {
         sun_weights_destroy((sun_weights*)w);
@@ -641,7 +642,6 @@ int sun_qweights_create(const sun_model_cfg* cfg, const sun_qweight_ptrs* d, int
     {   // lm_head stays dense (Appendix A.1)
         Mat& m = w->lm;
         mat_dims(c, 4, m.N, m.K);
-        m.vocab = true;
         const void* src[3] = {d->wlm, nullptr, nullptr};
         const int rows[3] = {c.vocab, 0, 0};
         if (bf) {
@@ -656,7 +656,7 @@ int sun_qweights_create(const sun_model_cfg* cfg, const sun_qweight_ptrs* d, int
             m.src_rows[0] = c.vocab;
         }
     }
-    mark_streamed(*w, off);
+    mark_matrices(*w, off);
     if (e == hipSuccess && bf) e = hipStreamSynchronize(st);
     if (e != hipSuccess) {
         sun_weights_destroy((sun_weights*)w);
