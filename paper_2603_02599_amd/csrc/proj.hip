@@ -1033,8 +1033,18 @@ static constexpr int waves_by_cost(int strips, int kch, int mtiles, int most, in
 // Waves by starts and ends -> by the tile, us of the projection at 1 / 32 / 64 rows: 128 256 x 256 six -> four 20.6 / 23.7 / 26.5 -> 15.4 / 18.1 / 22.9;
 // 152 064 five -> seven x 1024 62.8 / 73.2 / 82.5 -> 58.6 / 70.7 / 78.1, x 4096 212 / 240 / 280 -> 205 / 235 / 251, x 5120 262 / 296 / 346 -> 252 / 288 /
 // 307; 256 000 x 2048 four -> seven 188 / 220 / 233 -> 184 / 213 / 225.  128 256 x 4096 (four by either) with five / six / seven is 2 to 20 % slower.
-static constexpr int vocab_waves(int strips, int kch) { return waves_by_cost(strips, kch, 1, 7, 1, strips >= 7 * 512 ? 2 * kch : 6); }
-static_assert(vocab_waves(4008, 2) == 4 && vocab_waves(4752, 8) == 7 && vocab_waves(4752, 40) == 7 && vocab_waves(8000, 16) == 7, "by the tile");
+// Up to 32 rows the tile is half as large, and with long k the four that starts and ends ask for stay (two such workgroups share a
+// compute unit): 256 000 x 3072 four -> seven 254 / 297 -> 266 / 302 us at 1 / 32 rows (334 -> 321 at 64), x 5120 409 / 468 -> 426 / 473
+// (531 -> 502), 262 144 x 5120 417 / 475 -> 427 / 482 (523 -> 510); five stay seven: 320 000 x 3072 326 / 386 -> 320 / 376, x 5120 524 / 617 -> 515 / 602.
+// Above 327 680 columns starts and ends choose again: 352 000 four -> five at 64 rows x 2048 319 -> 333, x 4096 609 -> 635.
+static constexpr int vocab_waves(int strips, int kch, int rows) {
+    const int by_ends = waves_by_cost(strips, kch, 1, 7, 1);
+    if (strips < 7 * 512 || strips > 10240 || (rows <= 32 && kch >= 24 && by_ends == 4)) return by_ends;
+    return waves_by_cost(strips, kch, 1, 7, 1, 2 * kch);
+}
+static_assert(vocab_waves(4008, 2, 1) == 4 && vocab_waves(4752, 8, 33) == 7 && vocab_waves(4752, 40, 1) == 7 && vocab_waves(8000, 16, 1) == 7, "by the tile");
+static_assert(vocab_waves(3583, 2, 1) == 7 && vocab_waves(8000, 24, 32) == 4 && vocab_waves(8192, 40, 32) == 4 && vocab_waves(11000, 32, 64) == 4, "by starts and ends");
+static_assert(vocab_waves(8000, 24, 33) == 7 && vocab_waves(8192, 40, 64) == 7 && vocab_waves(10000, 40, 1) == 7, "the larger tile; not four");
 
 // the wave count that goes with a given split factor
 static int proj_pick_waves(const Mat& W, int rows, int splits) {
@@ -1042,7 +1052,7 @@ static int proj_pick_waves(const Mat& W, int rows, int splits) {
     const ProjTiling t = proj_tiling(W, rows);
     const int mtiles = t.mtiles;
     if (W.kind == MAT_W4_PACKED && mtiles >= 2) return W.N / 32 >= 512 && mtiles <= 2 ? 7 : 4;
-    if (W.vocab && t.mb <= 4) return vocab_waves(strips, kch);
+    if (W.vocab && t.mb <= 4) return vocab_waves(strips, kch, rows);
     return waves_by_cost(strips, kch, mtiles, t.mb <= 4 ? 7 : 4, splits);
 }
 

@@ -246,16 +246,18 @@ def test_projections_on_both_sides_of_the_streaming_rule(H, rows):
     assert ((got["above", 4].double() - want).abs() <= 2e-4 + 1e-5 * want.abs()).all()
 
 
-@pytest.mark.parametrize("rows", [1, 33])
-@pytest.mark.parametrize("vocab", [114656, 114688, 120000, 152064])
-def test_vocabulary_projection_on_both_sides_of_the_rule_for_its_waves(H, vocab, rows):
-    """From 3584 strips of 32 columns on (more than two rounds of workgroups of seven waves) the waves are chosen by another cost: four below
-    it, seven, five and seven here, with a ragged last workgroup.  Against float64 (about 1e-6 of a logit from the sums; the bound of the other projections)."""
-    shape = dataclasses.replace(wl.SMALL128, name="vocab", n_layers=1, hidden=256, vocab=vocab)
+@pytest.mark.parametrize("rows", [1, 32, 33])
+@pytest.mark.parametrize("hidden,vocab", [(256, 114656), (256, 128256), (1024, 152064), (1024, 256000), (3072, 256000)])
+def test_vocabulary_projection_on_both_sides_of_the_rule_for_its_waves(H, hidden, vocab, rows):
+    """From 3584 strips of 32 columns on the waves of a workgroup are chosen by the activation tile that each stages again: four instead of six
+    at 128 256 columns of 256, seven instead of five at 152 064 of 1024, seven instead of four at 256 000; up to 32 rows,
+    with k of 3072 or more, a workgroup keeps the four that its start and end ask for.  114 656 columns are a strip below the rule.  Workgroups of seven
+    leave the last one ragged.  Against float64 (about 1e-6 of a logit from the sums; the bound of the other projections)."""
+    shape = dataclasses.replace(wl.SMALL128, name="vocab", n_layers=1, hidden=hidden, vocab=vocab, ffn=128)
     cfg = sun.make_cfg(shape, "bf16")
     w = wl.make_weights(shape, "bf16", H.DEV, 83)
     W = sun.sun_weights_create(cfg, w)
-    x = torch.randn((rows, 256), device=H.DEV, generator=torch.Generator(device=H.DEV).manual_seed(rows))
+    x = torch.randn((rows, hidden), device=H.DEV, generator=torch.Generator(device=H.DEV).manual_seed(rows))
     out = torch.full((rows, vocab), float("nan"), device=H.DEV)
     ws = torch.empty(sun.sun_workspace_bytes(cfg, rows, 1), dtype=torch.uint8, device=H.DEV)
     sun.sun_linear(W, 0, 4, x, out, ws)
