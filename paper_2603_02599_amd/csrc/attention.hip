@@ -299,16 +299,18 @@ __global__ __launch_bounds__(256) void attn_split_f32_kernel(AttnArgs a, int G) 
 // fp32, short tables: rotation, append, attention over all chunks and their merge in one launch
 // ---------------------------------------------------------------------------------
 // Bound by latency like the launches it replaces (rope_append_kernel, attn_split_f32_kernel, attn_combine_kernel: three of
-// a layer's seven); with a wave's first keys and values requested in front of everything else (page_dot has the other half) a launch
-// of the tiny configuration takes 6.4 us where it took 8.8.  A workgroup per request and KV head takes the new position's heads out of the q/k/v product, appends K
+// a layer's seven).  A workgroup per request and KV head takes the new position's heads out of the q/k/v product, appends K
 // and V, walks the request's chunks (a wave per chunk and query head, partial results in LDS) and merges them.  Every sum has
-// the order it has there, so the results are theirs bit for bit.  Tiny configuration, three launches -> this (us a step): 8 requests of 16 /
-// 100 / 250 / 500 / 900 cached tokens 78.7 / 79.2 / 82.2 / 83.4 / 83.4 -> 68.7 / 71.4 / 76.6 / 86.2 / 106.7, 48 of 250 105 -> 100,
-// 200 of 250 160 -> 146: a request is a few workgroups', so longer tables stay with the launches that spread it.  How long depends on a
-// workgroup's share, chunks x query heads x dims at 64 positions a chunk.  One request, two KV heads, hidden 512, tables of 64 / 128 / 192 /
-// 256 / 384 positions: 2 query heads of 128 each 86 / 87 / 87 / 88 / 92 -> 76 / 78 / 82 / 85 / 103, 4 of 64 82 / 83 / 85 / 85 / 85 -> 71 / 74 / 81 /
-// 85 / 94, 8 of 64 98 / 97 / 98 / 100 / 98 -> 83 / 90 / 99 / 113 / 130, 4 of 128 101 / 102 / 104 / 104 / 104 -> 88 / 93 / 109 / 113 / 133, 8 of 128
-// 131 / 133 / 134 / 133 / 134 -> 110 / 130 / 151 / 171 / 212 (32 requests the same way); hence kShortShare.
+// the order it has there, so the results are theirs bit for bit.  The compiler's registers count: more workgroups than compute units are two or more
+// on one.  With a wave's first keys and values requested in front of the new position's heads, and the new key selected instead of branched
+// to (248 registers with 64 dims, 256 and 16 in memory with 128), a step of the tiny shape with 8 / 128 / 256 requests of up to 128 / 370 / 370 tokens took 57 / 112 / 159
+// us, without (75 and 87 registers) 57 / 110 / 144; 4 query heads of 128 dims, 200 requests of 60 tokens 293 -> 280.
+// A request is a few workgroups', so longer tables stay with the launches that spread it.  How long depends on a workgroup's share, chunks x
+// query heads x dims at 64 positions a chunk.  Two KV heads, hidden 512, 8 requests, tables of 64 / 128 / 192 / 256 / 384 positions full, three launches -> this (us a
+// step): 2 query heads of 128 each 79 / 85 / 86 / 86 / 88 -> 70 / 80 / 83 / 84 / 94, 4 of 64 79 / 78 / 77 / 77 / 82 -> 67 / 69 / 73 / 75 / 87, 8 of 64 92 / 89 / 95 /
+// 99 / 97 -> 81 / 85 / 97 / 107 / 118, 4 of 128 94 / 97 / 99 / 101 / 101 -> 86 / 93 / 101 / 109 / 121, 8 of 128 120 / 121 / 121 / 121 / 122 -> 110 / 122 / 134 /
+// 146 / 171 (1 and 32 requests the same way); hence kShortShare.  From 128 requests on up to twice that share is faster here too (4 of 128, 256 requests,
+// 256 positions 376 -> 356), 8 of 128 is even.
 // Not for a prefill block, where a row attends to entries that other rows of the launch append.
 constexpr int kShortPart = (kShortTokens / kAttnSmall) * 8 * 130;   // floats of LDS for partial results: chunks, query heads, dims + 2
 
@@ -333,33 +335,6 @@ __global__ __launch_bounds__(512) void attn_short_f32_kernel(ShortArgs a) {
     const int32_t* pt = a.page_tables + (size_t)b * a.max_pages;
     const auto page_of = [&](int p) { return min(max(pt[p], 0), a.n_pages - 1); };
     uint16_t *kb = a.kbase + (int64_t)kh * a.k_head, *vb = a.vbase + (int64_t)kh * a.v_head;
-    int n_full, n_small, ch;
-    attn_chunking(n, a.batch, a.Hkv, n_full, n_small, ch);
-    const int nc = n_full + n_small;
-    // a wave's first keys and values depend on the tables alone: they are requested in front of the new position's heads
-    const auto chunk_from = [&](int ci) { return ci < n_full ? ci * ch : n_full * ch + (ci - n_full) * kAttnSmall; };
-    const auto chunk_to = [&](int ci) { return ci < n_full ? (ci + 1) * ch : min(n, chunk_from(ci) + kAttnSmall); };
-    const auto load_k = [&](u32x4 (&kw)[D / 8], int pos) {
-        const u32x4* kr = reinterpret_cast<const u32x4*>(kb + (int64_t)page_of(pos / kPageTokens) * a.k_page + (pos % kPageTokens) * D);
-#pragma unroll
-        for (int i = 0; i < D / 8; ++i) kw[i] = kr[i];
-    };
-    const auto load_v = [&](u32x4 (&v)[4][2], int t0, int t1, int p0, int j) {   // four pages; past the chunk the last one again
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int pg = min(p0 + i, (t1 - t0 - 1) / kPageTokens);
-            const u32x4* vr = reinterpret_cast<const u32x4*>(vb + (int64_t)page_of(t0 / kPageTokens + pg) * a.v_page + j * kPageTokens);
-            v[i][0] = vr[0];
-            v[i][1] = vr[1];
-        }
-    };
-    constexpr bool EARLY = D <= 64;   // twice the registers do not fit
-    u32x4 k_first[D / 8], v_first[4][2];
-    if (EARLY && wave < nc * G) {
-        const int t0 = chunk_from(wave / G), t1 = chunk_to(wave / G);
-        load_k(k_first, min(t0 + lane, t1 - 1));
-        load_v(v_first, t0, t1, 0, lane);
-    }
     for (int t = wave; t < G + 2; t += W) {                 // a wave per head; lane j holds elements j and j + D / 2
         const int hh = t < G ? kh * G + t : t == G ? a.Hq + kh : a.Hq + a.Hkv + kh, j = lane;
         const bool act = j < half;
@@ -408,24 +383,27 @@ __global__ __launch_bounds__(512) void attn_short_f32_kernel(ShortArgs a) {
             }
         }
     }
+    int n_full, n_small, ch;
+    attn_chunking(n, a.batch, a.Hkv, n_full, n_small, ch);
+    const int nc = n_full + n_small;
     __syncthreads();
     for (int task = wave; task < nc * G; task += W) {       // a wave per chunk and query head
         const int ci = task / G, g = task % G;
-        const int t0 = chunk_from(ci), t1 = chunk_to(ci), cnt = t1 - t0;
+        const int t0 = ci < n_full ? ci * ch : n_full * ch + (ci - n_full) * kAttnSmall, t1 = ci < n_full ? t0 + ch : min(n, t0 + kAttnSmall);
+        const int cnt = t1 - t0;
         float* s = sc[wave];
         float mx = -INFINITY;
         for (int tt = lane; tt < cnt; tt += 64) {           // scores: lane <-> token; the new one's K comes from LDS
             const int pos = t0 + tt;
             u32x4 kw[D / 8];
-            if (EARLY && task == wave && tt == lane) {
-#pragma unroll
-                for (int i = 0; i < D / 8; ++i) kw[i] = k_first[i];
-            } else {
-                load_k(kw, pos);
-            }
             if (pos == L) {
+                asm volatile("");                           // a branch: as selects the entry takes registers beside every key's
 #pragma unroll
                 for (int i = 0; i < D / 8; ++i) kw[i] = reinterpret_cast<const u32x4*>(kv[0])[i];
+            } else {
+                const u32x4* kr = reinterpret_cast<const u32x4*>(kb + (int64_t)page_of(pos / kPageTokens) * a.k_page + (pos % kPageTokens) * D);
+#pragma unroll
+                for (int i = 0; i < D / 8; ++i) kw[i] = kr[i];
             }
             const f32x4* qg = reinterpret_cast<const f32x4*>(qs + g * D);
             float acc = 0.f;
@@ -461,14 +439,12 @@ __global__ __launch_bounds__(512) void attn_short_f32_kernel(ShortArgs a) {
             float acc = 0.f;
             for (int p0 = 0; p0 * kPageTokens < cnt; p0 += 4) {
                 u32x4 v[4][2];
-                if (EARLY && task == wave && !p0 && j == lane) {
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        v[i][0] = v_first[i][0];
-                        v[i][1] = v_first[i][1];
-                    }
-                } else {
-                    load_v(v, t0, t1, p0, j);
+                for (int i = 0; i < 4; ++i) {
+                    const int pg = min(p0 + i, (cnt - 1) / kPageTokens);
+                    const u32x4* vr = reinterpret_cast<const u32x4*>(vb + (int64_t)page_of(t0 / kPageTokens + pg) * a.v_page + j * kPageTokens);
+                    v[i][0] = vr[0];
+                    v[i][1] = vr[1];
                 }
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {

@@ -15,6 +15,10 @@ def assembly(src, out):
     from paper_2603_02599_amd.build import FLAGS
     flags = [f for f in FLAGS if f != "-fPIC"]
     subprocess.run(["hipcc", *flags, "--offload-device-only", "-S", str(src), "-o", str(out)], check=True, capture_output=True)
+    return instructions(out)
+
+
+def instructions(out):
     kernels, name = {}, None
     for line in open(out):
         line = line.split(";")[0].strip()
@@ -171,8 +175,15 @@ def projection_code(tmp_path_factory):
 
 
 @pytest.fixture(scope="module")
-def attention_code(tmp_path_factory):
-    return assembly(os.path.join(CSRC, "attention.hip"), tmp_path_factory.mktemp("asm") / "attention.s")
+def attention_file(tmp_path_factory):
+    out = tmp_path_factory.mktemp("asm") / "attention.s"
+    assembly(os.path.join(CSRC, "attention.hip"), out)
+    return out
+
+
+@pytest.fixture(scope="module")
+def attention_code(attention_file):
+    return instructions(attention_file)
 
 
 def test_the_kernel_of_all_layers_keeps_its_registers(tmp_path):
@@ -182,3 +193,18 @@ def test_the_kernel_of_all_layers_keeps_its_registers(tmp_path):
     assert len(kernels) == 3
     for name, code in kernels.items():
         assert not any(s.startswith("scratch_") for s in code), name
+
+
+@pytest.mark.parametrize("dims", [64, 128])
+def test_the_short_attention_leaves_room_for_a_second_workgroup(attention_registers, dims):
+    """More requests x KV heads than compute units are two workgroups of eight waves on one: four waves a SIMD, 128 of its 512 registers each."""
+    (used, spilled), = [v for n, v in attention_registers.items() if f"attn_short_f32_kernelILi{dims}E" in n]
+    assert used <= 128 and spilled == 0
+
+
+@pytest.fixture(scope="module")
+def attention_registers(attention_file):
+    """kernel name -> its vector registers, how many of them are kept in memory"""
+    text = open(attention_file).read()
+    found = re.findall(r"\.name:\s+(_Z\w+)\n(?:(?!\.name:).)*?\.vgpr_count:\s+(\d+)\n\s+\.vgpr_spill_count:\s+(\d+)", text, re.S)
+    return {n: (int(a), int(b)) for n, a, b in found}
