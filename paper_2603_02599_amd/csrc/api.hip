@@ -51,8 +51,8 @@ static int check_cfg(const sun_model_cfg* c) {
     if (c->n_layers < 1 || c->hidden < 8 || c->n_q_heads < 1 || c->n_kv_heads < 1 || c->ffn < 1 || c->vocab < 1)
         return fail(SUN_ERR_SHAPE, "non-positive model dimension");
     if (c->head_dim != 64 && c->head_dim != 128) return fail(SUN_ERR_SHAPE, "head_dim must be 64 or 128");
-    if (c->n_q_heads % c->n_kv_heads || c->n_q_heads / c->n_kv_heads > 8)
-        return fail(SUN_ERR_SHAPE, "n_q_heads must be a multiple (<= 8x) of n_kv_heads");
+    if (c->n_q_heads % c->n_kv_heads || c->n_q_heads / c->n_kv_heads > kMaxGroup)
+        return fail(SUN_ERR_SHAPE, "n_q_heads must be a multiple (<= %dx) of n_kv_heads", kMaxGroup);
     if (c->hidden % 8 || (c->n_q_heads * c->head_dim) % 128)
         return fail(SUN_ERR_SHAPE, "hidden must be a multiple of 8 and n_q_heads*head_dim of 128");
     if (c->act_dtype == SUN_BF16) {

@@ -63,7 +63,8 @@ __device__ __forceinline__ void split_pair(float x0, float x1, uint32_t& hi, uin
     lo = pack_bf16(x0 - bf16_lo(hi), x1 - bf16_hi(hi));
 }
 
-// The items of workgroup wg out of nwg, by its eight waves.  GT: query heads per KV head, 0: taken from the arguments.
+// The items of workgroup wg out of nwg, by its eight waves.  GT: query heads per KV head, 0: taken from the arguments; eight at most
+// (kMaxGroup, which every model is checked for): rows 8 to 15 of the operand of heads are nobody's and are not stored.
 // SHARED: the partials are read again by other workgroups of the same launch.  list_cursor: LDS; the previous use of it is over.
 // before() (SHARED) is what to wait for before q and the newest entry of every request may be read; items without the newest
 // entry request their first K and V in front of it, except for wave 0's, which polls there.
@@ -72,6 +73,7 @@ __device__ __forceinline__ void attn_split_items(const AttnArgs& a, int wg, int 
     const int G = GT ? GT : a.Hq / a.Hkv;
     constexpr int NS = D / 32;  // dim slices of a QK MFMA
     constexpr int NB = D / 16;  // dim blocks of a PV MFMA
+    static_assert(GT <= kMaxGroup && kMaxGroup <= 8 && NB % 4 == 0, "partials of eight heads leave in stores of four blocks");
     constexpr bool QUADS = NS == 4;  // K through load_stream and turn_k
     const int c16 = lane & 15, kq = lane >> 4;
     // One workgroup of 8 waves per compute unit.  Items are dealt to workgroups statically: full

@@ -40,6 +40,7 @@ __host__ __device__ inline void attn_chunking(int n, int batch, int Hkv, int& n_
     n_small = (n - n_full * ch + kAttnSmall - 1) / kAttnSmall;
 }
 constexpr int kGroup = 128;         // quantisation group along K (Appendix A.1)
+constexpr int kMaxGroup = 8;        // query heads per KV head
 constexpr int kMaxBatchTile = 256;  // rows of a decode batch
 constexpr int kMaxPrefillTile = 2048;  // rows of a prefill block (bf16 projections only)
 
