@@ -458,6 +458,7 @@ static void mark_matrices(Weights& w, size_t packed_bytes) {
     }
     w.lm.stream = stream;
     w.lm.vocab = true;
+    w.packed = packed_bytes;
 }
 
 static int check_ptr_arrays(const void* const* const arrs[], int n_arrs, int n_layers) {
@@ -722,13 +723,15 @@ static int validate_device_arrays(const KvPool& pool, int batch, const int32_t* 
 }
 
 // Chunk counts of the batch (all chunks; full chunks) from lengths the host knows, as the plan kernel computes
-// them on the device; -1 when the host has no lengths.
+// them on the device; -1 when the host has no lengths.  tokens: the batch's, or the most that its tables and the pool can hold.
 struct ChunkHint {
     int total, full;
+    long long tokens;
 };
-static ChunkHint chunks_from_host(const int32_t* host, int len_plus, int batch, int max_pages, int Hkv) {
-    if (!host) return ChunkHint{-1, -1};
-    long long tot = 0, full = 0;
+static ChunkHint chunks_from_host(const KvPool& pool, const int32_t* host, int len_plus, int batch, int max_pages) {
+    const int Hkv = pool.cfg.n_kv_heads;
+    if (!host) return ChunkHint{-1, -1, std::min((long long)batch * max_pages, (long long)pool.lay.n_pages) * kPageTokens};
+    long long tot = 0, full = 0, tokens = 0;
     const long long cap = (long long)max_pages * kPageTokens;
     for (int b = 0; b < batch; ++b) {
         const long long n = std::min(std::max<long long>((long long)host[b] + len_plus, 1), cap);
@@ -736,8 +739,9 @@ static ChunkHint chunks_from_host(const int32_t* host, int len_plus, int batch, 
         attn_chunking((int)n, batch, Hkv, nf, ns, ch);
         tot += nf + ns;
         full += nf;
+        tokens += n;
     }
-    return ChunkHint{(int)std::min<long long>(tot, 0x7fffffff), (int)std::min<long long>(full, 0x7fffffff)};
+    return ChunkHint{(int)std::min<long long>(tot, 0x7fffffff), (int)std::min<long long>(full, 0x7fffffff), tokens};
 }
 
 // fp32: out = projection of rmsnorm(x; gain); a normed input that is not computed inside the projection lies where
@@ -790,7 +794,7 @@ static int step_impl(sun_kv_pool* pool_, const sun_weights* weights_, bool want_
     const bool prof = flags & SUN_PROFILE;
     const bool bf = c.act_dtype == SUN_BF16;
     const int H = c.hidden;
-    const ChunkHint hint = chunks_from_host(seq_lens_host, 1, batch, max_pages, c.n_kv_heads);
+    const ChunkHint hint = chunks_from_host(pool, seq_lens_host, 1, batch, max_pages);
     float* logits = logits_out ? logits_out : ws.logits;
     // All layers of a small batch in one launch, in the place of the activation tiles and slabs that the single launches use.  Under
     // SUN_PROFILE every operation is a launch of its own, which is what is timed; under capture as well, since a
@@ -841,7 +845,7 @@ static int step_impl(sun_kv_pool* pool_, const sun_weights* weights_, bool want_
         if (!short_f32) {
             ProfScope p(prof, 0, st);
             SUN_HIP_CHECK(launch_attn_split(pool, l, ws.plan, attn_q, page_tables, max_pages, seq_lens, 1, batch, hint.total,
-                                            hint.full, !bf, st));
+                                            hint.full, attn_k_read(c, &W, hint.tokens), !bf, st));
         }
         if (!short_f32) {
             ProfScope p(prof, 1, st);
@@ -1321,10 +1325,10 @@ int sun_paged_attention(sun_kv_pool* pool_, int layer, int batch, const float* q
     const Workspace ws = carve(c, batch, max_pages, (char*)workspace);
     if (ws.bytes > workspace_bytes) return fail(SUN_ERR_WORKSPACE, "workspace has %zu bytes, need %zu", workspace_bytes, ws.bytes);
     hipStream_t st = (hipStream_t)stream;
-    const ChunkHint hint = chunks_from_host(n_tokens_host, 0, batch, max_pages, c.n_kv_heads);
+    const ChunkHint hint = chunks_from_host(pool, n_tokens_host, 0, batch, max_pages);
     SUN_HIP_CHECK(launch_attn_plan(ws.plan, n_tokens, 0, batch, page_tables, max_pages, (int)pool.lay.n_pages, c.n_kv_heads, st));
     SUN_HIP_CHECK(launch_attn_split(pool, layer, ws.plan, q, page_tables, max_pages, n_tokens, 0, batch, hint.total, hint.full,
-                                    c.act_dtype == SUN_F32, st));
+                                    attn_k_read(c, nullptr, hint.tokens), c.act_dtype == SUN_F32, st));
     SUN_HIP_CHECK(launch_attn_combine(c, ws.plan, batch, out, nullptr, nullptr, st));
     return SUN_OK;
 }
@@ -1371,12 +1375,12 @@ int sun_paged_attention_static(sun_kv_pool* pool_, int layer, int batch, const f
     if (int rc = static_scratch(&base)) return rc;
     const Workspace ws = carve_attention(c, batch, max_pages, (char*)base);
     hipStream_t st = (hipStream_t)stream;
-    const ChunkHint hint = chunks_from_host(n_tokens_host, 0, batch, max_pages, c.n_kv_heads);
+    const ChunkHint hint = chunks_from_host(pool, n_tokens_host, 0, batch, max_pages);
     // nothing in the scratch has to start at zero: the plan kernels write every prefix sum and every record the
     // split kernel reads, the split kernel every partial the combine kernel reads
     SUN_HIP_CHECK(launch_attn_plan(ws.plan, n_tokens, 0, batch, page_tables, max_pages, (int)pool.lay.n_pages, c.n_kv_heads, st));
     SUN_HIP_CHECK(launch_attn_split(pool, layer, ws.plan, q, page_tables, max_pages, n_tokens, 0, batch, hint.total, hint.full,
-                                    c.act_dtype == SUN_F32, st));
+                                    attn_k_read(c, nullptr, hint.tokens), c.act_dtype == SUN_F32, st));
     SUN_HIP_CHECK(launch_attn_combine(c, ws.plan, batch, out, nullptr, nullptr, st));
     return SUN_OK;
 }

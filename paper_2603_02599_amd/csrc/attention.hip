@@ -178,10 +178,10 @@ hipError_t launch_step_begin(const sun_model_cfg& cfg, const void* embed, const 
 // ---------------------------------------------------------------------------------
 // split kernel, matrix-core variant
 // ---------------------------------------------------------------------------------
-template <int D, int G>
+template <int D, int G, KRead K_READ>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_split_kernel(AttnArgs a) {
     __shared__ int list_cursor;
-    attn_split_items<D, G, false>(a, blockIdx.x, gridDim.x, threadIdx.x & 63, &list_cursor, [] {});
+    attn_split_items<D, G, false, K_READ>(a, blockIdx.x, gridDim.x, threadIdx.x & 63, &list_cursor, [] {});
 }
 
 // One dim's share of a page: acc + p[0] v[0] + ... in the order of the tokens, the first `count` of them (slots past the end may hold
@@ -501,11 +501,28 @@ hipError_t launch_attn_short_f32(const KvPool& pool, int layer, const float* qkv
     return hipGetLastError();
 }
 
-template <int D>
+// What fits the memory-side cache (256 MB) from one step to the next is read through it: K of all layers, beside the weights where
+// those stay there too (bf16, no more than kStreamWeightBytes).  Streamed -> through the caches, us a step: hidden 512, 2 layers, 20 MB of weights, K of
+// 107 / 184 MB 209 -> 202 / 239 -> 230; hidden 1024, 4 layers, 120 MB, K of 41 / 73 / 115 / 131 MB 216 -> 211 / 415 -> 406 / 232 -> 234 / 272 -> 276; hidden
+// 1024, 8 layers, 197 MB, K of 20 / 37 MB 405 -> 402 / 749 -> 757; weights past the caches: hidden 2048, 4 layers, K of 131 / 307 MB 380 -> 367 / 737 -> 737,
+// hidden 4096, 2 layers, 184 / 524 MB 394 -> 385 / 807 -> 805, 32 query heads on 4, hidden 2048, 246 / 393 MB 452 -> 449 / 518 -> 527.  With 4-bit weights, which are
+// never streamed, K of 7 to 246 MB 272 -> 278 up to 399 -> 409.  In the one launch of all layers K is always streamed: never slower than
+// the cached loads of the operand as it lies that stood there before, and by turns 1 % behind and 8 % ahead of cached rows.
+// In rows or in place: turning the rows costs the vector ALU, in place an instruction takes 16 bytes of each of 64 half lines.  Steps take rows, in place is
+// 1 to 2 % slower there up to some 60 MB of K (and as much faster at 184); attention alone, 256 requests of 400 / 700 tokens, 8 query heads on 2, two layers 65.8 -> 60.9 / 86 ->
+// 81 us, 64 of 1000, 32 on 8, one layer 55.5 -> 52.9.
+KRead attn_k_read(const sun_model_cfg& c, const Weights* W, long long tokens) {
+    constexpr size_t kKept = (size_t)224 << 20;
+    const size_t beside = !W || W->layers[0].qkv.stream ? 0 : W->packed;
+    if ((W && W->quant) || beside + (size_t)tokens * c.n_kv_heads * c.head_dim * 2 * c.n_layers > kKept) return K_STREAMED;
+    return W ? K_ROWS : K_IN_PLACE;
+}
+
+template <int D, KRead K_READ>
 static hipError_t launch_split_d(const AttnArgs& a, int G, int grid, hipStream_t st) {
     switch (G) {
 #define SUN_CASE(g) \
-    case g: hipLaunchKernelGGL((attn_split_kernel<D, g>), dim3(grid), dim3(512), 0, st, a); break;
+    case g: hipLaunchKernelGGL((attn_split_kernel<D, g, K_READ>), dim3(grid), dim3(512), 0, st, a); break;
         SUN_CASE(1) SUN_CASE(2) SUN_CASE(3) SUN_CASE(4) SUN_CASE(5) SUN_CASE(6) SUN_CASE(7) SUN_CASE(8)
 #undef SUN_CASE
     default: return hipErrorInvalidValue;
@@ -515,7 +532,7 @@ static hipError_t launch_split_d(const AttnArgs& a, int G, int grid, hipStream_t
 
 hipError_t launch_attn_split(const KvPool& pool, int layer, const AttnPlan& plan, const float* q,
                              const int32_t* page_tables, int max_pages, const int32_t* n_or_len, int len_plus,
-                             int batch, int total_chunks_hint, int full_chunks_hint, bool f32_exact, hipStream_t st) {
+                             int batch, int total_chunks_hint, int full_chunks_hint, KRead k_read, bool f32_exact, hipStream_t st) {
     const sun_model_cfg& c = pool.cfg;
     const sun_kv_layout& L = pool.lay;
     const int D = c.head_dim, G = c.n_q_heads / c.n_kv_heads;
@@ -540,8 +557,13 @@ hipError_t launch_attn_split(const KvPool& pool, int layer, const AttnPlan& plan
         a.total_items = total_chunks_hint * c.n_kv_heads;
     }
     const int grid = (int)max(1LL, min((items + 7) / 8, 256LL));
-    if (D == 64) return launch_split_d<64>(a, G, grid, st);
-    if (D == 128) return launch_split_d<128>(a, G, grid, st);
+    if (D == 64) return launch_split_d<64, K_IN_PLACE>(a, G, grid, st);
+    if (D != 128) return hipErrorInvalidValue;
+    switch (k_read) {
+    case K_STREAMED: return launch_split_d<128, K_STREAMED>(a, G, grid, st);
+    case K_ROWS: return launch_split_d<128, K_ROWS>(a, G, grid, st);
+    case K_IN_PLACE: return launch_split_d<128, K_IN_PLACE>(a, G, grid, st);
+    }
     return hipErrorInvalidValue;
 }
 

@@ -68,13 +68,15 @@ __device__ __forceinline__ void split_pair(float x0, float x1, uint32_t& hi, uin
 // SHARED: the partials are read again by other workgroups of the same launch.  list_cursor: LDS; the previous use of it is over.
 // before() (SHARED) is what to wait for before q and the newest entry of every request may be read; items without the newest
 // entry request their first K and V in front of it, except for wave 0's, which polls there.
-template <int D, int GT, bool SHARED, class Before>
+template <int D, int GT, bool SHARED, KRead K_READ, class Before>
 __device__ __forceinline__ void attn_split_items(const AttnArgs& a, int wg, int nwg, int lane, int* list_cursor, Before before) {
     const int G = GT ? GT : a.Hq / a.Hkv;
     constexpr int NS = D / 32;  // dim slices of a QK MFMA
     constexpr int NB = D / 16;  // dim blocks of a PV MFMA
     static_assert(GT <= kMaxGroup && kMaxGroup <= 8 && NB % 4 == 0, "partials of eight heads leave in stores of four blocks");
-    constexpr bool QUADS = NS == 4;  // K through load_stream and turn_k
+    constexpr bool QUADS = NS == 4;  // operand register s holds dims 32 kq + 8 s instead of 32 s + 8 kq
+    constexpr bool ROWS = K_READ != K_IN_PLACE;  // K in whole token rows and through turn_k
+    static_assert(QUADS || !ROWS, "a row of 64 dims is not four quads'");
     const int c16 = lane & 15, kq = lane >> 4;
     // One workgroup of 8 waves per compute unit.  Items are dealt to workgroups statically: full
     // chunks (all of one size) round-robin; the workgroups that got one full chunk fewer are
@@ -108,7 +110,8 @@ __device__ __forceinline__ void attn_split_items(const AttnArgs& a, int wg, int 
     };
     // K operand rows: MFMA row i of tile 0 <-> page (i>>3), token 8*((i>>2)&1) + (i&3); tile 1: +4
     const int k_psel = c16 >> 3, k_tok = 8 * ((c16 >> 2) & 1) + (c16 & 3);
-    const int64_t k_lane_off = (int64_t)k_tok * D + kq * 8;
+    constexpr int SLICE = QUADS ? 8 : 32, OCTET = QUADS ? 32 : 8;   // dims from one register, from one kq to the next
+    const int64_t k_lane_off = (int64_t)k_tok * D + kq * OCTET;
     // V^T operand: lane (dim c16 of a 16-dim block, token octet kq): page (kq>>1), tokens 8*(kq&1)..+7
     const int v_psel = kq >> 1;
     const int64_t v_lane_off = (int64_t)c16 * kPageTokens + 8 * (kq & 1);
@@ -120,20 +123,20 @@ __device__ __forceinline__ void attn_split_items(const AttnArgs& a, int wg, int 
         int pB = __builtin_amdgcn_readlane(recv, 2 * pp + 1);
         if (pB < 0) pB = pA;
         const uint16_t* kh = a.kbase + head * a.k_head;
-        if constexpr (QUADS) {
+        if constexpr (ROWS) {
             const uint16_t* kp = kh + (int64_t)(lane & 8 ? pB : pA) * a.k_page + ((lane >> 2) & 1) * 8 * D + kq * 32 + (lane & 3) * 8;
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                kr[0][r] = load_stream(reinterpret_cast<const u32x4_s*>(kp + r * D));
-                kr[1][r] = load_stream(reinterpret_cast<const u32x4_s*>(kp + (4 + r) * D));
+            for (int r = 0; r < 8; ++r) {
+                const u32x4_s* row = reinterpret_cast<const u32x4_s*>(kp + (r & 3) * D + (r >> 2) * 4 * D);
+                kr[r >> 2][r & 3] = K_READ == K_STREAMED ? load_stream(row) : *row;
             }
             return;
         }
         const uint16_t* kp = kh + (int64_t)(k_psel ? pB : pA) * a.k_page + k_lane_off;
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
-            kr[0][s] = *reinterpret_cast<const u32x4_s*>(kp + s * 32);
-            kr[1][s] = *reinterpret_cast<const u32x4_s*>(kp + 4 * D + s * 32);
+            kr[0][s] = *reinterpret_cast<const u32x4_s*>(kp + s * SLICE);
+            kr[1][s] = *reinterpret_cast<const u32x4_s*>(kp + 4 * D + s * SLICE);
         }
     };
     // V^T is requested with streaming loads: every instruction reads two runs of 512 contiguous bytes, which
@@ -155,7 +158,7 @@ __device__ __forceinline__ void attn_split_items(const AttnArgs& a, int wg, int 
     };
 
     auto turn_k = [&]() {
-        if constexpr (QUADS) {
+        if constexpr (ROWS) {
             const bool b0 = lane & 1, b1 = lane & 2;
 #pragma unroll
             for (int t = 0; t < 2; ++t)
@@ -178,15 +181,14 @@ __device__ __forceinline__ void attn_split_items(const AttnArgs& a, int wg, int 
         }
     };
     bf16x8 qhi[NS], qlo[NS];
-    // q as MFMA B operand: lane (head g = c16, dim octet kq) per 32-dim slice, hi + lo bf16; with QUADS slice s is dims 8 s .. + 7
-    // of every 32
+    // q as MFMA B operand, hi + lo bf16: lane (head g = c16, dim octet kq) per slice s, the dims of K's registers
     auto load_q = [&](int req, int head) {
         const float* qp = a.q + ((size_t)req * a.Hq + head * G + (c16 < G ? c16 : 0)) * D;
         f32x4 q[NS][2];
 #pragma unroll
         for (int s = 0; s < NS; ++s)
 #pragma unroll
-            for (int i = 0; i < 2; ++i) q[s][i] = *reinterpret_cast<const f32x4*>(qp + (QUADS ? kq * 32 + s * 8 : s * 32 + kq * 8) + 4 * i);
+            for (int i = 0; i < 2; ++i) q[s][i] = *reinterpret_cast<const f32x4*>(qp + kq * OCTET + s * SLICE + 4 * i);
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
             u32x4_s h, l;

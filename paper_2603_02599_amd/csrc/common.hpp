@@ -307,6 +307,7 @@ struct LayerW {
 struct Weights {
     sun_model_cfg cfg;
     bool quant;
+    size_t packed;   // bytes of the packed matrices
     const void* embed;
     const void* gf;
     Mat lm;

@@ -57,6 +57,8 @@ struct AttnPlan {           // device arrays inside the workspace
 size_t attn_max_chunks(int batch, int max_pages, int Hkv);
 hipError_t launch_attn_plan(const AttnPlan& plan, const int32_t* n_or_len, int len_plus, int batch,
                             const int32_t* page_tables, int max_pages, int n_pages, int Hkv, hipStream_t st);
+// K in whole token rows past the caches, the same through the caches, or as the operand lies through the caches.
+enum KRead { K_STREAMED, K_ROWS, K_IN_PLACE };
 // First launch of a decode step: launch_embed_rope and launch_attn_plan (n_tokens = seq_lens + 1) together.
 // Counters of the launch that runs all layers, and its word that says it was given up, start at zero.
 struct LayersZero {
@@ -71,7 +73,9 @@ hipError_t launch_step_begin(const sun_model_cfg& cfg, const void* embed, const 
 // chunks) when the host knows the lengths, else < 0.
 hipError_t launch_attn_split(const KvPool& pool, int layer, const AttnPlan& plan, const float* q,
                              const int32_t* page_tables, int max_pages, const int32_t* n_or_len, int len_plus,
-                             int batch, int total_chunks_hint, int full_chunks_hint, bool f32_exact, hipStream_t st);
+                             int batch, int total_chunks_hint, int full_chunks_hint, KRead k_read, bool f32_exact, hipStream_t st);
+// How the K of the cached tokens is read (128 dims; the same sums whichever).  W: NULL where attention is all that runs.
+KRead attn_k_read(const sun_model_cfg& c, const Weights* W, long long tokens);
 // out: fp32 row-major [batch, Hq*d] (out_f32) and/or the O projection's input: two-plane tiled bf16, or, with
 // qscale given, the fixed-point tile of a 4-bit projection and its (scale, integer sum) pairs.
 hipError_t launch_attn_combine(const sun_model_cfg& cfg, const AttnPlan& plan, int batch, float* out_f32,

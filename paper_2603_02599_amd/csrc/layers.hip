@@ -637,7 +637,7 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 
             at.q = a.q + (size_t)(l % a.ring) * a.q_step;
             // with 4-bit weights what depends on the lane does not fit beside the other phases' registers from layer to layer (741 -> 731 us
             // at five requests; the bf16 kernel has the room and would lose 0.3 %)
-            attn_split_items<128, 0, true>(at, blockIdx.x, gridDim.x, W4 ? lane_here() : threadIdx.x & 63, &sh.cursor, wait);
+            attn_split_items<128, 0, true, K_STREAMED>(at, blockIdx.x, gridDim.x, W4 ? lane_here() : threadIdx.x & 63, &sh.cursor, wait);
         }
         arrive();
         {

@@ -202,6 +202,17 @@ def test_the_short_attention_leaves_room_for_a_second_workgroup(attention_regist
     assert used <= 128 and spilled == 0
 
 
+@pytest.mark.parametrize("heads", [1, 4, 8])
+def test_attention_streams_v_always_and_k_where_it_is_told(attention_code, heads):
+    """Sixteen loads of a page pair: eight of K, eight of V; those past the caches are marked."""
+    def share(k_read):   # streamed, rows through the caches, in place through the caches
+        code, = [v for n, v in attention_code.items() if f"attn_split_kernelILi128ELi{heads}ELNS_5KReadE{k_read}E" in n]
+        loads = [s for s in code if s.startswith("global_load_dwordx4") and "lds" not in s]
+        return sum(s.endswith(" nt") for s in loads), len(loads)
+    streamed, rows, in_place = share(0), share(1), share(2)
+    assert streamed[1] == rows[1] == in_place[1] and streamed[0] == 2 * rows[0] == 2 * in_place[0] > 0
+
+
 @pytest.fixture(scope="module")
 def attention_registers(attention_file):
     """kernel name -> its vector registers, how many of them are kept in memory"""

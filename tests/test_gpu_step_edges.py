@@ -246,6 +246,36 @@ def test_projections_on_both_sides_of_the_streaming_rule(H, rows):
     assert ((got["above", 4].double() - want).abs() <= 2e-4 + 1e-5 * want.abs()).all()
 
 
+@pytest.mark.parametrize("heads", [(2, 2), (8, 2), (10, 2), (8, 1)], ids=lambda h: f"{h[0]}on{h[1]}")
+def test_k_through_the_caches_and_past_them(H, heads):
+    """The K of a step that fits the memory-side cache is read through it, a larger one past it.  Without the lengths on the host the tables
+    and the pool count (20 requests of up to 16 000 positions, 328 MB of K), with them the tokens (4 MB): the same bits, the oracle's logits.
+    Attention alone reads a small K as its operand lies: the same bits again."""
+    shape = dataclasses.replace(wl.SMALL128, name="k", hidden=128 * heads[0], n_q_heads=heads[0], n_kv_heads=heads[1])
+    work = wl.make_workload("cfg1", shape=shape, dtype="bf16", batch=20, seed=996)
+    rng = np.random.default_rng(7)
+    work.seq_lens = rng.integers(0, 200, size=20).astype(np.int32)
+    work.page_tables, _ = wl.deal_page_tables(work.seq_lens, rng)
+    work.page_tables = np.pad(work.page_tables, ((0, 0), (0, 1000 - work.page_tables.shape[1])), constant_values=-1)
+    work.n_pages = 20000 // heads[1]
+    case = H.GpuCase(work)
+    ref = H.run_oracle(case, list(range(20)))
+    pool0, got = case.pool_mem.clone(), []
+    for host_lens in (True, False):
+        case.pool_mem.copy_(pool0)
+        case.logits.fill_(float("nan"))
+        case.step(host_lens=host_lens)
+        got.append((case.logits.clone(), case.pool_mem.clone()))
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+    H.check_logits(got[0][0].cpu().numpy(), ref["logits"], "bf16")
+    q, n = torch.randn((20, 128 * heads[0]), device=H.DEV), case.lens + 1
+    outs = [torch.full_like(q, float("nan")) for _ in range(2)]
+    for out, host in zip(outs, (n.cpu().numpy(), None)):
+        sun.sun_paged_attention(case.pool, 1, q, case.tables, n, out, case.ws, n_tokens_host=host)
+    torch.cuda.synchronize()
+    assert torch.equal(*outs) and bool(torch.isfinite(outs[0]).all())
+
+
 @pytest.mark.parametrize("rows", [1, 32, 33])
 @pytest.mark.parametrize("hidden,vocab", [(256, 114656), (256, 128256), (1024, 152064), (1024, 256000), (3072, 256000)])
 def test_vocabulary_projection_on_both_sides_of_the_rule_for_its_waves(H, hidden, vocab, rows):
