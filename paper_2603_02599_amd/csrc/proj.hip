@@ -1184,7 +1184,11 @@ __device__ __forceinline__ float wave_rows(float (&v)[2]) {
 // loads of UN steps along k are in flight together; the sums keep the order of one step at a time (lane l adds k = l, l + 64,
 // ... and the lanes meet in a butterfly), the norm's that of a workgroup with a thread per eight columns.  Tiny
 // configuration, 8 requests: 5.3 us a launch against 6.4 of the bare products, and 18 launches a step instead of 29; with the first
-// weights and the value that is added to requested in front of the rows 4.0 to 4.9 (a run of 16 steps 967 -> 927 us).
+// weights and the value that is added to requested in front of the rows 4.0 to 4.9, now 3.2 to 4.6.
+// The weights' format is asked for in front of the steps: asked at each weight it left a step's loads waiting for one another.  All weights of a step in
+// front of its rows, asked for each, against a weight and its rows in turn, asked for once (us): run of 16 steps 849 -> 779; a step of
+// 2 layers, hidden 1024 at 1 / 8 / 64 requests 130 / 147 / 339 -> 84 / 99 / 288, 2048 at 1 / 8 319 / 384 -> 176 / 241, 4096 at 1 / 8 669 / 933 -> 380 / 634 (636 /
+// 833 where every weight stood beside its rows); 4-bit, hidden 2048 at 1 / 8 / 64 336 / 480 / 1454 -> 236 / 316 / 998.
 // BT rows a wave: 8 or 2 (f32_two_rows; the sums are the same ones).
 template <int BT, int UN, bool NORM, int EPI>
 __global__ __launch_bounds__(256) void proj_f32_kernel(F32Mat m, const float* __restrict__ x, int nrows, float* out) {
@@ -1211,28 +1215,30 @@ __global__ __launch_bounds__(256) void proj_f32_kernel(F32Mat m, const float* __
     for (int j = 0; j < BT; ++j) row[j] = x + (size_t)min(b0 + j, nrows - 1) * K;
     const int ng = K / kGroup;
     float wv[UN][NC], gv[UN];
-    const auto load_w = [&](int k0) {
+    const auto load_w = [&](auto quant, int i, int at) {
+        const int k = min(at, K - 1);  // past the end: valid, not added
 #pragma unroll
-        for (int i = 0; i < UN; ++i) {
-            const int k = min(k0 + i * 64, K - 1);  // past the end: valid, not added
-#pragma unroll
-            for (int c = 0; c < NC; ++c) {
-                if (m.quant) {
-                    const uint8_t byte = m.q[src[c]][(size_t)r[c] * (K / 2) + (k >> 1)];
-                    const float code = (float)((k & 1) ? (byte >> 4) : (byte & 15));
-                    const size_t g = (size_t)r[c] * ng + k / kGroup;
-                    const float zf = m.z[src[c]] ? __half2float(__ushort_as_half(m.z[src[c]][g])) : 8.f;
-                    const float sf = __half2float(__ushort_as_half(m.s[src[c]][g]));
-                    wv[i][c] = (code - zf) * sf;  // exact: 5-bit integer times an 11-bit significand
-                } else {
-                    wv[i][c] = m.w[src[c]][(size_t)r[c] * K + k];
-                }
+        for (int c = 0; c < NC; ++c) {
+            if constexpr (quant) {
+                const uint8_t byte = m.q[src[c]][(size_t)r[c] * (K / 2) + (k >> 1)];
+                const float code = (float)((k & 1) ? (byte >> 4) : (byte & 15));
+                const size_t g = (size_t)r[c] * ng + k / kGroup;
+                const float zf = m.z[src[c]] ? __half2float(__ushort_as_half(m.z[src[c]][g])) : 8.f;
+                const float sf = __half2float(__ushort_as_half(m.s[src[c]][g]));
+                wv[i][c] = (code - zf) * sf;  // exact: 5-bit integer times an 11-bit significand
+            } else {
+                wv[i][c] = m.w[src[c]][(size_t)r[c] * K + k];
             }
-            if constexpr (NORM) gv[i] = m.gain[k];
         }
+        if constexpr (NORM) gv[i] = m.gain[k];
+    };
+    const auto first = [&](auto quant) {
+#pragma unroll
+        for (int i = 0; i < UN; ++i) load_w(quant, i, lane + i * 64);
     };
     // what does not wait for the rows is requested in front of them: the first weights and the value that is added to
-    load_w(lane);
+    if (m.quant) first(std::true_type{});
+    else first(std::false_type{});
     const int b = b0 + (lane >> 3);
     const bool mine = lane < BT * 8 && (lane & 7) == 0 && b < nrows;
     float* o = out + (size_t)min(b, nrows - 1) * n_out + n;
@@ -1263,25 +1269,30 @@ __global__ __launch_bounds__(256) void proj_f32_kernel(F32Mat m, const float* __
     for (int c = 0; c < NC; ++c)
 #pragma unroll
         for (int j = 0; j < BT; ++j) acc[c][j] = 0.f;
-    for (int k0 = lane; k0 < K; k0 += 64 * UN) {
-        float xv[UN][BT];
-        if (k0 >= 64 * UN) load_w(k0);
+    const auto add_up = [&](auto quant) {
+        for (int k0 = lane; k0 < K; k0 += 64 * UN) {
+            float xv[UN][BT];
 #pragma unroll
-        for (int i = 0; i < UN; ++i)
+            for (int i = 0; i < UN; ++i) {
+                if (k0 >= 64 * UN) load_w(quant, i, k0 + i * 64);
 #pragma unroll
-            for (int j = 0; j < BT; ++j) xv[i][j] = row[j][min(k0 + i * 64, K - 1)];
-#pragma unroll
-        for (int i = 0; i < UN; ++i)
-            if (k0 + i * 64 < K) {
-#pragma unroll
-                for (int j = 0; j < BT; ++j) {
-                    float y = xv[i][j];
-                    if constexpr (NORM) y = y * rinv[j] * gv[i];
-#pragma unroll
-                    for (int c = 0; c < NC; ++c) acc[c][j] = fmaf(wv[i][c], y, acc[c][j]);
-                }
+                for (int j = 0; j < BT; ++j) xv[i][j] = row[j][min(k0 + i * 64, K - 1)];
             }
-    }
+#pragma unroll
+            for (int i = 0; i < UN; ++i)
+                if (k0 + i * 64 < K) {
+#pragma unroll
+                    for (int j = 0; j < BT; ++j) {
+                        float y = xv[i][j];
+                        if constexpr (NORM) y = y * rinv[j] * gv[i];
+#pragma unroll
+                        for (int c = 0; c < NC; ++c) acc[c][j] = fmaf(wv[i][c], y, acc[c][j]);
+                    }
+                }
+        }
+    };
+    if (m.quant) add_up(std::true_type{});
+    else add_up(std::false_type{});
     float v[NC];
 #pragma unroll
     for (int c = 0; c < NC; ++c) v[c] = wave_rows(acc[c]);
@@ -1294,9 +1305,9 @@ __global__ __launch_bounds__(256) void proj_f32_kernel(F32Mat m, const float* __
 static int f32_out_cols(const Mat& W, int epilogue) { return epilogue == F32_SWIGLU ? W.src_rows[0] : W.N; }
 
 // The norm rides along as long as summing each row's squares in every wave costs less than the launch it saves, about 4 us.
-// Step of 4 layers, inside / launch of its own (us): hidden 256, ffn 688 at 8 / 32 / 64 / 128 rows 142 / 170 / 188 / 238 against
-// 164 / 177 / 187 / 217, hidden 512, ffn 1024 at 8 / 32 / 64 rows 178 / 221 / 275 against 195 / 220 / 258, hidden 1024, ffn 2816 at
-// 4 / 8 / 64 rows 269 / 307 / 768 against 274 / 287 / 612, hidden 2048 at 256 rows 10.8 ms against 7.7.  Above 8192 columns the norm
+// Step of 4 layers, inside / launch of its own (us): hidden 256, ffn 688 at 1 / 8 / 32 / 64 / 128 rows 81 / 102 / 121 / 149 / 189 against
+// 115 / 121 / 127 / 141 / 164, hidden 512, ffn 1024 at 8 / 32 / 64 rows 115 / 175 / 236 against 129 / 168 / 211, hidden 1024, ffn 2816 at
+// 1 / 4 / 8 / 64 rows 150 / 163 / 200 / 687 against 152 / 163 / 176 / 515, hidden 2048 at 256 rows 8.4 ms against 5.7.  Above 8192 columns the norm
 // kernel sums in another order than a wave does here.
 bool f32_fuses_norm(const Mat& W, int rows, int epilogue) {
     return W.K <= 8192 && (long long)f32_out_cols(W, epilogue) * rows * W.K <= (W.K <= 512 ? 1 << 24 : 1 << 23);
@@ -1304,9 +1315,9 @@ bool f32_fuses_norm(const Mat& W, int rows, int epilogue) {
 
 // Two rows a wave, or eight: two where eight would leave most of the chip without a workgroup (eight workgroups fit a compute
 // unit), as long as the matrix, which every group of rows reads again, is not the larger cost.  Down projection, two / eight
-// rows a wave (us): 1024 x 2816 at 1 / 8 / 16 rows 9.3 / 12.9 / 22.8 against 13.3 / 13.8 / 15.4, 2048 x 2048 at 1 / 4 / 8 rows 8.7 /
-// 10.1 / 17.1 against 11.8 / 11.8 / 11.9, 2048 x 6144 at 8 rows 47 against 52, 4096 x 14336 at 1 / 4 / 8 rows 97 / 104 / 203 against
-// 130 / 129 / 130.
+// rows a wave (us): 1024 x 2816 at 1 / 8 / 16 rows 7.0 / 7.1 / 11.2 against 8.7 / 8.3 / 11.9, 2048 x 2048 (O) at 1 / 4 / 8 rows 7.1 /
+// 7.1 / 9.0 against 8.1 / 7.9 / 8.0, 2048 x 6144 at 1 / 8 rows 14 / 24 against 24 / 24, 4096 x 14336 at 1 / 4 / 6 / 8 rows 36 / 68 / 100 / 132 against
+// 71 / 70 / 71 / 80.
 static bool f32_two_rows(const Mat& W, int cols, int rows) {
     const int groups = (rows + 1) / 2;
     return groups == 1 || (long long)cols * groups <= (groups == 2 || W.K >= 4096 ? 2048 : 1024);
@@ -1350,8 +1361,8 @@ hipError_t launch_proj_f32(const Mat& W, const float* x, int rows, const void* g
         }
         return hipGetLastError();
     };
-    // steps of 64 along k in flight: four for one group of rows (2048 x 6144 at 8 rows 52 us, one step 60), one where several
-    // groups of waves cover each other's waits (at 16 / 32 / 256 rows 60 / 77 / 591 us, four steps 54 / 111 / 604)
+    // steps of 64 along k in flight: four for one group of rows (2048 x 6144 at 8 rows 24 us, one step 39), one where several
+    // groups of waves cover each other's waits (at 16 / 24 / 32 / 64 / 256 rows 40 / 47 / 68 / 123 / 479 us, four steps 32 / 51 / 62 / 125 / 492)
     if (f32_two_rows(W, cols, rows)) return go(std::integral_constant<int, 2>{}, std::integral_constant<int, 4>{});
     if (rows <= 8) return go(std::integral_constant<int, 8>{}, std::integral_constant<int, 4>{});
     return go(std::integral_constant<int, 8>{}, std::integral_constant<int, 1>{});

@@ -174,6 +174,24 @@ def projection_code(tmp_path_factory):
     return assembly(os.path.join(CSRC, "proj.hip"), tmp_path_factory.mktemp("asm") / "proj.s")
 
 
+@pytest.mark.parametrize("epilogue", [0, 1, 2])
+@pytest.mark.parametrize("rows,ahead,norm", [(2, 4, 0), (2, 4, 1), (8, 4, 0), (8, 4, 1), (8, 1, 0), (8, 1, 1)])
+def test_the_fp32_projection_has_a_step_of_loads_in_flight(projection_code, rows, ahead, norm, epilogue):
+    """A step along k is `ahead` times a weight (gate and up: two), the rows' values and the norm's gain, with nothing asked between their
+    loads (but whether the last of four lies within k): a question whether the weights are 4-bit, asked at each weight, made a step as many
+    round trips as it has of them."""
+    found = [v for n, v in projection_code.items() if f"proj_f32_kernelILi{rows}ELi{ahead}ELb{norm}ELi{epilogue}E" in n]
+    if (norm, epilogue) == (1, 1):
+        assert not found   # the sum behind attention and down has no norm in front
+        return
+    code, = found
+    most = n = 0
+    for s in code:
+        n = 0 if s.endswith(":") or s.startswith(("s_cbranch", "s_branch")) else n + bool(re.match(r"(global|flat)_load_dword ", s))
+        most = max(most, n)
+    assert most >= max(1, ahead - 1) * (rows + (2 if epilogue == 2 else 1) + norm)
+
+
 @pytest.fixture(scope="module")
 def attention_file(tmp_path_factory):
     out = tmp_path_factory.mktemp("asm") / "attention.s"
