@@ -126,10 +126,12 @@ __device__ __forceinline__ void attn_split_items(const AttnArgs& a, int wg, int 
         if constexpr (ROWS) {
             const uint16_t* kp = kh + (int64_t)(lane & 8 ? pB : pA) * a.k_page + ((lane >> 2) & 1) * 8 * D + kq * 32 + (lane & 3) * 8;
 #pragma unroll
-            for (int r = 0; r < 8; ++r) {
-                const u32x4_s* row = reinterpret_cast<const u32x4_s*>(kp + (r & 3) * D + (r >> 2) * 4 * D);
-                kr[r >> 2][r & 3] = K_READ == K_STREAMED ? load_stream(row) : *row;
-            }
+            for (int r = 0; r < 4; ++r)
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    const u32x4_s* row = reinterpret_cast<const u32x4_s*>(kp + (4 * t + r) * D);
+                    kr[t][r] = K_READ == K_STREAMED ? load_stream(row) : *row;
+                }
             return;
         }
         const uint16_t* kp = kh + (int64_t)(k_psel ? pB : pA) * a.k_page + k_lane_off;
