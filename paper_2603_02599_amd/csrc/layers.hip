@@ -10,8 +10,8 @@
 // cached tokens: 8B shape bf16 1154 -> 879 / 1185 -> 968 / 1217 -> 1077, 4-bit at 1 / 4 / 8 817 -> 607 / 835 -> 640 / 837 -> 675; hidden
 // 2048, ffn 8192 bf16 644 -> 400 / 666 -> 457 / 697 -> 566, 4-bit at 1 / 8 510 -> 332 / 538 -> 384; hidden 1024 440 -> 283 / 476 -> 328 /
 // 494 -> 403, 403 -> 282 / 430 -> 333.  Eight rows are what an operand of the 4-bit products holds beside their low planes; with
-// two rows a wave and operands of 16 4-bit steps at 12 / 16 requests (4 layers, 8B shape) took 549 -> 552 / 524 -> 553.  Hence kLayersRows and
-// kLayersRowsW4.
+// two rows a wave and an operand of 16 for each plane (and the barrier on 16 counters) 4-bit steps at 12 / 16 requests (4 layers, 8B shape) took 549 -> 552 / 524 -> 553;
+// two operands of eight rows were not built.  Hence kLayersRows and kLayersRowsW4.
 //
 // Hand-over between workgroups.  Data that another workgroup reads in the same launch is stored through to memory (st_agent),
 // and its storer waits for vmcnt before it counts itself as arrived.  Readers either pass their caches by (ld_agent: the residual
@@ -715,8 +715,8 @@ static size_t up256(size_t v) { return (v + 255) / 256 * 256; }
 // Column blocks and split along k.  As many units as there are workgroups at most; every wave that shares k gets a step.
 // A row's sums depend on the matrix alone.  Widths whose blocks fill the chip badly lose part of the gain, not all of it (4 layers, launch
 // per operation -> this, us): 296 gate/up blocks on 256 workgroups (hidden 3584, ffn 18 944) at 1 / 16 requests 577 -> 489 / 593 -> 591;
-// 272 of 4-bit weights (hidden 5120, ffn 17 408) at 1 / 8 468 -> 399 / 473 -> 434 (136 of twice the columns;
-// on longer requests those 395 / 467, these 375 / 449), bf16 at 1 / 16 724 -> 644 / 747 -> 746; 14B shape 847 ->
+// 272 of 4-bit weights (hidden 5120, ffn 17 408) at 1 / 8 406 -> 356 / 415 -> 416, on requests of 2000 to 6000 tokens 422 -> 370 / 508 -> 509 (136 of twice the
+// columns, with an operand for each plane: 379 / 435, 398 / 524), bf16 at 1 / 16 724 -> 644 / 747 -> 746; 14B shape 847 ->
 // 697 / 886 -> 780, 4-bit 613 -> 554 / 634 -> 600; hidden 8192, ffn 28 672 1351 -> 1258 / 1376 -> 1346, 4-bit 706 -> 607 / 740 -> 655.
 static void cut(MatP& m, int N, int K, bool w4) {
     m.K = K;
@@ -767,12 +767,14 @@ static LayersLayout layers_layout(const sun_model_cfg& c, int rows, bool w4, siz
     return L;
 }
 
-// The cooperative launch costs about 26 us more than it saves outside the layers, and a layer saves, at the narrowest widths that were
-// timed (hidden 1024; wider ones two or three times that), 19 us at one row down to 4 at 16 (bf16), 11 at one row down to 4 at 8
-// (4-bit): few layers are faster with a launch per operation.  Hidden 1024, launch per operation -> this (us): one layer 12 / 16
-// requests 80 -> 97 / 81 -> 101, 4-bit 5 / 8 75 -> 94 / 76 -> 97; two layers one request 126 -> 117, 4-bit 117 -> 120; four at 12 / 16
-// 240 -> 233 / 244 -> 255, 4-bit at 5 218 -> 211; eight 473 -> 419 / 480 -> 469, 4-bit at 8 411 -> 395 (all with the barrier's arrivals on 16
-// counters; on 64 eight layers take 403 at 16 requests).
+// The cooperative launch costs about 28 us more than it saves outside the layers, and a layer saves, at the narrowest widths that were
+// timed (hidden 1024; wider ones two or three times that), 17 us at one row down to 7 at 16 (bf16), 13 at one row down to 10 at 8
+// (4-bit): few layers are faster with a launch per operation.  Hidden 1024, launch per operation -> this (us), at 1 / 12 / 16 rows: one layer 65 / 72 / 71 ->
+// 77 / 89 / 92, two 112 / 123 / 127 -> 107 / 134 / 141, three 158 / 174 / 177 -> 135 / 173 / 187, four 212 / 226 / 235 -> 174 / 215 / 241, six 303 / 334 / 343 ->
+// 234 / 302 / 335, eight 415 / 451 / 471 -> 307 / 402 / 441; 4-bit at 1 / 8 rows, one layer 59 / 65 -> 75 / 84, two 100 / 111 -> 103 / 119, three 141 / 157 ->
+// 133 / 154, four 188 / 200 -> 161 / 188, six 264 / 293 -> 217 / 262.  The line keeps clear of what is slower: it was drawn when a layer saved 4 us
+// at 16 rows and at 8 of 4-bit weights, and sends stacks to separate launches that break even or better here today: at 16 rows five and six layers (288 ->
+// 288, 343 -> 335; hidden 2048 from two on, 179 -> 177, six 470 -> 398), 4-bit at 8 three to six (hidden 2048 three 186 -> 170, six 347 -> 289).
 static bool layers_shape(const Weights& W, int rows) {
     return W.cfg.act_dtype == SUN_BF16 && W.cfg.head_dim == 128 && rows <= (W.quant ? kLayersRowsW4 : kLayersRows) &&
            W.cfg.n_layers * ((W.quant ? 12 : 20) - rows) >= 26;

@@ -296,6 +296,27 @@ def test_vocabulary_projection_on_both_sides_of_the_rule_for_its_waves(H, hidden
     assert ((out.double() - want).abs() <= 2e-4 + 1e-5 * want.abs()).all()
 
 
+def test_activations_are_rounded_to_nearest_even(H):
+    """Every lower half of a float under signs, exponents and mantissas of all kinds, through a projection by the unit matrix: its input is
+    split into two bf16 planes, whose sum, exact in fp32, is that of torch's rounding."""
+    shape = dataclasses.replace(wl.SMALL128, name="rounding", n_layers=1, hidden=1024, n_q_heads=8, n_kv_heads=8)
+    cfg = sun.make_cfg(shape, "bf16")
+    w = wl.make_weights(shape, "bf16", H.DEV, 85)
+    w["wo"][0].copy_(torch.eye(1024))
+    W = sun.sun_weights_create(cfg, w)
+    rng = np.random.default_rng(85)
+    ws = torch.empty(sun.sun_workspace_bytes(cfg, 64, 1), dtype=torch.uint8, device=H.DEV)
+    for upper in rng.integers(0, 1 << 16, size=(4, 1 << 16)):
+        upper = (upper & 0x807F) | (64 + (upper >> 7 & 127)) << 7     # exponents 64 to 190: the lower plane is normal too
+        bits = (upper.astype(np.uint32) << 16) | rng.permutation(1 << 16).astype(np.uint32)
+        x = torch.from_numpy(bits.view(np.float32).reshape(64, 1024)).to(H.DEV)
+        out = torch.full_like(x, float("nan"))
+        sun.sun_linear(W, 0, 1, x, out, ws)
+        torch.cuda.synchronize()
+        high = x.bfloat16().float()
+        assert torch.equal(out, high + (x - high).bfloat16().float())
+
+
 @pytest.mark.parametrize("rows", [1, 32])
 @pytest.mark.parametrize("ffn", [57344, 58368, 65536])
 def test_wide_4_bit_gate_up_is_not_split_along_k(H, ffn, rows):
